@@ -65,9 +65,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "Lloyd iters/s + point×centroid distances/s; objective ratio vs fp32 oracle"
-PEAK = {"fp32": 157.3, "bf16": 2500.0, "int8": 5000.0, "hbm_gbs": 8000.0}
-PEAK_UNIT = {"fp32": "TFLOP/s", "bf16": "TFLOP/s", "int8": "TOP/s"}
+PEAK = {"fp32": 157.3, "fp16": 2500.0, "bf16": 2500.0, "int8": 5000.0, "hbm_gbs": 8000.0}
+PEAK_UNIT = {"fp32": "TFLOP/s", "fp16": "TFLOP/s", "bf16": "TFLOP/s", "int8": "TOP/s"}
 ASSIGN_SOURCES = ("paper_2608_14648_amd/csrc/assign.hip", "paper_2608_14648_amd/csrc/common.hpp")
+# fp32 assignment issues three fp16 matrix products per fp32 one
+SPLIT_WORK = "3 x 2 d multiply-adds' operations per (point, centroid) pair: the fp16 products of an fp32 one"
 COPY_PROBE_FLOATS = 256 << 20  # 1 GiB of fp32
 
 
@@ -150,13 +152,14 @@ def copy_probe(torch):
     log(f"copy probe done ({COPY_PROBE_FLOATS * 4} bytes)")
 
 
-def roofline(workload, stats, work_per_launch, peak, kernel, kernel_key):
+def roofline(workload, stats, work_per_launch, peak, kernel, kernel_key,
+             work="2 d multiply-adds' operations per (point, centroid) pair"):
     a_ms = stats["assign_ms"] / max(1, stats["assign_passes"])
     ach = work_per_launch / (a_ms * 1e-3) / 1e12
     return {"bound": "mfma", "kernel": kernel, "achieved": ach, "peak": PEAK[peak], "unit": PEAK_UNIT[peak],
             "frac": ach / PEAK[peak], "traffic": counted_traffic(workload, kernel_key),
             "avg_launch_ms": a_ms, "work_per_launch": work_per_launch,
-            "work": "2 d multiply-adds' operations per (point, centroid) pair"}
+            "work": work}
 
 
 def update_hbm(stats, bytes_per_update, what):
@@ -264,8 +267,8 @@ def wl_c1(cfg, torch, km, args):
         return line(T * K / elapsed, "Lloyd iters/s", "f32",
                     {"workload": cfg["name"], "N": spec.n, "d": spec.d, "k": k, "iters": T, "format": "f32"},
                     distances_per_s=(T + 1) * spec.n * k * K / elapsed,
-                    roofline=roofline(cfg["name"], s, 2.0 * spec.n * k * spec.d, "fp32",
-                                      "assign_f32_kernel", "assign_f32_kernel"),
+                    roofline=roofline(cfg["name"], s, 6.0 * spec.n * k * spec.d, "fp16",
+                                      "assign_split_kernel", "assign_split_kernel", SPLIT_WORK),
                     update_hbm=update_hbm(s, spec.n * (4 * spec.d + 4), "4d+4 per point"),
                     stages={"f32": stage_summary(s)})
 
@@ -303,8 +306,8 @@ def wl_c2_f32(cfg, torch, km, args):
                      "components": spec.components, "sigma": spec.sigma},
                     distances_per_s=(T + 1) * spec.n * k * K / elapsed,
                     partition_cost=float(out["cost"].item()),
-                    roofline=roofline(wname, s, 2.0 * spec.n * k * spec.d, "fp32", "assign_f32_kernel",
-                                      "assign_f32_kernel"),
+                    roofline=roofline(wname, s, 6.0 * spec.n * k * spec.d, "fp16", "assign_split_kernel",
+                                      "assign_split_kernel", SPLIT_WORK),
                     update_hbm=update_hbm(s, spec.n * (4 * spec.d + 4), "4d+4 per point"),
                     stages={"f32": stage_summary(s)})
 
@@ -459,8 +462,8 @@ def wl_c4(cfg, torch, km, args):
                      "format": "f32 (PCA-projected)"},
                     distances_per_s=(T + 1) * spec.n * k * K / elapsed,
                     partition_cost=float(out["cost"].item()),
-                    roofline=roofline(cfg["name"], s, 2.0 * spec.n * k * dout, "fp32", "assign_f32_kernel",
-                                      "assign_f32_kernel"),
+                    roofline=roofline(cfg["name"], s, 6.0 * spec.n * k * dout, "fp16", "assign_split_kernel",
+                                      "assign_split_kernel", SPLIT_WORK),
                     update_hbm=update_hbm(s, spec.n * (4 * dout + 4), "4d'+4 per point"),
                     host_eigensolve_ms_per_step=timer.host_ms.get("eigensolve", 0.0) / K,
                     stages={"pca": stage_summary(s)})
@@ -748,7 +751,7 @@ def wl_hier(fmt):
             work = K * ((Tm + 1) * work_meso + (Tf + 1) * work_fine)
             ach = work / (s["assign_ms"] * 1e-3) / 1e12
             peak = "fp32" if fmt == "f32" else "int8"
-            kern = "assign_f32_kernel" if fmt == "f32" else "assign_q8_kernel<sq8>"
+            kern = "assign_split_kernel (meso), assign_f32_kernel (fine)" if fmt == "f32" else "assign_q8_kernel<sq8>"
             return line(K / elapsed, "fits/s", "f32" if fmt == "f32" else "u8",
                         {"workload": wname, "N": spec.n, "d": spec.d, "k": k, "k_meso": kmeso, "iters_meso": Tm,
                          "iters_fine": Tf, "iters_refine": 0, "format": fmt},

@@ -77,6 +77,7 @@ class Scratch {
     hipError_t e = hipMallocAsync(&p_, std::max<size_t>(bytes, 256), s_);
     if (e == hipErrorOutOfMemory) {
       p_ = nullptr;
+      (void)hipGetLastError();  // reported here, not by the next launch (a caller may go on with less)
       set_error("scratch allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
       return KM_ENOMEM;
     }
@@ -189,6 +190,7 @@ static km_status check_points(const km_points *P, Points *out) {
       KMQ_CHECK(P->d_front == 0, KM_EINVAL, "d_front must be 0 for this format");
     }
   }
+  p.split = fmt == KM_F32 && p.d >= 32;
   *out = p;
   return KM_OK;
 }
@@ -328,6 +330,11 @@ struct AssignScratch {
 static AssignScratch assign_scratch(const Points &p, int k, const float *score, const double *objective) {
   AssignScratch a;
   a.b_prep = al(prep_bytes(p, k));
+  if (p.split) {  // the objective needs neither scores nor point-only terms
+    a.b_score = a.b_xc = 0;
+    a.b_part = objective ? al(direct_objective_bytes()) : 0;
+    return a;
+  }
   a.b_score = objective != nullptr && score == nullptr ? al(sizeof(float) * (size_t)p.n) : 0;
   a.b_xc = objective ? al(sizeof(float) * (size_t)p.n) : 0;
   a.b_part = objective ? al(sizeof(double) * (size_t)objective_blocks(p.n)) : 0;
@@ -356,6 +363,7 @@ static km_status assign_on(const Points &p, const void *C, int32_t k, int32_t *a
   if (st != KM_OK) return st;
   st = launch_assign(p, C, cp, k, assign, sc, s);
   if (st != KM_OK) return st;
+  if (objective && p.split) return launch_direct_objective(p, static_cast<const float *>(C), k, assign, objective, part, s);
   if (objective) {
     st = launch_xconst(p, xc, s);
     if (st != KM_OK) return st;
@@ -374,9 +382,14 @@ km_status kmeans_assign(const km_points *P, const void *C, int32_t k, int32_t *a
   km_status st = check_assign_args(P, C, k, assign, &p);
   if (st != KM_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const AssignScratch a = assign_scratch(p, k, score, objective);
+  AssignScratch a = assign_scratch(p, k, score, objective);
   Scratch ws(s);
   st = ws.alloc(a.total());
+  if (st == KM_ENOMEM && p.split) {  // the fp32 kernel needs less
+    p.split = false;
+    a = assign_scratch(p, k, score, objective);
+    st = ws.alloc(a.total());
+  }
   if (st != KM_OK) return st;
   return assign_on(p, C, k, assign, score, objective, a, ws.get(), s);
 }
@@ -387,7 +400,11 @@ km_status kmeans_assign_noalloc(const km_points *P, const void *C, int32_t k, in
   Points p;
   km_status st = check_assign_args(P, C, k, assign, &p);
   if (st != KM_OK) return st;
-  const AssignScratch a = assign_scratch(p, k, score, objective);
+  AssignScratch a = assign_scratch(p, k, score, objective);
+  if (p.split && a.total() > kStaticScratchBytes) {  // the fp32 kernel needs less
+    p.split = false;
+    a = assign_scratch(p, k, score, objective);
+  }
   KMQ_CHECK(a.total() <= kStaticScratchBytes, KM_EINVAL,
             "kmeans_assign_noalloc needs %zu bytes of scratch for n = %lld, k = %d; its static buffer holds %zu",
             a.total(), (long long)p.n, k, kStaticScratchBytes);
@@ -493,14 +510,19 @@ static km_status check_init_idx(const int64_t *init_idx, int k, int64_t n) {
 
 // Lloyd on validated arguments: STEP 1 from init_idx (HOST; NULL = C holds the
 // start), iters x (STEP 2, STEP 3), final STEP 2; objective: DEVICE double[iters + 1].
-static km_status fit_impl(const Points &p, int k, int iters, const int64_t *init_idx, void *C, int32_t *assign,
+static km_status fit_on(const Points &p, int k, int iters, const int64_t *init_idx, void *C, int32_t *assign,
                           double *objective, int policy, StageClock &clk, hipStream_t s) {
   km_status st;
   const size_t b_prep = al(prep_bytes(p, k));
   const size_t b_upd = al(std::max(update_bytes(p, k), p.raw ? update_bytes(raw_points(p), k) : (size_t)0));
-  const size_t b_score = objective ? al(sizeof(float) * (size_t)p.n) : 0;
-  const size_t b_xc = objective ? al(sizeof(float) * (size_t)p.n) : 0;
-  const size_t b_part = objective ? al(sizeof(double) * (size_t)objective_blocks(p.n)) : 0;
+  // p.split: the objective of a pass is summed by the update that follows it, from the
+  // rows that reads, and directly where none does or it reads the raw rows
+  const bool direct = objective && p.split;
+  const bool scores = objective && !p.split;
+  const size_t b_score = scores ? al(sizeof(float) * (size_t)p.n) : 0;
+  const size_t b_xc = scores ? al(sizeof(float) * (size_t)p.n) : 0;
+  const size_t b_part = direct ? al(direct_objective_bytes())
+                               : scores ? al(sizeof(double) * (size_t)objective_blocks(p.n)) : 0;
   const size_t b_idx = init_idx ? al(sizeof(int64_t) * (size_t)k) : 0;
   Scratch ws(s);
   st = ws.alloc(b_prep + b_upd + b_score + b_xc + b_part + b_idx);
@@ -508,7 +530,7 @@ static km_status fit_impl(const Points &p, int k, int iters, const int64_t *init
   uint8_t *w = ws.get();
   uint8_t *wprep = w;
   uint8_t *wupd = w + b_prep;
-  float *sc = objective ? reinterpret_cast<float *>(w + b_prep + b_upd) : nullptr;
+  float *sc = scores ? reinterpret_cast<float *>(w + b_prep + b_upd) : nullptr;
   float *xc = reinterpret_cast<float *>(w + b_prep + b_upd + b_score);
   double *part = reinterpret_cast<double *>(w + b_prep + b_upd + b_score + b_xc);
   int64_t *didx = reinterpret_cast<int64_t *>(w + b_prep + b_upd + b_score + b_xc + b_part);
@@ -516,21 +538,36 @@ static km_status fit_impl(const Points &p, int k, int iters, const int64_t *init
     KMQ_HIP(hipMemcpyAsync(didx, init_idx, sizeof(int64_t) * (size_t)k, hipMemcpyHostToDevice, s));
     KMQ_STAGE(clk, kStOther, launch_gather_init(p, didx, k, C, s));
   }
-  if (objective) KMQ_STAGE(clk, kStOther, launch_xconst(p, xc, s));
+  if (scores) KMQ_STAGE(clk, kStOther, launch_xconst(p, xc, s));
   CentroidPrep cp;
   for (int it = 0; it <= iters; ++it) {
     KMQ_STAGE(clk, kStPrep, launch_prep(p, C, k, wprep, &cp, s));
     KMQ_STAGE(clk, kStAssign, launch_assign(p, C, cp, k, assign, sc, s));
-    if (objective)
+    const bool from_raw = p.raw && it == iters - 1;  // the last update averages the raw rows (Sec. 4.1)
+    if (direct && (it == iters || from_raw))
+      KMQ_STAGE(clk, kStOther,
+                launch_direct_objective(p, static_cast<const float *>(C), k, assign, objective + it, part, s));
+    if (scores)
       KMQ_STAGE(clk, kStOther, launch_objective(p, xc, sc, p.n, objective + it, part, objective_blocks(p.n), s));
     if (it == iters) break;  // the last pass only assigns (the final STEP 2)
-    if (p.raw && it == iters - 1) {  // last update from the raw rows (Sec. 4.1)
+    if (from_raw) {
       KMQ_STAGE(clk, kStUpdate, launch_update(raw_points(p), assign, k, C, nullptr, policy, wupd, s));
     } else {
-      KMQ_STAGE(clk, kStUpdate, launch_update(p, assign, k, C, nullptr, policy, wupd, s));
+      KMQ_STAGE(clk, kStUpdate, launch_update(p, assign, k, C, nullptr, policy, wupd, s, nullptr, nullptr,
+                                              direct ? objective + it : nullptr));
     }
   }
   return KM_OK;
+}
+
+static km_status fit_impl(Points p, int k, int iters, const int64_t *init_idx, void *C, int32_t *assign,
+                          double *objective, int policy, StageClock &clk, hipStream_t s) {
+  km_status st = fit_on(p, k, iters, init_idx, C, assign, objective, policy, clk, s);
+  if (st == KM_ENOMEM && p.split) {  // nothing was launched; the fp32 kernel needs less scratch
+    p.split = false;
+    st = fit_on(p, k, iters, init_idx, C, assign, objective, policy, clk, s);
+  }
+  return st;
 }
 
 // Nearest integer to sqrt(k) (k is never the square of a half-integer).
@@ -586,11 +623,13 @@ static std::vector<int> fine_counts_sqrt(const std::vector<int64_t> &n_i) {
 // FINE-CLUSTERING (Sec. 4.4) on validated arguments.  sqrt_rule: the paper's fine
 // counts, k being the capacity of C; *k_used (nullable) receives the number of fine
 // centroids.
-static km_status fine_impl(const Points &p, const int32_t *meso, int k_meso, int k, int iters, bool c_given,
+static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, int k, int iters, bool c_given,
                            bool sqrt_rule, int *k_used, void *C, int32_t *assign, int32_t *k_fine, double *objective,
                            int policy, StageClock &clk,
                            hipStream_t s) {
   km_status st;
+  Points p = p0;
+  p.split = false;  // the segmented passes take the fp32 kernel
   // meso-cluster order of the points (stable) and the meso-cluster sizes
   Scratch wsort(s);
   st = wsort.alloc(sort_bytes(p.n, k_meso));
@@ -818,32 +857,18 @@ km_status kmeans_assign_pruned(const km_points *P, const void *C, int32_t k, con
   return KM_OK;
 }
 
-km_status kmeans_fit_pruned(const km_points *P, int32_t k, int32_t iters, const int64_t *init_idx, void *C,
-                            int32_t *assign, double *objective, int32_t policy, const km_prune *pr,
-                            km_fit_stats *stats, uint64_t *counters, km_stream stream) {
-  g_err[0] = 0;
-  Points p;
-  km_status st = check_points(P, &p);
-  if (st != KM_OK) return st;
-  st = check_centroids(p, C, k);
-  if (st != KM_OK) return st;
-  KMQ_CHECK(assign != nullptr, KM_EINVAL, "assign is NULL");
-  KMQ_CHECK(k <= p.n, KM_EINVAL, "k = %d exceeds n = %lld", k, (long long)p.n);
-  KMQ_CHECK(iters >= 0, KM_EINVAL, "iters = %d must be >= 0", iters);
-  KMQ_CHECK(policy == KM_EMPTY_SPLIT || policy == KM_EMPTY_KEEP, KM_EINVAL, "unknown empty-cluster policy %d", policy);
-  int D0 = 0;
-  st = check_prune(p, pr, &D0);
-  if (st != KM_OK) return st;
-  if (init_idx) {
-    st = check_init_idx(init_idx, k, p.n);
-    if (st != KM_OK) return st;
-  }
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+static km_status fit_pruned_on(const Points &p, int k, int iters, const int64_t *init_idx, void *C, int32_t *assign,
+                               double *objective, int policy, const km_prune *pr, int D0, km_fit_stats *stats,
+                               uint64_t *counters, hipStream_t s) {
+  km_status st;
   const size_t b_prep = al(prep_bytes(p, k));
   const size_t b_upd = al(std::max(update_bytes(p, k), p.raw ? update_bytes(raw_points(p), k) : (size_t)0));
-  const size_t b_score = objective ? al(sizeof(float) * (size_t)p.n) : 0;
-  const size_t b_xc = objective ? al(sizeof(float) * (size_t)p.n) : 0;
-  const size_t b_part = objective ? al(sizeof(double) * (size_t)objective_blocks(p.n)) : 0;
+  const bool scores = objective && !p.split;
+  const size_t b_score = scores ? al(sizeof(float) * (size_t)p.n) : 0;
+  const size_t b_xc = scores ? al(sizeof(float) * (size_t)p.n) : 0;
+  const size_t b_part = !objective ? 0
+                        : scores ? al(sizeof(double) * (size_t)objective_blocks(p.n))
+                                 : al(direct_objective_bytes());
   const size_t b_idx = init_idx ? al(sizeof(int64_t) * (size_t)k) : 0;
   const size_t b_pr = al(pruned_bytes(p, k));
   const size_t b_cnt = al(3 * sizeof(unsigned long long));
@@ -853,7 +878,7 @@ km_status kmeans_fit_pruned(const km_points *P, int32_t k, int32_t iters, const 
   uint8_t *w = ws.get();
   uint8_t *wprep = w;
   uint8_t *wupd = w + b_prep;
-  float *sc = objective ? reinterpret_cast<float *>(wupd + b_upd) : nullptr;
+  float *sc = scores ? reinterpret_cast<float *>(wupd + b_upd) : nullptr;
   float *xc = reinterpret_cast<float *>(wupd + b_upd + b_score);
   double *part = reinterpret_cast<double *>(wupd + b_upd + b_score + b_xc);
   int64_t *didx = reinterpret_cast<int64_t *>(wupd + b_upd + b_score + b_xc + b_part);
@@ -870,7 +895,9 @@ km_status kmeans_fit_pruned(const km_points *P, int32_t k, int32_t iters, const 
     CentroidPrep cp;
     KMQ_STAGE(clk, kStPrep, launch_prep(p, C, k, wprep, &cp, s));
     KMQ_STAGE(clk, kStAssign, launch_assign(p, C, cp, k, assign, sc, s));
-    if (objective) {
+    if (objective && p.split)
+      KMQ_STAGE(clk, kStOther, launch_direct_objective(p, static_cast<const float *>(C), k, assign, objective, part, s));
+    if (scores) {
       KMQ_STAGE(clk, kStOther, launch_xconst(p, xc, s));
       KMQ_STAGE(clk, kStOther, launch_objective(p, xc, sc, p.n, objective, part, objective_blocks(p.n), s));
     }
@@ -899,6 +926,35 @@ km_status kmeans_fit_pruned(const km_points *P, int32_t k, int32_t iters, const 
     return KM_ENOMEM;
   }
   return KM_OK;
+}
+
+km_status kmeans_fit_pruned(const km_points *P, int32_t k, int32_t iters, const int64_t *init_idx, void *C,
+                            int32_t *assign, double *objective, int32_t policy, const km_prune *pr,
+                            km_fit_stats *stats, uint64_t *counters, km_stream stream) {
+  g_err[0] = 0;
+  Points p;
+  km_status st = check_points(P, &p);
+  if (st != KM_OK) return st;
+  st = check_centroids(p, C, k);
+  if (st != KM_OK) return st;
+  KMQ_CHECK(assign != nullptr, KM_EINVAL, "assign is NULL");
+  KMQ_CHECK(k <= p.n, KM_EINVAL, "k = %d exceeds n = %lld", k, (long long)p.n);
+  KMQ_CHECK(iters >= 0, KM_EINVAL, "iters = %d must be >= 0", iters);
+  KMQ_CHECK(policy == KM_EMPTY_SPLIT || policy == KM_EMPTY_KEEP, KM_EINVAL, "unknown empty-cluster policy %d", policy);
+  int D0 = 0;
+  st = check_prune(p, pr, &D0);
+  if (st != KM_OK) return st;
+  if (init_idx) {
+    st = check_init_idx(init_idx, k, p.n);
+    if (st != KM_OK) return st;
+  }
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  st = fit_pruned_on(p, k, iters, init_idx, C, assign, objective, policy, pr, D0, stats, counters, s);
+  if (st == KM_ENOMEM && p.split) {  // nothing was launched; the fp32 kernel needs less scratch
+    p.split = false;
+    st = fit_pruned_on(p, k, iters, init_idx, C, assign, objective, policy, pr, D0, stats, counters, s);
+  }
+  return st;
 }
 
 km_status kmeans_fine(const km_points *P, const int32_t *meso_assign, int32_t k_meso, int32_t k, int32_t iters,

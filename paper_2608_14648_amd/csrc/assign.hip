@@ -79,6 +79,10 @@ struct AssignArgs {
   // [segs[i].z, + segs[i].w) (indices into the full centroid and prepared arrays)
   const int4 *segs;
   const int2 *tiles;
+  // fp32 kernel behind the split kernel (route set): only the point tiles flagged
+  // there, or all of them when the route says so
+  const SplitRoute *route;
+  const int *tflag;
 };
 
 // (score, index) as one 64-bit key whose unsigned order is the lexicographic
@@ -1876,6 +1880,7 @@ __global__ __launch_bounds__(kQThreads, 1) void assign_f32_kernel(AssignArgs A0)
     g = (int)(l % NG);
     if (pt >= A.n_ptiles) return;  // whole workgroup, before any barrier
   }
+  if (!SEG && A.route && A.route->ok && !A.tflag[pt]) return;
   const int64_t p0 = SEG ? seg_p0 : pt * TP;
   const int S = (A.df + 31) / 32;
   const int nct = (A.k + TC - 1) / TC;
@@ -2452,7 +2457,7 @@ __global__ __launch_bounds__(kQThreads, 1) void assign_hyb_kernel(AssignArgs A) 
 template <int FMT>
 __global__ __launch_bounds__(256) void prep_kernel(const void *Cv, int k, int d, int d0, const float *m,
                                                    float *cn, int *qsum, float *u, float *sig2, int8_t *q,
-                                                   uint16_t *cb) {
+                                                   uint16_t *cb, uint32_t *rmax) {
   __shared__ double shd[256];
   __shared__ float shf[256];
   __shared__ int shi[256];
@@ -2462,9 +2467,22 @@ __global__ __launch_bounds__(256) void prep_kernel(const void *Cv, int k, int d,
     const float *c = static_cast<const float *>(Cv) + (int64_t)j * d;
     const int dd = FMT == KM_F32 ? d : d0;
     double s = 0.0;
-    for (int i = t; i < dd; i += 256) s += (double)c[i] * (double)c[i];
+    uint32_t mx = 0;
+    for (int i = t; i < dd; i += 256) {
+      s += (double)c[i] * (double)c[i];
+      mx = max(mx, __float_as_uint(c[i]) & 0x7fffffffu);
+    }
     s = block_sum_f64(s, shd);
     if (t == 0) cn[j] = (float)s;
+    if (rmax) {  // largest |c| as a bit pattern (NaN and infinities are the largest)
+      shi[t] = (int)mx;
+      __syncthreads();
+      for (int st = 128; st > 0; st >>= 1) {
+        if (t < st) shi[t] = max(shi[t], shi[t + st]);
+        __syncthreads();
+      }
+      if (t == 0) rmax[j] = (uint32_t)shi[0];
+    }
   }
   if (FMT == KM_BF16) {  // round the fp32 centroid to bfloat16; ||c||^2 of the rounded values
     const float *c = static_cast<const float *>(Cv) + (int64_t)j * d;
@@ -2795,6 +2813,50 @@ __global__ __launch_bounds__(256) void cost_kernel(const float *X, int64_t n, in
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
+// ---- objective of fp32 points from the distances: sum ||x - c_a||^2 -----------------
+// One pass over the rows, as the point-only terms ||x||^2 need, and no cancellation: for
+// points close to their centroid ||x||^2 + score is a small difference whose rounding
+// adds up over the points.  One wave per point at a time, fp32 per lane and point, fp64
+// above; HBM bound.  A point without a centroid (its row holds NaN) or a sum that is
+// not finite gives NaN.
+__global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, int64_t n, int d, int64_t ldx,
+                                                               const float *C, int k, const int32_t *assign,
+                                                               double *partials) {
+  __shared__ double sh[256];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  double s = 0.0;
+  const int64_t stride = (int64_t)gridDim.x * 4;
+  for (int64_t p = (int64_t)blockIdx.x * 4 + wv; p < n; p += 2 * stride) {
+    // two points at a time: their loads are in flight together
+    const int64_t p2 = min<int64_t>(p + stride, n - 1);
+    const int a0 = assign[p], a1 = assign[p2];
+    const bool in0 = a0 >= 0 && a0 < k, in1 = a1 >= 0 && a1 < k;
+    const float *x0 = X + p * ldx, *x1 = X + p2 * ldx;
+    const float *c0 = C + (int64_t)(in0 ? a0 : 0) * d, *c1 = C + (int64_t)(in1 ? a1 : 0) * d;
+    f32x4 t0 = {0.f, 0.f, 0.f, 0.f}, t1 = t0;
+    for (int i = 4 * lane; i < d; i += 256) {
+      const f32x4 e0 = *reinterpret_cast<const f32x4 *>(x0 + i) - *reinterpret_cast<const f32x4 *>(c0 + i);
+      const f32x4 e1 = *reinterpret_cast<const f32x4 *>(x1 + i) - *reinterpret_cast<const f32x4 *>(c1 + i);
+      t0 += e0 * e0;
+      t1 += e1 * e1;
+    }
+    s += in0 ? (double)t0[0] + t0[1] + t0[2] + t0[3] : (double)NAN;
+    if (p + stride < n) s += in1 ? (double)t1[0] + t1[1] + t1[2] + t1[3] : (double)NAN;
+  }
+  s = block_sum_f64(s, sh);
+  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+}
+
+__global__ __launch_bounds__(256) void direct_objective_sum_kernel(const double *partials, int np, double *out) {
+  __shared__ double sh[256];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < np; i += 256) s += partials[i];
+  s = block_sum_f64(s, sh);
+  if (threadIdx.x == 0) *out = isfinite(s) ? s : (double)NAN;
+}
+
+constexpr int kDirectBlocks = 2048;  // 8 workgroups of 4 waves on each of 256 CUs
+
 constexpr int kObjBlocks = 1024;
 
 // Centroid-tile groups of the hybrid kernel: up to 8 workgroups share a point
@@ -2835,6 +2897,21 @@ int assign_groups(const Points &P, int k) {
   }
   if (P.fmt == KM_BF16 || P.fmt == KM_LVQ4 || (P.fmt == KM_SQ8 && P.d <= kQMaxDimSQ8)) return tile_groups(P.n, k);
   return 1;
+}
+
+SplitArgs split_args(const Points &P, const CentroidPrep &cp, int k, int32_t *assign, float *score) {
+  SplitArgs B{};
+  B.x = static_cast<const float *>(P.data);
+  B.ldx = P.ld;
+  B.d = P.d;
+  B.sp = cp.sp;
+  B.kall = (int)(cp.sp.cstage / 64);
+  B.k = k;
+  B.n = P.n;
+  B.assign = assign;
+  B.score = score;
+  B.ngroups = 1;
+  return B;
 }
 
 template <int FMT>
@@ -2943,6 +3020,17 @@ km_status launch_assign_t(const Points &P, const void *C, const CentroidPrep &cp
       hipLaunchKernelGGL(keys_init_kernel, gp, dim3(256), 0, s, cp.keys, P.n);
     }
     const dim3 grid((unsigned)(ng > 1 ? cdiv(npt, 8) * 8 * ng : npt));
+    if (cp.sp.route) {
+      SplitArgs B = split_args(P, cp, k, assign, score);
+      B.aoff = aoff;
+      B.ngroups = ng;
+      B.n_ptiles = npt;
+      B.keys = A.keys;
+      const km_status st = launch_split_assign(B, grid.x, q8_tile_centroids(k), s);
+      if (st != KM_OK) return st;
+      A.route = cp.sp.route;
+      A.tflag = cp.sp.tflag;
+    }
     if (q8_tile_centroids(k) == 128)
       hipLaunchKernelGGL((assign_f32_kernel<false, 2>), grid, dim3(kQThreads), 0, s, A);
     else
@@ -3006,6 +3094,7 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t prep_bytes(const Points &P, int k) {
   size_t b = align256(16 * (size_t)k) + align256(prep_codes_bytes(P, k));
   if (assign_groups(P, k) > 1) b += align256(8 * (size_t)P.n);
+  if (P.split) b += split_bytes(P.n, k, P.d);
   return b;
 }
 
@@ -3026,33 +3115,42 @@ km_status launch_prep(const Points &P, const void *C, int k, void *ws, CentroidP
   out->sig2 = sig2;
   out->q = q;
   out->cb = cb;
+  out->sp = SplitPrep{};
+  if (P.split) out->sp = split_layout(P.n, k, P.d, w + prep_bytes(P, k) - split_bytes(P.n, k, P.d));
   const int d0 = P.fmt == KM_HYBRID ? P.d_front : 0;
   switch (P.fmt) {
     case KM_F32:
-      hipLaunchKernelGGL(prep_kernel<KM_F32>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb);
+      hipLaunchKernelGGL(prep_kernel<KM_F32>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb,
+                         out->sp.rmax);
+      if (P.split) {
+        const km_status st = launch_split_prep(static_cast<const float *>(C), P.d, P.n, k, P.d, cn, out->sp, s);
+        if (st != KM_OK) return st;
+      }
       break;
     case KM_BF16:
-      hipLaunchKernelGGL(prep_kernel<KM_BF16>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q,
-                         cb);
+      hipLaunchKernelGGL(prep_kernel<KM_BF16>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb,
+                         nullptr);
       break;
     case KM_SQ8:
-      hipLaunchKernelGGL(prep_kernel<KM_SQ8>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb);
+      hipLaunchKernelGGL(prep_kernel<KM_SQ8>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb,
+                         nullptr);
       break;
     case KM_SIGN1:
-      hipLaunchKernelGGL(prep_kernel<KM_SIGN1>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, P.center, cn, qsum, u, sig2,
-                         q, cb);
+      hipLaunchKernelGGL(prep_kernel<KM_SIGN1>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, P.center, cn, qsum, u, sig2, q, cb,
+                         nullptr);
       break;
     case KM_LVQ4:
-      hipLaunchKernelGGL(prep_kernel<KM_LVQ4>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q,
-                         cb);
+      hipLaunchKernelGGL(prep_kernel<KM_LVQ4>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb,
+                         nullptr);
       break;
     case KM_RABITQ:
-      hipLaunchKernelGGL(prep_kernel<KM_RABITQ>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q,
-                         cb);
+      hipLaunchKernelGGL(prep_kernel<KM_RABITQ>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb,
+                         nullptr);
       break;
     case KM_HYBRID:
       hipLaunchKernelGGL(prep_kernel<KM_HYBRID>, dim3(k), dim3(256), 0, s, C, k, P.d, d0, P.center, cn, qsum, u,
-                         sig2, q, cb);
+                         sig2, q, cb,
+                         nullptr);
       break;
     default:
       return KM_EUNSUPPORTED;
@@ -3183,6 +3281,18 @@ km_status launch_objective(const Points &P, const float *xc, const float *score,
   hipLaunchKernelGGL(objective_partial_kernel, dim3(nb), dim3(256), 0, s, xc, score, n, partials);
   hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
   KMQ_LAUNCH_CHECK("objective");
+  return KM_OK;
+}
+
+size_t direct_objective_bytes() { return sizeof(double) * kDirectBlocks; }
+
+km_status launch_direct_objective(const Points &P, const float *C, int k, const int32_t *assign, double *out,
+                                  double *partials, hipStream_t s) {
+  const int nb = (int)std::min<int64_t>(kDirectBlocks, cdiv(P.n, 4));
+  hipLaunchKernelGGL(direct_objective_kernel, dim3(nb), dim3(256), 0, s, static_cast<const float *>(P.data), P.n, P.d,
+                     P.ld, C, k, assign, partials);
+  hipLaunchKernelGGL(direct_objective_sum_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
+  KMQ_LAUNCH_CHECK("direct objective");
   return KM_OK;
 }
 

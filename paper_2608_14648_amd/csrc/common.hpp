@@ -31,12 +31,31 @@ struct Points {
   const float *raw;    // nullable: fp32 rows in the clustering space (last update of a fit)
   int64_t raw_ld;
   const float *vparams;  // LVQ4: per-vector (s, b, A, N)
+  bool split;            // F32: assignments take the fp16 matrix cores (split.hpp) where the data allow
 };
 
 // 1-bit point formats (codes + one scale per point)
 __host__ __device__ constexpr bool is_bits_fmt(int fmt) {
   return fmt == KM_SIGN1 || fmt == KM_HYBRID || fmt == KM_RABITQ;
 }
+
+// What the preparation decides for one pass on the fp16 matrix cores (in device memory).
+struct SplitRoute {
+  int ok;    // 0: the fp32 kernel takes the pass
+  float s;   // power of two that scales points and centroids
+  float m2;  // -2 / s^2
+  int pad;
+};
+
+// The centroids for the fp16 matrix cores (split.hip), rebuilt with CentroidPrep.
+struct SplitPrep {
+  SplitRoute *route;  // NULL: not used
+  uint32_t *rmax;     // [k] bit pattern of the row's largest |c|
+  float *seed;        // [k + pad] -s^2 ||c||^2 / 2, then -inf
+  int *tflag;         // point tiles the fp32 kernel has to redo
+  uint8_t *img;       // stage-major: 64 bytes (16 hi, 16 lo halves) of every row per 16 dims
+  int64_t cstage;     // bytes of one stage of img
+};
 
 // Per-centroid data rebuilt before each assignment pass.
 struct CentroidPrep {
@@ -48,6 +67,7 @@ struct CentroidPrep {
                        // 0..15, k x d, each 8 dims ordered 0 2 4 6 1 3 5 7 (the unpacked point order)
   const uint16_t *cb;  // BF16: centroids rounded to bfloat16, k x d
   unsigned long long *keys;  // centroid-tile groups (F32/HYBRID/SQ8/BF16/LVQ4): per-point (score, index) keys
+  SplitPrep sp;              // F32 with Points::split
 };
 
 // Host-side error plumbing.
@@ -100,17 +120,45 @@ km_status launch_xconst(const Points &P, float *xc, hipStream_t s);
 km_status launch_objective(const Points &P, const float *xc, const float *score, int64_t n, double *out,
                            double *partials, int nblk_max, hipStream_t s);
 int objective_blocks(int64_t n);
+// the same sum for fp32 points from the distances themselves (direct_objective_bytes of partials)
+km_status launch_direct_objective(const Points &P, const float *C, int k, const int32_t *assign, double *out,
+                                  double *partials, hipStream_t s);
+size_t direct_objective_bytes();
 km_status launch_gather_init(const Points &P, const int64_t *idx, int k, void *C, hipStream_t s);
 km_status launch_cost(const float *X, int64_t n, int d, int64_t ldx, const float *C, int k,
                       const int32_t *assign, double *out, double *partials, hipStream_t s);
 
+// split.hip: fp32 points on the fp16 matrix cores
+struct SplitArgs {
+  const float *x;  // n x ldx
+  int64_t ldx;
+  int d;
+  SplitPrep sp;
+  int kall;  // rows in sp (sp.seed[kall] is -inf)
+  int coff;  // first centroid of this launch in sp
+  int k;
+  int64_t n;
+  int32_t *assign;
+  float *score;
+  int aoff;
+  int ngroups;
+  int64_t n_ptiles;
+  unsigned long long *keys;
+};
+size_t split_bytes(int64_t n, int k, int d);
+SplitPrep split_layout(int64_t n, int k, int d, void *ws);
+km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d, const float *cn, const SplitPrep &sp,
+                            hipStream_t s);
+km_status launch_split_assign(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s);
+
 // update.hip
 size_t update_bytes(const Points &P, int k);
 // seg_lo / seg_hi (nullable, int[k]): the split takes the donor of empty cluster j
-// from clusters [seg_lo[j], seg_hi[j]) only.
+// from clusters [seg_lo[j], seg_hi[j]) only.  objective (nullable, DEVICE, F32 only): the
+// sum of the members' squared distances to the centroids passed in.
 km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, int64_t *counts,
                         int policy, void *ws, hipStream_t s, const int *seg_lo = nullptr,
-                        const int *seg_hi = nullptr);
+                        const int *seg_hi = nullptr, double *objective = nullptr);
 struct SortOut {
   const int *perm;    // [n]: point indices ordered by cluster, point order kept inside a cluster
   const int *cnt;     // [k]: members per cluster (ids outside [0, k) are left out)

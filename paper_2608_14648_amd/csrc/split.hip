@@ -1,0 +1,495 @@
+// STEP 2 for fp32 points on the fp16 matrix cores (split.hpp), and the preparation
+// of the centroids for it.
+#include <float.h>
+#include <limits.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "split.hpp"
+
+namespace kmq {
+namespace {
+
+constexpr int kTP = 256;       // points per workgroup
+constexpr int kThr = 512;      // 8 waves
+constexpr int kSD = 16;        // dims per stage
+constexpr int kRow = 4 * kSD;  // bytes of a row per stage: 16 floats, or 16 hi then 16 lo halves
+constexpr int kRing = 4;       // stage buffers
+constexpr int kSeedPad = 256;  // -inf seeds past the last centroid
+
+// ---- centroid preparation ------------------------------------------------------
+// From every row's largest |c| (bit pattern) and ||c||^2: the common scale, whether
+// the split holds for these centroids, the split image and the accumulator seeds.
+// Each workgroup reads all k maxima itself (k floats from L2): the launch that
+// would reduce them first costs more.
+//
+// The scale puts the largest |c| of all centroids at [2^7, 2^8): every coordinate is
+// held to 2^-33 of that maximum or 2^-23 of itself, and points up to 2^8 times larger
+// stay below fp16's 65504 (larger ones, infinities and NaN give NaN scores, which flag
+// their tile for the fp32 kernel).  The absolute part disappears behind the fp32
+// rounding of ||c||^2 (2^-25 of it) as long as no centroid is tiny beside that
+// maximum: ||c|| >= 2^-8 max|c| is asked of every centroid (or ||c|| = 0, whose products
+// are exact).  Centroids with NaN or infinities, or so large or small that the
+// scale's square leaves fp32's range, take the fp32 kernel as well.
+__global__ __launch_bounds__(256) void split_prep_kernel(const float *C, int64_t ldc, int k, int d,
+                                                         const uint32_t *rmax, const float *cn, SplitPrep sp,
+                                                         int64_t ntflag) {
+  __shared__ uint32_t shm[256];
+  __shared__ float shn[256];
+  const int t = threadIdx.x;
+  uint32_t m = 0;
+  float lo = FLT_MAX;
+  for (int j = t; j < k; j += 256) {
+    m = max(m, rmax[j]);
+    const float c = cn[j];
+    if (c != 0.f) lo = fminf(lo, c);
+  }
+  shm[t] = m;
+  shn[t] = lo;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if (t < st) {
+      shm[t] = max(shm[t], shm[t + st]);
+      shn[t] = fminf(shn[t], shn[t + st]);
+    }
+    __syncthreads();
+  }
+  m = shm[0];
+  lo = shn[0];
+  const int e = (int)(m >> 23) - 127;
+  const bool ok = e >= -50 && e <= 50 && lo >= ldexpf(1.0f, 2 * e - 16);
+  const float sc = ldexpf(1.0f, 7 - (ok ? e : 0));
+  const int64_t g0 = (int64_t)blockIdx.x * 256 + t, gs = (int64_t)gridDim.x * 256;
+  if (g0 == 0) *sp.route = SplitRoute{ok ? 1 : 0, sc, -2.0f / (sc * sc), 0};
+  for (int64_t i = g0; i < ntflag; i += gs) sp.tflag[i] = 0;
+  if (!ok) return;
+  for (int64_t j = g0; j < (int64_t)k + kSeedPad; j += gs) sp.seed[j] = j < k ? cn[j] * (-0.5f * sc * sc) : -INFINITY;
+  // one unit: 8 dims of one row
+  const int ch = 2 * ((d + kSD - 1) / kSD);
+  const int64_t units = (int64_t)k * ch;
+  for (int64_t u = g0; u < units; u += gs) {
+    const int64_t row = u / ch;
+    const int c = (int)(u - row * ch);
+    const float *src = C + row * ldc + 8 * c;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+    if (8 * c < d) a = *reinterpret_cast<const f32x4 *>(src);  // d % 4 == 0
+    if (8 * c + 4 < d) b = *reinterpret_cast<const f32x4 *>(src + 4);
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      split2(q < 2 ? a[2 * q] : b[2 * q - 4], q < 2 ? a[2 * q + 1] : b[2 * q - 3], sc, hi[q], lo[q]);
+    uint8_t *dst = sp.img + (int64_t)(c >> 1) * sp.cstage + row * kRow + 16 * (c & 1);
+    *reinterpret_cast<uint4 *>(dst) = uint4{hi[0], hi[1], hi[2], hi[3]};
+    *reinterpret_cast<uint4 *>(dst + 32) = uint4{lo[0], lo[1], lo[2], lo[3]};
+  }
+}
+
+// (score, index) keys as in the other assignment kernels: the order of the keys is
+// the order of (score, index), -0 taken as +0
+__device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
+  uint32_t u = __float_as_uint(sc == 0.0f ? 0.0f : sc);
+  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return ((unsigned long long)u << 32) | (uint32_t)idx;
+}
+
+// ---- assignment ------------------------------------------------------------------
+// 8 waves, 256 points x TC = 64 CB centroids, each wave 32 CB x 64.  A stage is 16
+// dims: of every point 16 floats, of every centroid 16 hi and 16 lo halves, both 64
+// bytes, copied straight into LDS.  Two 32-row blocks share 128-byte LDS rows
+// (block b's row r in half b & 1 of row r), 16-byte chunk c in slot c ^ ((r >> 1) & 7),
+// the conflict-free order for 128-byte rows.  Points are split as they are read.
+//
+// Four buffers and one barrier per stage: step i multiplies stage i from registers
+// while it reads stage i + 1 into them and the copies of stages i + 2 and i + 3 fly
+// (stage i + 3 goes where stage i - 1 was, whose last reads were used in step i - 1).
+// Within a step the points' first block is multiplied while the second is split,
+// and the second while the first of the next stage is read and split and every
+// centroid operand is replaced as it is used: nothing waits behind the barrier.  The
+// largest of acc - s^2 ||c||^2 / 2 wins; the first block's argmax of a tile runs under
+// the second block's MFMAs, the second's under the next tile's first.  (Starting the
+// accumulators at -s^2 ||c||^2 / 2 would save an addition per pair, but then every
+// partial sum rounds at that magnitude: points far from all centroids came out 5 times
+// less exact.)
+//
+// Measured against the fp32 kernel: 10M x 256, k = 4096 158.9 -> 59.5 ms (352 TFLOP/s of
+// fp32 products, 1057 of fp16 ones); 1M x 768, k = 1000 11.6 -> 4.1 ms; 1024 x 768, k =
+// 1000 193 -> 66 us.  What bounds it is power: on random data the chip runs this
+// kernel at 1.6 - 1.8 GHz, and a large f16 library product reaches 1290 - 1310 TFLOP/s;
+// with constant data (few bits toggling) the same pass at 2M points takes 8.9 instead
+// of 11.8 ms.  The matrix cores are busy 56 % of the cycles.
+template <int CB>
+__global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
+  constexpr int TC = 64 * CB;
+  constexpr int NCC = CB / 2;  // centroid copies per wave and stage
+  constexpr int CREG = TC * kRow, STAGE = CREG + kTP * kRow;
+  if (!A.sp.route->ok) return;  // every workgroup: the fp32 kernel takes this call
+  __shared__ __align__(16) uint8_t ring[kRing * STAGE];
+  __shared__ __align__(16) float seeds[4][TC];
+  const int t = threadIdx.x;
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int r = lane & 31, h = lane >> 5;
+  const int wc = wave & 1, wp = wave >> 1;
+  const int NG = A.ngroups;
+  int64_t pt = blockIdx.x;
+  int g = 0;
+  if (NG > 1) {
+    const int64_t l = blockIdx.x >> 3;
+    pt = (l / NG) * 8 + (blockIdx.x & 7);
+    g = (int)(l % NG);
+    if (pt >= A.n_ptiles) return;  // whole workgroup, before any barrier
+  }
+  const int64_t p0 = pt * kTP;
+  const int S = (A.d + kSD - 1) / kSD;
+  const bool ragged = A.d % kSD != 0;
+  const int nct = (A.k + TC - 1) / TC;
+  const int nmy = (nct - g + NG - 1) / NG;
+  const int prmax = (int)min<int64_t>(A.n - 1 - p0, kTP - 1);
+  const float sx = A.sp.route->s;
+  const float *pbase = A.x + p0 * A.ldx;
+  const uint8_t *cbase = A.sp.img + (int64_t)A.coff * kRow;
+
+  // copy j of a region fills its slots 64 j .. 64 j + 63; wave w makes copies w and
+  // w + 8 of the points, and w (and w + 8 for CB = 4) of the centroids.  Copy w + 8
+  // lies 128 rows further on.
+  uint32_t xoff[2], coff;
+  int xchunk;
+  {
+    const int slot = wave * 64 + lane;
+    const int sr = (slot >> 3) & 31, c8 = (slot & 7) ^ ((sr >> 1) & 7);
+    const int row = ((slot >> 8) * 2 + (c8 >> 2)) * 32 + sr;
+    xchunk = c8 & 3;
+    coff = (uint32_t)(row * kRow + 16 * xchunk);
+    xoff[0] = (uint32_t)(min(row, prmax) * (int)A.ldx * 4 + 16 * xchunk);
+    xoff[1] = (uint32_t)(min(row + 128, prmax) * (int)A.ldx * 4 + 16 * xchunk);
+  }
+  const uint32_t ring0 = (uint32_t)(size_t)(lds_byte *)ring;
+  const uint32_t seeds0 = (uint32_t)(size_t)(lds_byte *)seeds;
+  int kc_s = 0, kc_t = 0;  // stage (dims) and tile of the next copy
+  uint32_t kbuf = 0;       // its buffer's offset
+  // the copies of one stage: NCC + 2, and the tile's seeds with its first stage
+  auto copy_stage = [&]() {
+    const int c0 = (g + kc_t * NG) * TC;
+    const uint8_t *cb = cbase + (int64_t)kc_s * A.sp.cstage + (int64_t)c0 * kRow;
+    const float *xb = pbase + kSD * kc_s;
+    const uint32_t l0 = ring0 + kbuf + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < NCC; ++i) lds_copy16_at(cb, coff + 8192u * i, l0 + 8192u * i);
+    if (ragged && kc_s == S - 1) {  // chunks past the last dim hold zeros
+      const bool in = kSD * kc_s + 4 * xchunk < A.d;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (in) {
+          lds_copy16_at(xb, xoff[i], l0 + CREG + 8192u * i);
+        } else {
+          *reinterpret_cast<uint4 *>(ring + kbuf + wave * 1024 + CREG + 8192 * i + 16 * lane) = uint4{0u, 0u, 0u, 0u};
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) lds_copy16_at(xb, xoff[i], l0 + CREG + 8192u * i);
+    }
+    if (kc_s == 0) {
+      // wave w copies the seeds of rows 64 (w mod TC / 64) ..: all waves have the same
+      // number of copies in flight; rows past the last centroid read a -inf
+      const int row = (wave & (TC / 64 - 1)) * 64 + lane;
+      const int j = c0 + row < A.k ? A.coff + c0 + row : A.kall;
+      lds_copy4_at(A.sp.seed, 4u * (uint32_t)j,
+                   seeds0 + 4u * (uint32_t)((kc_t & 3) * TC + (wave & (TC / 64 - 1)) * 64));
+    }
+    if (++kc_s == S) {
+      kc_s = 0;
+      ++kc_t;
+      kc_t = min(kc_t, nmy - 1);  // past the end the last tile again: valid copies that nothing reads
+    }
+    kbuf = kbuf == (kRing - 1) * STAGE ? 0 : kbuf + STAGE;
+  };
+
+  // LDS byte offsets of this lane's operands inside a stage: chunk c of block b is at
+  // (b >> 1) * 4096 + r * 128 + 16 * ((4 (b & 1) + c) ^ ((r >> 1) & 7))
+  const uint32_t lrow = (uint32_t)(r * 128), kx = (uint32_t)((r >> 1) & 7);
+  auto at = [&](int b, int c) -> uint32_t {
+    return (uint32_t)(b >> 1) * 4096u + lrow + 16u * ((4u * (b & 1) + c) ^ kx);
+  };
+  typedef __attribute__((address_space(3))) const i32x4 lds_i32x4;
+  auto rd16 = [&](uint32_t off) -> i32x4 { return *(lds_i32x4 *)(size_t)(ring0 + off); };
+
+  f32x16 acc[CB][2];
+  h16x8 ch[CB], cl[CB];
+  uint32_t xh[2][4], xl[2][4];  // the two point blocks of the stage, split
+  f32x4 w[2][2];                // those of the next stage, as floats
+  float best[2];
+  int code[2];  // 64 * tile + row id of the best, -1 while there is none
+#pragma unroll
+  for (int pb = 0; pb < 2; ++pb) {
+    best[pb] = -INFINITY;
+    code[pb] = -1;
+  }
+  auto read_ch = [&](int cb, uint32_t buf) { ch[cb] = __builtin_bit_cast(h16x8, rd16(buf + at(wc * CB + cb, h))); };
+  auto read_cl = [&](int cb, uint32_t buf) { cl[cb] = __builtin_bit_cast(h16x8, rd16(buf + at(wc * CB + cb, 2 + h))); };
+  auto read_x = [&](int pb, int q, uint32_t buf) {
+    w[pb][q] = __builtin_bit_cast(f32x4, rd16(buf + CREG + at(wp * 2 + pb, 2 * h + q)));
+  };
+  // pair q of a point block
+  auto conv = [&](int pb, int q) {
+    split2(w[pb][q >> 1][2 * (q & 1)], w[pb][q >> 1][2 * (q & 1) + 1], sx, xh[pb][q], xl[pb][q]);
+    asm volatile("" : "+v"(xh[pb][q]), "+v"(xl[pb][q]));
+  };
+  auto op = [&](const uint32_t (&v)[4]) {
+    const i32x4 q = {(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+    return __builtin_bit_cast(h16x8, q);
+  };
+
+  // The largest value acc + seed of one point block of a tile and the first row that
+  // has it (rows ascend with (cb, i) in a lane, and only a larger value takes over,
+  // so the smallest index wins ties).  Maxima first, half an instruction per value,
+  // then the row: the first centroid block that holds the maximum, its 16 values, the
+  // first equal one; with the seeds 2.9 instructions per value where adding,
+  // comparing and two selects take 4.  In twelve pieces, to run between MFMAs.
+  f32x16 z;
+  float mb[CB], mx = 0.f;
+  int id = 0, pos = 0;
+  auto argmax_piece = [&](int j, int pb, int ct) {
+    auto seeds_of = [&](int cb) {
+      const float *sd = seeds[ct & 3] + wc * 32 * CB + 4 * h + 32 * cb;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(sd + 8 * m);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[4 * m + e] = v[e];
+      }
+    };
+    if (j < CB) {
+      if (j == 0) seeds_of(0);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[j][pb][i] += z[i];
+      float m = acc[j][pb][0];
+#pragma unroll
+      for (int i = 1; i < 15; i += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, acc[j][pb][i]), acc[j][pb][i + 1]);
+      mb[j] = __builtin_fmaxf(m, acc[j][pb][15]);
+      asm volatile("" : "+v"(mb[j]));
+      if (j + 1 < CB) seeds_of(j + 1);
+    } else if (j == 4) {
+      mx = mb[0];
+#pragma unroll
+      for (int cb = 1; cb < CB; ++cb) mx = __builtin_fmaxf(mx, mb[cb]);
+      id = 16 * (CB - 1);
+#pragma unroll
+      for (int b = 1; b < CB; ++b) id = mb[CB - 1 - b] == mx ? 16 * (CB - 1 - b) : id;
+      pos = 15;
+      asm volatile("" : "+v"(mx), "+v"(id));
+    } else if (j >= 5 && j < 9) {
+#pragma unroll
+      for (int i = 4 * (j - 5); i < 4 * (j - 4); ++i) {
+        float v = acc[CB - 1][pb][i];
+#pragma unroll
+        for (int b = 1; b < CB; ++b) v = mb[CB - 1 - b] == mx ? acc[CB - 1 - b][pb][i] : v;
+        asm volatile("" : "+v"(v));
+        z[i] = v;
+      }
+    } else if (j == 9 || j == 10) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const int i = (j == 9 ? 15 : 7) - b;
+        pos = z[i] == mx ? i : pos;
+      }
+      asm volatile("" : "+v"(pos));
+    } else if (j == 11) {
+      const bool take = mx > best[pb];
+      best[pb] = take ? mx : best[pb];
+      code[pb] = take ? 64 * ct + id + pos : code[pb];
+      asm volatile("" : "+v"(best[pb]), "+v"(code[pb]));
+    }
+  };
+
+  uint32_t nbuf = 0;  // offset of the buffer that step i reads ahead from (stage i + 1)
+  // One step: 2 x 3 CB slots of one MFMA and what runs beside it, in this order (the
+  // scheduling barriers keep the compiler from gathering the reads, which then wait
+  // for LDS, and the conversions).
+  constexpr int NM = 3 * CB;
+  auto pin = [&]() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto step = [&](int ct, auto first_, auto last_) {
+    constexpr bool FIRST = decltype(first_)::value, LAST = decltype(last_)::value;
+    copy_stage();
+    pin();
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+#pragma unroll
+      for (int j = 0; j < NM; ++j) {
+        const int pr = j / CB, cb = j % CB;
+        const h16x8 a = pr == 0 ? cl[cb] : ch[cb];
+        const h16x8 b = pr == 1 ? op(xl[pb]) : op(xh[pb]);
+        if (FIRST && pr == 0) {
+          const f32x16 zero = {0.f};
+          acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, zero, 0, 0, 0);
+        } else {
+          acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc[cb][pb], 0, 0, 0);
+        }
+        // the next stage's floats of this block, over two slots
+        if (j < 2) read_x(pb, j, nbuf);
+        // the other block's conversion, a pair at a time: the second block of this
+        // stage, then the first of the next
+        constexpr int CS = CB == 4 ? 2 : 1;
+        if (j >= CS && (j - CS) % CS == 0 && (j - CS) / CS < 4) conv(1 - pb, (j - CS) / CS);
+        if (pb == 1) {  // operands used for the last time are replaced
+          if (j >= 1 && j <= CB) read_cl(j - 1, nbuf);
+          if (j >= 2 * CB + 1) read_ch(j - 2 * CB - 1, nbuf);
+        }
+        if ((FIRST && pb == 0) || (LAST && pb == 1)) {
+          if constexpr (CB == 4) {
+            argmax_piece(j, FIRST && pb == 0 ? 1 : 0, FIRST && pb == 0 ? ct - 1 : ct);
+          } else {
+            argmax_piece(2 * j, FIRST && pb == 0 ? 1 : 0, FIRST && pb == 0 ? ct - 1 : ct);
+            argmax_piece(2 * j + 1, FIRST && pb == 0 ? 1 : 0, FIRST && pb == 0 ? ct - 1 : ct);
+          }
+        }
+        pin();
+      }
+    }
+    read_ch(CB - 1, nbuf);
+    // stage i + 2 has landed when only the copies of stage i + 3 are out (a tile's
+    // seeds may be among them: then the wait is for a little more)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCC + 2) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    nbuf = nbuf == (kRing - 1) * STAGE ? 0 : nbuf + STAGE;
+  };
+
+  // before the first tile there is none whose second block's argmax is due: -inf
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[cb][1][i] = -INFINITY;
+  if (t < TC) seeds[3][t] = 0.f;  // the slot of tile -1, and of tile 3, copied no sooner than in tile 0's first step
+  for (int i = 0; i < kRing - 1; ++i) copy_stage();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+#pragma unroll
+  for (int pb = 0; pb < 2; ++pb) {
+    read_x(pb, 0, 0);
+    read_x(pb, 1, 0);
+  }
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    read_ch(cb, 0);
+    read_cl(cb, 0);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) conv(0, q);
+  nbuf = STAGE;
+  constexpr std::true_type T{};
+  constexpr std::false_type F{};
+  for (int ct = 0; ct < nmy; ++ct) {
+    step(ct, T, F);
+    for (int s = 2; s < S; ++s) step(ct, F, F);
+    step(ct, F, T);
+  }
+#pragma unroll
+  for (int j = 0; j < 12; ++j) argmax_piece(j, 1, nmy - 1);
+
+  // the copies past the end are still under way, into the LDS that the merge uses
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  // row ids to centroid indices, then merge the lane halves and the wave halves
+  int bidx[2];
+#pragma unroll
+  for (int pb = 0; pb < 2; ++pb) {
+    const int id = code[pb] & 63;
+    const int row = wc * 32 * CB + (id >> 4) * 32 + ((id >> 2) & 3) * 8 + (id & 3) + 4 * h;
+    bidx[pb] = code[pb] < 0 ? INT_MAX : (g + (code[pb] >> 6) * NG) * TC + row;
+    const float os = __shfl_xor(best[pb], 32);
+    const int oi = __shfl_xor(bidx[pb], 32);
+    if (os > best[pb] || (os == best[pb] && oi < bidx[pb])) {
+      best[pb] = os;
+      bidx[pb] = oi;
+    }
+  }
+  float *ms = reinterpret_cast<float *>(ring);
+  int *mi = reinterpret_cast<int *>(ring + kTP * sizeof(float));
+  if (wc == 1 && h == 0) {
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+      ms[wp * 64 + pb * 32 + r] = best[pb];
+      mi[wp * 64 + pb * 32 + r] = bidx[pb];
+    }
+  }
+  __syncthreads();
+  if (wc == 0 && h == 0) {
+    const float m2 = A.sp.route->m2;
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+      const int pc = wp * 64 + pb * 32 + r;
+      const float os = ms[pc];
+      const int oi = mi[pc];
+      if (os > best[pb] || (os == best[pb] && oi < bidx[pb])) {
+        best[pb] = os;
+        bidx[pb] = oi;
+      }
+      const int64_t p = p0 + pc;
+      if (p < A.n) {
+        if (bidx[pb] == INT_MAX) {  // only NaN scores: the fp32 kernel redoes this tile
+          A.sp.tflag[pt] = 1;
+        } else if (A.keys) {
+          atomicMin(A.keys + p, split_key(best[pb] * m2, bidx[pb]));
+        } else {
+          A.assign[p] = bidx[pb] + A.aoff;
+          if (A.score) A.score[p] = best[pb] * m2;
+        }
+      }
+    }
+  }
+}
+
+}  // namespace
+
+size_t split_bytes(int64_t n, int k, int d) {
+  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t S = (size_t)cdiv(d, kSD);
+  return 256 + al(4 * (size_t)k) + al(4 * ((size_t)k + kSeedPad)) + al(4 * (size_t)cdiv(n, kTP)) +
+         al(S * k * kRow + 256 * kRow);
+}
+
+SplitPrep split_layout(int64_t n, int k, int d, void *ws) {
+  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  uint8_t *w = static_cast<uint8_t *>(ws);
+  SplitPrep sp{};
+  sp.route = reinterpret_cast<SplitRoute *>(w);
+  w += 256;
+  sp.rmax = reinterpret_cast<uint32_t *>(w);
+  w += al(4 * (size_t)k);
+  sp.seed = reinterpret_cast<float *>(w);
+  w += al(4 * ((size_t)k + kSeedPad));
+  sp.tflag = reinterpret_cast<int *>(w);
+  w += al(4 * (size_t)cdiv(n, kTP));
+  sp.img = w;
+  sp.cstage = (int64_t)k * kRow;
+  return sp;
+}
+
+km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d, const float *cn, const SplitPrep &sp,
+                            hipStream_t s) {
+  const int64_t units = (int64_t)k * 2 * cdiv(d, kSD);
+  // every workgroup reads k maxima first: fewer, longer workgroups as k grows
+  const int64_t grid = std::min<int64_t>(std::max<int64_t>(1, cdiv(units, 256)), 512);
+  hipLaunchKernelGGL(split_prep_kernel, dim3((unsigned)grid), dim3(256), 0, s, C, ldc, k, d, sp.rmax, cn, sp,
+                     cdiv(n, kTP));
+  KMQ_LAUNCH_CHECK("split_prep_kernel");
+  return KM_OK;
+}
+
+km_status launch_split_assign(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s) {
+  if (tile_c == 128)
+    hipLaunchKernelGGL(assign_split_kernel<2>, dim3((unsigned)grid), dim3(kThr), 0, s, A);
+  else
+    hipLaunchKernelGGL(assign_split_kernel<4>, dim3((unsigned)grid), dim3(kThr), 0, s, A);
+  KMQ_LAUNCH_CHECK("assign_split_kernel");
+  return KM_OK;
+}
+
+}  // namespace kmq

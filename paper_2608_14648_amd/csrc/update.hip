@@ -57,6 +57,7 @@ struct UpdWs {
   uint32_t *partialA; // [maxchunks] 1-bit formats: sum of the scaled alphas per chunk
   float *partialM;    // [maxchunks] 1-bit formats: largest alpha per chunk; LVQ4: largest scale
   double *partialB;   // [maxchunks] LVQ4: sum of the biases per chunk
+  double *partialO;   // [maxchunks * ceil(d / 256)] F32: squared distances to the old centroid per workgroup
   void *Z;       // [k * dp] float or uint8
   uint8_t *fresh;  // [k]
   int64_t *cntw;   // [k]
@@ -91,6 +92,7 @@ UpdWs carve(const Points &P, int k, void *base, size_t *bytes_out) {
   w.partialA = (uint32_t *)take(sizeof(uint32_t) * (size_t)w.maxchunks);
   w.partialM = (float *)take(sizeof(float) * (size_t)w.maxchunks);
   w.partialB = (double *)take(sizeof(double) * (size_t)w.maxchunks);
+  w.partialO = (double *)take(P.fmt == KM_F32 ? sizeof(double) * (size_t)w.maxchunks * (size_t)cdiv(P.d, 256) : 0);
   w.Z = take(sizeof(float) * (size_t)k * (size_t)w.dp);
   w.fresh = (uint8_t *)take((size_t)k);
   w.cntw = (int64_t *)take(sizeof(int64_t) * (size_t)k);
@@ -276,11 +278,18 @@ __device__ __forceinline__ int find_cluster(const int *choff, int k, int c) {
   return lo;
 }
 
-// fp32 rows: one slice of 256 columns per workgroup
+// fp32 rows: one slice of 256 columns per workgroup.  OBJ: also the squared distances
+// of the members to their centroid before the update (Cold), fp32 per lane (at most
+// 128 members) and fp64 above, one partial per workgroup: the objective of the pass
+// that made the assignment, from rows that are read here anyway (the kernel waits for
+// HBM; the three vector instructions per value are free).
+template <bool OBJ>
 __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t ld, int df, const int *perm,
                                                          const int *cnt, const int *cstart, const int *choff, int k,
-                                                         float *partial, int dp) {
+                                                         float *partial, int dp, const float *Cold,
+                                                         double *partialO) {
   __shared__ f32x4 red[4][64];
+  __shared__ double shd[256];
   const int c = blockIdx.x;
   if (c >= choff[k]) return;
   const int j = find_cluster(choff, k, c);
@@ -290,7 +299,15 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = blockIdx.y * 256 + 4 * lane;
   const bool ok = col < df;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f}, dist = acc, old = acc;
+  if (OBJ && ok) old = *reinterpret_cast<const f32x4 *>(Cold + (int64_t)j * dp + col);
+  auto add = [&](f32x4 v) {
+    acc += v;
+    if (OBJ) {
+      const f32x4 e = v - old;
+      dist += e * e;
+    }
+  };
   int m = m0 + wave;
   for (; m + 28 < m1; m += 32) {
     int pp[8];
@@ -301,12 +318,12 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = *reinterpret_cast<const f32x4 *>(X + (int64_t)pp[e] * ld + col);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc += v[e];
+      for (int e = 0; e < 8; ++e) add(v[e]);
     }
   }
   for (; m < m1; m += 4) {
     const int p = perm[m];
-    if (ok) acc += *reinterpret_cast<const f32x4 *>(X + (int64_t)p * ld + col);
+    if (ok) add(*reinterpret_cast<const f32x4 *>(X + (int64_t)p * ld + col));
   }
   red[wave][lane] = acc;
   __syncthreads();
@@ -317,6 +334,23 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
     s += red[3][lane];
     *reinterpret_cast<f32x4 *>(partial + (int64_t)c * dp + col) = s;
   }
+  if (OBJ) {
+    const double o = block_sum_f64((double)dist[0] + dist[1] + dist[2] + dist[3], shd);
+    if (threadIdx.x == 0) partialO[(int64_t)c * gridDim.y + blockIdx.y] = o;
+  }
+}
+
+// The objective from segsum_f32_kernel's partials (`slices` per chunk): NaN when a
+// point belongs to no cluster (its row holds NaN) or the sum is not finite.
+__global__ __launch_bounds__(256) void objective_fold_kernel(const double *partialO, const int *choff, const int *cstart,
+                                                             const int *cnt, int k, int slices, int64_t n,
+                                                             double *out) {
+  __shared__ double shd[256];
+  double s = 0.0;
+  const int64_t np = (int64_t)choff[k] * slices;
+  for (int64_t i = threadIdx.x; i < np; i += 256) s += partialO[i];
+  s = block_sum_f64(s, shd);
+  if (threadIdx.x == 0) *out = (int64_t)cstart[k - 1] + cnt[k - 1] == n && isfinite(s) ? s : (double)NAN;
 }
 
 // bfloat16 rows: one slice of 512 columns per workgroup; lane = 8 values (16 bytes),
@@ -870,7 +904,7 @@ km_status launch_cluster_sort(const int32_t *assign, int64_t n, int k, void *ws,
 }
 
 km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, int64_t *counts, int policy,
-                        void *ws, hipStream_t s, const int *seg_lo, const int *seg_hi) {
+                        void *ws, hipStream_t s, const int *seg_lo, const int *seg_hi, double *objective) {
   UpdWs w = carve(P, k, ws, nullptr);
   km_status sst = launch_sort(assign, P.n, k, w, s);
   if (sst != KM_OK) return sst;
@@ -910,9 +944,17 @@ km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, 
       hipLaunchKernelGGL(segsum_bf16_kernel, dim3(w.maxchunks, (unsigned)cdiv(d, 512)), dim3(256), 0, s,
                          static_cast<const uint16_t *>(P.data), P.ld, d, w.perm, w.cnt, w.cstart, w.choff, k,
                          static_cast<float *>(w.partial), w.dp);
-    if (df > 0)
-      hipLaunchKernelGGL(segsum_f32_kernel, dim3(w.maxchunks, (unsigned)cdiv(df, 256)), dim3(256), 0, s, F, fld, df,
-                         w.perm, w.cnt, w.cstart, w.choff, k, static_cast<float *>(w.partial), w.dp);
+    const unsigned slices = (unsigned)cdiv(df, 256);
+    if (objective && P.fmt == KM_F32) {
+      hipLaunchKernelGGL(segsum_f32_kernel<true>, dim3(w.maxchunks, slices), dim3(256), 0, s, F, fld, df, w.perm,
+                         w.cnt, w.cstart, w.choff, k, static_cast<float *>(w.partial), w.dp,
+                         static_cast<const float *>(C), w.partialO);
+      hipLaunchKernelGGL(objective_fold_kernel, dim3(1), dim3(256), 0, s, w.partialO, w.choff, w.cstart, w.cnt, k,
+                         (int)slices, P.n, objective);
+    } else if (df > 0) {
+      hipLaunchKernelGGL(segsum_f32_kernel<false>, dim3(w.maxchunks, slices), dim3(256), 0, s, F, fld, df, w.perm,
+                         w.cnt, w.cstart, w.choff, k, static_cast<float *>(w.partial), w.dp, nullptr, nullptr);
+    }
     const int d_bits = P.fmt == KM_HYBRID ? P.d_front : 0;
     if (is_bits_fmt(P.fmt)) {
       const int dt = d - d_bits;

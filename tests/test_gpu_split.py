@@ -1,0 +1,155 @@
+"""fp32 assignment on the fp16 matrix cores (csrc/split.hip): tile edges, odd sizes, and the
+inputs that go back to the fp32 kernel (whole calls by their centroids, single tiles by their points).
+
+Score bound: a dot product is rounded 6 times per 16 dims, each time by at most 2^-23 of a partial sum
+(<= ||x|| ||c||), the split leaves out 3 2^-22 ||x|| ||c||, and ||c||^2 and the score are rounded to fp32.
+"""
+import numpy as np
+import pytest
+
+from gpu_util import NEAR_TIE_REL, host, to_dev, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    return torch_cuda()
+
+
+@pytest.fixture(scope="module")
+def km(torch):
+    import paper_2608_14648_amd as m
+    m.lib()
+    return m
+
+
+def points(n, d, k, seed, spread=0.2):
+    g = np.random.default_rng(seed)
+    C = g.standard_normal((k, d)).astype(np.float32)
+    X = (C[g.integers(0, k, n)] + spread * g.standard_normal((n, d))).astype(np.float32)
+    return X, C
+
+
+def check(X, C, a, sc, rows=None):
+    """a, sc against 64-bit scores on the given rows."""
+    rows = np.arange(len(X)) if rows is None else rows
+    Xd, Cd = X[rows].astype(np.float64), C.astype(np.float64)
+    cn, xn = (Cd ** 2).sum(1), (Xd ** 2).sum(1)
+    s = cn - 2 * (Xd @ Cd.T)
+    got, best = a[rows], s.argmin(1)
+    assert got.min() >= 0 and got.max() < len(C)
+    i = np.arange(len(rows))
+    gap = (s[i, got] - s[i, best]) / np.maximum(xn + np.maximum(cn[got], cn[best]), 1e-300)
+    assert gap.max() <= NEAR_TIE_REL, gap.max()
+    steps = 6 * -(-X.shape[1] // 16)
+    xc = np.sqrt(xn * cn[got])
+    bound = 2 * (steps * 2.0 ** -23 + 3 * 2.0 ** -22) * xc + 2.0 ** -22 * (cn[got] + np.abs(s[i, got]))
+    err = np.abs(sc[rows].astype(np.float64) - s[i, got])
+    assert (err <= bound).all(), (err / bound).max()
+    return xn + s[i, got]
+
+
+# k around the 128- and 256-centroid tiles and the centroid-tile groups, n around the 256-point tile, d from the
+# smallest split one (two stages of 16 dims) through ragged last stages
+@pytest.mark.parametrize("n,d,k", [(1, 32, 1), (5, 36, 2), (255, 32, 127), (256, 48, 128), (257, 44, 129), (300, 100, 255),
+                                   (513, 64, 257), (1000, 132, 513), (3000, 96, 1100), (700, 772, 300), (64, 2048, 40)])
+def test_edges(km, torch, n, d, k):
+    X, C = points(n, d, k, n + d + k)
+    a, sc, obj = km.kmeans_assign(km.points_f32(to_dev(X, torch)), to_dev(C, torch), objective=True)
+    dist = check(X, C, host(a), host(sc))
+    # summed from the distances: fp32 squares of fp32 differences, fp64 sums
+    assert abs(host(obj)[0] - dist.sum()) <= 2.0 ** -20 * dist.sum() + 1e-12 * (X.astype(np.float64) ** 2).sum()
+
+
+def test_smallest_index_wins(km, torch):
+    """Equal centroids in other blocks, lane halves, wave halves, tiles and groups of the sweep."""
+    n, d, k = 700, 64, 1300
+    X, C = points(n, d, k, 3, spread=0.0)
+    for src, copies in {5: (9, 37, 133, 300, 1299), 64: (68, 200, 700), 250: (251, 255, 513)}.items():
+        C[list(copies)] = C[src]
+    X[:300] = C[[5, 64, 250] * 100]
+    a, _, _ = km.kmeans_assign(km.points_f32(to_dev(X, torch)), to_dev(C, torch))
+    np.testing.assert_array_equal(host(a)[:300], [5, 64, 250] * 100)
+
+
+@pytest.mark.parametrize("how", ["tiny_centroid", "zero_centroid", "wide_centroids", "huge", "small", "far_points"])
+@pytest.mark.parametrize("k", [60, 300])
+def test_ranges(km, torch, how, k):
+    """Scales at and past the ends of what the split takes: results keep the fp32 kernel's bound."""
+    n, d = 900, 96
+    X, C = points(n, d, k, 11)
+    if how == "tiny_centroid":      # 2^-12 of the others: the fp32 kernel takes the call
+        C[7] *= np.float32(2.0 ** -12)
+        X[::9] = C[7] * np.float32(1.25)
+    elif how == "zero_centroid":    # its products are exact
+        C[7] = 0
+        X[::9] *= np.float32(2.0 ** -10)
+    elif how == "wide_centroids":   # within 2^-8
+        C[::3] *= np.float32(2.0 ** -5)
+        X[::9] = C[3] * np.float32(1.25)
+    elif how == "huge":
+        X, C = X * np.float32(2.0 ** 55), C * np.float32(2.0 ** 55)
+    elif how == "small":
+        X, C = X * np.float32(2.0 ** -55), C * np.float32(2.0 ** -55)
+    else:                           # past fp16's range at the centroids' scale: their tile goes to the fp32 kernel
+        X[300] *= np.float32(2.0 ** 14)
+        X[301] *= np.float32(2.0 ** 7)
+    a, sc, obj = km.kmeans_assign(km.points_f32(to_dev(X, torch)), to_dev(C, torch), objective=True)
+    dist = check(X, C, host(a), host(sc))
+    assert abs(host(obj)[0] - dist.sum()) <= 2.0 ** -20 * dist.sum() + 1e-12 * (X.astype(np.float64) ** 2).sum()
+
+
+@pytest.mark.parametrize("k", [60, 300, 2600])
+def test_not_finite(km, torch, k):
+    """Rows with NaN or infinities: they answer as in the fp32 kernel and leave the others alone; the objective is NaN."""
+    n, d = 3000, 64
+    X, C = points(n, d, k, 5)
+    X[260, 3], X[700, 63] = np.nan, np.inf
+    P = km.points_f32(to_dev(X, torch))
+    a, sc, obj = km.kmeans_assign(P, to_dev(C, torch), objective=True)
+    a, sc = host(a), host(sc)
+    check(X, C, a, sc, np.setdiff1d(np.arange(n), [260, 700]))
+    assert a[260] == np.iinfo(np.int32).max and sc[260] == np.inf  # no score is smaller than the start's
+    assert a[700] == np.nonzero(C[:, 63] > 0)[0][0] and sc[700] == -np.inf
+    assert np.isnan(host(obj)[0])
+    Cn, _, J = km.kmeans_fit(P, k, 1, C=to_dev(C, torch))  # the fit's objective comes from its update
+    assert np.isnan(host(J)).all()
+    C[k // 2, 1] = np.nan  # a centroid with NaN never wins
+    a, _, _ = km.kmeans_assign(P, to_dev(C, torch))
+    assert not (host(a) == k // 2).any()
+
+
+def test_fit_objective(km, torch):
+    """Every pass's objective (from the update that follows it, the last one directly) against 64 bits, with rows
+    that have a stride and with the last update from raw rows."""
+    n, d, k, T = 5000, 68, 90, 3
+    X, C = points(n, d, k, 8, spread=1.0)
+    wide = torch.zeros((n, 80), device="cuda")
+    wide[:, :d] = to_dev(X, torch)
+    raw = to_dev(X[::-1], torch)
+    for Xt, r in ((to_dev(X, torch), None), (wide[:, :d], None), (to_dev(X, torch), raw)):
+        P = km.Points(km.KM_F32, Xt, d, raw=r)
+        _, _, J = km.kmeans_fit(P, k, T, C=to_dev(C, torch))
+        Ct, want = C.astype(np.float64), []
+        for t in range(T + 1):
+            s = (Ct ** 2).sum(1) - 2 * (X.astype(np.float64) @ Ct.T)
+            a = s.argmin(1)
+            want.append(((X - Ct[a]) ** 2).sum())
+            src = X[::-1] if r is not None and t == T - 1 else X
+            for j in range(k):
+                if (a == j).any():
+                    Ct[j] = src[a == j].astype(np.float64).mean(0)
+        np.testing.assert_allclose(host(J), want, rtol=1e-5)
+
+
+def test_noalloc_past_its_scratch(km, torch):
+    """A split image of 80 MB does not fit the static 64 MiB: the call is taken by the fp32 kernel, as before."""
+    n, d, k = 300, 1024, 20000
+    X, C = points(n, d, k, 2)
+    P, Ct = km.points_f32(to_dev(X, torch)), to_dev(C, torch)
+    a = torch.empty(n, dtype=torch.int32, device="cuda")
+    sc = torch.empty(n, device="cuda")
+    km.kmeans_assign_noalloc(P, Ct, a, sc)
+    b, _, _ = km.kmeans_assign(P, Ct)
+    np.testing.assert_array_equal(host(a), host(b))

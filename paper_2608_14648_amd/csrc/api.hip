@@ -190,7 +190,7 @@ static km_status check_points(const km_points *P, Points *out) {
       KMQ_CHECK(P->d_front == 0, KM_EINVAL, "d_front must be 0 for this format");
     }
   }
-  p.split = fmt == KM_F32 && p.d >= 32;
+  p.split = fmt == KM_F32 ? p.d >= 32 : fmt == KM_HYBRID && p.d - p.d_front <= 32 * kSplitTailWords;
   *out = p;
   return KM_OK;
 }
@@ -363,7 +363,7 @@ static km_status assign_on(const Points &p, const void *C, int32_t k, int32_t *a
   if (st != KM_OK) return st;
   st = launch_assign(p, C, cp, k, assign, sc, s);
   if (st != KM_OK) return st;
-  if (objective && p.split) return launch_direct_objective(p, static_cast<const float *>(C), k, assign, objective, part, s);
+  if (objective && p.split) return launch_direct_objective(p, static_cast<const float *>(C), cp, k, assign, objective, part, s);
   if (objective) {
     st = launch_xconst(p, xc, s);
     if (st != KM_OK) return st;
@@ -515,10 +515,11 @@ static km_status fit_on(const Points &p, int k, int iters, const int64_t *init_i
   km_status st;
   const size_t b_prep = al(prep_bytes(p, k));
   const size_t b_upd = al(std::max(update_bytes(p, k), p.raw ? update_bytes(raw_points(p), k) : (size_t)0));
-  // p.split: the objective of a pass is summed by the update that follows it, from the
-  // rows that reads, and directly where none does or it reads the raw rows
+  // direct: the objective of a pass over fp32 points is summed by the update that follows
+  // it, from the rows that reads; by a pass of its own where none does or it reads the
+  // raw rows, and for hybrid points
   const bool direct = objective && p.split;
-  const bool scores = objective && !p.split;
+  const bool scores = objective && !direct;
   const size_t b_score = scores ? al(sizeof(float) * (size_t)p.n) : 0;
   const size_t b_xc = scores ? al(sizeof(float) * (size_t)p.n) : 0;
   const size_t b_part = direct ? al(direct_objective_bytes())
@@ -544,9 +545,10 @@ static km_status fit_on(const Points &p, int k, int iters, const int64_t *init_i
     KMQ_STAGE(clk, kStPrep, launch_prep(p, C, k, wprep, &cp, s));
     KMQ_STAGE(clk, kStAssign, launch_assign(p, C, cp, k, assign, sc, s));
     const bool from_raw = p.raw && it == iters - 1;  // the last update averages the raw rows (Sec. 4.1)
-    if (direct && (it == iters || from_raw))
+    const bool by_update = direct && p.fmt == KM_F32 && it < iters && !from_raw;
+    if (direct && !by_update)
       KMQ_STAGE(clk, kStOther,
-                launch_direct_objective(p, static_cast<const float *>(C), k, assign, objective + it, part, s));
+                launch_direct_objective(p, static_cast<const float *>(C), cp, k, assign, objective + it, part, s));
     if (scores)
       KMQ_STAGE(clk, kStOther, launch_objective(p, xc, sc, p.n, objective + it, part, objective_blocks(p.n), s));
     if (it == iters) break;  // the last pass only assigns (the final STEP 2)
@@ -554,7 +556,7 @@ static km_status fit_on(const Points &p, int k, int iters, const int64_t *init_i
       KMQ_STAGE(clk, kStUpdate, launch_update(raw_points(p), assign, k, C, nullptr, policy, wupd, s));
     } else {
       KMQ_STAGE(clk, kStUpdate, launch_update(p, assign, k, C, nullptr, policy, wupd, s, nullptr, nullptr,
-                                              direct ? objective + it : nullptr));
+                                              by_update ? objective + it : nullptr));
     }
   }
   return KM_OK;
@@ -896,7 +898,7 @@ static km_status fit_pruned_on(const Points &p, int k, int iters, const int64_t 
     KMQ_STAGE(clk, kStPrep, launch_prep(p, C, k, wprep, &cp, s));
     KMQ_STAGE(clk, kStAssign, launch_assign(p, C, cp, k, assign, sc, s));
     if (objective && p.split)
-      KMQ_STAGE(clk, kStOther, launch_direct_objective(p, static_cast<const float *>(C), k, assign, objective, part, s));
+      KMQ_STAGE(clk, kStOther, launch_direct_objective(p, static_cast<const float *>(C), cp, k, assign, objective, part, s));
     if (scores) {
       KMQ_STAGE(clk, kStOther, launch_xconst(p, xc, s));
       KMQ_STAGE(clk, kStOther, launch_objective(p, xc, sc, p.n, objective, part, objective_blocks(p.n), s));

@@ -79,7 +79,7 @@ struct AssignArgs {
   // [segs[i].z, + segs[i].w) (indices into the full centroid and prepared arrays)
   const int4 *segs;
   const int2 *tiles;
-  // fp32 kernel behind the split kernel (route set): only the point tiles flagged
+  // fp32 or hybrid kernel behind the split kernel (route set): only the point tiles flagged
   // there, or all of them when the route says so
   const SplitRoute *route;
   const int *tflag;
@@ -105,11 +105,6 @@ __device__ __forceinline__ float key_score(unsigned long long key) {
   uint32_t u = (uint32_t)(key >> 32);
   u = (u & 0x80000000u) ? (u & 0x7fffffffu) : ~u;
   return __uint_as_float(u);
-}
-
-__device__ __forceinline__ uint32_t spread4(uint32_t b4) {
-  // 4 bits -> 4 bytes holding 0 or 1 (bit j -> byte j)
-  return (b4 * 0x00204081u) & 0x01010101u;
 }
 
 template <int FMT>
@@ -922,23 +917,6 @@ constexpr int kBTC = 128;  // centroids per tile
 constexpr int kBStageBytes = kBTC * kRowBytes;
 constexpr int kBWordsSmall = 32;  // 4-wave shape: d - d0 <= 1024
 constexpr int kBWordsLarge = 40;  // 8-wave shape: d - d0 <= 1280
-
-__device__ __forceinline__ uint32_t regroup_bits(uint32_t w) {
-  uint32_t o = 0;
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) o |= spread4((w >> (16 * h + 4 * q)) & 15u) << (4 * h + q);
-  return o;
-}
-
-// x: a regrouped word shifted right by 4h.  Register q takes bit 8j + q of x as
-// byte j with the value 0 or 2, so the products sum to 2D; seeded with -T the
-// accumulator ends at 2D - T.
-__device__ __forceinline__ i32x4 widen_regrouped2(uint32_t x) {
-  constexpr uint32_t M2 = 0x02020202u;
-  return i32x4{(int)((x << 1) & M2), (int)(x & M2), (int)((x >> 1) & M2), (int)((x >> 2) & M2)};
-}
 
 // Direct copy of 16 bytes per lane from global memory into LDS: the wave's 64 lanes
 // fill 1 KB at LDS byte address lds (wave-uniform) in lane order.  Written as
@@ -2136,6 +2114,7 @@ __global__ __launch_bounds__(kQThreads, 1) void assign_hyb_kernel(AssignArgs A) 
     g = (int)(l % NG);
     if (pt >= A.n_ptiles) return;  // whole workgroup, before any barrier
   }
+  if (A.route && A.route->ok && !A.tflag[pt]) return;
   const int64_t p0 = pt * TP;
   const int SI = (A.di + kRowBytes - 1) / kRowBytes;  // tail stages
   const int SF = (A.df + 31) / 32;                    // front stages
@@ -2813,35 +2792,84 @@ __global__ __launch_bounds__(256) void cost_kernel(const float *X, int64_t n, in
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-// ---- objective of fp32 points from the distances: sum ||x - c_a||^2 -----------------
+// ---- objective from the distances: sum ||x - c_a||^2 --------------------------------
 // One pass over the rows, as the point-only terms ||x||^2 need, and no cancellation: for
 // points close to their centroid ||x||^2 + score is a small difference whose rounding
 // adds up over the points.  One wave per point at a time, fp32 per lane and point, fp64
 // above; HBM bound.  A point without a centroid (its row holds NaN) or a sum that is
-// not finite gives NaN.
+// not finite gives NaN.  HYB: the front dims like that, plus the tail's score
+// sigma^2 Q - alpha 2 sigma (2D - T) and its point-only term alpha^2 (d - d0), in fp64.
+template <bool HYB>
 __global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, int64_t n, int d, int64_t ldx,
-                                                               const float *C, int k, const int32_t *assign,
+                                                               const float *C, int64_t ldc, int k,
+                                                               const int32_t *assign, Points P, CentroidPrep cp,
                                                                double *partials) {
   __shared__ double sh[256];
+  constexpr int NP = 4;  // points at a time: their loads are in flight together
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   double s = 0.0;
   const int64_t stride = (int64_t)gridDim.x * 4;
-  for (int64_t p = (int64_t)blockIdx.x * 4 + wv; p < n; p += 2 * stride) {
-    // two points at a time: their loads are in flight together
-    const int64_t p2 = min<int64_t>(p + stride, n - 1);
-    const int a0 = assign[p], a1 = assign[p2];
-    const bool in0 = a0 >= 0 && a0 < k, in1 = a1 >= 0 && a1 < k;
-    const float *x0 = X + p * ldx, *x1 = X + p2 * ldx;
-    const float *c0 = C + (int64_t)(in0 ? a0 : 0) * d, *c1 = C + (int64_t)(in1 ? a1 : 0) * d;
-    f32x4 t0 = {0.f, 0.f, 0.f, 0.f}, t1 = t0;
-    for (int i = 4 * lane; i < d; i += 256) {
-      const f32x4 e0 = *reinterpret_cast<const f32x4 *>(x0 + i) - *reinterpret_cast<const f32x4 *>(c0 + i);
-      const f32x4 e1 = *reinterpret_cast<const f32x4 *>(x1 + i) - *reinterpret_cast<const f32x4 *>(c1 + i);
-      t0 += e0 * e0;
-      t1 += e1 * e1;
+  const int dt = P.d - P.d_front;
+  for (int64_t p = (int64_t)blockIdx.x * 4 + wv; p < n; p += NP * stride) {
+    int64_t pt[NP];
+    int a[NP];
+    bool in[NP];
+    const float *x[NP], *c[NP];
+#pragma unroll
+    for (int e = 0; e < NP; ++e) {
+      pt[e] = min<int64_t>(p + e * stride, n - 1);
+      const int j = assign[pt[e]];
+      in[e] = j >= 0 && j < k;
+      a[e] = in[e] ? j : 0;
+      x[e] = X + pt[e] * ldx;
+      c[e] = C + (int64_t)a[e] * ldc;
     }
-    s += in0 ? (double)t0[0] + t0[1] + t0[2] + t0[3] : (double)NAN;
-    if (p + stride < n) s += in1 ? (double)t1[0] + t1[1] + t1[2] + t1[3] : (double)NAN;
+    int D[NP] = {0, 0, 0, 0};
+    if constexpr (HYB) {
+      for (int i = 16 * lane; i < dt; i += 1024) {
+        uint4 q[NP];
+        uint32_t w[NP];
+#pragma unroll
+        for (int e = 0; e < NP; ++e) {
+          q[e] = *reinterpret_cast<const uint4 *>(cp.q + (int64_t)a[e] * dt + i);
+          w[e] = static_cast<const uint32_t *>(P.data)[pt[e] * (P.d / 32) + (P.d_front + i) / 32] >> (i & 16);
+        }
+#pragma unroll
+        for (int e = 0; e < NP; ++e) {
+          D[e] = __builtin_amdgcn_sdot4((int)q[e].x, (int)spread4(w[e] & 15u), D[e], false);
+          D[e] = __builtin_amdgcn_sdot4((int)q[e].y, (int)spread4((w[e] >> 4) & 15u), D[e], false);
+          D[e] = __builtin_amdgcn_sdot4((int)q[e].z, (int)spread4((w[e] >> 8) & 15u), D[e], false);
+          D[e] = __builtin_amdgcn_sdot4((int)q[e].w, (int)spread4((w[e] >> 12) & 15u), D[e], false);
+        }
+      }
+    }
+    f32x4 t[NP];
+#pragma unroll
+    for (int e = 0; e < NP; ++e) t[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 4 * lane; i < d; i += 256) {
+      f32x4 xv[NP], cv[NP];
+#pragma unroll
+      for (int e = 0; e < NP; ++e) {
+        xv[e] = *reinterpret_cast<const f32x4 *>(x[e] + i);
+        cv[e] = *reinterpret_cast<const f32x4 *>(c[e] + i);
+      }
+#pragma unroll
+      for (int e = 0; e < NP; ++e) {
+        const f32x4 df = xv[e] - cv[e];
+        t[e] += df * df;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < NP; ++e) {
+      if (p + e * stride >= n) continue;
+      s += in[e] ? (double)t[e][0] + t[e][1] + t[e][2] + t[e][3] : (double)NAN;
+      // alpha 2 sigma per set bit less T, on every lane's own dims; the point's terms on lane 0
+      if (HYB && in[e]) {
+        const double al = P.alpha[pt[e]], v = al * cp.sig2[a[e]];
+        s -= v * (2 * D[e]);
+        if (lane == 0) s += v * cp.qsum[a[e]] + cp.u[a[e]] + al * al * dt;
+      }
+    }
   }
   s = block_sum_f64(s, sh);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
@@ -2901,9 +2929,10 @@ int assign_groups(const Points &P, int k) {
 
 SplitArgs split_args(const Points &P, const CentroidPrep &cp, int k, int32_t *assign, float *score) {
   SplitArgs B{};
-  B.x = static_cast<const float *>(P.data);
-  B.ldx = P.ld;
-  B.d = P.d;
+  const bool hyb = P.fmt == KM_HYBRID;
+  B.x = hyb ? P.front : static_cast<const float *>(P.data);
+  B.ldx = hyb ? P.d_front : P.ld;
+  B.d = hyb ? P.d_front : P.d;
   B.sp = cp.sp;
   B.kall = (int)(cp.sp.cstage / 64);
   B.k = k;
@@ -3050,6 +3079,24 @@ km_status launch_assign_t(const Points &P, const void *C, const CentroidPrep &cp
       hipLaunchKernelGGL(keys_init_kernel, gp, dim3(256), 0, s, cp.keys, P.n);
     }
     const dim3 grid((unsigned)(ng > 1 ? cdiv(npt, 8) * 8 * ng : npt));
+    if (cp.sp.route) {
+      SplitArgs B = split_args(P, cp, k, assign, score);
+      B.aoff = aoff;
+      B.ngroups = ng;
+      B.n_ptiles = npt;
+      B.keys = A.keys;
+      B.pbits = A.pbits;
+      B.pbw = A.pbw;
+      B.pbw0 = A.pbw0;
+      B.ci8 = A.ci8;
+      B.cild = A.cild;
+      B.di = A.di;
+      B.alpha = A.alpha;
+      const km_status st = launch_split_assign(B, grid.x, q8_tile_centroids(k), s);
+      if (st != KM_OK) return st;
+      A.route = cp.sp.route;
+      A.tflag = cp.sp.tflag;
+    }
     if (q8_tile_centroids(k) == 128)
       hipLaunchKernelGGL((assign_hyb_kernel<2>), grid, dim3(kQThreads), 0, s, A);
     else
@@ -3091,10 +3138,15 @@ static size_t prep_codes_bytes(const Points &P, int k) {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+static size_t split_scratch(const Points &P, int k) {
+  const bool hyb = P.fmt == KM_HYBRID;
+  return split_bytes(P.n, k, hyb ? P.d_front : P.d, hyb);
+}
+
 size_t prep_bytes(const Points &P, int k) {
   size_t b = align256(16 * (size_t)k) + align256(prep_codes_bytes(P, k));
   if (assign_groups(P, k) > 1) b += align256(8 * (size_t)P.n);
-  if (P.split) b += split_bytes(P.n, k, P.d);
+  if (P.split) b += split_scratch(P, k);
   return b;
 }
 
@@ -3116,16 +3168,14 @@ km_status launch_prep(const Points &P, const void *C, int k, void *ws, CentroidP
   out->q = q;
   out->cb = cb;
   out->sp = SplitPrep{};
-  if (P.split) out->sp = split_layout(P.n, k, P.d, w + prep_bytes(P, k) - split_bytes(P.n, k, P.d));
+  if (P.split)
+    out->sp = split_layout(P.n, k, P.fmt == KM_HYBRID ? P.d_front : P.d, P.fmt == KM_HYBRID,
+                           w + prep_bytes(P, k) - split_scratch(P, k));
   const int d0 = P.fmt == KM_HYBRID ? P.d_front : 0;
   switch (P.fmt) {
     case KM_F32:
       hipLaunchKernelGGL(prep_kernel<KM_F32>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb,
                          out->sp.rmax);
-      if (P.split) {
-        const km_status st = launch_split_prep(static_cast<const float *>(C), P.d, P.n, k, P.d, cn, out->sp, s);
-        if (st != KM_OK) return st;
-      }
       break;
     case KM_BF16:
       hipLaunchKernelGGL(prep_kernel<KM_BF16>, dim3(k), dim3(256), 0, s, C, k, P.d, 0, nullptr, cn, qsum, u, sig2, q, cb,
@@ -3150,12 +3200,14 @@ km_status launch_prep(const Points &P, const void *C, int k, void *ws, CentroidP
     case KM_HYBRID:
       hipLaunchKernelGGL(prep_kernel<KM_HYBRID>, dim3(k), dim3(256), 0, s, C, k, P.d, d0, P.center, cn, qsum, u,
                          sig2, q, cb,
-                         nullptr);
+                         out->sp.rmax);
       break;
     default:
       return KM_EUNSUPPORTED;
   }
   KMQ_LAUNCH_CHECK("prep_kernel");
+  if (P.split)
+    return launch_split_prep(static_cast<const float *>(C), P.d, P.n, k, P.fmt == KM_HYBRID ? P.d_front : P.d, *out, s);
   return KM_OK;
 }
 
@@ -3286,11 +3338,15 @@ km_status launch_objective(const Points &P, const float *xc, const float *score,
 
 size_t direct_objective_bytes() { return sizeof(double) * kDirectBlocks; }
 
-km_status launch_direct_objective(const Points &P, const float *C, int k, const int32_t *assign, double *out,
-                                  double *partials, hipStream_t s) {
+km_status launch_direct_objective(const Points &P, const float *C, const CentroidPrep &cp, int k,
+                                  const int32_t *assign, double *out, double *partials, hipStream_t s) {
   const int nb = (int)std::min<int64_t>(kDirectBlocks, cdiv(P.n, 4));
-  hipLaunchKernelGGL(direct_objective_kernel, dim3(nb), dim3(256), 0, s, static_cast<const float *>(P.data), P.n, P.d,
-                     P.ld, C, k, assign, partials);
+  if (P.fmt == KM_HYBRID)
+    hipLaunchKernelGGL(direct_objective_kernel<true>, dim3(nb), dim3(256), 0, s, P.front, P.n, P.d_front,
+                       (int64_t)P.d_front, C, (int64_t)P.d, k, assign, P, cp, partials);
+  else
+    hipLaunchKernelGGL(direct_objective_kernel<false>, dim3(nb), dim3(256), 0, s, static_cast<const float *>(P.data),
+                       P.n, P.d, P.ld, C, (int64_t)P.d, k, assign, P, cp, partials);
   hipLaunchKernelGGL(direct_objective_sum_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
   KMQ_LAUNCH_CHECK("direct objective");
   return KM_OK;

@@ -31,7 +31,7 @@ struct Points {
   const float *raw;    // nullable: fp32 rows in the clustering space (last update of a fit)
   int64_t raw_ld;
   const float *vparams;  // LVQ4: per-vector (s, b, A, N)
-  bool split;            // F32: assignments take the fp16 matrix cores (split.hpp) where the data allow
+  bool split;            // F32, HYBRID: assignments take the fp16 matrix cores (split.hpp) where the data allow
 };
 
 // 1-bit point formats (codes + one scale per point)
@@ -53,6 +53,7 @@ struct SplitPrep {
   uint32_t *rmax;     // [k] bit pattern of the row's largest |c|
   float *seed;        // [k + pad] -s^2 ||c||^2 / 2, then -inf
   int *tflag;         // point tiles the fp32 kernel has to redo
+  float *tail;        // HYBRID: -T (int bits), u and 2 sigma times -s^2 / 2, k + pad each; else NULL
   uint8_t *img;       // stage-major: 64 bytes (16 hi, 16 lo halves) of every row per 16 dims
   int64_t cstage;     // bytes of one stage of img
 };
@@ -67,7 +68,7 @@ struct CentroidPrep {
                        // 0..15, k x d, each 8 dims ordered 0 2 4 6 1 3 5 7 (the unpacked point order)
   const uint16_t *cb;  // BF16: centroids rounded to bfloat16, k x d
   unsigned long long *keys;  // centroid-tile groups (F32/HYBRID/SQ8/BF16/LVQ4): per-point (score, index) keys
-  SplitPrep sp;              // F32 with Points::split
+  SplitPrep sp;              // F32 and HYBRID with Points::split
 };
 
 // Host-side error plumbing.
@@ -120,9 +121,9 @@ km_status launch_xconst(const Points &P, float *xc, hipStream_t s);
 km_status launch_objective(const Points &P, const float *xc, const float *score, int64_t n, double *out,
                            double *partials, int nblk_max, hipStream_t s);
 int objective_blocks(int64_t n);
-// the same sum for fp32 points from the distances themselves (direct_objective_bytes of partials)
-km_status launch_direct_objective(const Points &P, const float *C, int k, const int32_t *assign, double *out,
-                                  double *partials, hipStream_t s);
+// the same sum for fp32 and hybrid points from the distances (direct_objective_bytes of partials)
+km_status launch_direct_objective(const Points &P, const float *C, const CentroidPrep &cp, int k,
+                                  const int32_t *assign, double *out, double *partials, hipStream_t s);
 size_t direct_objective_bytes();
 km_status launch_gather_init(const Points &P, const int64_t *idx, int k, void *C, hipStream_t s);
 km_status launch_cost(const float *X, int64_t n, int d, int64_t ldx, const float *C, int k,
@@ -134,8 +135,7 @@ struct SplitArgs {
   int64_t ldx;
   int d;
   SplitPrep sp;
-  int kall;  // rows in sp (sp.seed[kall] is -inf)
-  int coff;  // first centroid of this launch in sp
+  int kall;  // rows in sp (its seed[kall] is -inf)
   int k;
   int64_t n;
   int32_t *assign;
@@ -144,10 +144,19 @@ struct SplitArgs {
   int ngroups;
   int64_t n_ptiles;
   unsigned long long *keys;
+  // HYBRID: the points' 1-bit codes (words per row, first tail word), the centroids' codes, tail dims
+  const uint32_t *pbits;
+  int64_t pbw;
+  int pbw0;
+  const int8_t *ci8;
+  int64_t cild;
+  int di;
+  const float *alpha;
 };
-size_t split_bytes(int64_t n, int k, int d);
-SplitPrep split_layout(int64_t n, int k, int d, void *ws);
-km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d, const float *cn, const SplitPrep &sp,
+constexpr int kSplitTailWords = 20;  // resident tail words per point (640 tail dims)
+size_t split_bytes(int64_t n, int k, int d, bool tail);
+SplitPrep split_layout(int64_t n, int k, int d, bool tail, void *ws);
+km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d, const CentroidPrep &cp,
                             hipStream_t s);
 km_status launch_split_assign(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s);
 
@@ -218,6 +227,29 @@ __device__ __forceinline__ uint32_t bf16_bits(float x) {
   const uint32_t u = __float_as_uint(x);
   if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
   return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+}
+
+__device__ __forceinline__ uint32_t spread4(uint32_t b4) {
+  // 4 bits -> 4 bytes holding 0 or 1 (bit j -> byte j)
+  return (b4 * 0x00204081u) & 0x01010101u;
+}
+
+// A word of 1-bit codes for the matrix cores: bit 16 h + 4 q + j goes to bit 8 j + 4 h + q.
+__device__ __forceinline__ uint32_t regroup_bits(uint32_t w) {
+  uint32_t o = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o |= spread4((w >> (16 * h + 4 * q)) & 15u) << (4 * h + q);
+  return o;
+}
+
+// x: a regrouped word shifted right by 4h.  Register q takes bit 8j + q of x as
+// byte j with the value 0 or 2, so the products sum to 2D; seeded with -T the
+// accumulator ends at 2D - T.
+__device__ __forceinline__ i32x4 widen_regrouped2(uint32_t x) {
+  constexpr uint32_t M2 = 0x02020202u;
+  return i32x4{(int)((x << 1) & M2), (int)(x & M2), (int)((x >> 1) & M2), (int)((x >> 2) & M2)};
 }
 
 __device__ __forceinline__ float bf16_value(uint32_t b) { return __uint_as_float(b << 16); }

@@ -33,7 +33,8 @@ constexpr int kSeedPad = 256;  // -inf seeds past the last centroid
 // are exact).  Centroids with NaN or infinities, or so large or small that the
 // scale's square leaves fp32's range, take the fp32 kernel as well.
 __global__ __launch_bounds__(256) void split_prep_kernel(const float *C, int64_t ldc, int k, int d,
-                                                         const uint32_t *rmax, const float *cn, SplitPrep sp,
+                                                         const uint32_t *rmax, const float *cn, const int *qsum,
+                                                         const float *u, const float *sig2, SplitPrep sp,
                                                          int64_t ntflag) {
   __shared__ uint32_t shm[256];
   __shared__ float shn[256];
@@ -65,6 +66,15 @@ __global__ __launch_bounds__(256) void split_prep_kernel(const float *C, int64_t
   for (int64_t i = g0; i < ntflag; i += gs) sp.tflag[i] = 0;
   if (!ok) return;
   for (int64_t j = g0; j < (int64_t)k + kSeedPad; j += gs) sp.seed[j] = j < k ? cn[j] * (-0.5f * sc * sc) : -INFINITY;
+  if (sp.tail) {  // hybrid: -T, and u and 2 sigma times the factor that makes tail scores seeds
+    const int64_t kp = k + kSeedPad;
+    for (int64_t j = g0; j < kp; j += gs) {
+      const bool in = j < k;
+      sp.tail[j] = in ? __int_as_float(-qsum[j]) : 0.f;
+      sp.tail[kp + j] = in ? u[j] * (-0.5f * sc * sc) : 0.f;
+      sp.tail[2 * kp + j] = in ? sig2[j] * (-0.5f * sc * sc) : 0.f;
+    }
+  }
   // one unit: 8 dims of one row
   const int ch = 2 * ((d + kSD - 1) / kSD);
   const int64_t units = (int64_t)k * ch;
@@ -118,14 +128,28 @@ __device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
 // kernel at 1.6 - 1.8 GHz, and a large f16 library product reaches 1290 - 1310 TFLOP/s;
 // with constant data (few bits toggling) the same pass at 2M points takes 8.9 instead
 // of 11.8 ms.  The matrix cores are busy 56 % of the cycles.
-template <int CB>
+//
+// HYB (fp32 front dims plus 1-bit tail): a tile begins with stages of the tail, 128
+// bytes of every centroid's int8 residual codes (32 KB for 256 centroids, as a front
+// stage), multiplied with the points' bits, which stay in LDS for the whole workgroup,
+// regrouped so that widening to {0, 2} bytes is a shift and a mask.  The accumulators
+// start at -T and end at the exact 2D - T; in fp32, in the order of Eq. 4 that the
+// oracle uses, that becomes the tail score ts = fmaf(-(alpha 2 sigma), 2D - T,
+// sigma^2 Q), and -s^2 ts / 2 (the factor, a power of two, is in the constants) starts
+// the front's accumulators.  2M points, front 384 + tail 640, k = 4096:
+// 54.4 -> 21.7 ms per pass against the fp32 front (assign_hyb_kernel)
+template <int CB, bool HYB>
 __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
   constexpr int TC = 64 * CB;
+  constexpr int NCONST = HYB ? 4 : 1;  // constants per centroid: seed; -T, u, 2 sigma
+  constexpr int CRING = HYB ? 2 : 4;   // tiles of constants (a hybrid tile has 3 stages or more, and ends its argmax)
   constexpr int NCC = CB / 2;  // centroid copies per wave and stage
   constexpr int CREG = TC * kRow, STAGE = CREG + kTP * kRow;
   if (!A.sp.route->ok) return;  // every workgroup: the fp32 kernel takes this call
   __shared__ __align__(16) uint8_t ring[kRing * STAGE];
-  __shared__ __align__(16) float seeds[4][TC];
+  __shared__ __align__(16) float seeds[CRING][NCONST][TC];
+  __shared__ uint32_t bitsT[HYB ? kSplitTailWords * kTP : 1];
+  __shared__ float alp[HYB ? kTP : 1];
   const int t = threadIdx.x;
   const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r = lane & 31, h = lane >> 5;
@@ -140,14 +164,14 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
     if (pt >= A.n_ptiles) return;  // whole workgroup, before any barrier
   }
   const int64_t p0 = pt * kTP;
-  const int S = (A.d + kSD - 1) / kSD;
+  const int SI = HYB ? (A.di + 127) / 128 : 0;  // tail stages of a tile
+  const int S = SI + (A.d + kSD - 1) / kSD;     // all its stages
   const bool ragged = A.d % kSD != 0;
   const int nct = (A.k + TC - 1) / TC;
   const int nmy = (nct - g + NG - 1) / NG;
   const int prmax = (int)min<int64_t>(A.n - 1 - p0, kTP - 1);
   const float sx = A.sp.route->s;
   const float *pbase = A.x + p0 * A.ldx;
-  const uint8_t *cbase = A.sp.img + (int64_t)A.coff * kRow;
 
   // copy j of a region fills its slots 64 j .. 64 j + 63; wave w makes copies w and
   // w + 8 of the points, and w (and w + 8 for CB = 4) of the centroids.  Copy w + 8
@@ -165,38 +189,75 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
   }
   const uint32_t ring0 = (uint32_t)(size_t)(lds_byte *)ring;
   const uint32_t seeds0 = (uint32_t)(size_t)(lds_byte *)seeds;
+  // hybrid: resident tail bits, word-major and regrouped; words past the tail up to the
+  // last stage's end are zero (so are their products with whatever codes are there)
+  if constexpr (HYB) {
+    const int TW = A.di / 32;
+    for (int e = t; e < 4 * SI * kTP; e += kThr) {
+      const int w = e / kTP, pp = e - w * kTP;
+      uint32_t v = 0u;
+      if (w < TW) v = regroup_bits(A.pbits[(p0 + min(pp, prmax)) * A.pbw + A.pbw0 + w]);
+      bitsT[w * kTP + pp] = v;
+    }
+    if (t < kTP) alp[t] = A.alpha[p0 + min(t, prmax)];
+  }
   int kc_s = 0, kc_t = 0;  // stage (dims) and tile of the next copy
   uint32_t kbuf = 0;       // its buffer's offset
-  // the copies of one stage: NCC + 2, and the tile's seeds with its first stage
+  // the copies of one stage: NCC + 2, and the tile's constants with its first stage
   auto copy_stage = [&]() {
     const int c0 = (g + kc_t * NG) * TC;
-    const uint8_t *cb = cbase + (int64_t)kc_s * A.sp.cstage + (int64_t)c0 * kRow;
-    const float *xb = pbase + kSD * kc_s;
     const uint32_t l0 = ring0 + kbuf + wave * 1024;
+    if (HYB && kc_s < SI) {  // rows of codes as 128-byte LDS rows, chunk c in slot c ^ ((row >> 1) & 7)
+      const int crmax = A.k - 1 - c0;
 #pragma unroll
-    for (int i = 0; i < NCC; ++i) lds_copy16_at(cb, coff + 8192u * i, l0 + 8192u * i);
-    if (ragged && kc_s == S - 1) {  // chunks past the last dim hold zeros
-      const bool in = kSD * kc_s + 4 * xchunk < A.d;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if (in) {
-          lds_copy16_at(xb, xoff[i], l0 + CREG + 8192u * i);
-        } else {
-          *reinterpret_cast<uint4 *>(ring + kbuf + wave * 1024 + CREG + 8192 * i + 16 * lane) = uint4{0u, 0u, 0u, 0u};
-        }
+      for (int i = 0; i < NCC + 2; ++i) {
+        const int ii = i % CB;  // CB = 2: the third copy is the first again (all stages have as many)
+        const int row = (ii * 8 + wave) * 8 + (lane >> 3);
+        const int b = 128 * kc_s + 16 * ((lane & 7) ^ ((row >> 1) & 7));
+        lds_copy16_at(A.ci8 + (int64_t)c0 * A.cild, (uint32_t)(min(row, crmax) * (int)A.cild + (b < A.di ? b : 0)),
+                      l0 + 8192u * ii);
       }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     } else {
+      const int fs = kc_s - SI;
+      const uint8_t *cb = A.sp.img + (int64_t)fs * A.sp.cstage + (int64_t)c0 * kRow;
+      const float *xb = pbase + kSD * fs;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) lds_copy16_at(xb, xoff[i], l0 + CREG + 8192u * i);
+      for (int i = 0; i < NCC; ++i) lds_copy16_at(cb, coff + 8192u * i, l0 + 8192u * i);
+      if (ragged && kc_s == S - 1) {  // chunks past the last dim hold zeros
+        const bool in = kSD * fs + 4 * xchunk < A.d;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (in) {
+            lds_copy16_at(xb, xoff[i], l0 + CREG + 8192u * i);
+          } else {
+            *reinterpret_cast<uint4 *>(ring + kbuf + wave * 1024 + CREG + 8192 * i + 16 * lane) = uint4{0u, 0u, 0u, 0u};
+          }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) lds_copy16_at(xb, xoff[i], l0 + CREG + 8192u * i);
+      }
     }
     if (kc_s == 0) {
-      // wave w copies the seeds of rows 64 (w mod TC / 64) ..: all waves have the same
-      // number of copies in flight; rows past the last centroid read a -inf
-      const int row = (wave & (TC / 64 - 1)) * 64 + lane;
-      const int j = c0 + row < A.k ? A.coff + c0 + row : A.kall;
-      lds_copy4_at(A.sp.seed, 4u * (uint32_t)j,
-                   seeds0 + 4u * (uint32_t)((kc_t & 3) * TC + (wave & (TC / 64 - 1)) * 64));
+      // wave w copies rows 64 (w mod TC / 64) .. of its constants, so that all waves have
+      // the same number of copies in flight; rows past the last centroid read a -inf seed
+      const int seg = wave & (TC / 64 - 1);
+      const int row = seg * 64 + lane;
+      const int j = c0 + row < A.k ? c0 + row : A.kall;
+      const uint32_t ls = seeds0 + 4u * (uint32_t)((kc_t & (CRING - 1)) * NCONST * TC + seg * 64);
+      if constexpr (HYB) {
+        const int kp = A.kall + kSeedPad;
+        const int q0 = wave / (TC / 64);  // CB = 4: waves 0-3 and 4-7 share the four; CB = 2: one each
+#pragma unroll
+        for (int i = 0; i < CB / 2; ++i) {
+          const int q = q0 + i * (8 / (TC / 64));
+          const float *src = q == 0 ? A.sp.seed : A.sp.tail + (int64_t)(q - 1) * kp;
+          lds_copy4_at(src, 4u * (uint32_t)j, ls + 4u * (uint32_t)(q * TC));
+        }
+      } else {
+        lds_copy4_at(A.sp.seed, 4u * (uint32_t)j, ls);
+      }
     }
     if (++kc_s == S) {
       kc_s = 0;
@@ -252,7 +313,7 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
   int id = 0, pos = 0;
   auto argmax_piece = [&](int j, int pb, int ct) {
     auto seeds_of = [&](int cb) {
-      const float *sd = seeds[ct & 3] + wc * 32 * CB + 4 * h + 32 * cb;
+      const float *sd = seeds[ct & (CRING - 1)][0] + wc * 32 * CB + 4 * h + 32 * cb;
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
         const f32x4 v = *reinterpret_cast<const f32x4 *>(sd + 8 * m);
@@ -312,6 +373,17 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
+  auto next_buf = [&]() { nbuf = nbuf == (kRing - 1) * STAGE ? 0 : nbuf + STAGE; };
+  auto end_step = [&]() {
+    // stage i + 2 has landed when only the copies of stage i + 3 are out (a tile's
+    // constants may be among them: then the wait is for a little more)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCC + 2) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    next_buf();
+  };
   auto step = [&](int ct, auto first_, auto last_) {
     constexpr bool FIRST = decltype(first_)::value, LAST = decltype(last_)::value;
     copy_stage();
@@ -323,7 +395,7 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
         const int pr = j / CB, cb = j % CB;
         const h16x8 a = pr == 0 ? cl[cb] : ch[cb];
         const h16x8 b = pr == 1 ? op(xl[pb]) : op(xh[pb]);
-        if (FIRST && pr == 0) {
+        if (!HYB && FIRST && pr == 0) {
           const f32x16 zero = {0.f};
           acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, zero, 0, 0, 0);
         } else {
@@ -339,7 +411,7 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
           if (j >= 1 && j <= CB) read_cl(j - 1, nbuf);
           if (j >= 2 * CB + 1) read_ch(j - 2 * CB - 1, nbuf);
         }
-        if ((FIRST && pb == 0) || (LAST && pb == 1)) {
+        if ((!HYB && FIRST && pb == 0) || (LAST && pb == 1)) {
           if constexpr (CB == 4) {
             argmax_piece(j, FIRST && pb == 0 ? 1 : 0, FIRST && pb == 0 ? ct - 1 : ct);
           } else {
@@ -351,47 +423,122 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
       }
     }
     read_ch(CB - 1, nbuf);
-    // stage i + 2 has landed when only the copies of stage i + 3 are out (a tile's
-    // seeds may be among them: then the wait is for a little more)
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCC + 2) : "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-    nbuf = nbuf == (kRing - 1) * STAGE ? 0 : nbuf + STAGE;
+    end_step();
   };
 
-  // before the first tile there is none whose second block's argmax is due: -inf
+  // one tail stage: four steps of 32 dims, operands read as they are needed
+  [[maybe_unused]] auto tail_step = [&](int s) {
+    copy_stage();
+    pin();
+    const uint32_t buf = nbuf, hsh = 4u * (uint32_t)h;
+    const uint32_t row0 = buf + (uint32_t)((wc * 32 * CB + r) * 128);
+    i32x4 av[2][CB];
+    auto read = [&](int gg, int set) {
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
+      for (int cb = 0; cb < CB; ++cb) av[set][cb] = rd16(row0 + 4096u * cb + 16u * ((uint32_t)(2 * gg + h) ^ kx));
+    };
+    read(0, 0);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[cb][1][i] = -INFINITY;
-  if (t < TC) seeds[3][t] = 0.f;  // the slot of tile -1, and of tile 3, copied no sooner than in tile 0's first step
+    for (int gg = 0; gg < 4; ++gg) {
+      i32x4 bv[2];
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb) bv[pb] = widen_regrouped2(bitsT[(4 * s + gg) * kTP + wp * 64 + pb * 32 + r] >> hsh);
+      if (gg < 3) read(gg + 1, (gg + 1) & 1);
+      pin();
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int pb = 0; pb < 2; ++pb)
+          acc[cb][pb] = __builtin_bit_cast(f32x16, __builtin_amdgcn_mfma_i32_32x32x32_i8(
+                                                       av[gg & 1][cb], bv[pb], __builtin_bit_cast(i32x16, acc[cb][pb]),
+                                                       0, 0, 0));
+    }
+    end_step();
+  };
+  // constant q of this lane's rows of block cb: rows 8 m + 4 h + e at [4 m + e]
+  [[maybe_unused]] auto consts_of = [&](int q, int cb, int ct, float (&v)[16]) {
+    const float *p = seeds[ct & (CRING - 1)][HYB ? q : 0] + wc * 32 * CB + 32 * cb + 4 * h;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const f32x4 x = *reinterpret_cast<const f32x4 *>(p + 8 * m);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * m + e] = x[e];
+    }
+  };
+
+  if constexpr (!HYB) {
+    // before the first tile there is none whose second block's argmax is due: -inf
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[cb][1][i] = -INFINITY;
+    // the slot of tile -1, and of tile 3, copied no sooner than in tile 0's first step
+    if (t < TC) seeds[CRING - 1][0][t] = 0.f;
+  }
   for (int i = 0; i < kRing - 1; ++i) copy_stage();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
+  // the operands of the stage at nbuf, with nothing before them to read ahead
+  auto open_front = [&]() {
 #pragma unroll
-  for (int pb = 0; pb < 2; ++pb) {
-    read_x(pb, 0, 0);
-    read_x(pb, 1, 0);
-  }
+    for (int pb = 0; pb < 2; ++pb) {
+      read_x(pb, 0, nbuf);
+      read_x(pb, 1, nbuf);
+    }
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    read_ch(cb, 0);
-    read_cl(cb, 0);
-  }
+    for (int cb = 0; cb < CB; ++cb) {
+      read_cl(cb, nbuf);
+      read_ch(cb, nbuf);
+    }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) conv(0, q);
-  nbuf = STAGE;
+    for (int q = 0; q < 4; ++q) conv(0, q);
+    next_buf();
+  };
   constexpr std::true_type T{};
   constexpr std::false_type F{};
-  for (int ct = 0; ct < nmy; ++ct) {
-    step(ct, T, F);
-    for (int s = 2; s < S; ++s) step(ct, F, F);
-    step(ct, F, T);
-  }
+  if constexpr (HYB) {
+    for (int ct = 0; ct < nmy; ++ct) {
 #pragma unroll
-  for (int j = 0; j < 12; ++j) argmax_piece(j, 1, nmy - 1);
+      for (int cb = 0; cb < CB; ++cb) {
+        float nt[16];
+        consts_of(1, cb, ct, nt);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[cb][0][i] = acc[cb][1][i] = nt[i];
+      }
+      for (int s = 0; s < SI; ++s) tail_step(s);
+      float al[2];
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb) al[pb] = alp[wp * 64 + pb * 32 + r];
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        float u16[16], s16[16];
+        consts_of(2, cb, ct, u16);
+        consts_of(3, cb, ct, s16);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int pb = 0; pb < 2; ++pb)
+            acc[cb][pb][i] = fmaf(-(al[pb] * s16[i]), (float)__float_as_int(acc[cb][pb][i]), u16[i]);
+        pin();
+      }
+      open_front();
+      for (int s = SI + 1; s < S; ++s) step(ct, F, F);
+      step(ct, F, T);
+#pragma unroll
+      for (int j = 0; j < 12; ++j) argmax_piece(j, 1, ct);
+      // step moved nbuf one stage ahead of the tail stage that comes next
+      nbuf = nbuf == 0 ? (kRing - 1) * STAGE : nbuf - STAGE;
+    }
+  } else {
+    open_front();
+    for (int ct = 0; ct < nmy; ++ct) {
+      step(ct, T, F);
+      for (int s = 2; s < S; ++s) step(ct, F, F);
+      step(ct, F, T);
+    }
+#pragma unroll
+    for (int j = 0; j < 12; ++j) argmax_piece(j, 1, nmy - 1);
+  }
 
   // the copies past the end are still under way, into the LDS that the merge uses
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -448,14 +595,14 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
 
 }  // namespace
 
-size_t split_bytes(int64_t n, int k, int d) {
+size_t split_bytes(int64_t n, int k, int d, bool tail) {
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t S = (size_t)cdiv(d, kSD);
-  return 256 + al(4 * (size_t)k) + al(4 * ((size_t)k + kSeedPad)) + al(4 * (size_t)cdiv(n, kTP)) +
+  return (tail ? al(12 * ((size_t)k + kSeedPad)) : 0) + 256 + al(4 * (size_t)k) + al(4 * ((size_t)k + kSeedPad)) + al(4 * (size_t)cdiv(n, kTP)) +
          al(S * k * kRow + 256 * kRow);
 }
 
-SplitPrep split_layout(int64_t n, int k, int d, void *ws) {
+SplitPrep split_layout(int64_t n, int k, int d, bool tail, void *ws) {
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   uint8_t *w = static_cast<uint8_t *>(ws);
   SplitPrep sp{};
@@ -467,27 +614,41 @@ SplitPrep split_layout(int64_t n, int k, int d, void *ws) {
   w += al(4 * ((size_t)k + kSeedPad));
   sp.tflag = reinterpret_cast<int *>(w);
   w += al(4 * (size_t)cdiv(n, kTP));
+  if (tail) {
+    sp.tail = reinterpret_cast<float *>(w);
+    w += al(12 * ((size_t)k + kSeedPad));
+  }
   sp.img = w;
   sp.cstage = (int64_t)k * kRow;
   return sp;
 }
 
-km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d, const float *cn, const SplitPrep &sp,
+km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d, const CentroidPrep &cp,
                             hipStream_t s) {
+  const SplitPrep &sp = cp.sp;
   const int64_t units = (int64_t)k * 2 * cdiv(d, kSD);
   // every workgroup reads k maxima first: fewer, longer workgroups as k grows
   const int64_t grid = std::min<int64_t>(std::max<int64_t>(1, cdiv(units, 256)), 512);
-  hipLaunchKernelGGL(split_prep_kernel, dim3((unsigned)grid), dim3(256), 0, s, C, ldc, k, d, sp.rmax, cn, sp,
+  hipLaunchKernelGGL(split_prep_kernel, dim3((unsigned)grid), dim3(256), 0, s, C, ldc, k, d, sp.rmax, cp.cn, cp.qsum,
+                     cp.u, cp.sig2, sp,
                      cdiv(n, kTP));
   KMQ_LAUNCH_CHECK("split_prep_kernel");
   return KM_OK;
 }
 
 km_status launch_split_assign(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s) {
-  if (tile_c == 128)
-    hipLaunchKernelGGL(assign_split_kernel<2>, dim3((unsigned)grid), dim3(kThr), 0, s, A);
-  else
-    hipLaunchKernelGGL(assign_split_kernel<4>, dim3((unsigned)grid), dim3(kThr), 0, s, A);
+  const dim3 gr((unsigned)grid), th(kThr);
+  if (A.pbits) {
+    if (tile_c == 128)
+      hipLaunchKernelGGL((assign_split_kernel<2, true>), gr, th, 0, s, A);
+    else
+      hipLaunchKernelGGL((assign_split_kernel<4, true>), gr, th, 0, s, A);
+  } else {
+    if (tile_c == 128)
+      hipLaunchKernelGGL((assign_split_kernel<2, false>), gr, th, 0, s, A);
+    else
+      hipLaunchKernelGGL((assign_split_kernel<4, false>), gr, th, 0, s, A);
+  }
   KMQ_LAUNCH_CHECK("assign_split_kernel");
   return KM_OK;
 }

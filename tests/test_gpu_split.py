@@ -153,3 +153,53 @@ def test_noalloc_past_its_scratch(km, torch):
     km.kmeans_assign_noalloc(P, Ct, a, sc)
     b, _, _ = km.kmeans_assign(P, Ct)
     np.testing.assert_array_equal(host(a), host(b))
+
+
+# the tail's stages of 128 dims whole and partial, front of 2 stages and more, tiles of 128 and 256 centroids, groups
+@pytest.mark.parametrize("n,d,d0,k", [(1, 64, 32, 1), (257, 96, 32, 128), (300, 160, 64, 129), (513, 288, 96, 300),
+                                      (700, 704, 64, 257), (1500, 1024, 384, 1100)])
+@pytest.mark.parametrize("how", ["plain", "tiny_centroid", "not_finite"])
+def test_hybrid(km, torch, n, d, d0, k, how):
+    """Front dims plus 1-bit tail against the 64-bit scores of the same codes."""
+    import oracle as orc
+    X, C = points(n, d, k, n + d0)
+    if how == "tiny_centroid":  # the front of one centroid 2^-12 of the others: the fp32 kernel takes the call
+        C[0, :d0] *= np.float32(2.0 ** -12)
+        X[::9, :d0] = C[0, :d0] * np.float32(1.25)
+    m = orc.col_mean(X)
+    bits, alpha = orc.sign1_encode(X, m, d0)
+    front = np.ascontiguousarray(X[:, :d0])
+    bad = []
+    if how == "not_finite":
+        front[n // 2, 1] = np.nan
+        bad = [n // 2]
+    P = km.points_hybrid(to_dev(front, torch), to_dev(bits.view(np.int32), torch), to_dev(alpha, torch),
+                         to_dev(m, torch), d)
+    a, sc, obj = km.kmeans_assign(P, to_dev(C, torch), objective=True)
+    a, sc = host(a), host(sc)
+    rows = np.setdiff1d(np.arange(n), bad)
+    assert (a[bad] == np.iinfo(np.int32).max).all() and (sc[bad] == np.inf).all()
+    r = C[:, d0:] - m[d0:]  # residual codes in fp32, as the interface defines them
+    sg = np.where(np.abs(r).max(1) > 0, np.abs(r).max(1) / np.float32(127), np.float32(1)).astype(np.float32)
+    q = np.clip(np.rint(r / sg[:, None]), -127, 127).astype(np.float64)
+    b = ((bits[:, :, None] >> np.arange(32, dtype=np.uint32)) & 1).reshape(n, -1)[:, d0:].astype(np.float64) * 2 - 1
+    f, cf = front[rows].astype(np.float64), C[:, :d0].astype(np.float64)
+    cn = (cf ** 2).sum(1)
+    tail = sg.astype(np.float64) ** 2 * (q ** 2).sum(1) - 2 * alpha[rows, None] * sg.astype(np.float64) * (b[rows] @ q.T)
+    s = cn - 2 * f @ cf.T + tail
+    i = np.arange(len(rows))
+    if len(rows) == 0:
+        return
+    got = a[rows]
+    xn = (f ** 2).sum(1)
+    size = xn + cn[got] + np.abs(tail).max(1)
+    assert ((s[i, got] - s.min(1)) / size).max() <= NEAR_TIE_REL
+    # the front's bound, the partial sums starting at the tail's score
+    steps = 6 * (d0 // 16)
+    bound = 2 * (steps * 2.0 ** -23 + 3 * 2.0 ** -22) * size
+    assert (np.abs(sc[rows] - s[i, got]) <= bound).all()
+    if bad:
+        assert np.isnan(host(obj)[0])
+    else:  # from the distances: fp32 squares of the front's differences, the tail's scores in fp32, fp64 sums
+        want = (s[i, got] + xn + alpha.astype(np.float64) ** 2 * (d - d0)).sum()
+        assert abs(host(obj)[0] - want) <= 2.0 ** -21 * size.sum()

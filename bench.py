@@ -268,7 +268,7 @@ def wl_c1(cfg, torch, km, args):
                     {"workload": cfg["name"], "N": spec.n, "d": spec.d, "k": k, "iters": T, "format": "f32"},
                     distances_per_s=(T + 1) * spec.n * k * K / elapsed,
                     roofline=roofline(cfg["name"], s, 6.0 * spec.n * k * spec.d, "fp16",
-                                      "assign_split_kernel", "assign_split_kernel", SPLIT_WORK),
+                                      "split_kernel", "split_kernel", SPLIT_WORK),
                     update_hbm=update_hbm(s, spec.n * (4 * spec.d + 4), "4d+4 per point"),
                     stages={"f32": stage_summary(s)})
 
@@ -306,8 +306,8 @@ def wl_c2_f32(cfg, torch, km, args):
                      "components": spec.components, "sigma": spec.sigma},
                     distances_per_s=(T + 1) * spec.n * k * K / elapsed,
                     partition_cost=float(out["cost"].item()),
-                    roofline=roofline(wname, s, 6.0 * spec.n * k * spec.d, "fp16", "assign_split_kernel",
-                                      "assign_split_kernel", SPLIT_WORK),
+                    roofline=roofline(wname, s, 6.0 * spec.n * k * spec.d, "fp16", "split_kernel",
+                                      "split_kernel", SPLIT_WORK),
                     update_hbm=update_hbm(s, spec.n * (4 * spec.d + 4), "4d+4 per point"),
                     stages={"f32": stage_summary(s)})
 
@@ -462,8 +462,8 @@ def wl_c4(cfg, torch, km, args):
                      "format": "f32 (PCA-projected)"},
                     distances_per_s=(T + 1) * spec.n * k * K / elapsed,
                     partition_cost=float(out["cost"].item()),
-                    roofline=roofline(cfg["name"], s, 6.0 * spec.n * k * dout, "fp16", "assign_split_kernel",
-                                      "assign_split_kernel", SPLIT_WORK),
+                    roofline=roofline(cfg["name"], s, 6.0 * spec.n * k * dout, "fp16", "split_kernel",
+                                      "split_kernel", SPLIT_WORK),
                     update_hbm=update_hbm(s, spec.n * (4 * dout + 4), "4d'+4 per point"),
                     host_eigensolve_ms_per_step=timer.host_ms.get("eigensolve", 0.0) / K,
                     stages={"pca": stage_summary(s)})
@@ -751,7 +751,7 @@ def wl_hier(fmt):
             work = K * ((Tm + 1) * work_meso + (Tf + 1) * work_fine)
             ach = work / (s["assign_ms"] * 1e-3) / 1e12
             peak = "fp32" if fmt == "f32" else "int8"
-            kern = "assign_split_kernel (meso), assign_f32_kernel (fine)" if fmt == "f32" else "assign_q8_kernel<sq8>"
+            kern = "split_kernel (meso), assign_f32_kernel (fine)" if fmt == "f32" else "assign_q8_kernel<sq8>"
             return line(K / elapsed, "fits/s", "f32" if fmt == "f32" else "u8",
                         {"workload": wname, "N": spec.n, "d": spec.d, "k": k, "k_meso": kmeso, "iters_meso": Tm,
                          "iters_fine": Tf, "iters_refine": 0, "format": fmt},

@@ -294,7 +294,7 @@ km_status pca_project(const float *X, int64_t n, int32_t d, const float *mean, c
   KMQ_CHECK(aligned16(X) && aligned16(mean), KM_EINVAL, "X and mean must be 16-byte aligned");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   Scratch ws(s);
-  km_status st = ws.alloc(pca_project_bytes(d, d_out));
+  km_status st = ws.alloc(pca_project_bytes(n, d, d_out));
   if (st != KM_OK) return st;
   return launch_pca_project(X, n, d, (int64_t)d, mean, W, d_out, Y, ws.get(), s);
 }

@@ -3055,7 +3055,7 @@ km_status launch_assign_t(const Points &P, const void *C, const CentroidPrep &cp
       B.ngroups = ng;
       B.n_ptiles = npt;
       B.keys = A.keys;
-      const km_status st = launch_split_assign(B, grid.x, q8_tile_centroids(k), s);
+      const km_status st = launch_split(B, grid.x, q8_tile_centroids(k), s);
       if (st != KM_OK) return st;
       A.route = cp.sp.route;
       A.tflag = cp.sp.tflag;
@@ -3092,7 +3092,7 @@ km_status launch_assign_t(const Points &P, const void *C, const CentroidPrep &cp
       B.cild = A.cild;
       B.di = A.di;
       B.alpha = A.alpha;
-      const km_status st = launch_split_assign(B, grid.x, q8_tile_centroids(k), s);
+      const km_status st = launch_split(B, grid.x, q8_tile_centroids(k), s);
       if (st != KM_OK) return st;
       A.route = cp.sp.route;
       A.tflag = cp.sp.tflag;

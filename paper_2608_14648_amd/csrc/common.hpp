@@ -152,13 +152,22 @@ struct SplitArgs {
   int64_t cild;
   int di;
   const float *alpha;
+  // projection: d dims to k outputs, Y n x k
+  const float *mean;
+  float *Y;
 };
+enum { kSplitAssign = 0, kSplitHybrid = 1, kSplitProject = 2 };
+constexpr int kSplitProjMaxD = 4096;  // the mean's place in LDS
+// Y = (X - mean) W on the fp16 matrix cores; out: the route and the point tiles (of 256) left to the fp32 kernel
+size_t split_project_bytes(int64_t n, int d, int d_out);
+km_status launch_split_project(const float *X, int64_t n, int d, int64_t ldx, const float *mean, const float *W,
+                               int d_out, float *Y, void *ws, SplitPrep *out, hipStream_t s);
 constexpr int kSplitTailWords = 20;  // resident tail words per point (640 tail dims)
 size_t split_bytes(int64_t n, int k, int d, bool tail);
 SplitPrep split_layout(int64_t n, int k, int d, bool tail, void *ws);
 km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d, const CentroidPrep &cp,
                             hipStream_t s);
-km_status launch_split_assign(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s);
+km_status launch_split(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s);
 
 // update.hip
 size_t update_bytes(const Points &P, int k);
@@ -211,7 +220,7 @@ km_status launch_pca_cov(const float *X, int64_t n, int d, float *mean, float *c
                          hipStream_t s);
 km_status launch_pca_project(const float *X, int64_t n, int d, int64_t ldx, const float *mean, const float *W,
                              int d_out, float *Y, void *ws, hipStream_t s);
-size_t pca_project_bytes(int d, int d_out);
+size_t pca_project_bytes(int64_t n, int d, int d_out);
 
 // ---- device helpers ---------------------------------------------------------
 

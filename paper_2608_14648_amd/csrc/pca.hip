@@ -7,9 +7,9 @@
 // copies 32 rows x 256 columns of both column blocks into LDS, centred when read.
 // The fp32 accumulators are added into a per-workgroup fp64 partial tile every
 // 8192 rows, and the partial tiles are folded in split order.
-// Projection: 128 points x 128 outputs per workgroup, 32 dims per stage; the
-// point rows are centred on load and W is pre-transposed so both MFMA operands
-// are read as 16 contiguous bytes per lane (k permuted identically on both).
+// Projection: on the fp16 matrix cores (split.hip); the fp32 kernels below take the
+// tiles and shapes it leaves, with the rows centred as they are read and W
+// pre-transposed so that both MFMA operands are 16 contiguous bytes per lane.
 #include <algorithm>
 
 #include "common.hpp"
@@ -338,7 +338,8 @@ constexpr int kPT = 256;  // points and outputs per workgroup
 
 __global__ __launch_bounds__(512, 1) void project_kernel(const float *X, int64_t n, int d, int64_t ldx,
                                                          const float *mean, const float *Wt, int d_out, float *Y,
-                                                         int n_ptiles, int n_otiles) {
+                                                         int n_ptiles, int n_otiles, const SplitRoute *route,
+                                                         const int *tflag) {
   constexpr int NCP = kPT / 64;            // point copies per thread and stage
   constexpr int NCOPY = 2 * kPT / 64;      // all copies per thread and stage
   constexpr int STAGE = 2 * kPT * 128;     // bytes: point rows, then W^T rows
@@ -353,6 +354,7 @@ __global__ __launch_bounds__(512, 1) void project_kernel(const float *X, int64_t
   const int ptile = group * 8 + rem % 8;
   const int otile = rem / 8;
   if (ptile >= n_ptiles) return;  // whole workgroup, before any barrier
+  if (route && route->ok && !tflag[ptile]) return;  // done on the fp16 matrix cores
   const int64_t p0 = (int64_t)ptile * kPT;
   const int o0 = otile * kPT;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -512,7 +514,15 @@ km_status launch_pca_cov(const float *X, int64_t n, int d, float *mean, float *c
   return KM_OK;
 }
 
-size_t pca_project_bytes(int d, int d_out) { return (size_t)d * d_out * sizeof(float) + 256; }
+// The fp16 matrix cores take the rows whose 256 span less than 2 GB (as the fp32
+// kernel's do), from two stages of 16 dims on.
+static bool project_split(int d, int64_t ldx) {
+  return d >= 32 && d <= kSplitProjMaxD && ldx % 4 == 0 && (int64_t)kPT * ldx * 4 < ((int64_t)1 << 31);
+}
+
+size_t pca_project_bytes(int64_t n, int d, int d_out) {
+  return (((size_t)d * d_out * sizeof(float) + 255) & ~(size_t)255) + 256 + split_project_bytes(n, d, d_out);
+}
 
 km_status launch_pca_project(const float *X, int64_t n, int d, int64_t ldx, const float *mean, const float *W,
                              int d_out, float *Y, void *ws, hipStream_t s) {
@@ -522,8 +532,14 @@ km_status launch_pca_project(const float *X, int64_t n, int d, int64_t ldx, cons
   if (d <= kProjMaxD && ldx % 4 == 0 && (int64_t)kPT * ldx * 4 < ((int64_t)1 << 31)) {
     const int n_ptiles = (int)cdiv(n, kPT), n_otiles = (int)cdiv(d_out, kPT);
     const int64_t nblk = cdiv(n_ptiles, 8) * 8 * n_otiles;
+    SplitPrep sp{};
+    if (project_split(d, ldx)) {
+      uint8_t *w = static_cast<uint8_t *>(ws) + ((e * sizeof(float) + 255) & ~(size_t)255);
+      const km_status st = launch_split_project(X, n, d, ldx, mean, W, d_out, Y, w, &sp, s);
+      if (st != KM_OK) return st;
+    }
     hipLaunchKernelGGL(project_kernel, dim3((unsigned)nblk), dim3(512), 0, s, X, n, d, ldx, mean, Wt, d_out, Y,
-                       n_ptiles, n_otiles);
+                       n_ptiles, n_otiles, sp.route, sp.tflag);
   } else {
     const int n_ptiles = (int)cdiv(n, kT), n_otiles = (int)cdiv(d_out, kT);
     const int64_t nblk = cdiv(n_ptiles, 8) * 8 * n_otiles;

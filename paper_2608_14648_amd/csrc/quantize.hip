@@ -317,7 +317,7 @@ static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 // workspace: column-mean partials | transposed P | zero centre (d) | rotated rows y
 // (n x d, only when the caller does not take them)
 size_t rabitq_encode_bytes(int64_t n, int d, bool y_given) {
-  return al256(colmean_bytes(n, d)) + al256(pca_project_bytes(d, d)) + al256((size_t)d * sizeof(float)) +
+  return al256(colmean_bytes(n, d)) + al256(pca_project_bytes(n, d, d)) + al256((size_t)d * sizeof(float)) +
          (y_given ? 0 : al256((size_t)n * d * sizeof(float)));
 }
 
@@ -328,7 +328,7 @@ km_status launch_rabitq_encode(const float *X, int64_t n, int d, int64_t ldx, co
   uint8_t *w = static_cast<uint8_t *>(ws);
   void *wmean = w;
   void *wproj = w + al256(colmean_bytes(n, d));
-  float *zero = reinterpret_cast<float *>(w + al256(colmean_bytes(n, d)) + al256(pca_project_bytes(d, d)));
+  float *zero = reinterpret_cast<float *>(w + al256(colmean_bytes(n, d)) + al256(pca_project_bytes(n, d, d)));
   if (Y == nullptr) Y = zero + al256((size_t)d * sizeof(float)) / sizeof(float);
   if (flags & KM_Q_FIT_PARAMS) {
     km_status st = launch_colmean(X, n, d, ldx, m, wmean, s);

@@ -95,6 +95,92 @@ __global__ __launch_bounds__(256) void split_prep_kernel(const float *C, int64_t
   }
 }
 
+// ---- projection: scales and the image of W ------------------------------------------
+// The largest |x - mean| of 1024 rows spread over X, as 256 partial bit patterns (NaN
+// and infinities are the largest).
+__global__ __launch_bounds__(256) void proj_sample_kernel(const float *X, int64_t n, int d, int64_t ldx,
+                                                          const float *mean, uint32_t *part, SplitRoute *route) {
+  __shared__ uint32_t sh[256];
+  const int t = threadIdx.x;
+  uint32_t m = 0;
+  const int rows = (int)min<int64_t>(n, 1024);
+  for (int i = blockIdx.x; i < rows; i += 256) {
+    const float *x = X + (int64_t)((double)i * (double)n / rows) * ldx;
+    for (int c = t; c < d; c += 256) m = max(m, __float_as_uint(x[c] - mean[c]) & 0x7fffffffu);
+  }
+  sh[t] = m;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if (t < st) sh[t] = max(sh[t], sh[t + st]);
+    __syncthreads();
+  }
+  if (t == 0) part[blockIdx.x] = sh[0];
+  if (t == 0 && blockIdx.x == 0) route->ok = 1;
+}
+
+// 16 columns of W per workgroup: each column's own scale (its largest |w| at
+// [2^7, 2^8)), its factor back to Y (in seed) and its rows of the image.  The points'
+// scale puts the sample's largest |x - mean| at [2^11, 2^12): sixteen times more fits.
+// A sample or W with NaN or infinities, or past 2^+-50, leaves the call to the fp32
+// kernel: the sample kernel sets the route's ok, whoever sees such a value clears it.
+__global__ __launch_bounds__(256) void proj_prep_kernel(const float *W, int d, int d_out, const uint32_t *part,
+                                                        SplitPrep sp, int64_t ntflag) {
+  __shared__ uint32_t sh[256];
+  __shared__ float scl[16];
+  const int t = threadIdx.x, o16 = t & 15, rg = t >> 4;
+  const int o = blockIdx.x * 16 + o16;
+  sh[t] = part[t];
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if (t < st) sh[t] = max(sh[t], sh[t + st]);
+    __syncthreads();
+  }
+  const int ex = (int)(sh[0] >> 23) - 127;
+  const bool okx = ex >= -50 && ex <= 50;
+  const float sx = ldexpf(1.0f, 11 - (okx ? ex : 0));
+  __syncthreads();
+  uint32_t m = 0;
+  if (o < d_out)
+    for (int i = rg; i < d; i += 16) m = max(m, __float_as_uint(W[(int64_t)i * d_out + o]) & 0x7fffffffu);
+  sh[t] = m;
+  __syncthreads();
+  for (int st = 128; st >= 16; st >>= 1) {
+    if (t < st) sh[t] = max(sh[t], sh[t + st]);
+    __syncthreads();
+  }
+  if (t < 16) {
+    const int ew = (int)(sh[t] >> 23) - 127;
+    const bool zero = sh[t] == 0u, okw = zero || (ew >= -50 && ew <= 50);
+    const float s = ldexpf(1.0f, 7 - (zero || !okw ? 0 : ew));
+    scl[t] = s;
+    if (o < d_out) {
+      sp.seed[o] = 1.0f / (s * sx);
+      if (!okw) sp.route->ok = 0;
+    }
+  }
+  const int64_t g0 = (int64_t)blockIdx.x * 256 + t, gs = (int64_t)gridDim.x * 256;
+  if (g0 == 0) {
+    sp.route->s = sx;
+    if (!okx) sp.route->ok = 0;
+  }
+  for (int64_t i = g0; i < ntflag; i += gs) sp.tflag[i] = 0;
+  __syncthreads();
+  if (!okx || o >= d_out) return;
+  const float s = scl[o16];
+  const int ch = 2 * ((d + kSD - 1) / kSD);
+  for (int c = rg; c < ch; c += 16) {
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = 8 * c + i < d ? W[(int64_t)(8 * c + i) * d_out + o] : 0.f;
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) split2(v[2 * q], v[2 * q + 1], s, hi[q], lo[q]);
+    uint8_t *dst = sp.img + (int64_t)(c >> 1) * sp.cstage + (int64_t)o * kRow + 16 * (c & 1);
+    *reinterpret_cast<uint4 *>(dst) = uint4{hi[0], hi[1], hi[2], hi[3]};
+    *reinterpret_cast<uint4 *>(dst + 32) = uint4{lo[0], lo[1], lo[2], lo[3]};
+  }
+}
+
 // (score, index) keys as in the other assignment kernels: the order of the keys is
 // the order of (score, index), -0 taken as +0
 __device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
@@ -138,8 +224,16 @@ __device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
 // sigma^2 Q), and -s^2 ts / 2 (the factor, a power of two, is in the constants) starts
 // the front's accumulators.  2M points, front 384 + tail 640, k = 4096:
 // 54.4 -> 21.7 ms per pass against the fp32 front (assign_hyb_kernel)
-template <int CB, bool HYB>
-__global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
+//
+// PROJ (Y = (X - mean) W): the columns of W in the place of the centroids, points and
+// centroids exchanged in the MFMA so that a lane holds one output of many points and
+// the stores are coalesced; s (x - mean) is formed as the points are read, and the
+// values go out with their column's scale instead of into an argmax.
+// 2M x 1024 -> 256: 8.6 -> 4.1 ms against project_kernel (10.2 GB read and written:
+// 2.1 ms at the rate of a large copy); 500k x 1024 x 1024 (RabitQ's rotation): 8.5 -> 4.1.
+template <int CB, int MODE>
+__global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
+  constexpr bool HYB = MODE == kSplitHybrid, PROJ = MODE == kSplitProject;
   constexpr int TC = 64 * CB;
   constexpr int NCONST = HYB ? 4 : 1;  // constants per centroid: seed; -T, u, 2 sigma
   constexpr int CRING = HYB ? 2 : 4;   // tiles of constants (a hybrid tile has 3 stages or more, and ends its argmax)
@@ -147,7 +241,8 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
   constexpr int CREG = TC * kRow, STAGE = CREG + kTP * kRow;
   if (!A.sp.route->ok) return;  // every workgroup: the fp32 kernel takes this call
   __shared__ __align__(16) uint8_t ring[kRing * STAGE];
-  __shared__ __align__(16) float seeds[CRING][NCONST][TC];
+  __shared__ __align__(16) float seeds[PROJ ? 1 : CRING][NCONST][PROJ ? 1 : TC];
+  __shared__ __align__(16) float msh[PROJ ? kSplitProjMaxD + kSD : 1];  // s mean, 0 past d
   __shared__ uint32_t bitsT[HYB ? kSplitTailWords * kTP : 1];
   __shared__ float alp[HYB ? kTP : 1];
   const int t = threadIdx.x;
@@ -201,6 +296,9 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
     }
     if (t < kTP) alp[t] = A.alpha[p0 + min(t, prmax)];
   }
+  if constexpr (PROJ) {
+    for (int i = t; i < kSD * S + kSD; i += kThr) msh[i] = i < A.d ? A.mean[i] * sx : 0.f;
+  }
   int kc_s = 0, kc_t = 0;  // stage (dims) and tile of the next copy
   uint32_t kbuf = 0;       // its buffer's offset
   // the copies of one stage: NCC + 2, and the tile's constants with its first stage
@@ -239,7 +337,7 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
         for (int i = 0; i < 2; ++i) lds_copy16_at(xb, xoff[i], l0 + CREG + 8192u * i);
       }
     }
-    if (kc_s == 0) {
+    if (!PROJ && kc_s == 0) {
       // wave w copies rows 64 (w mod TC / 64) .. of its constants, so that all waves have
       // the same number of copies in flight; rows past the last centroid read a -inf seed
       const int seg = wave & (TC / 64 - 1);
@@ -292,8 +390,22 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
   auto read_x = [&](int pb, int q, uint32_t buf) {
     w[pb][q] = __builtin_bit_cast(f32x4, rd16(buf + CREG + at(wp * 2 + pb, 2 * h + q)));
   };
+  f32x4 mreg[2];                // PROJ: s mean of this lane's dims
+  uint32_t seen[2] = {0u, 0u};  // PROJ: the bits of every value of the point, together
+  // a 1 the compiler does not see through: fma(t, 1, ..) keeps split2's mixed instructions
+  float one = 1.0f;
+  if constexpr (PROJ) asm volatile("" : "+s"(one));
   // pair q of a point block
   auto conv = [&](int pb, int q) {
+    if constexpr (PROJ) {
+      const f32x4 v = w[pb][q >> 1], m = mreg[q >> 1];
+      const int e = 2 * (q & 1);
+      const float t0 = __builtin_fmaf(v[e], sx, -m[e]), t1 = __builtin_fmaf(v[e + 1], sx, -m[e + 1]);
+      seen[pb] |= __float_as_uint(t0) | __float_as_uint(t1);
+      split2(t0, t1, one, xh[pb][q], xl[pb][q]);
+      asm volatile("" : "+v"(xh[pb][q]), "+v"(xl[pb][q]), "+v"(seen[pb]));
+      return;
+    }
     split2(w[pb][q >> 1][2 * (q & 1)], w[pb][q >> 1][2 * (q & 1) + 1], sx, xh[pb][q], xl[pb][q]);
     asm volatile("" : "+v"(xh[pb][q]), "+v"(xl[pb][q]));
   };
@@ -395,7 +507,9 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
         const int pr = j / CB, cb = j % CB;
         const h16x8 a = pr == 0 ? cl[cb] : ch[cb];
         const h16x8 b = pr == 1 ? op(xl[pb]) : op(xh[pb]);
-        if (!HYB && FIRST && pr == 0) {
+        if constexpr (PROJ) {
+          acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, a, acc[cb][pb], 0, 0, 0);
+        } else if (!HYB && FIRST && pr == 0) {
           const f32x16 zero = {0.f};
           acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, zero, 0, 0, 0);
         } else {
@@ -403,6 +517,7 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
         }
         // the next stage's floats of this block, over two slots
         if (j < 2) read_x(pb, j, nbuf);
+        if (PROJ && pb == 1 && j < 2) mreg[j] = *reinterpret_cast<const f32x4 *>(&msh[kSD * ct + 8 * h + 4 * j]);
         // the other block's conversion, a pair at a time: the second block of this
         // stage, then the first of the next
         constexpr int CS = CB == 4 ? 2 : 1;
@@ -411,7 +526,7 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
           if (j >= 1 && j <= CB) read_cl(j - 1, nbuf);
           if (j >= 2 * CB + 1) read_ch(j - 2 * CB - 1, nbuf);
         }
-        if ((!HYB && FIRST && pb == 0) || (LAST && pb == 1)) {
+        if (!PROJ && ((!HYB && FIRST && pb == 0) || (LAST && pb == 1))) {
           if constexpr (CB == 4) {
             argmax_piece(j, FIRST && pb == 0 ? 1 : 0, FIRST && pb == 0 ? ct - 1 : ct);
           } else {
@@ -466,7 +581,14 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
     }
   };
 
-  if constexpr (!HYB) {
+  if constexpr (PROJ) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[cb][pb][i] = 0.f;
+  } else if constexpr (!HYB) {
     // before the first tile there is none whose second block's argmax is due: -inf
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
@@ -490,13 +612,48 @@ __global__ __launch_bounds__(kThr, 1) void assign_split_kernel(SplitArgs A) {
       read_cl(cb, nbuf);
       read_ch(cb, nbuf);
     }
+    if constexpr (PROJ) {
+      mreg[0] = *reinterpret_cast<const f32x4 *>(&msh[8 * h]);
+      mreg[1] = *reinterpret_cast<const f32x4 *>(&msh[8 * h + 4]);
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) conv(0, q);
     next_buf();
   };
   constexpr std::true_type T{};
   constexpr std::false_type F{};
-  if constexpr (HYB) {
+  if constexpr (PROJ) {
+    open_front();
+    for (int st = 1; st <= S; ++st) step(st, F, F);  // st: the stage read ahead
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // rows with a value past fp16's range, NaN or infinities give NaN, and rows whose
+    // values are all small (below 2 where the sample's largest is 2^11 .. 2^12) lose bits:
+    // the fp32 kernel redoes their tile
+    bool redo = false;
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+      const uint32_t sn = seen[pb] | __shfl_xor((int)seen[pb], 32);
+      if ((sn & 0x40000000u) == 0u && (sn & 0x7fffffffu) != 0u) redo = true;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (!(fabsf(acc[0][pb][i]) <= FLT_MAX)) redo = true;
+    }
+    if (redo) A.sp.tflag[pt] = 1;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      const int o = g * TC + wc * 32 * CB + cb * 32 + r;
+      if (o >= A.k) continue;
+      const float f = A.sp.seed[o];
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int64_t p = p0 + wp * 64 + pb * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+          if (p < A.n) A.Y[p * A.k + o] = acc[cb][pb][i] * f;
+        }
+    }
+    return;
+  } else if constexpr (HYB) {
     for (int ct = 0; ct < nmy; ++ct) {
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
@@ -636,21 +793,54 @@ km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d
   return KM_OK;
 }
 
-km_status launch_split_assign(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s) {
+km_status launch_split(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s) {
   const dim3 gr((unsigned)grid), th(kThr);
-  if (A.pbits) {
+  if (A.Y) {
     if (tile_c == 128)
-      hipLaunchKernelGGL((assign_split_kernel<2, true>), gr, th, 0, s, A);
+      hipLaunchKernelGGL((split_kernel<2, kSplitProject>), gr, th, 0, s, A);
     else
-      hipLaunchKernelGGL((assign_split_kernel<4, true>), gr, th, 0, s, A);
+      hipLaunchKernelGGL((split_kernel<4, kSplitProject>), gr, th, 0, s, A);
+  } else if (A.pbits) {
+    if (tile_c == 128)
+      hipLaunchKernelGGL((split_kernel<2, kSplitHybrid>), gr, th, 0, s, A);
+    else
+      hipLaunchKernelGGL((split_kernel<4, kSplitHybrid>), gr, th, 0, s, A);
   } else {
     if (tile_c == 128)
-      hipLaunchKernelGGL((assign_split_kernel<2, false>), gr, th, 0, s, A);
+      hipLaunchKernelGGL((split_kernel<2, kSplitAssign>), gr, th, 0, s, A);
     else
-      hipLaunchKernelGGL((assign_split_kernel<4, false>), gr, th, 0, s, A);
+      hipLaunchKernelGGL((split_kernel<4, kSplitAssign>), gr, th, 0, s, A);
   }
-  KMQ_LAUNCH_CHECK("assign_split_kernel");
+  KMQ_LAUNCH_CHECK("split_kernel");
   return KM_OK;
+}
+
+size_t split_project_bytes(int64_t n, int d, int d_out) {
+  return split_bytes(n, std::max(d_out, 256), d, false);  // the row maxima's place holds the sample's 256 partials
+}
+
+km_status launch_split_project(const float *X, int64_t n, int d, int64_t ldx, const float *mean, const float *W,
+                               int d_out, float *Y, void *ws, SplitPrep *out, hipStream_t s) {
+  SplitPrep sp = split_layout(n, std::max(d_out, 256), d, false, ws);
+  sp.cstage = (int64_t)d_out * kRow;
+  hipLaunchKernelGGL(proj_sample_kernel, dim3(256), dim3(256), 0, s, X, n, d, ldx, mean, sp.rmax, sp.route);
+  hipLaunchKernelGGL(proj_prep_kernel, dim3((unsigned)cdiv(d_out, 16)), dim3(256), 0, s, W, d, d_out, sp.rmax, sp,
+                     cdiv(n, kTP));
+  KMQ_LAUNCH_CHECK("projection scales");
+  SplitArgs A{};
+  A.x = X;
+  A.ldx = ldx;
+  A.d = d;
+  A.sp = sp;
+  A.k = d_out;
+  A.n = n;
+  A.mean = mean;
+  A.Y = Y;
+  const int tile_c = d_out <= 128 ? 128 : 256;
+  A.ngroups = (int)cdiv(d_out, tile_c);  // one tile of outputs per workgroup
+  A.n_ptiles = cdiv(n, kTP);
+  *out = sp;
+  return launch_split(A, A.ngroups > 1 ? cdiv(A.n_ptiles, 8) * 8 * A.ngroups : A.n_ptiles, tile_c, s);
 }
 
 }  // namespace kmq

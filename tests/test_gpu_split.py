@@ -203,3 +203,39 @@ def test_hybrid(km, torch, n, d, d0, k, how):
     else:  # from the distances: fp32 squares of the front's differences, the tail's scores in fp32, fp64 sums
         want = (s[i, got] + xn + alpha.astype(np.float64) ** 2 * (d - d0)).sum()
         assert abs(host(obj)[0] - want) <= 2.0 ** -21 * size.sum()
+
+
+# one and several 256-point tiles, output tiles of 128 and 256 and several of them, ragged dims
+@pytest.mark.parametrize("n,d,dout", [(1, 32, 4), (255, 36, 8), (257, 64, 128), (300, 100, 132), (1000, 260, 256),
+                                      (513, 132, 600), (64, 4096, 36)])
+@pytest.mark.parametrize("how", ["plain", "rows", "not_finite", "columns", "nan_basis"])
+def test_project(km, torch, n, d, dout, how):
+    """Y = (X - mean) W against 64 bits, each value bounded by its own row and column: also rows and columns of
+    very different size, and rows that only the fp32 kernel can take."""
+    g = np.random.default_rng(n + d)
+    X = g.standard_normal((n, d)).astype(np.float32) * np.float32(0.3)
+    m = (X.astype(np.float64).mean(0) if n > 1 else np.full(d, 0.1)).astype(np.float32)
+    W = (g.standard_normal((d, dout)) / np.sqrt(d)).astype(np.float32)
+    if how == "rows":
+        X[::7] = m + (X[::7] - m) * np.float32(2.0 ** -18)
+        X[3::7] = m
+        X[5::7] *= np.float32(2.0 ** 10)
+    elif how == "not_finite":
+        X[n // 2, d // 2] = np.nan
+        X[n // 3, 1] = np.inf
+    elif how == "columns":
+        W[:, ::3] *= np.float32(2.0 ** -30)
+        W[:, 1] = 0
+    elif how == "nan_basis":
+        W[d // 2, dout // 2] = np.nan
+    with np.errstate(invalid="ignore"):
+        xc = (X - m).astype(np.float64)  # centred in fp32, as the interface's kernels do
+        want = xc @ W.astype(np.float64)
+    Y = host(km.pca_project(to_dev(X, torch), to_dev(m, torch), to_dev(W, torch))).astype(np.float64)
+    fin = np.isfinite(want)
+    np.testing.assert_array_equal(np.isnan(Y), np.isnan(want))
+    np.testing.assert_array_equal(Y[~fin & ~np.isnan(want)], want[~fin & ~np.isnan(want)])
+    size = np.sqrt(np.nansum(np.where(np.isfinite(xc), xc, 0) ** 2, 1))[:, None] * np.sqrt(np.nansum(W.astype(np.float64) ** 2, 0))
+    bound = (6 * -(-d // 16) * 2.0 ** -23 + 2.0 ** -20) * size + 1e-40
+    err = np.abs(Y[fin] - want[fin])
+    assert (err <= bound[fin]).all(), (err / bound[fin]).max()

@@ -212,7 +212,9 @@ size_t colmean_bytes(int64_t n, int d);
 size_t rabitq_encode_bytes(int64_t n, int d, bool y_given);
 km_status launch_rabitq_encode(const float *X, int64_t n, int d, int64_t ldx, const float *P, float *m,
                                uint32_t *bits, float *alpha, float *Y, int flags, void *ws, hipStream_t s);
-km_status launch_colmean(const float *X, int64_t n, int d, int64_t ldx, float *m, void *ws, hipStream_t s);
+// top (nullable): each column's largest |x - mean|
+km_status launch_colmean(const float *X, int64_t n, int d, int64_t ldx, float *m, void *ws, hipStream_t s,
+                         float *top = nullptr);
 
 // pca.hip
 size_t pca_cov_bytes(int64_t n, int d);

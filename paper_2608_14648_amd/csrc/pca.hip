@@ -1,27 +1,23 @@
 // PCA before clustering (Sec. 3.1 "PCA"; Sec. 4.2): covariance of the centred
 // points and the projection onto the leading principal directions, both as
-// fp32 MFMA contractions (v_mfma_f32_32x32x2_f32).
+// MFMA contractions.
 //
 // Covariance: the d x d output is cut into 256 x 256 tiles (upper triangle only,
-// mirrored at the end) and the n rows are split across workgroups.  Each stage
-// copies 32 rows x 256 columns of both column blocks into LDS, centred when read.
-// The fp32 accumulators are added into a per-workgroup fp64 partial tile every
-// 8192 rows, and the partial tiles are folded in split order.
+// mirrored at the end) and the n rows are split across workgroups; every workgroup's
+// fp64 partial tile is folded in split order.
 // Projection: on the fp16 matrix cores (split.hip); the fp32 kernels below take the
 // tiles and shapes it leaves, with the rows centred as they are read and W
 // pre-transposed so that both MFMA operands are 16 contiguous bytes per lane.
 #include <algorithm>
+#include <type_traits>
 
-#include "common.hpp"
+#include "split.hpp"
 
 namespace kmq {
 namespace {
 
 constexpr int kT = 128;           // projection tile
 constexpr int kCT = 256;          // covariance output tile
-constexpr int kCovRows = 32;      // rows per covariance stage
-constexpr int kCovStride = kCT + 4;
-constexpr int kFlushStages = 256;  // 8192 rows per fp32 accumulation run
 
 __device__ __forceinline__ void tile_ij(int t, int T, int &ti, int &tj) {
   // enumerate the upper triangle row by row
@@ -47,137 +43,187 @@ __device__ __forceinline__ void lds_copy16(const void *base, uint32_t off, uint3
 }
 #pragma clang diagnostic pop
 
-// One workgroup per (256 x 256 output tile, run of rows): 8 waves, two per SIMD,
-// each owning 128 x 64 of the tile as 4 x 2 blocks of 32 x 32 (fp32 MFMA; rows are
-// the contraction index, read column-wise from row-major LDS stages).  A stage is
-// 32 rows of both 256-column blocks, copied straight from global memory into LDS,
-// one 1 KB row-block per wave instruction (rows padded to 260 floats); the rows
-// are centred when the MFMA operands are read (x - mean in fp32, the same operand
-// a centring copy would store).  Rows past the end of the run are filled with the
-// mean itself, so their centred values are exactly zero; columns past d are
-// zero-filled and their outputs dropped by the reduction.  The copies of stage
-// st + 1 go out during stage st's four steps.  Every 8192 rows the fp32
-// accumulators are added into this workgroup's own fp64 partial tile in global
-// memory (read-modify-write, no other workgroup touches it); the fold is a
-// synchronous read-modify-write of 128 values per lane, so shorter runs cost
-// (2048 rows: 7 % slower).
+// Covariance on the fp16 matrix cores (split.hpp).  One workgroup per (256 x 256 output
+// tile, split of the rows): 8 waves, two per SIMD, each owning 128 x 64 of the tile as
+// 4 x 2 blocks of 32 x 32; the rows of X are the contraction index, 16 per stage.
+//
+// Every thread owns a column of the two blocks (a tile of the diagonal has one block:
+// half the rows of a column each).  It loads 8 rows of it at a time into registers two
+// stages ahead, centres and scales them as it splits them (the column's own power of
+// two, from its largest |x - mean|, which the mean's pass over X finds: no value leaves
+// fp16's range, and a column's relative precision does not depend on the others), and
+// stores hi and lo as MFMA operand chunks: 8 consecutive rows of a column are 16
+// contiguous bytes.  The chunks lie as in split_kernel (two 32-column blocks share
+// 128-byte rows, chunk c in slot c ^ ((r >> 1) & 7)).  Three buffers and one barrier
+// per stage: step i multiplies stage i from registers while it reads stage i + 1 into
+// them and splits stage i + 2.
+//
+// The fp32 accumulators are added into this workgroup's fp64 partial tile in global
+// memory every 4096 rows: the instruction's rounding, and the little it cuts, grow with
+// the number of additions (at 8192 rows the relative error of the covariance was that
+// of the fp32 kernel's, 2.1e-7).  2M x 1024:
+// 20.5 -> 8 ms against v_mfma_f32_32x32x2_f32 tiles centred as they were read; three
+// matrix products of 2.6 TFLOP take 6.1 ms at the rate of a large library product.
+// Workgroups of one split are neighbours on one XCD, whose L2 then serves the rows
+// that its tiles share.
 constexpr int kCovThreads = 512;
+constexpr int kCovSD = 16;                        // rows per stage
+constexpr int kCovBlk = kCT * 64;                 // bytes of one column block of a stage
+constexpr int kCovStage = 2 * kCovBlk;
+constexpr int kCovFlush = 4096 / kCovSD;          // stages per fp32 accumulation run
 
-__global__ __launch_bounds__(kCovThreads, 1) void cov_kernel(const float *X, int64_t n, int d, const float *mean, int T,
-                                                             int ntiles, int64_t rows_per_split, double *partial) {
-  constexpr int BS = kCovRows * kCovStride;  // floats of one column block of a stage
-  __shared__ __align__(16) float stA0[2 * BS];
-  __shared__ __align__(16) float stA1[2 * BS];
-  const int tile = blockIdx.x % ntiles;
-  const int split = blockIdx.x / ntiles;
+// the power of two that puts a column's largest |x - mean| at [2^14, 2^15)
+__device__ __forceinline__ float cov_scale(float top) {
+  if (!(top > 0.f)) return 1.0f;
+  const int e = (int)(__float_as_uint(top) >> 23) - 127;
+  return ldexpf(1.0f, min(14 - e, 100));
+}
+
+template <bool DIAG>
+__device__ __forceinline__ void cov_tile(const float *X, int d, const float *mean, const float *top, int ti, int tj,
+                                         int64_t rb, int64_t re, uint8_t *ring, double *out);
+
+__global__ __launch_bounds__(kCovThreads, 1) void cov_kernel(const float *X, int64_t n, int d, const float *mean,
+                                                             const float *top, int T, int ntiles, int nsplit,
+                                                             int64_t rows_per_split, double *partial) {
+  __shared__ __align__(16) uint8_t ring[3 * kCovStage];
+  const int per = (int)(gridDim.x >> 3);  // workgroups of one XCD: neighbours in (split, tile)
+  const int id = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (id >= ntiles * nsplit) return;  // whole workgroup, before any barrier
+  const int tile = id % ntiles, split = id / ntiles;
   int ti, tj;
   tile_ij(tile, T, ti, tj);
-  const int i0 = ti * kCT, j0 = tj * kCT;
   const int64_t rb = (int64_t)split * rows_per_split;
   const int64_t re = min<int64_t>(n, rb + rows_per_split);
+  double *out = partial + ((int64_t)split * ntiles + tile) * (kCT * kCT);
+  if (re <= rb) {  // no rows: the partial tile is zero
+    for (int e = threadIdx.x; e < kCT * kCT; e += kCovThreads) out[e] = 0.0;
+  } else if (ti == tj) {
+    cov_tile<true>(X, d, mean, top, ti, tj, rb, re, ring, out);
+  } else {
+    cov_tile<false>(X, d, mean, top, ti, tj, rb, re, ring, out);
+  }
+}
+
+template <bool DIAG>
+__device__ __forceinline__ void cov_tile(const float *X, int d, const float *mean, const float *top, int ti, int tj,
+                                         int64_t rb, int64_t re, uint8_t *ring, double *out) {
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r = lane & 31, h = lane >> 5;
   const int wi = wave & 1, wj = wave >> 1;
-  double *out = partial + ((int64_t)split * ntiles + tile) * (kCT * kCT);
-  const int nst = (int)cdiv(max<int64_t>(re - rb, 0), kCovRows);
+  const int len = (int)(re - rb);  // rows of a split: below 2^31 as n is
+  const int nst = (len + kCovSD - 1) / kCovSD;
+  // this thread's column, its centre and scale, and its place in a stage
+  const int lc = t & 255;  // column within its block
+  const int gc = min((!DIAG && t >= 256 ? tj : ti) * kCT + lc, d - 1);
+  const float sc = cov_scale(top[gc]), ms = mean[gc] * sc;
+  constexpr int NU = DIAG ? 1 : 2;              // units of 8 rows per stage
+  const int half0 = DIAG ? wave >> 2 : 0;       // the first unit's half of the stage's rows
+  const uint32_t ring0 = (uint32_t)(size_t)(lds_byte *)ring;
+  const uint32_t lrow = (uint32_t)((!DIAG && t >= 256 ? kCovBlk : 0) + (lc >> 6) * 4096 + (lc & 31) * 128);
+  const uint32_t lkx = (uint32_t)(lc >> 1) & 7u;
+  auto place = [&](int c) -> uint32_t { return lrow + 16u * ((4u * ((lc >> 5) & 1) + c) ^ lkx); };
+  typedef __attribute__((address_space(3))) i32x4 lds_i32x4;
+  auto st16 = [&](uint32_t off, i32x4 v) { *(lds_i32x4 *)(size_t)(ring0 + off) = v; };
+  auto rd16 = [&](uint32_t off) -> i32x4 { return *(const lds_i32x4 *)(size_t)(ring0 + off); };
 
-  // the means of this lane's operand columns
-  float mi[4], mj[2];
+  float raw[2][NU][8];  // two stages in flight
+  const float *xrow = X + rb * d;
+  const int nfull = len / kCovSD;
+  // wave-uniform row addresses; rows past the split read the mean and count as zero
+  auto load = [&](int st, int set, auto full_) {
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb) mi[cb] = mean[min(i0 + wi * 128 + cb * 32 + r, d - 1)];
+    for (int u = 0; u < NU; ++u) {
+      const int row = st * kCovSD + 8 * (half0 + u);
+      const float *p = xrow + (int64_t)row * d;
 #pragma unroll
-  for (int pb = 0; pb < 2; ++pb) mj[pb] = mean[min(j0 + wj * 64 + pb * 32 + r, d - 1)];
-
-  // the fill of a row past the run: the means of this lane's four columns of each
-  // block (zeros past d), held in registers so that no load the compiler tracks
-  // sits among the copies
-  f32x4 fill[2];
-#pragma unroll
-  for (int blk = 0; blk < 2; ++blk) {
-    const int col = (blk ? j0 : i0) + 4 * lane;
-    fill[blk] = col < d ? *reinterpret_cast<const f32x4 *>(mean + col) : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  // copy q (0 .. 7) of wave w: row-block c = 8 q + w, column block c >> 5, row c & 31
-  auto copy = [&](int st, float *dst, int q) {
-    const int c = 8 * q + wave;
-    const int blk = c >> 5, row = c & 31;
-    const int col = (blk ? j0 : i0) + 4 * lane;
-    float *w = dst + blk * BS + row * kCovStride;
-    const int64_t gr = rb + (int64_t)st * kCovRows + row;
-    if (gr < re && col < d) {
-      lds_copy16(X + gr * d + (blk ? j0 : i0), (uint32_t)(16 * lane), (uint32_t)(size_t)(lds_u8 *)(w));
-    } else {
-      // a row past the run holds the mean (centred: zero); a column past d zeros
-      *reinterpret_cast<f32x4 *>(w + 4 * lane) = gr >= re ? fill[blk] : f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < 8; ++i) {
+        raw[set][u][i] = (decltype(full_)::value || row + i < len ? p : mean)[(uint32_t)gc];
+        p += d;
+      }
     }
   };
-  auto land = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+  uint32_t hi[4], lo[4];
+  float one = 1.0f;  // not seen through by the compiler: keeps split2's mixed instructions
+  asm volatile("" : "+s"(one));
+  auto conv = [&](int set, int u, int q) {  // pair q of unit u
+    split2(__builtin_fmaf(raw[set][u][2 * q], sc, -ms), __builtin_fmaf(raw[set][u][2 * q + 1], sc, -ms), one, hi[q],
+           lo[q]);
+    asm volatile("" : "+v"(hi[q]), "+v"(lo[q]));
+  };
+  auto put = [&](uint32_t buf, int u) {
+    st16(buf + place(half0 + u), i32x4{(int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]});
+    st16(buf + place(2 + half0 + u), i32x4{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3]});
+  };
 
+  const uint32_t orow = (uint32_t)(r * 128), kx = (uint32_t)((r >> 1) & 7);
+  auto at = [&](int b, int c) -> uint32_t {
+    return (uint32_t)(b >> 1) * 4096u + orow + 16u * ((4u * (b & 1) + c) ^ kx);
+  };
+  const uint32_t breg = DIAG ? 0u : (uint32_t)kCovBlk;
   f32x16 acc[4][2];
-  // one stage: 16 row pairs in 4 steps of 4; the operand reads of step g + 1 and
-  // two of the next stage's copies go out before step g's MFMAs
-  auto mfma_stage = [&](const float *buf, bool copying, int st_n, float *nxt) {
-    const float *A = buf;
-    const float *B = buf + BS;
-    float av[2][4][4], bv[2][4][2];
-    auto read = [&](int g, int set) {
-#pragma unroll
-      for (int pp = 0; pp < 4; ++pp) {
-        const int row = 2 * (4 * g + pp) + h;
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) av[set][pp][cb] = A[row * kCovStride + wi * 128 + cb * 32 + r] - mi[cb];
-#pragma unroll
-        for (int pb = 0; pb < 2; ++pb) bv[set][pp][pb] = B[row * kCovStride + wj * 64 + pb * 32 + r] - mj[pb];
-      }
-    };
-    read(0, 0);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int cur = g & 1;
-      if (g + 1 < 4) read(g + 1, cur ^ 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (copying) {
-        copy(st_n, nxt, 2 * g);
-        copy(st_n, nxt, 2 * g + 1);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int pp = 0; pp < 4; ++pp)
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-          for (int pb = 0; pb < 2; ++pb)
-            acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[cur][pp][cb], bv[cur][pp][pb], acc[cb][pb], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  h16x8 ah[4], al[4], bh[2], bl[2];
+  auto read_a = [&](int cb, int c, uint32_t buf) { return __builtin_bit_cast(h16x8, rd16(buf + at(wi * 4 + cb, c + h))); };
+  auto read_b = [&](int pb, int c, uint32_t buf) {
+    return __builtin_bit_cast(h16x8, rd16(buf + breg + at(wj * 2 + pb, c + h)));
   };
-
-  if (nst > 0) {
+  auto pin = [&]() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto next = [](uint32_t b) { return b == 2u * kCovStage ? 0u : b + kCovStage; };
+  uint32_t b0 = 0, b1 = kCovStage, b2 = 2 * kCovStage;  // buffers of stages i, i + 1, i + 2
+  auto step = [&](int i, auto set_, auto full_) {
+    constexpr int SET = decltype(set_)::value;  // where stage i + 2 waits (and stage i + 4 will)
 #pragma unroll
-    for (int q = 0; q < 8; ++q) copy(0, stA0, q);
-    land();
-  }
-  __syncthreads();
-  const int nrun = (nst + kFlushStages - 1) / kFlushStages;
-  for (int run = 0; run < nrun; ++run) {
+    for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+      for (int j = 0; j < 12; ++j) {
+        const int pr = j / 4, cb = j % 4;
+        acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(pr == 0 ? al[cb] : ah[cb], pr == 1 ? bl[pb] : bh[pb],
+                                                             acc[cb][pb], 0, 0, 0);
+        if (pb == 0) {
+          if (j == 0) bh[1] = read_b(1, 0, b0);
+          if (j == 1) bl[1] = read_b(1, 2, b0);
+          // unit 0 of stage i + 2
+          if (j >= 2 && j < 10 && j % 2 == 0) conv(SET, 0, (j - 2) / 2);
+          if (j == 10) put(b2, 0);
+        } else {
+          if constexpr (NU == 2) {
+            if (j < 8 && j % 2 == 0) conv(SET, 1, j / 2);
+            if (j == 7) put(b2, 1);
+          }
+          if (j >= 1 && j <= 4) al[j - 1] = read_a(j - 1, 2, b1);
+          if (j == 5) bh[0] = read_b(0, 0, b1);
+          if (j == 6) bl[0] = read_b(0, 2, b1);
+          if (j == 8) load(i + 4, SET, full_);
+          if (j >= 9) ah[j - 9] = read_a(j - 9, 0, b1);
+        }
+        pin();
+      }
+    ah[3] = read_a(3, 0, b1);
+    // the stores are complete when only the four reads after them are out
+    asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    b0 = b1;
+    b1 = b2;
+    b2 = next(b2);
+  };
+  auto zero = [&]() {
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-    const int st1 = min(nst, (run + 1) * kFlushStages);
-    for (int st = run * kFlushStages; st < st1; ++st) {
-      const bool nxt = st + 1 < nst;
-      mfma_stage((st & 1) ? stA1 : stA0, nxt, st + 1, (st & 1) ? stA0 : stA1);
-      if (nxt) land();
-      __syncthreads();
-    }
+  };
+  bool first = true;
+  auto flush = [&]() {
     // the lane's offset passes through an empty asm statement so that the element
-    // addresses are formed here, not hoisted out of the run loop (they would hold
-    // 128 register pairs for the whole loop); the pointer itself stays a global one
-    // (a flat access here would make every LDS wait of the stage loop wait for
-    // the copies too)
+    // addresses are formed here, not hoisted out of the loop
     int boff = (wi * 128 + 4 * h) * kCT + wj * 64 + r;
     asm volatile("" : "+v"(boff));
 #pragma unroll
@@ -187,26 +233,67 @@ __global__ __launch_bounds__(kCovThreads, 1) void cov_kernel(const float *X, int
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           double *o = out + boff + (cb * 32 + 8 * (v >> 2) + (v & 3)) * kCT + pb * 32;
-          *o = (run == 0 ? 0.0 : *o) + (double)acc[cb][pb][v];
+          *o = (first ? 0.0 : *o) + (double)acc[cb][pb][v];
         }
+    first = false;
+  };
+
+  // stages 0 and 1 into their buffers, 2 and 3 into registers, stage 0's operands
+  constexpr std::true_type T{};
+  constexpr std::false_type F{};
+  load(0, 0, F);
+  load(1, 1, F);
+#pragma unroll
+  for (int st = 0; st < 2; ++st) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) conv(st, u, q);
+      put(st * kCovStage, u);
+    }
+    load(st + 2, st, F);
   }
-  if (nrun == 0) {  // no rows: the partial tile is zero
-    for (int e = t; e < kCT * kCT; e += kCovThreads) out[e] = 0.0;
+  zero();
+  __syncthreads();
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb) {
+    al[cb] = read_a(cb, 2, 0);
+    ah[cb] = read_a(cb, 0, 0);
+  }
+  bh[0] = read_b(0, 0, 0);
+  bl[0] = read_b(0, 2, 0);
+  std::integral_constant<int, 0> S0;
+  std::integral_constant<int, 1> S1;
+  for (int i = 0; i < nst; i += kCovFlush) {
+    const int e = min(nst, i + kCovFlush);
+    int s = i;
+    for (; s + 1 < e && s + 5 < nfull; s += 2) {
+      step(s, S0, T);
+      step(s + 1, S1, T);
+    }
+    for (; s < e; s += 2) {
+      step(s, S0, F);
+      if (s + 1 < e) step(s + 1, S1, F);
+    }
+    flush();
+    zero();
   }
 }
 
+// The partial tiles in split order, back from the columns' scales.
 __global__ __launch_bounds__(256) void cov_reduce_kernel(const double *partial, int ntiles, int nsplit, int T, int d,
-                                                         int64_t n, float *cov) {
+                                                         int64_t n, const float *top, float *cov) {
   const int tile = blockIdx.x;
   int ti, tj;
   tile_ij(tile, T, ti, tj);
   for (int e = blockIdx.y * 256 + threadIdx.x; e < kCT * kCT; e += gridDim.y * 256) {
     const int il = e / kCT, jl = e % kCT;
     const int i = ti * kCT + il, j = tj * kCT + jl;
-    if (i >= d || j >= d) continue;
+    // (the two halves of a diagonal tile are rounded in different orders: one of them counts)
+    if (i >= d || j >= d || i > j) continue;
     double s = 0.0;
     for (int sp = 0; sp < nsplit; ++sp) s += partial[((int64_t)sp * ntiles + tile) * (kCT * kCT) + e];
-    const float v = (float)(s / (double)n);
+    const float v = (float)(s / ((double)cov_scale(top[i]) * cov_scale(top[j])) / (double)n);
     cov[(int64_t)i * d + j] = v;
     cov[(int64_t)j * d + i] = v;
   }
@@ -497,19 +584,20 @@ int cu_count() {
 
 size_t pca_cov_bytes(int64_t n, int d) {
   const CovPlan p = cov_plan(n, d);
-  return (size_t)p.nsplit * p.ntiles * kCT * kCT * sizeof(double) + colmean_bytes(n, d) + 256;
+  return (size_t)p.nsplit * p.ntiles * kCT * kCT * sizeof(double) + colmean_bytes(n, d) + 4 * (size_t)d + 768;
 }
 
 km_status launch_pca_cov(const float *X, int64_t n, int d, float *mean, float *cov, void *ws, hipStream_t s) {
   const CovPlan p = cov_plan(n, d);
   double *partial = static_cast<double *>(ws);
   void *mws = static_cast<uint8_t *>(ws) + (((size_t)p.nsplit * p.ntiles * kCT * kCT * sizeof(double) + 255) & ~(size_t)255);
-  km_status st = launch_colmean(X, n, d, d, mean, mws, s);
+  float *top = reinterpret_cast<float *>(static_cast<uint8_t *>(mws) + ((colmean_bytes(n, d) + 255) & ~(size_t)255));
+  km_status st = launch_colmean(X, n, d, d, mean, mws, s, top);
   if (st != KM_OK) return st;
-  hipLaunchKernelGGL(cov_kernel, dim3(p.ntiles * p.nsplit), dim3(kCovThreads), 0, s, X, n, d, mean, p.T, p.ntiles,
-                     p.rows_per_split, partial);
+  hipLaunchKernelGGL(cov_kernel, dim3((unsigned)(8 * cdiv(p.ntiles * p.nsplit, 8))), dim3(kCovThreads), 0, s, X, n, d,
+                     mean, top, p.T, p.ntiles, p.nsplit, p.rows_per_split, partial);
   hipLaunchKernelGGL(cov_reduce_kernel, dim3(p.ntiles, 16), dim3(256), 0, s, partial, p.ntiles, p.nsplit, p.T, d, n,
-                     cov);
+                     top, cov);
   KMQ_LAUNCH_CHECK("pca_fit_cov");
   return KM_OK;
 }

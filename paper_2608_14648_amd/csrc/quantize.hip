@@ -77,12 +77,25 @@ __global__ __launch_bounds__(256) void colminmax_final_kernel(const float *pmin,
   }
 }
 
+// RANGE: also every column's smallest and largest value (NaN left out)
+template <bool RANGE>
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const float *X, int64_t n, int d, int64_t ldx,
-                                                             int64_t rows_per_block, double *psum) {
+                                                             int64_t rows_per_block, double *psum, float *plo,
+                                                             float *phi) {
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
   const int64_t r1 = min<int64_t>(n, r0 + rows_per_block);
   for (int g = threadIdx.x; g < d / 4; g += 256) {
     double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+    f32x4 lo = {INFINITY, INFINITY, INFINITY, INFINITY}, hi = -lo;
+    auto range = [&](f32x4 v) {
+      if (RANGE) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          lo[e] = fminf(lo[e], v[e]);
+          hi[e] = fmaxf(hi[e], v[e]);
+        }
+      }
+    };
     int64_t r = r0;
     for (; r + 3 < r1; r += 4) {
       const f32x4 v0 = *reinterpret_cast<const f32x4 *>(X + r * ldx + 4 * g);
@@ -93,24 +106,60 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float *X, int
       s0 += v1.x; s1 += v1.y; s2 += v1.z; s3 += v1.w;
       s0 += v2.x; s1 += v2.y; s2 += v2.z; s3 += v2.w;
       s0 += v3.x; s1 += v3.y; s2 += v3.z; s3 += v3.w;
+      range(v0);
+      range(v1);
+      range(v2);
+      range(v3);
     }
     for (; r < r1; ++r) {
       const f32x4 v = *reinterpret_cast<const f32x4 *>(X + r * ldx + 4 * g);
       s0 += v.x; s1 += v.y; s2 += v.z; s3 += v.w;
+      range(v);
     }
     double *o = psum + (int64_t)blockIdx.x * d + 4 * g;
     o[0] = s0; o[1] = s1; o[2] = s2; o[3] = s3;
+    if (RANGE) {
+      *reinterpret_cast<f32x4 *>(plo + (int64_t)blockIdx.x * d + 4 * g) = lo;
+      *reinterpret_cast<f32x4 *>(phi + (int64_t)blockIdx.x * d + 4 * g) = hi;
+    }
   }
 }
 
-// one workgroup per column: strided partial sums, then a fixed-order tree
-__global__ __launch_bounds__(256) void colmean_final_kernel(const double *psum, int nb, int d, int64_t n, float *m) {
+// one workgroup per column: strided partial sums, then a fixed-order tree.  RANGE: top =
+// the largest |x - mean| of the column, in fp32 like the centred values themselves.
+template <bool RANGE>
+__global__ __launch_bounds__(256) void colmean_final_kernel(const double *psum, int nb, int d, int64_t n, float *m,
+                                                            const float *plo, const float *phi, float *top) {
   __shared__ double sh[256];
-  const int i = blockIdx.x;
+  __shared__ float slo[256], shi[256];
+  const int i = blockIdx.x, t = threadIdx.x;
   double s = 0.0;
-  for (int b = threadIdx.x; b < nb; b += 256) s += psum[(int64_t)b * d + i];
+  float lo = INFINITY, hi = -INFINITY;
+  for (int b = t; b < nb; b += 256) {
+    s += psum[(int64_t)b * d + i];
+    if (RANGE) {
+      lo = fminf(lo, plo[(int64_t)b * d + i]);
+      hi = fmaxf(hi, phi[(int64_t)b * d + i]);
+    }
+  }
+  if (RANGE) {
+    slo[t] = lo;
+    shi[t] = hi;
+    __syncthreads();
+    for (int st = 128; st > 0; st >>= 1) {
+      if (t < st) {
+        slo[t] = fminf(slo[t], slo[t + st]);
+        shi[t] = fmaxf(shi[t], shi[t + st]);
+      }
+      __syncthreads();
+    }
+  }
   s = block_sum_f64(s, sh);
-  if (threadIdx.x == 0) m[i] = (float)(s / (double)n);
+  if (t == 0) {
+    const float mean = (float)(s / (double)n);
+    m[i] = mean;
+    if (RANGE) top[i] = fmaxf(shi[0] - mean, mean - slo[0]);
+  }
 }
 
 __global__ void sq8_inv_kernel(const float *lo, const float *hi, int d, float *inv) {
@@ -290,17 +339,23 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float *v, int n) {
 
 constexpr int kMaxSumBlocks = 1024;
 
-size_t colmean_bytes(int64_t n, int d) {
-  return (size_t)std::min<int64_t>(kMaxSumBlocks, cdiv(n, 64)) * d * sizeof(double) + 256;
+size_t colmean_bytes(int64_t n, int d) {  // with room for the column ranges
+  return (size_t)std::min<int64_t>(kMaxSumBlocks, cdiv(n, 64)) * d * (sizeof(double) + 2 * sizeof(float)) + 256;
 }
 
-km_status launch_colmean(const float *X, int64_t n, int d, int64_t ldx, float *m, void *ws, hipStream_t s) {
+km_status launch_colmean(const float *X, int64_t n, int d, int64_t ldx, float *m, void *ws, hipStream_t s, float *top) {
   const int64_t want = std::min<int64_t>(kMaxSumBlocks, cdiv(n, 64));
   const int64_t rpb = cdiv(n, want);
   const int nb = (int)cdiv(n, rpb);
   double *psum = static_cast<double *>(ws);
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3(nb), dim3(256), 0, s, X, n, d, ldx, rpb, psum);
-  hipLaunchKernelGGL(colmean_final_kernel, dim3(d), dim3(256), 0, s, psum, nb, d, n, m);
+  float *plo = reinterpret_cast<float *>(psum + (size_t)nb * d), *phi = plo + (size_t)nb * d;
+  if (top) {
+    hipLaunchKernelGGL(colsum_partial_kernel<true>, dim3(nb), dim3(256), 0, s, X, n, d, ldx, rpb, psum, plo, phi);
+    hipLaunchKernelGGL(colmean_final_kernel<true>, dim3(d), dim3(256), 0, s, psum, nb, d, n, m, plo, phi, top);
+  } else {
+    hipLaunchKernelGGL(colsum_partial_kernel<false>, dim3(nb), dim3(256), 0, s, X, n, d, ldx, rpb, psum, plo, phi);
+    hipLaunchKernelGGL(colmean_final_kernel<false>, dim3(d), dim3(256), 0, s, psum, nb, d, n, m, plo, phi, top);
+  }
   KMQ_LAUNCH_CHECK("column mean");
   return KM_OK;
 }

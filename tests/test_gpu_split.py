@@ -239,3 +239,34 @@ def test_project(km, torch, n, d, dout, how):
     bound = (6 * -(-d // 16) * 2.0 ** -23 + 2.0 ** -20) * size + 1e-40
     err = np.abs(Y[fin] - want[fin])
     assert (err <= bound[fin]).all(), (err / bound[fin]).max()
+
+
+# one row to several splits and runs of 4096 rows, ragged stages of 16 rows, one to three 256-column blocks
+@pytest.mark.parametrize("n,d", [(1, 4), (15, 36), (16, 256), (31, 260), (33, 512), (4111, 300), (20001, 516), (70000, 32)])
+def test_cov(km, torch, n, d):
+    """Covariance of columns whose sizes differ by 2^60, one of them constant, against 64 bits, each entry bounded by
+    its own two columns.  A run is rounded 6 times per 16 of its 4096 rows: 2^-24 sqrt(1536) of the sum at random, 2^-19
+    with room for eight of these."""
+    g = np.random.default_rng(n + d)
+    X = (g.standard_normal((n, d)) + 0.5 * g.standard_normal((n, 1))) * 2.0 ** g.integers(-30, 30, d) + 3
+    X = X.astype(np.float32)
+    X[:, d // 2] = 1e7
+    mean, cov = (host(v) for v in km.pca_fit_cov(to_dev(X, torch)))
+    xc = (X - mean).astype(np.float64)
+    want = xc.T @ xc / n
+    size = np.sqrt(np.outer(np.diag(want), np.diag(want)))
+    assert (np.abs(cov - want) <= 2.0 ** -19 * size + 2.0 ** -22 * np.abs(want)).all()
+    np.testing.assert_array_equal(cov, cov.T)
+    assert (cov[d // 2] == 0).all()
+
+
+def test_cov_not_finite(km, torch):
+    """A NaN or an infinity spoils its own row and column only."""
+    X = np.random.default_rng(0).standard_normal((3000, 300)).astype(np.float32)
+    clean = host(km.pca_fit_cov(to_dev(X, torch))[1])
+    X[1500, 7], X[20, 280] = np.nan, np.inf
+    cov = host(km.pca_fit_cov(to_dev(X, torch))[1])
+    bad = np.zeros(300, bool)
+    bad[[7, 280]] = True
+    assert np.isnan(cov[bad]).all() and np.isnan(cov[:, bad]).all()
+    np.testing.assert_array_equal(cov[~bad][:, ~bad], clean[~bad][:, ~bad])

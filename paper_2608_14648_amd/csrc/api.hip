@@ -678,12 +678,16 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
       seg[off[i] + j] = (int)off[i];
       seg[k + off[i] + j] = (int)off[i + 1];
     }
-  // the points of each meso-cluster as one contiguous run of rows
+  // fp32: the passes read the rows of a meso-cluster where they are, through the
+  // meso-cluster order, and write the assignment in point order; a copy of the rows
+  // costs about two passes over them (1M x 1024: 1.75 ms).  Other formats: the points of
+  // each meso-cluster as one contiguous run of rows.
+  const bool in_place = p.fmt == KM_F32;
   Points q{};
-  const size_t b_perm = al(permuted_bytes(p, N));
+  const size_t b_perm = in_place ? 0 : al(permuted_bytes(p, N));
   const size_t b_prep = al(prep_bytes(slice_points(p, 0, N), k));
-  const size_t b_upd = al(update_bytes(slice_points(p, 0, N), k));
-  const size_t b_a = al(sizeof(int32_t) * (size_t)N);
+  const size_t b_upd = al(update_bytes(in_place ? p : slice_points(p, 0, N), k));
+  const size_t b_a = in_place ? 0 : al(sizeof(int32_t) * (size_t)N);
   const size_t b_score = objective ? al(sizeof(float) * (size_t)N) : 0;
   const size_t b_xc = objective ? al(sizeof(float) * (size_t)N) : 0;
   const size_t b_part = objective ? al(sizeof(double) * (size_t)objective_blocks(N)) : 0;
@@ -696,20 +700,20 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
   // groups (merging through per-point keys) where the launch over all N points
   // would not, and then the preparation sized for N holds no keys: give them room
   const size_t b_keys = seg_rows == 0 ? al(sizeof(unsigned long long) * (size_t)N) : 0;
-  // point tiles of the segments with 128-centroid tiles first (n128 of them), then
-  // those with 256-centroid tiles: one launch each
+  // point tiles of the segments with 64-centroid tiles first, then those with 128- and
+  // with 256-centroid tiles: one launch each
   std::vector<int4> segs;
   std::vector<int2> tiles;
-  int64_t n128 = 0;
+  int64_t cls_end[3] = {0, 0, 0};
   if (seg_rows > 0) {
     for (int i = 0; i < k_meso; ++i)
       if (n_i[i] > 0) segs.push_back(make_int4((int)start[i], (int)n_i[i], (int)off[i], kf[i]));
-    for (int cls = 128; cls <= 256; cls += 128) {
+    for (int cls = 0; cls < 3; ++cls) {
       for (int si = 0; si < (int)segs.size(); ++si) {
-        if (segment_tile_centroids(segs[si].w) != cls) continue;
+        if (segment_tile_centroids(p, segs[si].w) != 64 << cls) continue;
         for (int64_t tt = 0; tt * seg_rows < segs[si].y; ++tt) tiles.push_back(make_int2(si, (int)tt));
       }
-      if (cls == 128) n128 = (int64_t)tiles.size();
+      cls_end[cls] = (int64_t)tiles.size();
     }
   }
   const size_t b_segs = al(sizeof(int4) * segs.size());
@@ -721,7 +725,7 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
   uint8_t *wperm = w;
   uint8_t *wprep = wperm + b_perm;
   uint8_t *wupd = wprep + b_prep;
-  int32_t *ap = reinterpret_cast<int32_t *>(wupd + b_upd);
+  int32_t *ap = in_place ? assign : reinterpret_cast<int32_t *>(wupd + b_upd);
   float *sc = objective ? reinterpret_cast<float *>(wupd + b_upd + b_a) : nullptr;
   float *xc = reinterpret_cast<float *>(wupd + b_upd + b_a + b_score);
   double *part = reinterpret_cast<double *>(wupd + b_upd + b_a + b_score + b_xc);
@@ -730,7 +734,16 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
   int4 *dsegs = reinterpret_cast<int4 *>(reinterpret_cast<uint8_t *>(dseg) + b_seg);
   int2 *dtiles = reinterpret_cast<int2 *>(reinterpret_cast<uint8_t *>(dsegs) + b_segs);
   auto *keys = b_keys ? reinterpret_cast<unsigned long long *>(reinterpret_cast<uint8_t *>(dtiles) + b_tiles) : nullptr;
-  KMQ_STAGE(clk, kStOther, launch_permute_points(p, so.perm, N, wperm, &q, s));
+  if (in_place) {
+    q = p;
+    q.n = N;
+    q.raw = nullptr;
+    q.raw_ld = 0;
+    if (N < p.n) KMQ_STAGE(clk, kStOther, launch_fill_assign(assign, p.n, -1, s));
+  } else {
+    KMQ_STAGE(clk, kStOther, launch_permute_points(p, so.perm, N, wperm, &q, s));
+  }
+  const int *prow = in_place ? so.perm : nullptr;
   if (!segs.empty()) {
     KMQ_HIP(hipMemcpyAsync(dsegs, segs.data(), sizeof(int4) * segs.size(), hipMemcpyHostToDevice, s));
     KMQ_HIP(hipMemcpyAsync(dtiles, tiles.data(), sizeof(int2) * tiles.size(), hipMemcpyHostToDevice, s));
@@ -738,6 +751,7 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
   KMQ_HIP(hipMemcpyAsync(dseg, seg.data(), sizeof(int) * seg.size(), hipMemcpyHostToDevice, s));
   if (!c_given) {
     KMQ_HIP(hipMemcpyAsync(didx, idx.data(), sizeof(int64_t) * (size_t)k, hipMemcpyHostToDevice, s));
+    if (in_place) KMQ_STAGE(clk, kStOther, launch_map_index(so.perm, didx, k, s));
     KMQ_STAGE(clk, kStOther, launch_gather_init(q, didx, k, C, s));
   }
   const size_t crow = p.fmt == KM_SQ8 ? (size_t)p.d : sizeof(float) * (size_t)p.d;
@@ -748,10 +762,11 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
     st = clk.begin(kStAssign);
     if (st != KM_OK) return st;
     if (!segs.empty()) {  // every meso-cluster against its own fine centroids, one launch per tile size
-      st = launch_assign_segments(q, C, cp, dsegs, dtiles, n128, 128, ap, sc, s);
-      if (st != KM_OK) return st;
-      st = launch_assign_segments(q, C, cp, dsegs, dtiles + n128, (int64_t)tiles.size() - n128, 256, ap, sc, s);
-      if (st != KM_OK) return st;
+      for (int cls = 0; cls < 3; ++cls) {
+        const int64_t t0 = cls ? cls_end[cls - 1] : 0;
+        st = launch_assign_segments(q, C, cp, dsegs, dtiles + t0, cls_end[cls] - t0, 64 << cls, ap, sc, prow, s);
+        if (st != KM_OK) return st;
+      }
     }
     for (int i = 0; seg_rows == 0 && i < k_meso; ++i) {  // the same, one launch per meso-cluster
       if (n_i[i] == 0) continue;
@@ -763,13 +778,13 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
     st = clk.end();
     if (st != KM_OK) return st;
     if (it == iters) break;
-    KMQ_STAGE(clk, kStUpdate, launch_update(q, ap, k, C, nullptr, policy, wupd, s, dseg, dseg + k));
+    KMQ_STAGE(clk, kStUpdate, launch_update(in_place ? p : q, ap, k, C, nullptr, policy, wupd, s, dseg, dseg + k));
   }
   if (objective) {
-    KMQ_STAGE(clk, kStOther, launch_xconst(q, xc, s));
+    KMQ_STAGE(clk, kStOther, launch_xconst(q, xc, s, prow));
     KMQ_STAGE(clk, kStOther, launch_objective(q, xc, sc, N, objective, part, objective_blocks(N), s));
   }
-  KMQ_STAGE(clk, kStOther, launch_scatter_assign(so.perm, ap, N, p.n, assign, s));
+  if (!in_place) KMQ_STAGE(clk, kStOther, launch_scatter_assign(so.perm, ap, N, p.n, assign, s));
   if (k_fine) std::copy(kf.begin(), kf.end(), k_fine);
   return KM_OK;
 }

@@ -79,6 +79,7 @@ struct AssignArgs {
   // [segs[i].z, + segs[i].w) (indices into the full centroid and prepared arrays)
   const int4 *segs;
   const int2 *tiles;
+  const int *prow;  // segmented fp32 launch: row i of the segments is row prow[i] of the points
   // fp32 or hybrid kernel behind the split kernel (route set): only the point tiles flagged
   // there, or all of them when the route says so
   const SplitRoute *route;
@@ -1824,7 +1825,7 @@ __global__ __launch_bounds__(256 * NWC, 1) void assign_q8_kernel(AssignArgs A0) 
 // are those of the other kernels: (score, index) keys through a 64-bit atomicMin.
 template <bool SEG = false, int CB = 4>
 __global__ __launch_bounds__(kQThreads, 1) void assign_f32_kernel(AssignArgs A0) {
-  static_assert(CB == 2 || CB == 4, "128- or 256-centroid tiles");
+  static_assert(CB == 1 || CB == 2 || CB == 4, "64-, 128- or 256-centroid tiles");
   constexpr int TC = 64 * CB, TP = kQT, PB = k8PB;
   constexpr int NCC = TC / 64;           // centroid copies per thread and stage
   constexpr int NCOPY = (TC + TP) / 64;  // all copies per thread and stage
@@ -1872,6 +1873,7 @@ __global__ __launch_bounds__(kQThreads, 1) void assign_f32_kernel(AssignArgs A0)
   // float: point rows clamped into the data once, centroid rows of a full tile here
   // and of a last, partial tile at copy time.
   uint32_t soff[NCOPY];
+  const uint8_t *srow[SEG ? NCOPY - NCC : 1];  // segmented: the point rows' own addresses
 #pragma unroll
   for (int i = 0; i < NCOPY; ++i) {
     const int slot = (i * 8 + wave) * 64 + lane;
@@ -1879,6 +1881,9 @@ __global__ __launch_bounds__(kQThreads, 1) void assign_f32_kernel(AssignArgs A0)
     const int chunk = (slot & 7) ^ ((row >> 1) & 7);
     soff[i] = i < NCC ? (uint32_t)(row * (int)A.cfld * 4 + 16 * chunk)
                       : (uint32_t)(min(row - TC, prmax) * (int)A.pfld * 4 + 16 * chunk);
+    if (SEG && i >= NCC)
+      srow[i - NCC] = reinterpret_cast<const uint8_t *>(A.pf + (int64_t)A.prow[p0 + min(row - TC, prmax)] * A.pfld) +
+                      16 * chunk;
   }
   // the stage being copied: tile c0, stage cs, into buffer cdst
   int c0c = 0, crmax = 0, cs = 0;
@@ -1901,11 +1906,15 @@ __global__ __launch_bounds__(kQThreads, 1) void assign_f32_kernel(AssignArgs A0)
     if (i < NCC && crmax < TC - 1) off = (uint32_t)(min(row, crmax) * (int)A.cfld * 4 + 16 * chunk);
     const void *base = i < NCC ? (const void *)(A.cf + (int64_t)c0c * A.cfld + 32 * cs) : (const void *)(pbase + 32 * cs);
     lds_u8 *wdst = (lds_u8 *)cdst + (i * 8 + wave) * 1024;
-    if (cfull) {
+    const bool in = cfull || 32 * cs + 4 * chunk < A.df;
+    if (SEG && i >= NCC) {
+      if (in) lds_copy16(srow[i - NCC] + 128 * cs, (uint32_t)(size_t)wdst);
+    } else if (cfull) {
       lds_copy16(base, off, (uint32_t)(size_t)wdst);
-    } else if (32 * cs + 4 * chunk < A.df) {
+    } else if (in) {
       lds_copy16(base, off, (uint32_t)(size_t)wdst);
-    } else {
+    }
+    if (!in) {
       __attribute__((address_space(3))) uint32_t *z = (__attribute__((address_space(3))) uint32_t *)(wdst + 16 * lane);
       z[0] = z[1] = z[2] = z[3] = 0u;
     }
@@ -2065,7 +2074,7 @@ __global__ __launch_bounds__(kQThreads, 1) void assign_f32_kernel(AssignArgs A0)
         if (A.keys) {
           atomicMin(A.keys + p, score_key(best[pb], bidx[pb]));
         } else {
-          A.assign[p] = bidx[pb] + A.aoff;
+          A.assign[SEG ? A.prow[p] : p] = bidx[pb] + A.aoff;
           if (A.score) A.score[p] = best[pb];
         }
       }
@@ -2643,10 +2652,11 @@ __global__ __launch_bounds__(256) void prep_kernel(const void *Cv, int k, int d,
 // F32, BF16: ||x||^2 ; SQ8: ||code-128||^2 ; SIGN1: alpha^2 d ; HYBRID: ||x'||^2 + alpha^2 (d - d0)
 // One wave per point, 16-byte loads.
 template <int FMT>
-__global__ __launch_bounds__(256) void xconst_kernel(Points P, float *xc) {
+__global__ __launch_bounds__(256) void xconst_kernel(Points P, const int *prow, float *xc) {
   const int lane = threadIdx.x & 63;
-  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (p >= P.n) return;
+  const int64_t i0 = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i0 >= P.n) return;
+  const int64_t p = prow ? prow[i0] : i0;
   double s = 0.0;
   if (FMT == KM_F32 || FMT == KM_HYBRID) {
     const float *x = FMT == KM_F32 ? static_cast<const float *>(P.data) + p * P.ld : P.front + p * P.d_front;
@@ -2691,7 +2701,7 @@ __global__ __launch_bounds__(256) void xconst_kernel(Points P, float *xc) {
       const double a = P.alpha[p];
       s += a * a * (double)(P.d - (FMT == KM_HYBRID ? P.d_front : 0));
     }
-    xc[p] = (float)s;
+    xc[i0] = (float)s;
   }
 }
 
@@ -3225,7 +3235,9 @@ km_status launch_assign(const Points &P, const void *C, const CentroidPrep &cp, 
   }
 }
 
-int segment_tile_centroids(int k_seg) { return k_seg <= 128 ? 128 : 256; }
+int segment_tile_centroids(const Points &P, int k_seg) {
+  return P.fmt == KM_F32 && k_seg <= 64 ? 64 : k_seg <= 128 ? 128 : 256;
+}
 
 int assign_segment_rows(const Points &P) {
   if (P.fmt == KM_F32) return kQT;
@@ -3235,7 +3247,7 @@ int assign_segment_rows(const Points &P) {
 
 km_status launch_assign_segments(const Points &P, const void *C, const CentroidPrep &cp, const int4 *segs,
                                  const int2 *tiles, int64_t ntiles, int tile_c, int32_t *assign, float *score,
-                                 hipStream_t s) {
+                                 const int *prow, hipStream_t s) {
   if (assign_segment_rows(P) == 0) return KM_EUNSUPPORTED;
   if (ntiles == 0) return KM_OK;
   AssignArgs A{};
@@ -3252,7 +3264,10 @@ km_status launch_assign_segments(const Points &P, const void *C, const CentroidP
     A.cf = static_cast<const float *>(C);
     A.cfld = P.d;
     A.df = P.d;
-    if (tile_c == 128)
+    A.prow = prow;
+    if (tile_c == 64)
+      hipLaunchKernelGGL((assign_f32_kernel<true, 1>), dim3((unsigned)ntiles), dim3(kQThreads), 0, s, A);
+    else if (tile_c == 128)
       hipLaunchKernelGGL((assign_f32_kernel<true, 2>), dim3((unsigned)ntiles), dim3(kQThreads), 0, s, A);
     else
       hipLaunchKernelGGL((assign_f32_kernel<true, 4>), dim3((unsigned)ntiles), dim3(kQThreads), 0, s, A);
@@ -3308,16 +3323,16 @@ CentroidPrep prep_slice(const Points &P, const CentroidPrep &cp, int off, int64_
   return r;
 }
 
-km_status launch_xconst(const Points &P, float *xc, hipStream_t s) {
+km_status launch_xconst(const Points &P, float *xc, hipStream_t s, const int *prow) {
   const dim3 g((unsigned)cdiv(P.n, 4));
   switch (P.fmt) {
-    case KM_F32: hipLaunchKernelGGL(xconst_kernel<KM_F32>, g, dim3(256), 0, s, P, xc); break;
-    case KM_BF16: hipLaunchKernelGGL(xconst_kernel<KM_BF16>, g, dim3(256), 0, s, P, xc); break;
-    case KM_SQ8: hipLaunchKernelGGL(xconst_kernel<KM_SQ8>, g, dim3(256), 0, s, P, xc); break;
-    case KM_SIGN1: hipLaunchKernelGGL(xconst_kernel<KM_SIGN1>, g, dim3(256), 0, s, P, xc); break;
-    case KM_HYBRID: hipLaunchKernelGGL(xconst_kernel<KM_HYBRID>, g, dim3(256), 0, s, P, xc); break;
-    case KM_RABITQ: hipLaunchKernelGGL(xconst_kernel<KM_RABITQ>, g, dim3(256), 0, s, P, xc); break;
-    case KM_LVQ4: hipLaunchKernelGGL(xconst_kernel<KM_LVQ4>, g, dim3(256), 0, s, P, xc); break;
+    case KM_F32: hipLaunchKernelGGL(xconst_kernel<KM_F32>, g, dim3(256), 0, s, P, prow, xc); break;
+    case KM_BF16: hipLaunchKernelGGL(xconst_kernel<KM_BF16>, g, dim3(256), 0, s, P, prow, xc); break;
+    case KM_SQ8: hipLaunchKernelGGL(xconst_kernel<KM_SQ8>, g, dim3(256), 0, s, P, prow, xc); break;
+    case KM_SIGN1: hipLaunchKernelGGL(xconst_kernel<KM_SIGN1>, g, dim3(256), 0, s, P, prow, xc); break;
+    case KM_HYBRID: hipLaunchKernelGGL(xconst_kernel<KM_HYBRID>, g, dim3(256), 0, s, P, prow, xc); break;
+    case KM_RABITQ: hipLaunchKernelGGL(xconst_kernel<KM_RABITQ>, g, dim3(256), 0, s, P, prow, xc); break;
+    case KM_LVQ4: hipLaunchKernelGGL(xconst_kernel<KM_LVQ4>, g, dim3(256), 0, s, P, prow, xc); break;
     default: return KM_EUNSUPPORTED;
   }
   KMQ_LAUNCH_CHECK("xconst_kernel");

@@ -103,21 +103,26 @@ size_t prep_bytes(const Points &P, int k);
 // points: segment i is rows [segs[i].x, + segs[i].y) against centroids
 // [segs[i].z, + segs[i].w) of C and of the prepared constants; workgroup b takes
 // point tile tiles[b].y of segment tiles[b].x (tiles of assign_segment_rows(P) rows;
-// 0 = not supported for these points).  assign and score are indexed by absolute
-// row; centroid indices are absolute.  tile_c: centroids per tile (128 or 256) of
-// every segment of the launch (segment_tile_centroids picks it per segment).
+// 0 = not supported for these points).  Centroid indices are absolute; assign and
+// score are indexed by absolute row.  fp32: row i of the segments is row prow[i] of
+// the points and of assign (score stays in segment order).  tile_c: centroids per tile
+// of every segment of the launch (segment_tile_centroids picks it per segment).
 int assign_segment_rows(const Points &P);
-// 128 for a segment of at most 128 centroids, else 256: the 256-centroid kernel
-// does more MFMA work per stage, which outweighs its extra padding from 129 on
-int segment_tile_centroids(int k_seg);
+// 128 for a segment of at most 128 centroids, else 256: the 256-centroid kernel does
+// more MFMA work per stage, which outweighs its extra padding from 129 on.  fp32
+// segments of at most 64 take 64: the fp32 matrix work that a 128-centroid tile spends
+// on padding is the pass's time (1M x 1024 in 63 segments of about 63 centroids: 2.2 ms per
+// pass on 128-centroid tiles, 0.7 + 1.3 ms on tiles of 64 and of 128).
+int segment_tile_centroids(const Points &P, int k_seg);
 km_status launch_assign_segments(const Points &P, const void *C, const CentroidPrep &cp, const int4 *segs,
                                  const int2 *tiles, int64_t ntiles, int tile_c, int32_t *assign, float *score,
-                                 hipStream_t s);
+                                 const int *prow, hipStream_t s);
 km_status launch_assign(const Points &P, const void *C, const CentroidPrep &cp, int k, int32_t *assign,
                         float *score, hipStream_t s, int aoff = 0);
 // cp restricted to centroids [off, ...) and, for the per-point keys, to points [pstart, ...)
 CentroidPrep prep_slice(const Points &P, const CentroidPrep &cp, int off, int64_t pstart);
-km_status launch_xconst(const Points &P, float *xc, hipStream_t s);
+// prow (nullable): entry i is of row prow[i]
+km_status launch_xconst(const Points &P, float *xc, hipStream_t s, const int *prow = nullptr);
 km_status launch_objective(const Points &P, const float *xc, const float *score, int64_t n, double *out,
                            double *partials, int nblk_max, hipStream_t s);
 int objective_blocks(int64_t n);
@@ -190,6 +195,10 @@ size_t permuted_bytes(const Points &P, int64_t nrows);
 km_status launch_permute_points(const Points &P, const int *perm, int64_t nrows, void *ws, Points *out,
                                 hipStream_t s);
 Points slice_points(const Points &P, int64_t start, int64_t count);
+// idx[j] = perm[idx[j]], j < k
+km_status launch_map_index(const int *perm, int64_t *idx, int k, hipStream_t s);
+// a[i] = v, i < n
+km_status launch_fill_assign(int32_t *a, int64_t n, int32_t v, hipStream_t s);
 km_status launch_scatter_assign(const int *perm, const int32_t *a_perm, int64_t nsel, int64_t n, int32_t *assign,
                                 hipStream_t s);
 

@@ -35,6 +35,10 @@ __global__ __launch_bounds__(256) void scatter_assign_kernel(const int *perm, co
     assign[perm[r]] = a_perm[r];
 }
 
+__global__ __launch_bounds__(256) void map_index_kernel(const int *perm, int64_t *idx, int k) {
+  for (int j = blockIdx.x * 256 + threadIdx.x; j < k; j += gridDim.x * 256) idx[j] = perm[idx[j]];
+}
+
 unsigned copy_grid(int64_t work) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(work, 256), 8192)); }
 
 km_status permute(const void *src, int64_t sld, void *dst, int64_t rb, const int *perm, int64_t nrows, hipStream_t s) {
@@ -134,6 +138,18 @@ Points slice_points(const Points &P, int64_t start, int64_t count) {
   if (P.front) q.front = P.front + start * P.d_front;
   q.raw = nullptr;
   return q;
+}
+
+km_status launch_map_index(const int *perm, int64_t *idx, int k, hipStream_t s) {
+  hipLaunchKernelGGL(map_index_kernel, dim3(copy_grid(k)), dim3(256), 0, s, perm, idx, k);
+  KMQ_LAUNCH_CHECK("map index");
+  return KM_OK;
+}
+
+km_status launch_fill_assign(int32_t *a, int64_t n, int32_t v, hipStream_t s) {
+  hipLaunchKernelGGL(fill_assign_kernel, dim3(copy_grid(n)), dim3(256), 0, s, a, n, v);
+  KMQ_LAUNCH_CHECK("fill assign");
+  return KM_OK;
 }
 
 km_status launch_scatter_assign(const int *perm, const int32_t *a_perm, int64_t nsel, int64_t n, int32_t *assign,

@@ -368,3 +368,25 @@ def test_fine_split_donor_stays_in_meso_cluster(km, torch):
     assert_centroids(host(C), C_o, "split donor")
     np.testing.assert_array_equal(host(a)[:6], a_o[:6])
     assert_fp_assign(host(a), a_o, f32_dist(X, C_o), "split donor")
+
+
+def test_fine_f32_tiles_and_strides(km, torch):
+    """fp32 FINE reads the rows in place: meso-clusters whose fine counts fall on the 64-, 128- and 256-centroid tiles
+    and past them, rows with a stride, points without a meso-cluster, and ids out of order; the result is that of the
+    same points gathered meso-cluster by meso-cluster."""
+    rng = np.random.default_rng(3)
+    n, d, km_, k = 6000, 40, 5, 640
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    meso = rng.choice(km_ + 1, n, p=[.09, .1, .2, .5, .06, .05]).astype(np.int32)  # id 5: none
+    meso[meso == km_] = -1
+    wide = torch.zeros((n, 48), device="cuda")
+    wide[:, :d] = to_dev(X, torch)
+    C, a, kf, J = km.kmeans_fine(km.points_f32(wide[:, :d]), to_dev(meso, torch), km_, k, 2, objective=True)
+    assert kf.min() <= 64 and kf.max() > 256 and ((kf > 64) & (kf <= 128)).any()
+    order = np.argsort(np.where(meso < 0, km_, meso), kind="stable")[:(meso >= 0).sum()]
+    C2, a2, kf2, J2 = km.kmeans_fine(km.points_f32(to_dev(X[order], torch)), to_dev(meso[order], torch), km_, k, 2,
+                                     objective=True)
+    np.testing.assert_array_equal(kf, kf2)
+    np.testing.assert_array_equal(host(C), host(C2))
+    np.testing.assert_array_equal(host(a)[order], host(a2))
+    assert (host(a)[meso < 0] == -1).all() and host(J)[0] == host(J2)[0]

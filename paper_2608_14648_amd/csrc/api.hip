@@ -856,9 +856,14 @@ km_status kmeans_assign_pruned(const km_points *P, const void *C, int32_t k, con
   st = check_prune(p, pr, &D0);
   if (st != KM_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const size_t b_pr = al(pruned_bytes(p, k));
+  size_t b_pr = al(pruned_bytes(p, k));
   Scratch ws(s);
   st = ws.alloc(b_pr + al(3 * sizeof(unsigned long long)));
+  if (st == KM_ENOMEM && p.split) {  // the fp32 kernel needs less
+    p.split = false;
+    b_pr = al(pruned_bytes(p, k));
+    st = ws.alloc(b_pr + al(3 * sizeof(unsigned long long)));
+  }
   if (st != KM_OK) return st;
   unsigned long long *cnt = counters ? reinterpret_cast<unsigned long long *>(ws.get() + b_pr) : nullptr;
   if (cnt) {

@@ -160,8 +160,16 @@ struct SplitArgs {
   // projection: d dims to k outputs, Y n x k
   const float *mean;
   float *Y;
+  // pruning: front norms, thresholds, previous centroids, survivor bits (W4 words a row), partial counts
+  const float *xn, *tau;
+  float r0;
+  const int32_t *prev;
+  uint32_t *mask;
+  int W4;
+  unsigned long long *cnt;  // nullable, [2 ncnt]: two per 128 points
+  int64_t ncnt;
 };
-enum { kSplitAssign = 0, kSplitHybrid = 1, kSplitProject = 2 };
+enum { kSplitAssign = 0, kSplitHybrid = 1, kSplitProject = 2, kSplitPrune = 3 };
 constexpr int kSplitProjMaxD = 4096;  // the mean's place in LDS
 // Y = (X - mean) W on the fp16 matrix cores; out: the route and the point tiles (of 256) left to the fp32 kernel
 size_t split_project_bytes(int64_t n, int d, int d_out);
@@ -205,7 +213,7 @@ km_status launch_scatter_assign(const int *perm, const int32_t *a_perm, int64_t 
 // skm.hip: dimension pruning inside STEP 2
 double prune_factor(int D, int d, double eps0);
 int prune_front_default(int d);
-size_t pruned_bytes(const Points &P, int k);
+size_t pruned_bytes(const Points &P, int k);  // any d'
 km_status launch_assign_pruned(const Points &P, const void *C, int k, const int32_t *prev, int32_t *assign,
                                double *dist, double *objective, double eps0, int D0,
                                unsigned long long *cnt, void *ws, hipStream_t s);

@@ -7,11 +7,12 @@
 //
 //   front norms  ||x'||^2 of the points and ||c'||^2 of the centroids over d'
 //   tau          one wave per point: distance to the previous centroid (16-byte
-//                loads per lane)
+//                loads per lane); fp32 points: ||x'||^2 from the same read
 //   front        MFMA tile kernel (128 points x 128 centroids, fp32 or int8):
 //                p(d') = ||x'||^2 + ||c'||^2 - 2 <x', c'> for every pair, the test
 //                at d', one survivor bit per pair; each point's bits are one
-//                row of W4 words (W4 = ceil(k/128) * 4), written 16 bytes per tile
+//                row of W4 words (W4 = ceil(k/128) * 4), written 16 bytes per tile.
+//                fp32 points: split.hip on the fp16 matrix cores, this kernel behind it
 //   refine       one wave per point, lanes over 64 consecutive dims: the point's
 //                mask row is read with one load, then every survivor's row is
 //                loaded whole and its distance grows chunk by chunk with the test
@@ -54,6 +55,8 @@ struct SkmArgs {
   int32_t *assign;
   double *dist;
   unsigned long long *cnt;  // nullable: per-workgroup (front: 2 per group) / per-wave (refine) partial counts
+  const SplitRoute *route;  // front: set where the fp16 matrix cores go first; then only what they left
+  const int *tflag;         // (tiles of 256 points)
 };
 
 template <int FMT>
@@ -77,31 +80,42 @@ __device__ __forceinline__ T wave_sum(T v) {
 }
 
 // One wave per row: squared norm of the first D0 values (front norms).
+// rmax (nullable, F32): the largest |value| as a bit pattern.
 template <int FMT>
 __global__ __launch_bounds__(256) void skm_norm_kernel(const uint8_t *rows, int64_t ld, int64_t nrows, int D0,
-                                                       void *out) {
+                                                       void *out, uint32_t *rmax) {
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= nrows) return;
   const uint8_t *row = rows + r * ld;
   Val<FMT> s = 0;
+  uint32_t mx = 0;
   for (int i = lane; i < D0; i += 64) {
     Val<FMT> v = elem<FMT>(row, i);
     if constexpr (FMT == KM_SQ8) v -= 128;  // the int8 values the front MFMA multiplies
+    if constexpr (FMT == KM_F32) mx = max(mx, __float_as_uint(v) & 0x7fffffffu);
     s += v * v;
   }
   s = wave_sum(s);
   if (lane == 0) static_cast<Val<FMT> *>(out)[r] = s;
+  if (FMT == KM_F32 && rmax) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
+    if (lane == 0) rmax[r] = mx;
+  }
 }
 
+// fp32 points: the front norm as well, from the row that is read anyway (a pass of its
+// own over d' = 96 of 768 dims took 0.22 ms at 1M points)
 template <int FMT>
-__global__ __launch_bounds__(256) void skm_tau_kernel(SkmArgs A, void *tau) {
+__global__ __launch_bounds__(256) void skm_tau_kernel(SkmArgs A, void *tau, float *xn) {
   const int lane = threadIdx.x & 63;
   const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (p >= A.n) return;
   const int j = min(max(A.prev[p], 0), A.k - 1);
   Val<FMT> acc = 0;
-  if constexpr (FMT == KM_F32) {  // d % 4 == 0
+  float nrm = 0.f;
+  if constexpr (FMT == KM_F32) {  // d % 4 == 0, D0 % 4 == 0
     const float *x = reinterpret_cast<const float *>(A.X + p * A.xld);
     const float *c = reinterpret_cast<const float *>(A.C) + (int64_t)j * A.d;
     for (int i = 4 * lane; i < A.d; i += 256) {
@@ -111,6 +125,7 @@ __global__ __launch_bounds__(256) void skm_tau_kernel(SkmArgs A, void *tau) {
       for (int e = 0; e < 4; ++e) {
         const float t = xv[e] - cv[e];
         acc += t * t;
+        if (i < A.D0) nrm += xv[e] * xv[e];
       }
     }
   } else {  // d % 16 == 0
@@ -129,6 +144,10 @@ __global__ __launch_bounds__(256) void skm_tau_kernel(SkmArgs A, void *tau) {
   }
   acc = wave_sum(acc);
   if (lane == 0) static_cast<Val<FMT> *>(tau)[p] = acc;
+  if constexpr (FMT == KM_F32) {
+    nrm = wave_sum(nrm);
+    if (lane == 0) xn[p] = nrm;
+  }
 }
 
 // ---- front: all pairs over d' dims on the matrix cores, the test at d' -------
@@ -147,6 +166,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, r = lane & 31, h = lane >> 5;
   const int wc = w & 1, wp = w >> 1;
   const int64_t p0 = (int64_t)blockIdx.x * kFT;
+  if (A.route && A.route->ok && !A.tflag[blockIdx.x >> 1]) return;
   const int nct = (int)cdiv(A.k, kFT);
   const int bytes = A.D0 * esz;
   const int nch = (bytes + kFRow - 1) / kFRow;
@@ -496,7 +516,8 @@ size_t pruned_bytes(const Points &P, int k) {
   const size_t n = (size_t)P.n;
   const size_t W4 = 4 * (size_t)cdiv(k, kFT);
   return al256(4 * n) + al256(4 * n) + al256(4 * (size_t)k) + al256(4 * W4 * n) + al256(8 * n) +
-         al256(8 * kSumBlocks) + al256(16 * (size_t)front_blocks(P.n, k)) + al256(8 * 4 * (size_t)kRefineBlocks);
+         al256(8 * kSumBlocks) + al256(16 * (size_t)front_blocks(P.n, k)) + al256(8 * 4 * (size_t)kRefineBlocks) +
+         (P.fmt == KM_F32 && P.split ? split_bytes(P.n, k, std::min(P.d, 64 * kMaxFront), false) : 0);
 }
 
 km_status launch_assign_pruned(const Points &P, const void *C, int k, const int32_t *prev, int32_t *assign,
@@ -521,6 +542,7 @@ km_status launch_assign_pruned(const Points &P, const void *C, int k, const int3
   unsigned long long *cfront = reinterpret_cast<unsigned long long *>(w);
   w += al256(16 * (size_t)front_blocks(n, k));
   unsigned long long *crefine = reinterpret_cast<unsigned long long *>(w);
+  w += al256(8 * 4 * (size_t)kRefineBlocks);
 
   SkmArgs A{};
   A.n = n;
@@ -558,17 +580,47 @@ km_status launch_assign_pruned(const Points &P, const void *C, int k, const int3
   }
   const size_t cld = P.fmt == KM_F32 ? 4 * (size_t)d : (size_t)d;
   if (P.fmt == KM_F32) {
-    hipLaunchKernelGGL(skm_norm_kernel<KM_F32>, rows_grid, dim3(256), 0, s, A.X, A.xld, n, D0, xn);
+    // from two stages of 16 front dims on, the front runs on the fp16 matrix cores and the
+    // fp32 kernel takes what they leave (split.hip)
+    const bool split = P.split && D0 > 16;
+    CentroidPrep cp{};
+    cp.cn = static_cast<const float *>(cn);
+    if (split) cp.sp = split_layout(n, k, D0, false, w);
     hipLaunchKernelGGL(skm_norm_kernel<KM_F32>, dim3((unsigned)cdiv(k, 4)), dim3(256), 0, s, A.C, (int64_t)cld,
-                       (int64_t)k, D0, cn);
-    hipLaunchKernelGGL(skm_tau_kernel<KM_F32>, rows_grid, dim3(256), 0, s, A, tau);
+                       (int64_t)k, D0, cn, cp.sp.rmax);
+    hipLaunchKernelGGL(skm_tau_kernel<KM_F32>, rows_grid, dim3(256), 0, s, A, tau, static_cast<float *>(xn));
+    if (split) {
+      km_status st = launch_split_prep(static_cast<const float *>(C), d, n, k, D0, cp, s);
+      if (st != KM_OK) return st;
+      SplitArgs B{};
+      B.x = static_cast<const float *>(P.data);
+      B.ldx = P.ld;
+      B.d = D0;
+      B.sp = cp.sp;
+      B.kall = k;
+      B.k = k;
+      B.n = n;
+      B.ngroups = 1;
+      B.xn = static_cast<const float *>(xn);
+      B.tau = static_cast<const float *>(tau);
+      B.r0 = A.front_test ? A.r0 : INFINITY;  // no test at d' = d: everything stays
+      B.prev = prev;
+      B.mask = mask;
+      B.W4 = W4;
+      B.cnt = Af.cnt;
+      B.ncnt = nfb;
+      st = launch_split(B, cdiv(n, 256), k <= 128 ? 128 : 256, s);
+      if (st != KM_OK) return st;
+      Af.route = cp.sp.route;
+      Af.tflag = cp.sp.tflag;
+    }
     hipLaunchKernelGGL(skm_front_kernel<KM_F32>, front_grid, dim3(256), 0, s, Af);
     hipLaunchKernelGGL(skm_refine_kernel<KM_F32>, refine_grid, dim3(256), 0, s, Ar);
   } else if (P.fmt == KM_SQ8) {
-    hipLaunchKernelGGL(skm_norm_kernel<KM_SQ8>, rows_grid, dim3(256), 0, s, A.X, A.xld, n, D0, xn);
+    hipLaunchKernelGGL(skm_norm_kernel<KM_SQ8>, rows_grid, dim3(256), 0, s, A.X, A.xld, n, D0, xn, nullptr);
     hipLaunchKernelGGL(skm_norm_kernel<KM_SQ8>, dim3((unsigned)cdiv(k, 4)), dim3(256), 0, s, A.C, (int64_t)cld,
-                       (int64_t)k, D0, cn);
-    hipLaunchKernelGGL(skm_tau_kernel<KM_SQ8>, rows_grid, dim3(256), 0, s, A, tau);
+                       (int64_t)k, D0, cn, nullptr);
+    hipLaunchKernelGGL(skm_tau_kernel<KM_SQ8>, rows_grid, dim3(256), 0, s, A, tau, nullptr);
     hipLaunchKernelGGL(skm_front_kernel<KM_SQ8>, front_grid, dim3(256), 0, s, Af);
     hipLaunchKernelGGL(skm_refine_kernel<KM_SQ8>, refine_grid, dim3(256), 0, s, Ar);
   } else {

@@ -75,8 +75,11 @@ __global__ __launch_bounds__(256) void split_prep_kernel(const float *C, int64_t
       sp.tail[2 * kp + j] = in ? sig2[j] * (-0.5f * sc * sc) : 0.f;
     }
   }
-  // one unit: 8 dims of one row
+  // the rows read past the last one are finite (a NaN would flag tiles)
   const int ch = 2 * ((d + kSD - 1) / kSD);
+  for (int64_t i = g0; i < 256 * kRow / 16; i += gs)
+    *reinterpret_cast<uint4 *>(sp.img + (int64_t)(ch / 2) * sp.cstage + 16 * i) = uint4{0u, 0u, 0u, 0u};
+  // one unit: 8 dims of one row
   const int64_t units = (int64_t)k * ch;
   for (int64_t u = g0; u < units; u += gs) {
     const int64_t row = u / ch;
@@ -165,9 +168,12 @@ __global__ __launch_bounds__(256) void proj_prep_kernel(const float *W, int d, i
   }
   for (int64_t i = g0; i < ntflag; i += gs) sp.tflag[i] = 0;
   __syncthreads();
-  if (!okx || o >= d_out) return;
-  const float s = scl[o16];
+  if (!okx) return;
   const int ch = 2 * ((d + kSD - 1) / kSD);
+  for (int64_t i = g0; i < 256 * kRow / 16; i += gs)  // the rows read past the last one are finite
+    *reinterpret_cast<uint4 *>(sp.img + (int64_t)(ch / 2) * sp.cstage + 16 * i) = uint4{0u, 0u, 0u, 0u};
+  if (o >= d_out) return;
+  const float s = scl[o16];
   for (int c = rg; c < ch; c += 16) {
     float v[8];
 #pragma unroll
@@ -231,9 +237,15 @@ __device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
 // values go out with their column's scale instead of into an argmax.
 // 2M x 1024 -> 256: 8.6 -> 4.1 ms against project_kernel (10.2 GB read and written:
 // 2.1 ms at the rate of a large copy); 500k x 1024 x 1024 (RabitQ's rotation): 8.5 -> 4.1.
+//
+// PRUNE (the first test of a pruned pass, at d' dims): the threshold test of every pair,
+// acc - s^2 ||c'||^2 / 2 < (||x'||^2 - tau r(d')) s^2 / 2 drops it, and a point's survivors as
+// one bit per centroid.  1M points, d' = 96, k = 1000: 1.95 -> 0.75 ms against skm_front_kernel
+// (0.56 ms of it products at the rate of the assignment; six steps a tile do not hide the
+// epilogue that turns scores into bits).
 template <int CB, int MODE>
 __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
-  constexpr bool HYB = MODE == kSplitHybrid, PROJ = MODE == kSplitProject;
+  constexpr bool HYB = MODE == kSplitHybrid, PROJ = MODE == kSplitProject, PRUNE = MODE == kSplitPrune;
   constexpr int TC = 64 * CB;
   constexpr int NCONST = HYB ? 4 : 1;  // constants per centroid: seed; -T, u, 2 sigma
   constexpr int CRING = HYB ? 2 : 4;   // tiles of constants (a hybrid tile has 3 stages or more, and ends its argmax)
@@ -245,6 +257,7 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
   __shared__ __align__(16) float msh[PROJ ? kSplitProjMaxD + kSD : 1];  // s mean, 0 past d
   __shared__ uint32_t bitsT[HYB ? kSplitTailWords * kTP : 1];
   __shared__ float alp[HYB ? kTP : 1];
+  __shared__ __align__(16) uint32_t mrow[PRUNE ? kTP : 1][TC / 32];  // PRUNE: a tile's mask words of every point
   const int t = threadIdx.x;
   const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r = lane & 31, h = lane >> 5;
@@ -509,7 +522,7 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
         const h16x8 b = pr == 1 ? op(xl[pb]) : op(xh[pb]);
         if constexpr (PROJ) {
           acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, a, acc[cb][pb], 0, 0, 0);
-        } else if (!HYB && FIRST && pr == 0) {
+        } else if (!HYB && !PRUNE && FIRST && pr == 0) {
           const f32x16 zero = {0.f};
           acc[cb][pb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, zero, 0, 0, 0);
         } else {
@@ -526,7 +539,7 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
           if (j >= 1 && j <= CB) read_cl(j - 1, nbuf);
           if (j >= 2 * CB + 1) read_ch(j - 2 * CB - 1, nbuf);
         }
-        if (!PROJ && ((!HYB && FIRST && pb == 0) || (LAST && pb == 1))) {
+        if (!PROJ && !PRUNE && ((!HYB && FIRST && pb == 0) || (LAST && pb == 1))) {
           if constexpr (CB == 4) {
             argmax_piece(j, FIRST && pb == 0 ? 1 : 0, FIRST && pb == 0 ? ct - 1 : ct);
           } else {
@@ -588,7 +601,7 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
       for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[cb][pb][i] = 0.f;
-  } else if constexpr (!HYB) {
+  } else if constexpr (!HYB && !PRUNE) {
     // before the first tile there is none whose second block's argmax is due: -inf
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
@@ -622,7 +635,89 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
   };
   constexpr std::true_type T{};
   constexpr std::false_type F{};
-  if constexpr (PROJ) {
+  if constexpr (PRUNE) {
+    const float half_s2 = 0.5f * sx * sx;
+    float thr[2];
+    int pj[2];
+    bool nan = false;
+    unsigned tested = 0, passed = 0;  // per lane
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+      const int64_t pc = p0 + min(wp * 64 + pb * 32 + r, prmax);
+      thr[pb] = (A.xn[pc] - A.tau[pc] * A.r0) * half_s2;
+      pj[pb] = A.prev[pc];
+    }
+    open_front();
+    for (int ct = 0; ct < nmy; ++ct) {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[cb][pb][i] = 0.f;
+      for (int st = 0; st < S; ++st) step(ct, F, F);
+      const int c0 = ct * TC;
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb) {
+        nan |= acc[0][pb][0] != acc[0][pb][0];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          float sd[16];
+          consts_of(0, cb, ct, sd);
+          uint32_t m16 = 0;  // bit i: row 8 (i >> 2) + 4 h + (i & 3) of the block stays
+#pragma unroll
+          for (int i = 15; i >= 0; --i) m16 = 2 * m16 + !(acc[cb][pb][i] + sd[i] < thr[pb]);
+          uint32_t m = (m16 & 15u) | (m16 & 0xf0u) << 4 | (m16 & 0xf00u) << 8 | (m16 & 0xf000u) << 12;
+          m <<= 4 * h;
+          m |= __shfl_xor((int)m, 32);
+          const int jb = c0 + wc * 32 * CB + cb * 32;  // first centroid of the block
+          const int nvalid = A.k - jb;
+          uint32_t valid = nvalid >= 32 ? 0xffffffffu : nvalid > 0 ? (1u << nvalid) - 1u : 0u;
+          if (wp * 64 + pb * 32 + r > prmax) valid = 0u;
+          const int rel = pj[pb] - jb;
+          if (rel >= 0 && rel < 32) valid &= ~(1u << rel);
+          if (h == 0) {
+            mrow[wp * 64 + pb * 32 + r][wc * CB + cb] = m & valid;
+            if (A.r0 == INFINITY) continue;  // no test
+            tested += (unsigned)__popc(valid);
+            passed += (unsigned)__popc(m & valid);
+          }
+        }
+      }
+      __syncthreads();
+      // 16 bytes of a point's words per thread; rows hold whole groups of four words
+      for (int e = t; e < kTP * (TC / 128); e += kThr) {
+        const int row = e / (TC / 128), q = e % (TC / 128);
+        if (row <= prmax && c0 / 32 + 4 * q < A.W4)
+          *reinterpret_cast<uint4 *>(A.mask + (p0 + row) * A.W4 + c0 / 32 + 4 * q) =
+              *reinterpret_cast<const uint4 *>(&mrow[row][4 * q]);
+      }
+      __syncthreads();  // the next tile's words
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (nan) A.sp.tflag[pt] = 1;
+    if (A.cnt) {  // two partial counts per half of the tile (the fp32 kernel's tiles), here all in the first
+      unsigned long long *sh = reinterpret_cast<unsigned long long *>(&mrow[0][0]);
+      unsigned long long a = tested, b = passed;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_xor(a, off);
+        b += __shfl_xor(b, off);
+      }
+      if (lane == 0) {
+        sh[2 * wave] = a;
+        sh[2 * wave + 1] = b;
+      }
+      __syncthreads();
+      if (t < 2) {
+        unsigned long long v = 0;
+        for (int w8 = 0; w8 < 8; ++w8) v += sh[2 * w8 + t];
+        A.cnt[4 * pt + t] = v;
+        if (2 * pt + 1 < A.ncnt) A.cnt[4 * pt + 2 + t] = 0;
+      }
+    }
+    return;
+  } else if constexpr (PROJ) {
     open_front();
     for (int st = 1; st <= S; ++st) step(st, F, F);  // st: the stage read ahead
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -795,7 +890,12 @@ km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d
 
 km_status launch_split(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s) {
   const dim3 gr((unsigned)grid), th(kThr);
-  if (A.Y) {
+  if (A.mask) {
+    if (tile_c == 128)
+      hipLaunchKernelGGL((split_kernel<2, kSplitPrune>), gr, th, 0, s, A);
+    else
+      hipLaunchKernelGGL((split_kernel<4, kSplitPrune>), gr, th, 0, s, A);
+  } else if (A.Y) {
     if (tile_c == 128)
       hipLaunchKernelGGL((split_kernel<2, kSplitProject>), gr, th, 0, s, A);
     else

@@ -270,3 +270,50 @@ def test_cov_not_finite(km, torch):
     bad[[7, 280]] = True
     assert np.isnan(cov[bad]).all() and np.isnan(cov[:, bad]).all()
     np.testing.assert_array_equal(cov[~bad][:, ~bad], clean[~bad][:, ~bad])
+
+
+# front dims of two stages and more, whole and ragged; 128- and 256-centroid tiles; the last tile's words past the mask row
+@pytest.mark.parametrize("n,d,df,k", [(1, 64, 24, 2), (257, 96, 32, 128), (300, 128, 40, 129), (1000, 256, 96, 300),
+                                      (700, 512, 256, 1000), (513, 48, 48, 70)])
+@pytest.mark.parametrize("how", ["plain", "far_points", "tiny_centroid", "not_finite"])
+def test_pruned(km, torch, n, d, df, k, how):
+    """The pruned pass against its definition in 64 bits: a pair is dropped at d' when its partial distance exceeds
+    tau r(d'); candidates within 1e-5 of a threshold may go either way."""
+    X, C = points(n, d, k, n + df, spread=0.5)
+    g = np.random.default_rng(1)
+    if how == "far_points":
+        X[::5] *= np.float32(2.0 ** 14)
+    elif how == "tiny_centroid":
+        C[0] *= np.float32(2.0 ** -12)
+    elif how == "not_finite":
+        X[n // 2, 1] = np.nan
+    prev = g.integers(0, k, n).astype(np.int32)
+    a, dist, obj, cnt = km.kmeans_assign_pruned(km.points_f32(to_dev(X, torch)), to_dev(C, torch), to_dev(prev, torch),
+                                                d_front=df, objective=True, counters=True)
+    a, dist = host(a), host(dist)
+    Xd, Cd = X.astype(np.float64), C.astype(np.float64)
+    part = np.cumsum((Xd[:, None, :] - Cd[None]) ** 2, 2)
+    i = np.arange(n)
+    tau, full = part[i, prev, -1], part[:, :, -1]
+    alive, sure = np.ones((n, k), bool), np.ones((n, k), bool)  # in reach of the test, and clear of it
+    passed = np.zeros(2)
+    for D in range(df, d, 64):
+        lim = (tau * (1 + 2.1 / np.sqrt(D)) ** 2 * D / d)[:, None]
+        room = 1e-5 * ((Xd[:, None, :D] ** 2).sum(2) + (Cd[None, :, :D] ** 2).sum(2) + lim)
+        with np.errstate(invalid="ignore"):
+            alive &= part[:, :, D - 1] <= lim + room
+            sure &= part[:, :, D - 1] <= lim - room
+        if D == df:
+            passed = np.array([(m.sum() - m[i, prev].sum()) for m in (sure, alive)])
+    alive[i, prev] = sure[i, prev] = True
+    ok = np.isfinite(tau)
+    best = np.where(sure, full, np.inf).min(1)
+    assert alive[i, a][ok].all()
+    assert (full[i, a][ok] <= best[ok] * (1 + 1e-5) + 1e-9).all()
+    np.testing.assert_allclose(dist[ok], full[i, a][ok], rtol=2e-5)
+    if how != "not_finite" and df < d:
+        assert cnt[0] == n * (k - 1) and passed[0] <= cnt[1] <= passed[1]
+    elif df == d:
+        assert cnt[0] == cnt[1] == 0
+    else:
+        assert a[n // 2] == prev[n // 2] and np.isnan(dist[n // 2])

@@ -2927,7 +2927,11 @@ static int tile_groups(int64_t n, int k) {
 // hybrid points whose tail words fit the direct-copy kernel's resident LDS array
 static bool hyb_direct(const Points &P) { return P.fmt == KM_HYBRID && P.d - P.d_front <= 32 * kHybMaxTW; }
 
+// fp32 points and centroids of few tiles (split_small.hip)
+static bool small_f32(const Points &P, int k) { return P.fmt == KM_F32 && P.split && split_small(P.n, k); }
+
 int assign_groups(const Points &P, int k) {
+  if (small_f32(P, k)) return 1;  // its groups are its own
   if (P.fmt == KM_F32 || hyb_direct(P)) return tile_groups(P.n, k);
   if (P.fmt == KM_HYBRID) {
     constexpr int TC = Geo<Blocking<KM_F32>::CB, Blocking<KM_F32>::PB>::TC;
@@ -3049,6 +3053,9 @@ km_status launch_assign_t(const Points &P, const void *C, const CentroidPrep &cp
       hipLaunchKernelGGL(assign_i8_kernel<FMT>, dim3((unsigned)cdiv(P.n, kT8)), dim3(k8Threads), 0, s, A);
     }
   } else if constexpr (FMT == KM_F32) {
+    if (small_f32(P, k))
+      return launch_split_small(static_cast<const float *>(P.data), P.ld, static_cast<const float *>(C), cp, P.n, k, P.d,
+                                assign, score, aoff, s);
     const int64_t npt = cdiv(P.n, kQT);
     const int ng = assign_groups(P, k);
     A.n_ptiles = npt;
@@ -3150,6 +3157,7 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static size_t split_scratch(const Points &P, int k) {
   const bool hyb = P.fmt == KM_HYBRID;
+  if (small_f32(P, k)) return split_small_bytes(P.n, k);
   return split_bytes(P.n, k, hyb ? P.d_front : P.d, hyb);
 }
 
@@ -3178,6 +3186,9 @@ km_status launch_prep(const Points &P, const void *C, int k, void *ws, CentroidP
   out->q = q;
   out->cb = cb;
   out->sp = SplitPrep{};
+  if (small_f32(P, k))
+    return launch_split_small_prep(static_cast<const float *>(C), P.n, k, P.d, cn, w + prep_bytes(P, k) - split_scratch(P, k),
+                                   &out->sp, s);
   if (P.split)
     out->sp = split_layout(P.n, k, P.fmt == KM_HYBRID ? P.d_front : P.d, P.fmt == KM_HYBRID,
                            w + prep_bytes(P, k) - split_scratch(P, k));

@@ -56,6 +56,7 @@ struct SplitPrep {
   float *tail;        // HYBRID: -T (int bits), u and 2 sigma times -s^2 / 2, k + pad each; else NULL
   uint8_t *img;       // stage-major: 64 bytes (16 hi, 16 lo halves) of every row per 16 dims
   int64_t cstage;     // bytes of one stage of img
+  unsigned long long *keys;  // few tiles (split_small; route is NULL): the points' (score, index) keys
 };
 
 // Per-centroid data rebuilt before each assignment pass.
@@ -181,6 +182,30 @@ SplitPrep split_layout(int64_t n, int k, int d, bool tail, void *ws);
 km_status launch_split_prep(const float *C, int64_t ldc, int64_t n, int k, int d, const CentroidPrep &cp,
                             hipStream_t s);
 km_status launch_split(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t s);
+
+// split_small.hip: fp32 points and centroids of few tiles
+struct SmallArgs {
+  const float *x, *C;  // points (rows ldx floats apart), centroids (k x d)
+  int64_t ldx;
+  const float *cn;
+  const uint32_t *rmax;
+  int64_t n;
+  int k, d;
+  int ngroups;  // centroid tiles
+  int64_t n_ptiles;
+  unsigned long long *keys;  // ngroups > 1
+  int *count;
+  int32_t *assign;
+  float *score;  // nullable
+  int aoff;
+};
+bool split_small(int64_t n, int k);
+size_t split_small_bytes(int64_t n, int k);
+// fills cn; one assignment per preparation
+km_status launch_split_small_prep(const float *C, int64_t n, int k, int d, float *cn, void *ws, SplitPrep *out,
+                                  hipStream_t s);
+km_status launch_split_small(const float *X, int64_t ldx, const float *C, const CentroidPrep &cp, int64_t n, int k,
+                             int d, int32_t *assign, float *score, int aoff, hipStream_t s);
 
 // update.hip
 size_t update_bytes(const Points &P, int k);

@@ -187,14 +187,6 @@ __global__ __launch_bounds__(256) void proj_prep_kernel(const float *W, int d, i
   }
 }
 
-// (score, index) keys as in the other assignment kernels: the order of the keys is
-// the order of (score, index), -0 taken as +0
-__device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
-  uint32_t u = __float_as_uint(sc == 0.0f ? 0.0f : sc);
-  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return ((unsigned long long)u << 32) | (uint32_t)idx;
-}
-
 // ---- assignment ------------------------------------------------------------------
 // 8 waves, 256 points x TC = 64 CB centroids, each wave 32 CB x 64.  A stage is 16
 // dims: of every point 16 floats, of every centroid 16 hi and 16 lo halves, both 64
@@ -215,8 +207,8 @@ __device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
 // less exact.)
 //
 // Measured against the fp32 kernel: 10M x 256, k = 4096 158.9 -> 59.5 ms (352 TFLOP/s of
-// fp32 products, 1057 of fp16 ones); 1M x 768, k = 1000 11.6 -> 4.1 ms; 1024 x 768, k =
-// 1000 193 -> 66 us.  What bounds it is power: on random data the chip runs this
+// fp32 products, 1057 of fp16 ones); 1M x 768, k = 1000 11.6 -> 4.1 ms (few tiles:
+// split_small.hip).  What bounds it is power: on random data the chip runs this
 // kernel at 1.6 - 1.8 GHz, and a large f16 library product reaches 1290 - 1310 TFLOP/s;
 // with constant data (few bits toggling) the same pass at 2M points takes 8.9 instead
 // of 11.8 ms.  The matrix cores are busy 56 % of the cycles.
@@ -229,7 +221,7 @@ __device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
 // oracle uses, that becomes the tail score ts = fmaf(-(alpha 2 sigma), 2D - T,
 // sigma^2 Q), and -s^2 ts / 2 (the factor, a power of two, is in the constants) starts
 // the front's accumulators.  2M points, front 384 + tail 640, k = 4096:
-// 54.4 -> 21.7 ms per pass against the fp32 front (assign_hyb_kernel)
+// 54.4 -> 22.5 ms per pass against the fp32 front (assign_hyb_kernel)
 //
 // PROJ (Y = (X - mean) W): the columns of W in the place of the centroids, points and
 // centroids exchanged in the MFMA so that a lane holds one output of many points and

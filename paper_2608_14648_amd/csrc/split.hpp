@@ -57,4 +57,12 @@ __device__ __forceinline__ void lds_copy4_at(const void *base, uint32_t off, uin
 }
 #pragma clang diagnostic pop
 
+// (score, index) keys as in the other assignment kernels: the order of the keys is
+// the order of (score, index), -0 taken as +0
+__device__ __forceinline__ unsigned long long split_key(float sc, int idx) {
+  uint32_t u = __float_as_uint(sc == 0.0f ? 0.0f : sc);
+  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return ((unsigned long long)u << 32) | (uint32_t)idx;
+}
+
 }  // namespace kmq

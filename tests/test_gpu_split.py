@@ -1,4 +1,4 @@
-"""fp32 assignment on the fp16 matrix cores (csrc/split.hip): tile edges, odd sizes, and the
+"""fp32 assignment on the fp16 matrix cores (csrc/split.hip, few tiles: csrc/split_small.hip): tile edges, odd sizes, and the
 inputs that go back to the fp32 kernel (whole calls by their centroids, single tiles by their points).
 
 Score bound: a dot product is rounded 6 times per 16 dims, each time by at most 2^-23 of a partial sum
@@ -50,21 +50,38 @@ def check(X, C, a, sc, rows=None):
     return xn + s[i, got]
 
 
-# k around the 128- and 256-centroid tiles and the centroid-tile groups, n around the 256-point tile, d from the
+def spread_rows(n, k, tiles):
+    """Row numbers of a call that repeats n rows: as they are, up to 4 tiles of 64 x 64 per CU, or past that."""
+    if tiles == "few":
+        return np.arange(n)
+    return np.arange(n + 256 * -(-4 * 256 // (4 * -(-k // 64)))) % n
+
+
+few_and_many = pytest.mark.parametrize("tiles", ["few", "many"])
+
+
+# k around the 64-, 128- and 256-centroid tiles and the centroid-tile groups, n around the 256-point tile, d from the
 # smallest split one (two stages of 16 dims) through ragged last stages
 @pytest.mark.parametrize("n,d,k", [(1, 32, 1), (5, 36, 2), (255, 32, 127), (256, 48, 128), (257, 44, 129), (300, 100, 255),
                                    (513, 64, 257), (1000, 132, 513), (3000, 96, 1100), (700, 772, 300), (64, 2048, 40)])
-def test_edges(km, torch, n, d, k):
+@few_and_many
+def test_edges(km, torch, n, d, k, tiles):
     X, C = points(n, d, k, n + d + k)
-    a, sc, obj = km.kmeans_assign(km.points_f32(to_dev(X, torch)), to_dev(C, torch), objective=True)
-    dist = check(X, C, host(a), host(sc))
+    i = spread_rows(n, k, tiles)
+    a, sc, obj = km.kmeans_assign(km.points_f32(to_dev(X[i], torch)), to_dev(C, torch), objective=True)
+    a, sc = host(a), host(sc)
+    np.testing.assert_array_equal(a, a[i])
+    np.testing.assert_array_equal(sc, sc[i])
+    dist = check(X, C, a[:n], sc[:n])[i]
+    X = X[i]
     # summed from the distances: fp32 squares of fp32 differences, fp64 sums
     assert abs(host(obj)[0] - dist.sum()) <= 2.0 ** -20 * dist.sum() + 1e-12 * (X.astype(np.float64) ** 2).sum()
 
 
-def test_smallest_index_wins(km, torch):
+@few_and_many
+def test_smallest_index_wins(km, torch, tiles):
     """Equal centroids in other blocks, lane halves, wave halves, tiles and groups of the sweep."""
-    n, d, k = 700, 64, 1300
+    n, d, k = 700 if tiles == "few" else 5000, 64, 1300
     X, C = points(n, d, k, 3, spread=0.0)
     for src, copies in {5: (9, 37, 133, 300, 1299), 64: (68, 200, 700), 250: (251, 255, 513)}.items():
         C[list(copies)] = C[src]
@@ -75,7 +92,8 @@ def test_smallest_index_wins(km, torch):
 
 @pytest.mark.parametrize("how", ["tiny_centroid", "zero_centroid", "wide_centroids", "huge", "small", "far_points"])
 @pytest.mark.parametrize("k", [60, 300])
-def test_ranges(km, torch, how, k):
+@few_and_many
+def test_ranges(km, torch, how, k, tiles):
     """Scales at and past the ends of what the split takes: results keep the fp32 kernel's bound."""
     n, d = 900, 96
     X, C = points(n, d, k, 11)
@@ -95,16 +113,22 @@ def test_ranges(km, torch, how, k):
     else:                           # past fp16's range at the centroids' scale: their tile goes to the fp32 kernel
         X[300] *= np.float32(2.0 ** 14)
         X[301] *= np.float32(2.0 ** 7)
-    a, sc, obj = km.kmeans_assign(km.points_f32(to_dev(X, torch)), to_dev(C, torch), objective=True)
-    dist = check(X, C, host(a), host(sc))
+    i = spread_rows(n, k, tiles)
+    a, sc, obj = km.kmeans_assign(km.points_f32(to_dev(X[i], torch)), to_dev(C, torch), objective=True)
+    dist = check(X, C, host(a)[:n], host(sc)[:n])[i]
+    X = X[i]
     assert abs(host(obj)[0] - dist.sum()) <= 2.0 ** -20 * dist.sum() + 1e-12 * (X.astype(np.float64) ** 2).sum()
 
 
 @pytest.mark.parametrize("k", [60, 300, 2600])
-def test_not_finite(km, torch, k):
+@few_and_many
+def test_not_finite(km, torch, k, tiles):
     """Rows with NaN or infinities: they answer as in the fp32 kernel and leave the others alone; the objective is NaN."""
-    n, d = 3000, 64
-    X, C = points(n, d, k, 5)
+    n, d = 3000 if tiles == "few" else 70000, 64
+    if k == 2600:
+        n = 1500 if tiles == "few" else 3000
+    X, C = points(max(n, k), d, k, 5)
+    X = X[:n].copy()
     X[260, 3], X[700, 63] = np.nan, np.inf
     P = km.points_f32(to_dev(X, torch))
     a, sc, obj = km.kmeans_assign(P, to_dev(C, torch), objective=True)
@@ -113,11 +137,22 @@ def test_not_finite(km, torch, k):
     assert a[260] == np.iinfo(np.int32).max and sc[260] == np.inf  # no score is smaller than the start's
     assert a[700] == np.nonzero(C[:, 63] > 0)[0][0] and sc[700] == -np.inf
     assert np.isnan(host(obj)[0])
-    Cn, _, J = km.kmeans_fit(P, k, 1, C=to_dev(C, torch))  # the fit's objective comes from its update
-    assert np.isnan(host(J)).all()
+    if k <= n:
+        Cn, _, J = km.kmeans_fit(P, k, 1, C=to_dev(C, torch))  # the fit's objective comes from its update
+        assert np.isnan(host(J)).all()
     C[k // 2, 1] = np.nan  # a centroid with NaN never wins
     a, _, _ = km.kmeans_assign(P, to_dev(C, torch))
     assert not (host(a) == k // 2).any()
+
+
+def test_one_stage(km, torch):
+    """Fewer dims than a stage of few tiles, odd and even numbers of stages, points with a stride."""
+    for n, d, k in ((130, 32, 70), (65, 64, 64), (64, 68, 65), (200, 100, 1)):
+        X, C = points(n, d, k, d)
+        wide = torch.full((n, d + 12), float("nan"), device="cuda")
+        wide[:, :d] = to_dev(X, torch)
+        a, sc, _ = km.kmeans_assign(km.Points(km.KM_F32, wide[:, :d], d), to_dev(C, torch))
+        check(X, C, host(a), host(sc))
 
 
 def test_fit_objective(km, torch):

@@ -1,17 +1,15 @@
 // STEP 3 (Sec. 2.3): centroid update as a deterministic segmented sum.
 //
 //   1. hist     per block of points (about 1024 blocks), member counts of every cluster
-//               (LDS-privatised histogram), stored cluster-major [k][nblk].
-//   2. scan     exclusive scan of that table (block sums, then each block's
-//               scan plus the sum of the blocks before it): entry (j, b) is where
-//               block b's first member of cluster j goes in the cluster-sorted
-//               order; one workgroup then derives every cluster's count, start
-//               and chunk offset.
+//               (LDS-privatised histogram), one row [k] per block.
+//   2. scan     exclusive scan of every column: entry (b, j) is how many members of
+//               cluster j lie before block b; the workgroup that ends last scans the
+//               totals to every cluster's start and chunk offset.
 //   3. scatter  stable counting sort: points are ranked inside each wave among
 //               the lanes with the same cluster id (found with one ballot per
 //               id bit) and the four waves take their slots in order, so
 //               members stay in point order.
-//   4. segsum   fixed-size chunks (<= 512 members, never crossing a cluster)
+//   4. segsum   chunks of a fixed number of members (64 to 512, never crossing a cluster)
 //               are summed by one workgroup per (chunk, column slice): each
 //               wave adds every 4th member's slice of the row (coalesced
 //               1 KiB reads of fp32 rows, 256 B of codes, 128 B of bits); the
@@ -35,20 +33,19 @@ namespace kmq {
 namespace {
 
 constexpr int kHistBlocks = 512;   // target number of histogram / scatter blocks
-constexpr int kChunk = 512;        // members per segmented-sum chunk
+constexpr int kChunk = 512;        // most members per segmented-sum chunk
+constexpr int kChunkMin = 64;
 constexpr int kLdsCursorMax = 16384;
-constexpr int kScanSeg = 4096;     // elements per scan block (256 threads x 16)
 
 struct UpdWs {
   int ppb;       // points per histogram / scatter block (multiple of 256)
   int nblk;      // histogram blocks
   int64_t L;     // k * nblk
-  int nsb;       // scan blocks
+  int chunk;     // members per segmented-sum chunk
   int maxchunks;
   int dp;        // row length of partial sums / Z (F32: d, SQ8: d, SIGN1/HYBRID: d)
-  int *offs;     // [L]
-  int *bsum;     // [nsb + 1]
-  int *total;    // [4]
+  int *offs;     // [nblk][k]
+  int *arrive;   // scan workgroups that have ended
   int *cnt;      // [k]
   int *cstart;   // [k]
   int *choff;    // [k + 1]
@@ -66,13 +63,24 @@ struct UpdWs {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Chunks halve from 512 members until there are 2048 workgroups (8 per CU): a workgroup
+// reads its members in rounds of 32 and waits for each.  20k x 128 fp32 rows, 64
+// clusters: 13.6 us with chunks of 512, 7.2 with 64; 1M SQ8 rows of 768, 1000 clusters:
+// 147 us with 512 (1953 workgroups and the clusters' remainders), 148 with 256.
+int chunk_members(const Points &P) {
+  const int64_t slices = cdiv(P.d, P.fmt == KM_F32 || P.fmt == KM_HYBRID ? 256 : P.fmt == KM_BF16 ? 512 : 1024);
+  int c = kChunk;
+  while (c > kChunkMin && cdiv(P.n, c) * slices < 2048) c /= 2;
+  return c;
+}
+
 UpdWs carve(const Points &P, int k, void *base, size_t *bytes_out) {
   UpdWs w{};
   w.ppb = (int)std::max<int64_t>(256, cdiv(cdiv(P.n, kHistBlocks), 256) * 256);
   w.nblk = (int)cdiv(P.n, w.ppb);
   w.L = (int64_t)k * w.nblk;
-  w.nsb = (int)cdiv(w.L, kScanSeg);
-  w.maxchunks = (int)(cdiv(P.n, kChunk) + k);
+  w.chunk = chunk_members(P);
+  w.maxchunks = (int)(cdiv(P.n, w.chunk) + k);
   w.dp = P.d;
   uint8_t *b = static_cast<uint8_t *>(base);
   size_t o = 0;
@@ -82,8 +90,7 @@ UpdWs carve(const Points &P, int k, void *base, size_t *bytes_out) {
     return p;
   };
   w.offs = (int *)take(sizeof(int) * (size_t)w.L);
-  w.bsum = (int *)take(sizeof(int) * (size_t)(w.nsb + 1));
-  w.total = (int *)take(sizeof(int) * 4);
+  w.arrive = (int *)take(sizeof(int));
   w.cnt = (int *)take(sizeof(int) * (size_t)k);
   w.cstart = (int *)take(sizeof(int) * (size_t)k);
   w.choff = (int *)take(sizeof(int) * (size_t)(k + 1));
@@ -102,26 +109,34 @@ UpdWs carve(const Points &P, int k, void *base, size_t *bytes_out) {
 }
 
 // ---- 1. histogram ------------------------------------------------------------
-__global__ __launch_bounds__(256) void hist_kernel(const int32_t *assign, int64_t n, int k, int nblk, int ppb,
-                                                   int *offs, int use_lds) {
+__global__ __launch_bounds__(256) void hist_kernel(const int32_t *assign, int64_t n, int k, int ppb, int *offs,
+                                                   int use_lds, int *arrive) {
   extern __shared__ int lc[];
   const int b = blockIdx.x, t = threadIdx.x;
   const int64_t lo = (int64_t)b * ppb;
   const int64_t hi = min<int64_t>(n, lo + ppb);
+  int *row = offs + (int64_t)b * k;
+  if (b == 0 && t == 0) *arrive = 0;
   if (use_lds) {
     for (int j = t; j < k; j += 256) lc[j] = 0;
     __syncthreads();
-    for (int64_t p = lo + t; p < hi; p += 256) {
-      const int a = assign[p];
-      if (a >= 0 && a < k) atomicAdd(&lc[a], 1);
-    }
+  }
+  for (int64_t p = lo + t; p < hi; p += 8 * 256) {  // 8 loads at a time
+    int a[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) a[e] = p + 256 * e < hi ? assign[p + 256 * e] : -1;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (a[e] >= 0 && a[e] < k) {
+        if (use_lds)
+          atomicAdd(&lc[a[e]], 1);
+        else
+          atomicAdd(&row[a[e]], 1);
+      }
+  }
+  if (use_lds) {
     __syncthreads();
-    for (int j = t; j < k; j += 256) offs[(int64_t)j * nblk + b] = lc[j];
-  } else {
-    for (int64_t p = lo + t; p < hi; p += 256) {
-      const int a = assign[p];
-      if (a >= 0 && a < k) atomicAdd(&offs[(int64_t)a * nblk + b], 1);
-    }
+    for (int j = t; j < k; j += 256) row[j] = lc[j];
   }
 }
 
@@ -147,97 +162,110 @@ __device__ __forceinline__ int block_excl_scan_int(int v, int *sh, int *total) {
   return incl - v;
 }
 
-__global__ __launch_bounds__(256) void scan_reduce_kernel(const int *x, int64_t L, int *bsum) {
-  __shared__ int sh[256];
-  const int64_t base = (int64_t)blockIdx.x * kScanSeg;
-  int s = 0;
-  for (int i = threadIdx.x; i < kScanSeg; i += 256) {
-    const int64_t g = base + i;
-    if (g < L) s += x[g];
+// exclusive scan over 1024 thread values
+__device__ __forceinline__ int scan1024(int v, int *sh16, int *total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int s = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(s, off);
+    if (lane >= off) s += o;
   }
-  sh[threadIdx.x] = s;
+  if (lane == 63) sh16[wave] = s;
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-    __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int x = sh16[w];
+    before += w < wave ? x : 0;
+    all += x;
   }
-  if (threadIdx.x == 0) bsum[blockIdx.x] = sh[0];
+  *total = all;
+  __syncthreads();
+  return before + s - v;
 }
 
-// Exclusive scan of block b's segment plus the sum of the segments before it, which
-// the block adds up itself from the segment sums (a few thousand at most); the last
-// block also writes the grand total.
-__global__ __launch_bounds__(256) void scan_down_kernel(int *x, int64_t L, const int *bsum, int *total) {
-  __shared__ int sh[256];
-  __shared__ int pre[4];
-  const int b = blockIdx.x, t = threadIdx.x;
-  int ps = 0;
-  for (int i = t; i < b; i += 256) ps += bsum[i];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) ps += __shfl_xor(ps, o);
-  if ((t & 63) == 0) pre[t >> 6] = ps;
-  const int64_t base = (int64_t)b * kScanSeg + (int64_t)t * 16;
+// 32 clusters per workgroup, their columns (nblk <= 512 rows) in 32 groups of rows, a
+// thread per cluster and group, its rows in registers.  The last workgroup scans the
+// clusters' totals: counts and arrivals are only touched at device scope, and a count's
+// store has ended before the arrival goes out, so no cache needs writing back.
+// Waiting for memory bounds it: three launches (two for a scan over the cluster-major
+// table, one for the totals) took 13.9 us of a pass over 20k points and 64 clusters, 20.8
+// of one over 1M and 1000; this takes 5.7 and 7.2.
+__global__ __launch_bounds__(1024) void scan_kernel(int *offs, int nblk, int k, int chunk, int *cnt, int *cstart,
+                                                    int *choff, int *arrive) {
+  __shared__ int sums[32][33];
+  __shared__ int sh16[16];
+  __shared__ int last;
+  const int t = threadIdx.x;
+  const int c = t & 31, rg = t >> 5;
+  const int j = blockIdx.x * 32 + c;
+  const int per = (nblk + 31) / 32;  // <= 16
+  const int r0 = rg * per, r1 = min(nblk, r0 + per);
   int v[16];
   int s = 0;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    v[e] = base + e < L ? x[base + e] : 0;
-    s += v[e];
-  }
-  int tot;
-  int run = block_excl_scan_int(s, sh, &tot);  // its barriers also publish pre[]
-  const int prefix = pre[0] + pre[1] + pre[2] + pre[3];
-  run += prefix;
-  if (t == 0 && b == gridDim.x - 1) *total = prefix + tot;
+  for (int i = 0; i < 16; ++i) v[i] = j < k && r0 + i < r1 ? offs[(int64_t)(r0 + i) * k + j] : 0;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    if (base + e < L) x[base + e] = run;
-    run += v[e];
+  for (int i = 0; i < 16; ++i) s += v[i];
+  sums[rg][c] = s;
+  __syncthreads();
+  int run = 0, tot = 0;
+#pragma unroll
+  for (int g = 0; g < 32; ++g) {
+    const int x = sums[g][c];
+    run += g < rg ? x : 0;
+    tot += x;
   }
-}
-
-// counts and start offsets of each cluster from the scanned table, and the exclusive
-// scan of their chunk counts ceil(cnt / kChunk) (one workgroup; choff[k] = all chunks)
-__global__ __launch_bounds__(256) void counts_kernel(const int *offs, int nblk, int k, const int *total, int *cnt,
-                                                     int *cstart, int *choff) {
-  __shared__ int sh[256];
-  const int t = threadIdx.x;
-  const int per = (k + 255) / 256;
-  const int lo = min(k, t * per), hi = min(k, lo + per);
-  int sum = 0;
-  for (int j = lo; j < hi; ++j) {
-    const int s0 = offs[(int64_t)j * nblk];
-    const int e0 = j + 1 < k ? offs[(int64_t)(j + 1) * nblk] : total[0];
-    cnt[j] = e0 - s0;
-    cstart[j] = s0;
-    sum += (e0 - s0 + kChunk - 1) / kChunk;
+  if (rg == 0 && j < k) __hip_atomic_store(cnt + j, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if (j < k && r0 + i < r1) offs[(int64_t)(r0 + i) * k + j] = run;
+    run += v[i];
   }
-  int tot;
-  int run = block_excl_scan_int(sum, sh, &tot);
-  for (int j = lo; j < hi; ++j) {
-    choff[j] = run;
-    run += (cnt[j] + kChunk - 1) / kChunk;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (t == 0)
+    last = __hip_atomic_fetch_add(arrive, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  int start = 0, chunks = 0;  // of the clusters before this round of 1024
+  for (int b0 = 0; b0 < k; b0 += 1024) {
+    const int jj = b0 + t;
+    const int m = jj < k ? __hip_atomic_load(cnt + jj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const int nc = (m + chunk - 1) / chunk;
+    int tm, tc;
+    const int em = scan1024(m, sh16, &tm), ec = scan1024(nc, sh16, &tc);
+    if (jj < k) {
+      cstart[jj] = start + em;
+      choff[jj] = chunks + ec;
+    }
+    start += tm;
+    chunks += tc;
   }
-  if (t == 0) choff[k] = tot;
+  if (t == 0) choff[k] = chunks;
 }
 
 // ---- 3. stable scatter -------------------------------------------------------
-__global__ __launch_bounds__(256) void scatter_kernel(const int32_t *assign, int64_t n, int k, int nblk, int ppb,
-                                                      int *offs, int use_lds, int *perm) {
+__global__ __launch_bounds__(256) void scatter_kernel(const int32_t *assign, int64_t n, int k, int ppb, int *offs,
+                                                      const int *cstart, int use_lds, int *perm) {
   extern __shared__ int cur[];
   const int b = blockIdx.x, t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int64_t lo = (int64_t)b * ppb;
   const int64_t hi = min<int64_t>(n, lo + ppb);
+  int *row = offs + (int64_t)b * k;
   if (use_lds) {
-    for (int j = t; j < k; j += 256) cur[j] = offs[(int64_t)j * nblk + b];
+    for (int j = t; j < k; j += 256) cur[j] = cstart[j] + row[j];
     __syncthreads();
   }
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const int nbits = k > 1 ? 32 - __clz(k - 1) : 0;  // bits of a cluster id
+  int next = lo + t < hi ? assign[lo + t] : -1;
   for (int64_t base = lo; base < hi; base += 256) {
     const int64_t p = base + t;
-    int a = p < hi ? assign[p] : -1;
+    const int a = next;
+    next = p + 256 < hi ? assign[p + 256] : -1;
     const bool valid = a >= 0 && a < k;
     // lanes holding the same id: one ballot per id bit; then the rank among them
     // (lanes below), their number and their first lane
@@ -258,7 +286,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(const int32_t *assign, int
       if (wave == w) {
         int old = 0;
         if (valid && lane == leader) {
-          old = use_lds ? atomicAdd(&cur[a], cnt) : atomicAdd(&offs[(int64_t)a * nblk + b], cnt);
+          old = use_lds ? atomicAdd(&cur[a], cnt) : cstart[a] + atomicAdd(&row[a], cnt);
         }
         const int basepos = __shfl(old, leader);
         if (valid) perm[basepos + rank] = (int)p;
@@ -285,7 +313,7 @@ __device__ __forceinline__ int find_cluster(const int *choff, int k, int c) {
 // HBM; the three vector instructions per value are free).
 template <bool OBJ>
 __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t ld, int df, const int *perm,
-                                                         const int *cnt, const int *cstart, const int *choff, int k,
+                                                         const int *cnt, const int *cstart, const int *choff, int k, int chunk,
                                                          float *partial, int dp, const float *Cold,
                                                          double *partialO) {
   __shared__ f32x4 red[4][64];
@@ -294,8 +322,8 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
   if (c >= choff[k]) return;
   const int j = find_cluster(choff, k, c);
   const int ci = c - choff[j];
-  const int m0 = cstart[j] + ci * kChunk;
-  const int m1 = cstart[j] + min(cnt[j], (ci + 1) * kChunk);
+  const int m0 = cstart[j] + ci * chunk;
+  const int m1 = cstart[j] + min(cnt[j], (ci + 1) * chunk);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = blockIdx.y * 256 + 4 * lane;
   const bool ok = col < df;
@@ -340,31 +368,18 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
   }
 }
 
-// The objective from segsum_f32_kernel's partials (`slices` per chunk): NaN when a
-// point belongs to no cluster (its row holds NaN) or the sum is not finite.
-__global__ __launch_bounds__(256) void objective_fold_kernel(const double *partialO, const int *choff, const int *cstart,
-                                                             const int *cnt, int k, int slices, int64_t n,
-                                                             double *out) {
-  __shared__ double shd[256];
-  double s = 0.0;
-  const int64_t np = (int64_t)choff[k] * slices;
-  for (int64_t i = threadIdx.x; i < np; i += 256) s += partialO[i];
-  s = block_sum_f64(s, shd);
-  if (threadIdx.x == 0) *out = (int64_t)cstart[k - 1] + cnt[k - 1] == n && isfinite(s) ? s : (double)NAN;
-}
-
 // bfloat16 rows: one slice of 512 columns per workgroup; lane = 8 values (16 bytes),
 // decoded to fp32 and summed in fp32 within a chunk (as for fp32 rows)
 __global__ __launch_bounds__(256) void segsum_bf16_kernel(const uint16_t *X, int64_t ld, int d, const int *perm,
-                                                          const int *cnt, const int *cstart, const int *choff, int k,
+                                                          const int *cnt, const int *cstart, const int *choff, int k, int chunk,
                                                           float *partial, int dp) {
   __shared__ f32x4 red[4][2][64];
   const int c = blockIdx.x;
   if (c >= choff[k]) return;
   const int j = find_cluster(choff, k, c);
   const int ci = c - choff[j];
-  const int m0 = cstart[j] + ci * kChunk;
-  const int m1 = cstart[j] + min(cnt[j], (ci + 1) * kChunk);
+  const int m0 = cstart[j] + ci * chunk;
+  const int m1 = cstart[j] + min(cnt[j], (ci + 1) * chunk);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = blockIdx.y * 512 + 8 * lane;
   const bool ok = col < d;
@@ -424,7 +439,7 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
 
 __global__ __launch_bounds__(256) void segsum_bits_kernel(const uint32_t *bits, int64_t wpr, int w0, int dt,
                                                           const float *alpha, const int *perm, const int *cnt,
-                                                          const int *cstart, const int *choff, int k,
+                                                          const int *cstart, const int *choff, int k, int chunk,
                                                           uint32_t *partial, uint32_t *partialA, float *partialM,
                                                           int dp, int coff) {
   __shared__ int sperm[kChunk];
@@ -436,8 +451,8 @@ __global__ __launch_bounds__(256) void segsum_bits_kernel(const uint32_t *bits, 
   if (c >= choff[k]) return;
   const int j = find_cluster(choff, k, c);
   const int ci = c - choff[j];
-  const int m0 = cstart[j] + ci * kChunk;
-  const int len = min(cnt[j], (ci + 1) * kChunk) - ci * kChunk;
+  const int m0 = cstart[j] + ci * chunk;
+  const int len = min(cnt[j], (ci + 1) * chunk) - ci * chunk;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   // the chunk's member ids and alphas (two per thread), and its largest alpha
   float av[2] = {0.f, 0.f};
@@ -525,7 +540,7 @@ constexpr double kLvqSteps = 524287.0;  // 2^19 - 1
 
 __global__ __launch_bounds__(256) void segsum_lvq4_kernel(const uint8_t *codes, int64_t ld, const float *vparams,
                                                           int d, const int *perm, const int *cnt, const int *cstart,
-                                                          const int *choff, int k, uint32_t *partial, float *partialM,
+                                                          const int *choff, int k, int chunk, uint32_t *partial, float *partialM,
                                                           double *partialB, int dp) {
   __shared__ int sperm[kChunk];
   __shared__ uint32_t sq[kChunk];
@@ -536,8 +551,8 @@ __global__ __launch_bounds__(256) void segsum_lvq4_kernel(const uint8_t *codes, 
   if (c >= choff[k]) return;
   const int j = find_cluster(choff, k, c);
   const int ci = c - choff[j];
-  const int m0 = cstart[j] + ci * kChunk;
-  const int len = min(cnt[j], (ci + 1) * kChunk) - ci * kChunk;
+  const int m0 = cstart[j] + ci * chunk;
+  const int len = min(cnt[j], (ci + 1) * chunk) - ci * chunk;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   // the chunk's member ids and scales (two per thread), its largest scale and its
   // bias sum (fixed-order reductions)
@@ -633,15 +648,15 @@ __global__ __launch_bounds__(256) void segsum_lvq4_kernel(const uint8_t *codes, 
 
 // SQ8 codes: one slice of 1024 bytes (16 per lane) per workgroup, exact int32 sums
 __global__ __launch_bounds__(256) void segsum_sq8_kernel(const uint8_t *codes, int64_t ld, int d, const int *perm,
-                                                         const int *cnt, const int *cstart, const int *choff, int k,
+                                                         const int *cnt, const int *cstart, const int *choff, int k, int chunk,
                                                          int *partial) {
   __shared__ int red[4][64 * 17];
   const int c = blockIdx.x;
   if (c >= choff[k]) return;
   const int j = find_cluster(choff, k, c);
   const int ci = c - choff[j];
-  const int m0 = cstart[j] + ci * kChunk;
-  const int m1 = cstart[j] + min(cnt[j], (ci + 1) * kChunk);
+  const int m0 = cstart[j] + ci * chunk;
+  const int m1 = cstart[j] + min(cnt[j], (ci + 1) * chunk);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = blockIdx.y * 1024 + 16 * lane;
   const bool ok = col < d;
@@ -711,11 +726,26 @@ struct Compose {
 // (partialB set): W is the chunk's exact sum of its scaled scales times the codes,
 // partialM its largest scale and partialB its bias sum; the mean is the sum over
 // chunks of (partialM / (2^19 - 1)) W + partialB, over n.
+// One more workgroup, where objective is given, sums segsum_f32_kernel's partials
+// (`slices` per chunk): NaN when a point belongs to no cluster (its row holds NaN) or the
+// sum is not finite.
 __global__ __launch_bounds__(256) void finalize_f32_kernel(const float *partial, int dp, const int *cnt,
                                                            const int *choff, float *Z, uint8_t *fresh,
                                                            const uint32_t *partialA, const float *partialM,
-                                                           const double *partialB, int d_bits, Compose cm) {
+                                                           const double *partialB, int d_bits, Compose cm,
+                                                           const double *partialO, const int *cstart, int k, int slices,
+                                                           int64_t n, double *objective) {
+  __shared__ double shd[256];
   const int j = blockIdx.x;
+  if (j == k) {
+    if (blockIdx.y > 0) return;
+    double s = 0.0;
+    const int64_t np = (int64_t)choff[k] * slices;
+    for (int64_t i = threadIdx.x; i < np; i += 256) s += partialO[i];
+    s = block_sum_f64(s, shd);
+    if (threadIdx.x == 0) *objective = (int64_t)cstart[k - 1] + cnt[k - 1] == n && isfinite(s) ? s : (double)NAN;
+    return;
+  }
   const int col = blockIdx.y * 256 + threadIdx.x;
   const int nj = cnt[j];
   if (blockIdx.y == 0 && threadIdx.x == 0) {
@@ -871,12 +901,11 @@ static km_status launch_sort(const int32_t *assign, int64_t n, int k, const UpdW
   const bool lds = k <= kLdsCursorMax;
   const size_t lds_bytes = lds ? sizeof(int) * (size_t)k : 0;
   if (!lds) hipLaunchKernelGGL(fill_int_kernel, dim3(1024), dim3(256), 0, s, w.offs, w.L, 0);
-  hipLaunchKernelGGL(hist_kernel, dim3(w.nblk), dim3(256), lds_bytes, s, assign, n, k, w.nblk, w.ppb, w.offs,
-                     (int)lds);
-  hipLaunchKernelGGL(scan_reduce_kernel, dim3(w.nsb), dim3(256), 0, s, w.offs, w.L, w.bsum);
-  hipLaunchKernelGGL(scan_down_kernel, dim3(w.nsb), dim3(256), 0, s, w.offs, w.L, w.bsum, w.total);
-  hipLaunchKernelGGL(counts_kernel, dim3(1), dim3(256), 0, s, w.offs, w.nblk, k, w.total, w.cnt, w.cstart, w.choff);
-  hipLaunchKernelGGL(scatter_kernel, dim3(w.nblk), dim3(256), lds_bytes, s, assign, n, k, w.nblk, w.ppb, w.offs,
+  hipLaunchKernelGGL(hist_kernel, dim3(w.nblk), dim3(256), lds_bytes, s, assign, n, k, w.ppb, w.offs, (int)lds,
+                     w.arrive);
+  hipLaunchKernelGGL(scan_kernel, dim3((unsigned)cdiv(k, 32)), dim3(1024), 0, s, w.offs, w.nblk, k, w.chunk, w.cnt,
+                     w.cstart, w.choff, w.arrive);
+  hipLaunchKernelGGL(scatter_kernel, dim3(w.nblk), dim3(256), lds_bytes, s, assign, n, k, w.ppb, w.offs, w.cstart,
                      (int)lds, w.perm);
   KMQ_LAUNCH_CHECK("update: sort");
   return KM_OK;
@@ -918,7 +947,7 @@ km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, 
   cm.counts = counts;
   if (P.fmt == KM_SQ8) {
     hipLaunchKernelGGL(segsum_sq8_kernel, dim3(w.maxchunks, (unsigned)cdiv(d, 1024)), dim3(256), 0, s,
-                       static_cast<const uint8_t *>(P.data), P.ld, d, w.perm, w.cnt, w.cstart, w.choff, k,
+                       static_cast<const uint8_t *>(P.data), P.ld, d, w.perm, w.cnt, w.cstart, w.choff, k, w.chunk,
                        static_cast<int *>(w.partial));
     hipLaunchKernelGGL(finalize_sq8_kernel, dim3(k, (unsigned)cdiv(d, 256)), dim3(256), 0, s,
                        static_cast<const int *>(w.partial), d, w.cnt, w.choff, static_cast<uint8_t *>(w.Z), w.fresh,
@@ -939,34 +968,34 @@ km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, 
     if (P.fmt == KM_LVQ4)
       hipLaunchKernelGGL(segsum_lvq4_kernel, dim3(w.maxchunks, (unsigned)cdiv(d, 1024)), dim3(256), 0, s,
                          static_cast<const uint8_t *>(P.data), P.ld, P.vparams, d, w.perm, w.cnt, w.cstart, w.choff,
-                         k, static_cast<uint32_t *>(w.partial), w.partialM, w.partialB, w.dp);
+                         k, w.chunk, static_cast<uint32_t *>(w.partial), w.partialM, w.partialB, w.dp);
     if (P.fmt == KM_BF16)
       hipLaunchKernelGGL(segsum_bf16_kernel, dim3(w.maxchunks, (unsigned)cdiv(d, 512)), dim3(256), 0, s,
-                         static_cast<const uint16_t *>(P.data), P.ld, d, w.perm, w.cnt, w.cstart, w.choff, k,
+                         static_cast<const uint16_t *>(P.data), P.ld, d, w.perm, w.cnt, w.cstart, w.choff, k, w.chunk,
                          static_cast<float *>(w.partial), w.dp);
     const unsigned slices = (unsigned)cdiv(df, 256);
     if (objective && P.fmt == KM_F32) {
       hipLaunchKernelGGL(segsum_f32_kernel<true>, dim3(w.maxchunks, slices), dim3(256), 0, s, F, fld, df, w.perm,
-                         w.cnt, w.cstart, w.choff, k, static_cast<float *>(w.partial), w.dp,
+                         w.cnt, w.cstart, w.choff, k, w.chunk, static_cast<float *>(w.partial), w.dp,
                          static_cast<const float *>(C), w.partialO);
-      hipLaunchKernelGGL(objective_fold_kernel, dim3(1), dim3(256), 0, s, w.partialO, w.choff, w.cstart, w.cnt, k,
-                         (int)slices, P.n, objective);
     } else if (df > 0) {
       hipLaunchKernelGGL(segsum_f32_kernel<false>, dim3(w.maxchunks, slices), dim3(256), 0, s, F, fld, df, w.perm,
-                         w.cnt, w.cstart, w.choff, k, static_cast<float *>(w.partial), w.dp, nullptr, nullptr);
+                         w.cnt, w.cstart, w.choff, k, w.chunk, static_cast<float *>(w.partial), w.dp, nullptr, nullptr);
     }
     const int d_bits = P.fmt == KM_HYBRID ? P.d_front : 0;
     if (is_bits_fmt(P.fmt)) {
       const int dt = d - d_bits;
       hipLaunchKernelGGL(segsum_bits_kernel, dim3(w.maxchunks, (unsigned)cdiv(dt, 1024)), dim3(256), 0, s,
                          static_cast<const uint32_t *>(P.data), (int64_t)(d / 32), d_bits / 32, dt, P.alpha, w.perm,
-                         w.cnt, w.cstart, w.choff, k, static_cast<uint32_t *>(w.partial), w.partialA, w.partialM,
+                         w.cnt, w.cstart, w.choff, k, w.chunk, static_cast<uint32_t *>(w.partial), w.partialA, w.partialM,
                          w.dp, d_bits);
     }
-    hipLaunchKernelGGL(finalize_f32_kernel, dim3(k, (unsigned)cdiv(w.dp, 256)), dim3(256), 0, s,
+    const bool fold = objective && P.fmt == KM_F32;
+    hipLaunchKernelGGL(finalize_f32_kernel, dim3(k + fold, (unsigned)cdiv(w.dp, 256)), dim3(256), 0, s,
                        static_cast<const float *>(w.partial), w.dp, w.cnt, w.choff, static_cast<float *>(w.Z),
                        w.fresh, is_bits_fmt(P.fmt) ? w.partialA : nullptr, w.partialM,
-                       P.fmt == KM_LVQ4 ? w.partialB : nullptr, d_bits, cm);
+                       P.fmt == KM_LVQ4 ? w.partialB : nullptr, d_bits, cm, w.partialO, w.cstart, k, (int)slices, P.n,
+                       objective);
   }
   KMQ_LAUNCH_CHECK("update: segmented sums");
 

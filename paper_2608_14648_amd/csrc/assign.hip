@@ -1205,7 +1205,11 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void assign_bits_kernel(AssignArgs
 // (low nibbles, then high nibbles of each word: two masks and a shift), and the
 // centroid preparation writes the int8 centroid codes in that same order. The
 // epilogue evaluates Eq. 2 per pair from the point's (s, b, A) and the centroid's
-// (b, S, N, s).
+// (b, S, N, s): ten vector instructions per pair, more time than its MFMAs at a few hundred
+// dims.  So LVQ4 takes tiles of 128 x 128 on 4 waves (NWP = 2) and three workgroups share a CU
+// (52 KB, 155 registers): one's epilogue runs beside another's MFMAs, and centroids
+// are padded to 128.  250k x 416, k = 601: 160 us per pass on 256 x 256 tiles of 8 waves, one
+// workgroup per CU; 121 us so (a pass's vector instructions alone are 68).
 //
 // With ngroups > 1 the workgroup (pt, g) sweeps centroid tiles g, g + ngroups, ...
 // of point tile pt; the ngroups workgroups of a point tile are consecutive among
@@ -1213,12 +1217,13 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void assign_bits_kernel(AssignArgs
 // XCD's L2, and they merge through 64-bit (score, index) keys.
 constexpr int kQT = 256;                            // points per workgroup (and centroids per tile, CB = 4)
 constexpr int kQThreads = 512;                      // 8 waves
+constexpr int kLvT = 128;                           // LVQ4: points and centroids of a tile
 constexpr int kQWideThreads = 1024;                 // 16 waves (bf16, 256-centroid tiles)
 constexpr int kQMaxDimSQ8 = 8192;                   // |2<x~,c~> - ||c~||^2| < 2^31
 constexpr int kQPackMaxDim = 1024;                  // SQ8 packed selection keys (below)
 
 // CB: 32 x 32 centroid blocks per wave, 4 (256-centroid tiles) or 2 (128-centroid
-// tiles, for k <= 128, where a 256-centroid tile would be mostly padding)
+// tiles, for k <= 128, where a 256-centroid tile would be mostly padding, and LVQ4)
 //
 // NWC: waves along the centroids.  2 is the shape above; 4 (bf16 only, with CB = 2)
 // makes 16 waves of 64 centroids x 64 points on the same 256 x 256 tile.  A wave's
@@ -1238,21 +1243,21 @@ constexpr int kQPackMaxDim = 1024;                  // SQ8 packed selection keys
 // (acc << 7) + E (modulo 2^32, exact since the result is in range), orders pairs by
 // key and then by the smaller id: one shift-add and one max per pair select the
 // tile's winner instead of a compare and two selects.
-template <int FMT, bool SEG = false, int CB = 4, bool PK = false, int NWC = 2>
-__global__ __launch_bounds__(256 * NWC, 1) void assign_q8_kernel(AssignArgs A0) {
+template <int FMT, bool SEG = false, int CB = 4, bool PK = false, int NWC = 2, int NWP = 4>
+__global__ __launch_bounds__(64 * NWP * NWC, NWP == 2 ? 3 : 1) void assign_q8_kernel(AssignArgs A0) {
   constexpr bool BF = FMT == KM_BF16;
   constexpr bool LV = FMT == KM_LVQ4;
   static_assert(CB == 2 || CB == 4, "64 or 128 centroids per wave");
   static_assert(NWC == 2 || NWC == 4, "2 or 4 waves along the centroids");
-  constexpr int NW = 4 * NWC;                       // waves: NWC centroid groups x 4 point quarters
+  constexpr int NW = NWP * NWC;                     // waves: NWC centroid groups x NWP groups of 64 points
   constexpr int TC = 32 * CB * NWC;                 // centroids per tile
-  constexpr int TP = kQT;                           // points per workgroup
+  constexpr int TP = 64 * NWP;                      // points per workgroup
   constexpr int PRB = LV ? kRowBytes / 2 : kRowBytes;  // point bytes per row and stage (LVQ4: packed)
   constexpr int NCC = TC / (8 * NW);                // centroid copies per thread and stage
   constexpr int NCOPY = NCC + TP * PRB / (1024 * NW);  // all copies per thread and stage
   constexpr int NCONST = LV ? 4 : 1;                // per-centroid constants of the epilogue
   static_assert(NWC == 2 || (BF && CB == 2), "16 waves: bf16 with 64 centroids per wave (SQ8 spills there)");
-  static_assert(!LV || (!SEG && NWC == 2), "LVQ4: unsegmented, 8 waves");
+  static_assert(LV == (NWP == 2) && (!LV || (!SEG && NWC == 2 && CB == 2)), "LVQ4: unsegmented, 4 waves");
   constexpr int STAGE = TC * kRowBytes + TP * PRB;  // centroid rows, then point rows
   // a segmented launch narrows the arguments to this workgroup's segment
   AssignArgs A = A0;
@@ -1277,9 +1282,9 @@ __global__ __launch_bounds__(256 * NWC, 1) void assign_q8_kernel(AssignArgs A0) 
   // 128-centroid tiles of the 8-wave shape (k <= 128, and the hierarchical phases'
   // small centroid sets): a stage carries only ~1000 MFMA cycles per SIMD (SQ8)
   // against a copy latency of a microsecond or more, so three stage buffers (3 x 48
-  // KB; LVQ4 3 x 32 KB) keep the copies two stages ahead; SQ8 17 % faster on a
+  // KB) keep the copies two stages ahead; SQ8 17 % faster on a
   // 2M x 1024, k = 112 pass
-  constexpr bool TRI = CB == 2 && NWC == 2;
+  constexpr bool TRI = CB == 2 && NWC == 2 && NWP == 4;
   __shared__ __align__(16) uint8_t qst0[STAGE];
   __shared__ __align__(16) uint8_t qst1[STAGE];
   __shared__ __align__(16) uint8_t qst2[TRI ? STAGE : 16];
@@ -1441,7 +1446,7 @@ __global__ __launch_bounds__(256 * NWC, 1) void assign_q8_kernel(AssignArgs A0) 
 
   // SQ8 with packed keys spreads the next stage's copies over the stage's four
   // steps (5 % faster at 1M x 768); unpacked SQ8 and LVQ4 issue them all before the
-  // MFMAs (spreading them there spills: LVQ4 ran 15 % slower), and so does bf16
+  // MFMAs (spreading them there spills), and so does bf16
   // (spreading them gained nothing)
   constexpr bool SPREAD = PK;
   int sp_ct = 0, sp_s = 0;
@@ -2908,20 +2913,13 @@ static int q8_tile_centroids(int k) { return k <= 128 ? 128 : 256; }
 // This fills the GPU when the point tiles alone do not, and shortens the partly
 // filled last round (1M points: 3907 point tiles = 15.3 rounds alone, 30.5 with
 // g = 2); the smallest such g, since each group adds a key merge.
-static int tile_groups(int64_t n, int k) {
-  const int64_t npt = cdiv(n, kQT);
-  const int nct = (int)cdiv(k, q8_tile_centroids(k));
-  const int64_t cus = cu_count();
-  int best_g = 1;
-  int64_t best = -1;
-  for (int g = 1; g <= std::min(8, nct); ++g) {
-    const int64_t cost = cdiv(npt * g, cus) * cdiv(nct, g);
-    if (best < 0 || cost < best) {
-      best = cost;
-      best_g = g;
-    }
-  }
-  return best_g;
+static int tile_groups(int64_t npt, int nct, int64_t cus, int slack = 0) {
+  auto cost = [&](int g) { return cdiv(npt * g, cus) * cdiv(nct, g); };
+  int64_t best = cost(1);
+  for (int g = 2; g <= std::min(8, nct); ++g) best = std::min(best, cost(g));
+  int g = 1;
+  while (100 * cost(g) > (100 + slack) * best) ++g;
+  return g;
 }
 
 // hybrid points whose tail words fit the direct-copy kernel's resident LDS array
@@ -2932,12 +2930,18 @@ static bool small_f32(const Points &P, int k) { return P.fmt == KM_F32 && P.spli
 
 int assign_groups(const Points &P, int k) {
   if (small_f32(P, k)) return 1;  // its groups are its own
-  if (P.fmt == KM_F32 || hyb_direct(P)) return tile_groups(P.n, k);
+  const int64_t npt = cdiv(P.n, kQT);
+  const int nct = (int)cdiv(k, q8_tile_centroids(k));
+  if (P.fmt == KM_F32 || hyb_direct(P)) return tile_groups(npt, nct, cu_count());
+  // LVQ4's workgroups share CUs, so uneven rounds cost little and the keys (10 us at
+  // 250k points) count: within 5 % of the best.  250k x 416, k = 601 takes 121 us per pass in
+  // 1, 3 or 5 groups; a call of 20k x 768, k = 4096 117 us in 5 groups, 89 in 8.
+  if (P.fmt == KM_LVQ4) return tile_groups(cdiv(P.n, kLvT), (int)cdiv(k, kLvT), cu_count(), 5);
   if (P.fmt == KM_HYBRID) {
     constexpr int TC = Geo<Blocking<KM_F32>::CB, Blocking<KM_F32>::PB>::TC;
     return (int)std::min<int64_t>(8, cdiv(k, TC));
   }
-  if (P.fmt == KM_BF16 || P.fmt == KM_LVQ4 || (P.fmt == KM_SQ8 && P.d <= kQMaxDimSQ8)) return tile_groups(P.n, k);
+  if (P.fmt == KM_BF16 || (P.fmt == KM_SQ8 && P.d <= kQMaxDimSQ8)) return tile_groups(npt, nct, cu_count());
   return 1;
 }
 
@@ -3020,7 +3024,7 @@ km_status launch_assign_t(const Points &P, const void *C, const CentroidPrep &cp
     }
   } else if constexpr (FMT == KM_SQ8 || FMT == KM_BF16 || FMT == KM_LVQ4) {
     if (FMT != KM_SQ8 || P.d <= kQMaxDimSQ8) {
-      const int64_t npt = cdiv(P.n, kQT);
+      const int64_t npt = cdiv(P.n, FMT == KM_LVQ4 ? kLvT : kQT);
       const int ng = assign_groups(P, k);
       A.n_ptiles = npt;
       if (ng > 1) {
@@ -3030,20 +3034,24 @@ km_status launch_assign_t(const Points &P, const void *C, const CentroidPrep &cp
         hipLaunchKernelGGL(keys_init_kernel, gp, dim3(256), 0, s, cp.keys, P.n);
       }
       const dim3 grid((unsigned)(ng > 1 ? cdiv(npt, 8) * 8 * ng : npt));
-      const bool pk = FMT == KM_SQ8 && P.d <= kQPackMaxDim;
-      if (q8_tile_centroids(k) == 128) {
-        if (pk)
-          hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 2, FMT == KM_SQ8>), grid, dim3(kQThreads), 0, s, A);
-        else
-          hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 2>), grid, dim3(kQThreads), 0, s, A);
-      } else if constexpr (FMT == KM_BF16) {
-        // 16 waves of 64 x 64: half the direct copies per wave of the 8-wave shape
-        hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 2, false, 4>), grid, dim3(kQWideThreads), 0, s, A);
+      if constexpr (FMT == KM_LVQ4) {
+        hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 2, false, 2, 2>), grid, dim3(256), 0, s, A);
       } else {
-        if (pk)
-          hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 4, FMT == KM_SQ8>), grid, dim3(kQThreads), 0, s, A);
-        else
-          hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 4>), grid, dim3(kQThreads), 0, s, A);
+        const bool pk = FMT == KM_SQ8 && P.d <= kQPackMaxDim;
+        if (q8_tile_centroids(k) == 128) {
+          if (pk)
+            hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 2, FMT == KM_SQ8>), grid, dim3(kQThreads), 0, s, A);
+          else
+            hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 2>), grid, dim3(kQThreads), 0, s, A);
+        } else if constexpr (FMT == KM_BF16) {
+          // 16 waves of 64 x 64: half the direct copies per wave of the 8-wave shape
+          hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 2, false, 4>), grid, dim3(kQWideThreads), 0, s, A);
+        } else {
+          if (pk)
+            hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 4, FMT == KM_SQ8>), grid, dim3(kQThreads), 0, s, A);
+          else
+            hipLaunchKernelGGL((assign_q8_kernel<FMT, false, 4>), grid, dim3(kQThreads), 0, s, A);
+        }
       }
       if (ng > 1) {
         const dim3 gp((unsigned)cdiv(P.n, 256));

@@ -94,6 +94,13 @@ def test_assign_lvq4_bit_exact(km, torch, n, d, k):
     assert abs(host(obj)[0] - dist_o.sum()) <= 1e-5 * abs(dist_o.sum()) + 1e-6
 
 
+# the 128 x 128 tiles' edges, a last stage of 32 to 128 dims, groups of centroid tiles and none
+@pytest.mark.parametrize("n,d,k", [(127, 32, 127), (128, 96, 128), (129, 160, 129), (385, 416, 641), (20000, 64, 260),
+                                   (110000, 32, 131)])
+def test_assign_lvq4_tile_edges(km, torch, n, d, k):
+    test_assign_lvq4_bit_exact(km, torch, n, d, k)
+
+
 def test_assign_lvq4_strided_rows(km, torch):
     n, d, k = 777, 128, 70
     X = blobs(n, d, 20, seed=4)

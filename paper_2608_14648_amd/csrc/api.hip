@@ -689,8 +689,11 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
   const size_t b_upd = al(update_bytes(in_place ? p : slice_points(p, 0, N), k));
   const size_t b_a = in_place ? 0 : al(sizeof(int32_t) * (size_t)N);
   const size_t b_score = objective ? al(sizeof(float) * (size_t)N) : 0;
-  const size_t b_xc = objective ? al(sizeof(float) * (size_t)N) : 0;
-  const size_t b_part = objective ? al(sizeof(double) * (size_t)objective_blocks(N)) : 0;
+  // fp32: the sum of the points' squared norms comes from the last update, which reads
+  // the rows anyway (a pass over them for it: 0.72 ms at 1M x 1024)
+  const bool norms = objective && in_place && iters > 0;
+  const size_t b_xc = objective && !norms ? al(sizeof(float) * (size_t)N) : 0;
+  const size_t b_part = objective ? al(sizeof(double) * ((size_t)objective_blocks(N) + 1)) : 0;
   const size_t b_idx = al(sizeof(int64_t) * (size_t)k);
   const size_t b_seg = al(sizeof(int) * 2 * (size_t)k);
   // fp32, SQ8 and bf16: one assignment launch per pass over all meso-clusters
@@ -729,6 +732,7 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
   float *sc = objective ? reinterpret_cast<float *>(wupd + b_upd + b_a) : nullptr;
   float *xc = reinterpret_cast<float *>(wupd + b_upd + b_a + b_score);
   double *part = reinterpret_cast<double *>(wupd + b_upd + b_a + b_score + b_xc);
+  double *xsum = part + (objective ? objective_blocks(N) : 0);
   int64_t *didx = reinterpret_cast<int64_t *>(wupd + b_upd + b_a + b_score + b_xc + b_part);
   int *dseg = reinterpret_cast<int *>(wupd + b_upd + b_a + b_score + b_xc + b_part + b_idx);
   int4 *dsegs = reinterpret_cast<int4 *>(reinterpret_cast<uint8_t *>(dseg) + b_seg);
@@ -778,11 +782,14 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
     st = clk.end();
     if (st != KM_OK) return st;
     if (it == iters) break;
-    KMQ_STAGE(clk, kStUpdate, launch_update(in_place ? p : q, ap, k, C, nullptr, policy, wupd, s, dseg, dseg + k));
+    const bool sum_norms = norms && it == iters - 1;
+    KMQ_STAGE(clk, kStUpdate, launch_update(in_place ? p : q, ap, k, C, nullptr, policy, wupd, s, dseg, dseg + k,
+                                            sum_norms ? xsum : nullptr, sum_norms ? N : 0));
   }
   if (objective) {
-    KMQ_STAGE(clk, kStOther, launch_xconst(q, xc, s, prow));
-    KMQ_STAGE(clk, kStOther, launch_objective(q, xc, sc, N, objective, part, objective_blocks(N), s));
+    if (!norms) KMQ_STAGE(clk, kStOther, launch_xconst(q, xc, s, prow));
+    KMQ_STAGE(clk, kStOther, launch_objective(q, norms ? nullptr : xc, sc, N, objective, part, objective_blocks(N), s,
+                                              norms ? xsum : nullptr));
   }
   if (!in_place) KMQ_STAGE(clk, kStOther, launch_scatter_assign(so.perm, ap, N, p.n, assign, s));
   if (k_fine) std::copy(kf.begin(), kf.end(), k_fine);

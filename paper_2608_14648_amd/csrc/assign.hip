@@ -2710,24 +2710,25 @@ __global__ __launch_bounds__(256) void xconst_kernel(Points P, const int *prow, 
   }
 }
 
-// ---- objective: sum of (point term + score), deterministic two-level sum ----
+// ---- objective: sum of (point term + score), deterministic two-level sum; the
+// point terms one by one or (xc NULL) as their sum ----
 __global__ __launch_bounds__(256) void objective_partial_kernel(const float *xc, const float *score, int64_t n,
                                                                 double *partials) {
   __shared__ double sh[256];
   double s = 0.0;
   const int64_t stride = (int64_t)gridDim.x * 256;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < n; p += stride)
-    s += (double)xc[p] + (double)score[p];
+    s += (xc ? (double)xc[p] : 0.0) + (double)score[p];
   s = block_sum_f64(s, sh);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void sum_partials_kernel(const double *partials, int np, double *out) {
+__global__ __launch_bounds__(256) void sum_partials_kernel(const double *partials, int np, const double *xsum, double *out) {
   __shared__ double sh[256];
   double s = 0.0;
   for (int i = threadIdx.x; i < np; i += 256) s += partials[i];
   s = block_sum_f64(s, sh);
-  if (threadIdx.x == 0) *out = s;
+  if (threadIdx.x == 0) *out = xsum ? *xsum + s : s;
 }
 
 // ---- STEP 1: gather the sampled points as initial centroids -----------------
@@ -3361,11 +3362,11 @@ km_status launch_xconst(const Points &P, float *xc, hipStream_t s, const int *pr
 int objective_blocks(int64_t n) { return (int)std::min<int64_t>(kObjBlocks, std::max<int64_t>(1, cdiv(n, 256))); }
 
 km_status launch_objective(const Points &P, const float *xc, const float *score, int64_t n, double *out,
-                           double *partials, int nblk_max, hipStream_t s) {
+                           double *partials, int nblk_max, hipStream_t s, const double *xsum) {
   (void)P;
   const int nb = std::min(nblk_max, objective_blocks(n));
   hipLaunchKernelGGL(objective_partial_kernel, dim3(nb), dim3(256), 0, s, xc, score, n, partials);
-  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
+  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, partials, nb, xsum, out);
   KMQ_LAUNCH_CHECK("objective");
   return KM_OK;
 }
@@ -3405,7 +3406,7 @@ km_status launch_cost(const float *X, int64_t n, int d, int64_t ldx, const float
                       double *out, double *partials, hipStream_t s) {
   const int nb = (int)std::min<int64_t>(kObjBlocks, std::max<int64_t>(1, cdiv(n, 4)));
   hipLaunchKernelGGL(cost_kernel, dim3(nb), dim3(256), 0, s, X, n, d, ldx, C, k, assign, partials);
-  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
+  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, partials, nb, nullptr, out);
   KMQ_LAUNCH_CHECK("cost_kernel");
   return KM_OK;
 }

@@ -125,7 +125,7 @@ CentroidPrep prep_slice(const Points &P, const CentroidPrep &cp, int off, int64_
 // prow (nullable): entry i is of row prow[i]
 km_status launch_xconst(const Points &P, float *xc, hipStream_t s, const int *prow = nullptr);
 km_status launch_objective(const Points &P, const float *xc, const float *score, int64_t n, double *out,
-                           double *partials, int nblk_max, hipStream_t s);
+                           double *partials, int nblk_max, hipStream_t s, const double *xsum = nullptr);
 int objective_blocks(int64_t n);
 // the same sum for fp32 and hybrid points from the distances (direct_objective_bytes of partials)
 km_status launch_direct_objective(const Points &P, const float *C, const CentroidPrep &cp, int k,
@@ -211,10 +211,11 @@ km_status launch_split_small(const float *X, int64_t ldx, const float *C, const 
 size_t update_bytes(const Points &P, int k);
 // seg_lo / seg_hi (nullable, int[k]): the split takes the donor of empty cluster j
 // from clusters [seg_lo[j], seg_hi[j]) only.  objective (nullable, DEVICE, F32 only): the
-// sum of the members' squared distances to the centroids passed in.
+// sum of the members' squared distances to the centroids passed in; with norms_of the
+// sum of their squared norms, NaN unless there are that many members.
 km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, int64_t *counts,
                         int policy, void *ws, hipStream_t s, const int *seg_lo = nullptr,
-                        const int *seg_hi = nullptr, double *objective = nullptr);
+                        const int *seg_hi = nullptr, double *objective = nullptr, int64_t norms_of = 0);
 struct SortOut {
   const int *perm;    // [n]: point indices ordered by cluster, point order kept inside a cluster
   const int *cnt;     // [k]: members per cluster (ids outside [0, k) are left out)

@@ -310,7 +310,8 @@ __device__ __forceinline__ int find_cluster(const int *choff, int k, int c) {
 // of the members to their centroid before the update (Cold), fp32 per lane (at most
 // 128 members) and fp64 above, one partial per workgroup: the objective of the pass
 // that made the assignment, from rows that are read here anyway (the kernel waits for
-// HBM; the three vector instructions per value are free).
+// HBM; the three vector instructions per value are free).  Without Cold, the members'
+// squared norms.
 template <bool OBJ>
 __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t ld, int df, const int *perm,
                                                          const int *cnt, const int *cstart, const int *choff, int k, int chunk,
@@ -328,7 +329,7 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
   const int col = blockIdx.y * 256 + 4 * lane;
   const bool ok = col < df;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f}, dist = acc, old = acc;
-  if (OBJ && ok) old = *reinterpret_cast<const f32x4 *>(Cold + (int64_t)j * dp + col);
+  if (OBJ && ok && Cold) old = *reinterpret_cast<const f32x4 *>(Cold + (int64_t)j * dp + col);
   auto add = [&](f32x4 v) {
     acc += v;
     if (OBJ) {
@@ -933,7 +934,8 @@ km_status launch_cluster_sort(const int32_t *assign, int64_t n, int k, void *ws,
 }
 
 km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, int64_t *counts, int policy,
-                        void *ws, hipStream_t s, const int *seg_lo, const int *seg_hi, double *objective) {
+                        void *ws, hipStream_t s, const int *seg_lo, const int *seg_hi, double *objective,
+                        int64_t norms_of) {
   UpdWs w = carve(P, k, ws, nullptr);
   km_status sst = launch_sort(assign, P.n, k, w, s);
   if (sst != KM_OK) return sst;
@@ -977,7 +979,7 @@ km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, 
     if (objective && P.fmt == KM_F32) {
       hipLaunchKernelGGL(segsum_f32_kernel<true>, dim3(w.maxchunks, slices), dim3(256), 0, s, F, fld, df, w.perm,
                          w.cnt, w.cstart, w.choff, k, w.chunk, static_cast<float *>(w.partial), w.dp,
-                         static_cast<const float *>(C), w.partialO);
+                         norms_of ? nullptr : static_cast<const float *>(C), w.partialO);
     } else if (df > 0) {
       hipLaunchKernelGGL(segsum_f32_kernel<false>, dim3(w.maxchunks, slices), dim3(256), 0, s, F, fld, df, w.perm,
                          w.cnt, w.cstart, w.choff, k, w.chunk, static_cast<float *>(w.partial), w.dp, nullptr, nullptr);
@@ -994,7 +996,8 @@ km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, 
     hipLaunchKernelGGL(finalize_f32_kernel, dim3(k + fold, (unsigned)cdiv(w.dp, 256)), dim3(256), 0, s,
                        static_cast<const float *>(w.partial), w.dp, w.cnt, w.choff, static_cast<float *>(w.Z),
                        w.fresh, is_bits_fmt(P.fmt) ? w.partialA : nullptr, w.partialM,
-                       P.fmt == KM_LVQ4 ? w.partialB : nullptr, d_bits, cm, w.partialO, w.cstart, k, (int)slices, P.n,
+                       P.fmt == KM_LVQ4 ? w.partialB : nullptr, d_bits, cm, w.partialO, w.cstart, k, (int)slices,
+                       norms_of ? norms_of : P.n,
                        objective);
   }
   KMQ_LAUNCH_CHECK("update: segmented sums");

@@ -390,3 +390,22 @@ def test_fine_f32_tiles_and_strides(km, torch):
     np.testing.assert_array_equal(host(C), host(C2))
     np.testing.assert_array_equal(host(a)[order], host(a2))
     assert (host(a)[meso < 0] == -1).all() and host(J)[0] == host(J2)[0]
+
+
+@pytest.mark.parametrize("iters", [0, 1, 2])
+def test_fine_f32_objective(km, torch, iters):
+    """The objective (squared norms from the last update, or from a pass of their own) against 64 bits: fp32 scores
+    are within 2^-22 of ||x|| ||c|| + ||c||^2 each.  A row that holds NaN makes it NaN."""
+    rng = np.random.default_rng(iters)
+    n, d, km_, k = 3000, 300, 4, 90
+    X = (3 + rng.standard_normal((n, d))).astype(np.float32)
+    meso = rng.integers(-1, km_, n).astype(np.int32)
+    C, a, _, J = km.kmeans_fine(km.points_f32(to_dev(X, torch)), to_dev(meso, torch), km_, k, iters, objective=True)
+    a, C = host(a), host(C).astype(np.float64)
+    ok = meso >= 0
+    want = ((X[ok] - C[a[ok]]) ** 2).sum()
+    assert abs(host(J)[0] - want) <= 2.0 ** -22 * d ** 0.5 * (2 * (X[ok].astype(np.float64) ** 2).sum()) + 1e-7 * want
+    X[n // 2, 7] = np.nan
+    meso[n // 2] = 1
+    _, _, _, J = km.kmeans_fine(km.points_f32(to_dev(X, torch)), to_dev(meso, torch), km_, k, iters, objective=True)
+    assert np.isnan(host(J)[0])

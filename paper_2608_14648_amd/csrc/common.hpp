@@ -313,12 +313,14 @@ __device__ __forceinline__ double block_sum_f64(double v, double *sh) {
   const int t = threadIdx.x;
   sh[t] = v;
   __syncthreads();
+  if (t < 64) {  // the halving tree over 256 values, its last six levels inside a wave
+    v = (sh[t] + sh[t + 128]) + (sh[t + 64] + sh[t + 192]);
 #pragma unroll
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) sh[t] += sh[t + s];
-    __syncthreads();
+    for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s);
+    if (t == 0) sh[0] = v;
   }
-  double r = sh[0];
+  __syncthreads();
+  const double r = sh[0];
   __syncthreads();
   return r;
 }

@@ -808,6 +808,9 @@ __global__ __launch_bounds__(256) void split_kernel(void *Zv, int k, int dp, con
   __shared__ int shs[256];
   __shared__ int n_empty;
   const int t = threadIdx.x;
+  int any = 0;
+  for (int j = t; j < k; j += 256) any |= cnt[j] == 0;
+  if (!__syncthreads_or(any)) return;  // the usual case: the list and its scan are for splits only
   const int per = (k + 255) / 256;
   const int lo = min(k, t * per), hi = min(k, lo + per);
   int mine = 0;
@@ -819,7 +822,6 @@ __global__ __launch_bounds__(256) void split_kernel(void *Zv, int k, int dp, con
   if (t == 0) n_empty = tot;
   __syncthreads();
   const int ne = n_empty;
-  if (ne == 0) return;
   for (int j = t; j < k; j += 256) cntw[j] = cnt[j];
   __syncthreads();
   const float up = 1.0f + 0x1p-10f, dn = 1.0f - 0x1p-10f;

@@ -268,7 +268,7 @@ def wl_c1(cfg, torch, km, args):
                     {"workload": cfg["name"], "N": spec.n, "d": spec.d, "k": k, "iters": T, "format": "f32"},
                     distances_per_s=(T + 1) * spec.n * k * K / elapsed,
                     roofline=roofline(cfg["name"], s, 6.0 * spec.n * k * spec.d, "fp16",
-                                      "split_kernel", "split_kernel", SPLIT_WORK),
+                                      "assign_small_kernel", "assign_small_kernel", SPLIT_WORK),
                     update_hbm=update_hbm(s, spec.n * (4 * spec.d + 4), "4d+4 per point"),
                     stages={"f32": stage_summary(s)})
 
@@ -524,9 +524,9 @@ def wl_c5(cfg, torch, km, args):
                      "format": "hybrid (fp32 front + 1-bit tail)"},
                     distances_per_s=(T + 1) * spec.n * k * K / elapsed,
                     partition_cost=float(out["cost"].item()),
-                    roofline=dict(roofline(cfg["name"], s, 2.0 * spec.n * k * d0, "fp32", "assign_hyb_kernel",
-                                           "assign_hyb_kernel"),
-                                  work="2 d_front operations per (point, centroid) pair on fp32 MFMA (the front "
+                    roofline=dict(roofline(cfg["name"], s, 6.0 * spec.n * k * d0, "fp16", "split_kernel",
+                                           "split_kernel"),
+                                  work="3 x 2 d_front operations per (point, centroid) pair on fp16 MFMA (the front "
                                        "contraction; the 1-bit tail's int8 work rides in the same launch)"),
                     update_hbm=update_hbm(s, spec.n * (4 * d0 + (spec.d - d0) // 8 + 8),
                                           "4 d_front + (d - d_front)/8 + 8 per point"),
@@ -879,9 +879,11 @@ def wl_pruned(fmt):
             # the survivors), against the whole assignment stage's time (front, tau and
             # refinement kernels alike)
             d_front = 32 * ((spec.d + 255) // 256)
-            work = K * (2.0 * spec.n * k * spec.d + T * 2.0 * spec.n * k * d_front + 2.0 * spec.d * c[2])
+            # (fp32 points: three fp16 products per fp32 one on the matrix cores)
+            per = 6.0 if fmt == "f32" else 2.0
+            work = K * (per * spec.n * k * spec.d + T * per * spec.n * k * d_front + 2.0 * spec.d * c[2])
             ach = work / (s["assign_ms"] * 1e-3) / 1e12
-            peak = "fp32" if fmt == "f32" else "int8"
+            peak = "fp16" if fmt == "f32" else "int8"
             return line(T * K / elapsed, "Lloyd iters/s", "f32" if fmt == "f32" else "u8",
                         {"workload": wname, "N": spec.n, "d": spec.d, "k": k, "iters": T, "format": fmt,
                          "eps0": 2.1, "d_front": 32 * ((spec.d + 255) // 256), "rotation": "random orthogonal"},

@@ -344,7 +344,8 @@ km_status kmeans_fit_pruned(const km_points *P, int32_t k, int32_t iters, const 
  *   receives k_i.  objective (nullable): DEVICE double[1], the in-space objective of
  *   the final pass.
  *   The call waits for `stream` once, to read the meso-cluster sizes; it keeps a
- *   meso-ordered copy of the points in scratch memory while it runs.
+ *   meso-ordered copy of the points in scratch memory while it runs (fp32 points are read
+ *   in place).
  */
 km_status kmeans_fine(const km_points *P, const int32_t *meso_assign, int32_t k_meso, int32_t k, int32_t iters,
                       int32_t flags, void *C, int32_t *assign, int32_t *k_fine, double *objective, int32_t policy,

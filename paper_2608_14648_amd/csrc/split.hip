@@ -240,7 +240,10 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
   constexpr bool HYB = MODE == kSplitHybrid, PROJ = MODE == kSplitProject, PRUNE = MODE == kSplitPrune;
   constexpr int TC = 64 * CB;
   constexpr int NCONST = HYB ? 4 : 1;  // constants per centroid: seed; -T, u, 2 sigma
-  constexpr int CRING = HYB ? 2 : 4;   // tiles of constants (a hybrid tile has 3 stages or more, and ends its argmax)
+  // Tiles of constants, and the stage of a tile that they are copied with.  A hybrid tile has 3 stages or more
+  // and ends its argmax after its last barrier, so the next tile's first step may run while other waves still
+  // read the seeds: the copies into their slot wait for that tile's second step or a later one.
+  constexpr int CRING = HYB ? 2 : 4, CSTAGE = HYB ? 1 : 0;
   constexpr int NCC = CB / 2;  // centroid copies per wave and stage
   constexpr int CREG = TC * kRow, STAGE = CREG + kTP * kRow;
   if (!A.sp.route->ok) return;  // every workgroup: the fp32 kernel takes this call
@@ -306,7 +309,7 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
   }
   int kc_s = 0, kc_t = 0;  // stage (dims) and tile of the next copy
   uint32_t kbuf = 0;       // its buffer's offset
-  // the copies of one stage: NCC + 2, and the tile's constants with its first stage
+  // the copies of one stage: NCC + 2, and the tile's constants with its stage CSTAGE
   auto copy_stage = [&]() {
     const int c0 = (g + kc_t * NG) * TC;
     const uint32_t l0 = ring0 + kbuf + wave * 1024;
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
         for (int i = 0; i < 2; ++i) lds_copy16_at(xb, xoff[i], l0 + CREG + 8192u * i);
       }
     }
-    if (!PROJ && kc_s == 0) {
+    if (!PROJ && kc_s == CSTAGE) {
       // wave w copies rows 64 (w mod TC / 64) .. of its constants, so that all waves have
       // the same number of copies in flight; rows past the last centroid read a -inf seed
       const int seg = wave & (TC / 64 - 1);

@@ -240,6 +240,43 @@ def test_hybrid(km, torch, n, d, d0, k, how):
         assert abs(host(obj)[0] - want) <= 2.0 ** -21 * size.sum()
 
 
+def hybrid_scores(front, bits, alpha, C, m, d0):
+    """64-bit scores of hybrid points and their tail part, ||x'||^2 and ||c'||^2."""
+    r = C[:, d0:] - m[d0:]  # residual codes in fp32, as the interface defines them
+    sg = np.where(np.abs(r).max(1) > 0, np.abs(r).max(1) / np.float32(127), np.float32(1)).astype(np.float32)
+    q = np.clip(np.rint(r / sg[:, None]), -127, 127).astype(np.float64)
+    b = ((bits[:, :, None] >> np.arange(32, dtype=np.uint32)) & 1).reshape(len(bits), -1)[:, d0:].astype(np.float64) * 2 - 1
+    f, cf = front.astype(np.float64), C[:, :d0].astype(np.float64)
+    cn = (cf ** 2).sum(1)
+    tail = sg.astype(np.float64) ** 2 * (q ** 2).sum(1) - 2 * alpha[:, None] * sg.astype(np.float64) * (b @ q.T)
+    return cn - 2 * f @ cf.T + tail, tail, (f ** 2).sum(1), cn
+
+
+# A tile of 3 stages, the fewest there are (front of 32 dims, tail of one stage), in workgroups that sweep 8 and 16
+# tiles of 256 centroids: their constants take turns in two places.
+@pytest.mark.parametrize("d,k", [(64, 2048), (160, 4090)])
+def test_hybrid_three_stages(km, torch, d, k):
+    import oracle as orc
+    n, d0 = 600, 32
+    X, C = points(n, d, k, d)
+    C[:, :d0] *= (1 + np.arange(k, dtype=np.float32) % 7)[:, None]  # norms that differ from tile to tile
+    m = orc.col_mean(X)
+    bits, alpha = orc.sign1_encode(X, m, d0)
+    front = np.ascontiguousarray(X[:, :d0])
+    i = np.arange(65536) % n  # 256 point tiles, one per CU: a workgroup sweeps every centroid tile
+    P = km.points_hybrid(to_dev(front[i], torch), to_dev(bits[i].view(np.int32), torch), to_dev(alpha[i], torch),
+                         to_dev(m, torch), d)
+    a, sc, _ = km.kmeans_assign(P, to_dev(C, torch))
+    a, sc = host(a), host(sc)
+    np.testing.assert_array_equal(a, a[i])
+    np.testing.assert_array_equal(sc, sc[i])
+    s, tail, xn, cn = hybrid_scores(front, bits, alpha, C, m, d0)
+    r, got = np.arange(n), a[:n]
+    size = xn + cn[got] + np.abs(tail).max(1)
+    assert ((s[r, got] - s.min(1)) / size).max() <= NEAR_TIE_REL
+    assert (np.abs(sc[:n] - s[r, got]) <= 2 * (12 * 2.0 ** -23 + 3 * 2.0 ** -22) * size).all()
+
+
 # one and several 256-point tiles, output tiles of 128 and 256 and several of them, ragged dims
 @pytest.mark.parametrize("n,d,dout", [(1, 32, 4), (255, 36, 8), (257, 64, 128), (300, 100, 132), (1000, 260, 256),
                                       (513, 132, 600), (64, 4096, 36)])

@@ -403,13 +403,13 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
   // a 1 the compiler does not see through: fma(t, 1, ..) keeps split2's mixed instructions
   float one = 1.0f;
   if constexpr (PROJ) asm volatile("" : "+s"(one));
-  // pair q of a point block
-  auto conv = [&](int pb, int q) {
+  // pair q of a point block; past: a block past the last stage, which nothing multiplies and seen leaves out
+  auto conv = [&](int pb, int q, bool past = false) {
     if constexpr (PROJ) {
       const f32x4 v = w[pb][q >> 1], m = mreg[q >> 1];
       const int e = 2 * (q & 1);
       const float t0 = __builtin_fmaf(v[e], sx, -m[e]), t1 = __builtin_fmaf(v[e + 1], sx, -m[e + 1]);
-      seen[pb] |= __float_as_uint(t0) | __float_as_uint(t1);
+      if (!past) seen[pb] |= __float_as_uint(t0) | __float_as_uint(t1);
       split2(t0, t1, one, xh[pb][q], xl[pb][q]);
       asm volatile("" : "+v"(xh[pb][q]), "+v"(xl[pb][q]), "+v"(seen[pb]));
       return;
@@ -529,7 +529,7 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
         // the other block's conversion, a pair at a time: the second block of this
         // stage, then the first of the next
         constexpr int CS = CB == 4 ? 2 : 1;
-        if (j >= CS && (j - CS) % CS == 0 && (j - CS) / CS < 4) conv(1 - pb, (j - CS) / CS);
+        if (j >= CS && (j - CS) % CS == 0 && (j - CS) / CS < 4) conv(1 - pb, (j - CS) / CS, LAST && pb == 1);
         if (pb == 1) {  // operands used for the last time are replaced
           if (j >= 1 && j <= CB) read_cl(j - 1, nbuf);
           if (j >= 2 * CB + 1) read_ch(j - 2 * CB - 1, nbuf);
@@ -714,7 +714,8 @@ __global__ __launch_bounds__(kThr, 1) void split_kernel(SplitArgs A) {
     return;
   } else if constexpr (PROJ) {
     open_front();
-    for (int st = 1; st <= S; ++st) step(st, F, F);  // st: the stage read ahead
+    for (int st = 1; st < S; ++st) step(st, F, F);  // st: the stage read ahead
+    step(S, F, T);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // rows with a value past fp16's range, NaN or infinities give NaN, and rows whose
     // values are all small (below 2 where the sample's largest is 2^11 .. 2^12) lose bits:

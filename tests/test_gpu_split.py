@@ -313,6 +313,22 @@ def test_project(km, torch, n, d, dout, how):
     assert (err <= bound[fin]).all(), (err / bound[fin]).max()
 
 
+@pytest.mark.parametrize("row", [0, 31, 69, 32, 255])
+def test_project_one_small_row(km, torch, row):
+    """One row whose centred values are 2^-24 of the others', alone in its tile, in either block of a wave: the split
+    would keep 2^-37 of the others, so the row goes to the fp32 kernel, also where its uncentred values are large."""
+    n, d, dout = 256, 64, 40
+    g = np.random.default_rng(row)
+    m = np.where(np.arange(d) < 16, 64, 0).astype(np.float32)
+    X = (m + g.standard_normal((n, d)) * 2.0 ** 10).astype(np.float32)
+    X[row] = m + np.where(m > 0, 0, 2.0 ** -14 * g.standard_normal(d)).astype(np.float32)
+    W = (g.standard_normal((d, dout)) / 8).astype(np.float32)
+    xc = (X[row] - m).astype(np.float64)
+    Y = host(km.pca_project(to_dev(X, torch), to_dev(m, torch), to_dev(W, torch)))[row].astype(np.float64)
+    size = np.linalg.norm(xc) * np.linalg.norm(W.astype(np.float64), axis=0)
+    assert (np.abs(Y - xc @ W.astype(np.float64)) <= (6 * d // 16 * 2.0 ** -23 + 2.0 ** -20) * size).all()
+
+
 # one row to several splits and runs of 4096 rows, ragged stages of 16 rows, one to three 256-column blocks
 @pytest.mark.parametrize("n,d", [(1, 4), (15, 36), (16, 256), (31, 260), (33, 512), (4111, 300), (20001, 516), (70000, 32)])
 def test_cov(km, torch, n, d):

@@ -99,56 +99,77 @@ __global__ __launch_bounds__(256) void split_prep_kernel(const float *C, int64_t
 }
 
 // ---- projection: scales and the image of W ------------------------------------------
-// The largest |x - mean| of 1024 rows spread over X, as 256 partial bit patterns (NaN
-// and infinities are the largest).
-__global__ __launch_bounds__(256) void proj_sample_kernel(const float *X, int64_t n, int d, int64_t ldx,
-                                                          const float *mean, uint32_t *part, SplitRoute *route) {
-  __shared__ uint32_t sh[256];
+// Every dim's largest |x - mean| over 1024 rows spread over X, as a bit pattern (NaN and
+// infinities are the largest): 16 dims per workgroup, 64 rows at a time.
+__global__ __launch_bounds__(1024) void proj_sample_kernel(const float *X, int64_t n, int d, int64_t ldx,
+                                                           const float *mean, uint32_t *top, SplitRoute *route) {
+  __shared__ uint32_t sh[1024];
   const int t = threadIdx.x;
+  const int c = blockIdx.x * 16 + (t & 15);
   uint32_t m = 0;
   const int rows = (int)min<int64_t>(n, 1024);
-  for (int i = blockIdx.x; i < rows; i += 256) {
-    const float *x = X + (int64_t)((double)i * (double)n / rows) * ldx;
-    for (int c = t; c < d; c += 256) m = max(m, __float_as_uint(x[c] - mean[c]) & 0x7fffffffu);
+  if (c < d) {
+    const float mc = mean[c];
+#pragma unroll 4
+    for (int i = t >> 4; i < rows; i += 64)
+      m = max(m, __float_as_uint(X[(int64_t)((double)i * (double)n / rows) * ldx + c] - mc) & 0x7fffffffu);
   }
   sh[t] = m;
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
+  for (int st = 512; st >= 16; st >>= 1) {
     if (t < st) sh[t] = max(sh[t], sh[t + st]);
     __syncthreads();
   }
-  if (t == 0) part[blockIdx.x] = sh[0];
+  if (t < 16 && c < d) top[c] = sh[t];
   if (t == 0 && blockIdx.x == 0) route->ok = 1;
 }
 
 // 16 columns of W per workgroup: each column's own scale (its largest |w| at
 // [2^7, 2^8)), its factor back to Y (in seed) and its rows of the image.  The points'
-// scale puts the sample's largest |x - mean| at [2^11, 2^12): sixteen times more fits.
+// scale puts the sample's largest |x - mean| at [2^11, 2^12): eight times more always fits.
 // A sample or W with NaN or infinities, or past 2^+-50, leaves the call to the fp32
 // kernel: the sample kernel sets the route's ok, whoever sees such a value clears it.
-__global__ __launch_bounds__(256) void proj_prep_kernel(const float *W, int d, int d_out, const uint32_t *part,
+// So does a column that lives on dims far smaller than the largest, as the last
+// directions of data whose dims have different units do.  The points are held to 2^-36
+// of their largest value M and a column to 2^-32 of its largest weight w, whatever the
+// dim; against the column's largest term |w_i| max|x_i| that is 2^-24 and less, an fp32
+// product's own rounding, as long as this term is at least 2^-8 M w.
+__global__ __launch_bounds__(256) void proj_prep_kernel(const float *W, int d, int d_out, const uint32_t *top,
                                                         SplitPrep sp, int64_t ntflag) {
   __shared__ uint32_t sh[256];
+  __shared__ float shg[256];
   __shared__ float scl[16];
   const int t = threadIdx.x, o16 = t & 15, rg = t >> 4;
   const int o = blockIdx.x * 16 + o16;
-  sh[t] = part[t];
+  uint32_t mt = 0;
+  for (int i = t; i < d; i += 256) mt = max(mt, top[i]);
+  sh[t] = mt;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
     if (t < st) sh[t] = max(sh[t], sh[t + st]);
     __syncthreads();
   }
+  const float mx = __uint_as_float(sh[0]);
   const int ex = (int)(sh[0] >> 23) - 127;
   const bool okx = ex >= -50 && ex <= 50;
   const float sx = ldexpf(1.0f, 11 - (okx ? ex : 0));
   __syncthreads();
   uint32_t m = 0;
+  float term = 0.f;
   if (o < d_out)
-    for (int i = rg; i < d; i += 16) m = max(m, __float_as_uint(W[(int64_t)i * d_out + o]) & 0x7fffffffu);
+    for (int i = rg; i < d; i += 16) {
+      const float w = fabsf(W[(int64_t)i * d_out + o]);
+      m = max(m, __float_as_uint(w));
+      term = fmaxf(term, w * __uint_as_float(top[i]));
+    }
   sh[t] = m;
+  shg[t] = term;
   __syncthreads();
   for (int st = 128; st >= 16; st >>= 1) {
-    if (t < st) sh[t] = max(sh[t], sh[t + st]);
+    if (t < st) {
+      sh[t] = max(sh[t], sh[t + st]);
+      shg[t] = fmaxf(shg[t], shg[t + st]);
+    }
     __syncthreads();
   }
   if (t < 16) {
@@ -158,7 +179,7 @@ __global__ __launch_bounds__(256) void proj_prep_kernel(const float *W, int d, i
     scl[t] = s;
     if (o < d_out) {
       sp.seed[o] = 1.0f / (s * sx);
-      if (!okw) sp.route->ok = 0;
+      if (!okw || (!zero && shg[t] < 0x1p-8f * mx * __uint_as_float(sh[t]))) sp.route->ok = 0;
     }
   }
   const int64_t g0 = (int64_t)blockIdx.x * 256 + t, gs = (int64_t)gridDim.x * 256;
@@ -911,16 +932,17 @@ km_status launch_split(const SplitArgs &A, int64_t grid, int tile_c, hipStream_t
   return KM_OK;
 }
 
-size_t split_project_bytes(int64_t n, int d, int d_out) {
-  return split_bytes(n, std::max(d_out, 256), d, false);  // the row maxima's place holds the sample's 256 partials
+size_t split_project_bytes(int64_t n, int d, int d_out) {  // with the sample's maxima
+  return split_bytes(n, d_out, d, false) + 4 * (size_t)d;
 }
 
 km_status launch_split_project(const float *X, int64_t n, int d, int64_t ldx, const float *mean, const float *W,
                                int d_out, float *Y, void *ws, SplitPrep *out, hipStream_t s) {
-  SplitPrep sp = split_layout(n, std::max(d_out, 256), d, false, ws);
-  sp.cstage = (int64_t)d_out * kRow;
-  hipLaunchKernelGGL(proj_sample_kernel, dim3(256), dim3(256), 0, s, X, n, d, ldx, mean, sp.rmax, sp.route);
-  hipLaunchKernelGGL(proj_prep_kernel, dim3((unsigned)cdiv(d_out, 16)), dim3(256), 0, s, W, d, d_out, sp.rmax, sp,
+  const SplitPrep sp = split_layout(n, d_out, d, false, ws);
+  uint32_t *top = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(ws) + split_bytes(n, d_out, d, false));
+  hipLaunchKernelGGL(proj_sample_kernel, dim3((unsigned)cdiv(d, 16)), dim3(1024), 0, s, X, n, d, ldx, mean, top,
+                     sp.route);
+  hipLaunchKernelGGL(proj_prep_kernel, dim3((unsigned)cdiv(d_out, 16)), dim3(256), 0, s, W, d, d_out, top, sp,
                      cdiv(n, kTP));
   KMQ_LAUNCH_CHECK("projection scales");
   SplitArgs A{};

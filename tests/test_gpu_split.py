@@ -329,6 +329,29 @@ def test_project_one_small_row(km, torch, row):
     assert (np.abs(Y - xc @ W.astype(np.float64)) <= (6 * d // 16 * 2.0 ** -23 + 2.0 ** -20) * size).all()
 
 
+@pytest.mark.parametrize("how", ["small_dims", "small_weights", "one_column"])
+def test_project_dims_of_different_size(km, torch, how):
+    """Half of the dims 2^-20 of the others, and outputs that live on them: each output bounded by its own terms, as
+    fp32 products are (2^-24 each, and 6 roundings per 16 dims)."""
+    n, d, dout = 700, 128, 72
+    g = np.random.default_rng(4)
+    s = np.where(np.arange(d) % 2, 2.0 ** -20, 1.0)
+    X = (g.standard_normal((n, d)) * s).astype(np.float32)
+    W = g.standard_normal((d, dout)) / 8
+    if how == "small_dims":      # the large dims have no part in an output
+        W[0::2] = 0
+    elif how == "small_weights":  # all terms of the same size
+        W /= s[:, None] * 2.0 ** 20
+    else:
+        W[0::2, 50] = 0
+    W = W.astype(np.float32)
+    Y = host(km.pca_project(to_dev(X, torch), torch.zeros(d, device="cuda"), to_dev(W, torch))).astype(np.float64)
+    Xd, Wd = X.astype(np.float64), W.astype(np.float64)
+    bound = (6 * d // 16 * 2.0 ** -23 + 2.0 ** -23) * (np.abs(Xd) @ np.abs(Wd))
+    err = np.abs(Y - Xd @ Wd)
+    assert (err <= bound).all(), (err / bound).max()
+
+
 # one row to several splits and runs of 4096 rows, ragged stages of 16 rows, one to three 256-column blocks
 @pytest.mark.parametrize("n,d", [(1, 4), (15, 36), (16, 256), (31, 260), (33, 512), (4111, 300), (20001, 516), (70000, 32)])
 def test_cov(km, torch, n, d):

@@ -307,11 +307,11 @@ __device__ __forceinline__ int find_cluster(const int *choff, int k, int c) {
 }
 
 // fp32 rows: one slice of 256 columns per workgroup.  OBJ: also the squared distances
-// of the members to their centroid before the update (Cold), fp32 per lane (at most
-// 128 members) and fp64 above, one partial per workgroup: the objective of the pass
-// that made the assignment, from rows that are read here anyway (the kernel waits for
-// HBM; the three vector instructions per value are free).  Without Cold, the members'
-// squared norms.
+// of the members to their centroid before the update (Cold) in fp64, one partial per
+// workgroup: the objective of the pass that made the assignment, from rows that are read
+// here anyway (the kernel waits for HBM).  Without Cold, the members' squared norms, which
+// cancel against scores: fp32 sums over a lane's members (up to 128, all rounded the same way
+// where values repeat) would be 2^-22 of the norms off and more.
 template <bool OBJ>
 __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t ld, int df, const int *perm,
                                                          const int *cnt, const int *cstart, const int *choff, int k, int chunk,
@@ -328,13 +328,17 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = blockIdx.y * 256 + 4 * lane;
   const bool ok = col < df;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f}, dist = acc, old = acc;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f}, old = acc;
+  double dist[4] = {0.0, 0.0, 0.0, 0.0};
   if (OBJ && ok && Cold) old = *reinterpret_cast<const f32x4 *>(Cold + (int64_t)j * dp + col);
   auto add = [&](f32x4 v) {
     acc += v;
     if (OBJ) {
-      const f32x4 e = v - old;
-      dist += e * e;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double e = (double)v[q] - (double)old[q];
+        dist[q] = fma(e, e, dist[q]);
+      }
     }
   };
   int m = m0 + wave;
@@ -364,7 +368,7 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
     *reinterpret_cast<f32x4 *>(partial + (int64_t)c * dp + col) = s;
   }
   if (OBJ) {
-    const double o = block_sum_f64((double)dist[0] + dist[1] + dist[2] + dist[3], shd);
+    const double o = block_sum_f64((dist[0] + dist[1]) + (dist[2] + dist[3]), shd);
     if (threadIdx.x == 0) partialO[(int64_t)c * gridDim.y + blockIdx.y] = o;
   }
 }

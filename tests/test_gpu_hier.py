@@ -409,3 +409,15 @@ def test_fine_f32_objective(km, torch, iters):
     meso[n // 2] = 1
     _, _, _, J = km.kmeans_fine(km.points_f32(to_dev(X, torch)), to_dev(meso, torch), km_, k, iters, objective=True)
     assert np.isnan(host(J)[0])
+
+
+@pytest.mark.parametrize("v", [1.8964999914169312, 1.3515000343322754])
+def test_fine_f32_objective_of_repeated_values(km, torch, v):
+    """Rows of one repeated value, whose fp32 squares all round the same way when they are added up: the norms from the
+    last update are those of a pass of their own (one rounding per point, 2^-24), under the same last pass's scores."""
+    n, d, km_, k = 5000, 64, 2, 6
+    P = km.points_f32(torch.full((n, d), v, device="cuda"))
+    meso = to_dev(np.arange(n, dtype=np.int32) % km_, torch)
+    C, _, _, J1 = km.kmeans_fine(P, meso, km_, k, 1, policy=km.KM_EMPTY_KEEP, objective=True)
+    _, _, _, J0 = km.kmeans_fine(P, meso, km_, k, 0, C=C, objective=True)
+    assert abs(host(J1)[0] - host(J0)[0]) <= 2.0 ** -24 * n * d * v * v

@@ -193,6 +193,10 @@ km_status pca_project(const float *X, int64_t n, int32_t d, const float *mean, c
  *   objective (nullable): double[1], receives sum over points of the in-space
  *      distance (score plus the point-only term), fp64.  For the 1-bit formats the
  *      point-only term is the decoded point's squared norm alpha^2 d; for LVQ4 it is N_x.
+ *      A point that has no nearest centroid, since no score of it is a number below
+ *      infinity (its assign is then outside [0, k)), makes the objective NaN when it holds
+ *      NaN and +infinity when it does not.  One with a nearest centroid and infinite
+ *      coordinates (a score of -infinity) makes it NaN.
  *   1 <= k.
  */
 km_status kmeans_assign(const km_points *P, const void *C, int32_t k, int32_t *assign, float *score,

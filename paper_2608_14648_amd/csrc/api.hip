@@ -784,7 +784,7 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
     if (it == iters) break;
     const bool sum_norms = norms && it == iters - 1;
     KMQ_STAGE(clk, kStUpdate, launch_update(in_place ? p : q, ap, k, C, nullptr, policy, wupd, s, dseg, dseg + k,
-                                            sum_norms ? xsum : nullptr, sum_norms ? N : 0));
+                                            sum_norms ? xsum : nullptr, sum_norms));
   }
   if (objective) {
     if (!norms) KMQ_STAGE(clk, kStOther, launch_xconst(q, xc, s, prow));

@@ -2811,10 +2811,11 @@ __global__ __launch_bounds__(256) void cost_kernel(const float *X, int64_t n, in
 // ---- objective from the distances: sum ||x - c_a||^2 --------------------------------
 // One pass over the rows, as the point-only terms ||x||^2 need, and no cancellation: for
 // points close to their centroid ||x||^2 + score is a small difference whose rounding
-// adds up over the points.  One wave per point at a time, fp32 per lane and point, fp64
-// above; HBM bound.  A point without a centroid (its row holds NaN) or a sum that is
-// not finite gives NaN.  HYB: the front dims like that, plus the tail's score
-// sigma^2 Q - alpha 2 sigma (2D - T) and its point-only term alpha^2 (d - d0), in fp64.
+// adds up over the points.  One wave per point at a time, fp64; HBM bound.  A point without a
+// centroid (no score was a number below infinity) adds its squared norm and infinity: NaN
+// where its row holds NaN.  One with an infinite coordinate and a centroid had the score
+// -infinity and adds NaN.  HYB: the front dims like that, plus the tail's score
+// sigma^2 Q - alpha 2 sigma (2D - T) and its point-only term alpha^2 (d - d0).
 template <bool HYB>
 __global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, int64_t n, int d, int64_t ldx,
                                                                const float *C, int64_t ldc, int k,
@@ -2859,9 +2860,7 @@ __global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, i
         }
       }
     }
-    f32x4 t[NP];
-#pragma unroll
-    for (int e = 0; e < NP; ++e) t[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    double t[NP] = {0.0, 0.0, 0.0, 0.0};
     for (int i = 4 * lane; i < d; i += 256) {
       f32x4 xv[NP], cv[NP];
 #pragma unroll
@@ -2870,18 +2869,26 @@ __global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, i
         cv[e] = *reinterpret_cast<const f32x4 *>(c[e] + i);
       }
 #pragma unroll
-      for (int e = 0; e < NP; ++e) {
-        const f32x4 df = xv[e] - cv[e];
-        t[e] += df * df;
-      }
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < NP; ++e) {
+          const double df = (double)xv[e][q] - (double)cv[e][q];
+          t[e] = fma(df, df, t[e]);
+        }
     }
 #pragma unroll
     for (int e = 0; e < NP; ++e) {
       if (p + e * stride >= n) continue;
-      s += in[e] ? (double)t[e][0] + t[e][1] + t[e][2] + t[e][3] : (double)NAN;
+      const double al = HYB ? (double)P.alpha[pt[e]] : 0.0;
+      if (!in[e]) {
+        for (int i = lane; i < d; i += 64) s += (double)x[e][i] * (double)x[e][i];
+        s += al * al * dt + INFINITY;
+        continue;
+      }
+      s += isfinite(t[e]) ? t[e] : (double)NAN;
       // alpha 2 sigma per set bit less T, on every lane's own dims; the point's terms on lane 0
-      if (HYB && in[e]) {
-        const double al = P.alpha[pt[e]], v = al * cp.sig2[a[e]];
+      if (HYB) {
+        const double v = al * cp.sig2[a[e]];
         s -= v * (2 * D[e]);
         if (lane == 0) s += v * cp.qsum[a[e]] + cp.u[a[e]] + al * al * dt;
       }
@@ -2896,7 +2903,7 @@ __global__ __launch_bounds__(256) void direct_objective_sum_kernel(const double 
   double s = 0.0;
   for (int i = threadIdx.x; i < np; i += 256) s += partials[i];
   s = block_sum_f64(s, sh);
-  if (threadIdx.x == 0) *out = isfinite(s) ? s : (double)NAN;
+  if (threadIdx.x == 0) *out = s;
 }
 
 constexpr int kDirectBlocks = 2048;  // 8 workgroups of 4 waves on each of 256 CUs

@@ -211,11 +211,11 @@ km_status launch_split_small(const float *X, int64_t ldx, const float *C, const 
 size_t update_bytes(const Points &P, int k);
 // seg_lo / seg_hi (nullable, int[k]): the split takes the donor of empty cluster j
 // from clusters [seg_lo[j], seg_hi[j]) only.  objective (nullable, DEVICE, F32 only): the
-// sum of the members' squared distances to the centroids passed in; with norms_of the
-// sum of their squared norms, NaN unless there are that many members.
+// sum of the points' squared distances to the centroids passed in; with norms the sum of
+// the squared norms of all points but those with assign = -1.
 km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, int64_t *counts,
                         int policy, void *ws, hipStream_t s, const int *seg_lo = nullptr,
-                        const int *seg_hi = nullptr, double *objective = nullptr, int64_t norms_of = 0);
+                        const int *seg_hi = nullptr, double *objective = nullptr, bool norms = false);
 struct SortOut {
   const int *perm;    // [n]: point indices ordered by cluster, point order kept inside a cluster
   const int *cnt;     // [k]: members per cluster (ids outside [0, k) are left out)

@@ -55,6 +55,7 @@ struct UpdWs {
   float *partialM;    // [maxchunks] 1-bit formats: largest alpha per chunk; LVQ4: largest scale
   double *partialB;   // [maxchunks] LVQ4: sum of the biases per chunk
   double *partialO;   // [maxchunks * ceil(d / 256)] F32: squared distances to the old centroid per workgroup
+  double *loose;      // [4 nblk] F32: what the points of no cluster add to the objective, per wave of hist_kernel
   void *Z;       // [k * dp] float or uint8
   uint8_t *fresh;  // [k]
   int64_t *cntw;   // [k]
@@ -100,6 +101,7 @@ UpdWs carve(const Points &P, int k, void *base, size_t *bytes_out) {
   w.partialM = (float *)take(sizeof(float) * (size_t)w.maxchunks);
   w.partialB = (double *)take(sizeof(double) * (size_t)w.maxchunks);
   w.partialO = (double *)take(P.fmt == KM_F32 ? sizeof(double) * (size_t)w.maxchunks * (size_t)cdiv(P.d, 256) : 0);
+  w.loose = (double *)take(P.fmt == KM_F32 ? sizeof(double) * 4 * (size_t)w.nblk : 0);
   w.Z = take(sizeof(float) * (size_t)k * (size_t)w.dp);
   w.fresh = (uint8_t *)take((size_t)k);
   w.cntw = (int64_t *)take(sizeof(int64_t) * (size_t)k);
@@ -109,30 +111,58 @@ UpdWs carve(const Points &P, int k, void *base, size_t *bytes_out) {
 }
 
 // ---- 1. histogram ------------------------------------------------------------
+// The objective's points of no cluster (assign outside [0, k): no score was a number below
+// infinity), one sum per wave.
+struct LooseRows {
+  const float *X;
+  int64_t ld;
+  int d;
+  bool norms;   // sum their squared norms, but not those of points with assign = -1 (no meso-cluster);
+                // else their distances: NaN where the row holds NaN, infinity where not
+  double *sum;  // [4 blocks]; NULL: no objective
+};
+
+template <bool OBJ>
 __global__ __launch_bounds__(256) void hist_kernel(const int32_t *assign, int64_t n, int k, int ppb, int *offs,
-                                                   int use_lds, int *arrive) {
+                                                   int use_lds, int *arrive, LooseRows L) {
   extern __shared__ int lc[];
   const int b = blockIdx.x, t = threadIdx.x;
   const int64_t lo = (int64_t)b * ppb;
   const int64_t hi = min<int64_t>(n, lo + ppb);
   int *row = offs + (int64_t)b * k;
+  double loose = 0.0;
   if (b == 0 && t == 0) *arrive = 0;
   if (use_lds) {
     for (int j = t; j < k; j += 256) lc[j] = 0;
     __syncthreads();
   }
-  for (int64_t p = lo + t; p < hi; p += 8 * 256) {  // 8 loads at a time
+  for (int64_t base = lo; base < hi; base += 8 * 256) {  // 8 loads at a time
+    const int64_t p = base + t;
     int a[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) a[e] = p + 256 * e < hi ? assign[p + 256 * e] : -1;
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
+    for (int e = 0; e < 8; ++e) {
       if (a[e] >= 0 && a[e] < k) {
         if (use_lds)
           atomicAdd(&lc[a[e]], 1);
         else
           atomicAdd(&row[a[e]], 1);
       }
+      if (OBJ) {  // a wave takes its points of no cluster one by one
+        const bool out = (a[e] < 0 || a[e] >= k) && p + 256 * e < hi && !(L.norms && a[e] == -1);
+        for (uint64_t m = __ballot(out); m != 0; m &= m - 1) {
+          const float *x = L.X + (p + 256 * e - (t & 63) + __ffsll((unsigned long long)m) - 1) * L.ld;
+          for (int i = t & 63; i < L.d; i += 64) loose += (double)x[i] * (double)x[i];
+          if (!L.norms) loose += INFINITY;
+        }
+      }
+    }
+  }
+  if (OBJ) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) loose += __shfl_xor(loose, o);
+    if ((t & 63) == 0) L.sum[4 * b + (t >> 6)] = loose;
   }
   if (use_lds) {
     __syncthreads();
@@ -369,7 +399,8 @@ __global__ __launch_bounds__(256) void segsum_f32_kernel(const float *X, int64_t
   }
   if (OBJ) {
     const double o = block_sum_f64((dist[0] + dist[1]) + (dist[2] + dist[3]), shd);
-    if (threadIdx.x == 0) partialO[(int64_t)c * gridDim.y + blockIdx.y] = o;
+    // an infinite coordinate in a cluster: its score was -infinity, the distance no number
+    if (threadIdx.x == 0) partialO[(int64_t)c * gridDim.y + blockIdx.y] = Cold && !isfinite(o) ? (double)NAN : o;
   }
 }
 
@@ -732,14 +763,13 @@ struct Compose {
 // partialM its largest scale and partialB its bias sum; the mean is the sum over
 // chunks of (partialM / (2^19 - 1)) W + partialB, over n.
 // One more workgroup, where objective is given, sums segsum_f32_kernel's partials
-// (`slices` per chunk): NaN when a point belongs to no cluster (its row holds NaN) or the
-// sum is not finite.
+// (`slices` per chunk) and hist_kernel's (nloose).
 __global__ __launch_bounds__(256) void finalize_f32_kernel(const float *partial, int dp, const int *cnt,
                                                            const int *choff, float *Z, uint8_t *fresh,
                                                            const uint32_t *partialA, const float *partialM,
                                                            const double *partialB, int d_bits, Compose cm,
-                                                           const double *partialO, const int *cstart, int k, int slices,
-                                                           int64_t n, double *objective) {
+                                                           const double *partialO, const double *loose, int nloose, int k,
+                                                           int slices, double *objective) {
   __shared__ double shd[256];
   const int j = blockIdx.x;
   if (j == k) {
@@ -747,8 +777,9 @@ __global__ __launch_bounds__(256) void finalize_f32_kernel(const float *partial,
     double s = 0.0;
     const int64_t np = (int64_t)choff[k] * slices;
     for (int64_t i = threadIdx.x; i < np; i += 256) s += partialO[i];
+    for (int i = threadIdx.x; i < nloose; i += 256) s += loose[i];
     s = block_sum_f64(s, shd);
-    if (threadIdx.x == 0) *objective = (int64_t)cstart[k - 1] + cnt[k - 1] == n && isfinite(s) ? s : (double)NAN;
+    if (threadIdx.x == 0) *objective = s;
     return;
   }
   const int col = blockIdx.y * 256 + threadIdx.x;
@@ -904,12 +935,17 @@ size_t update_bytes(const Points &P, int k) {
 }
 
 // steps 1-3: counts, starts and the stable cluster-sorted order of the points
-static km_status launch_sort(const int32_t *assign, int64_t n, int k, const UpdWs &w, hipStream_t s) {
+static km_status launch_sort(const int32_t *assign, int64_t n, int k, const UpdWs &w, hipStream_t s,
+                             const LooseRows &L = LooseRows{}) {
   const bool lds = k <= kLdsCursorMax;
   const size_t lds_bytes = lds ? sizeof(int) * (size_t)k : 0;
   if (!lds) hipLaunchKernelGGL(fill_int_kernel, dim3(1024), dim3(256), 0, s, w.offs, w.L, 0);
-  hipLaunchKernelGGL(hist_kernel, dim3(w.nblk), dim3(256), lds_bytes, s, assign, n, k, w.ppb, w.offs, (int)lds,
-                     w.arrive);
+  if (L.sum)
+    hipLaunchKernelGGL(hist_kernel<true>, dim3(w.nblk), dim3(256), lds_bytes, s, assign, n, k, w.ppb, w.offs, (int)lds,
+                       w.arrive, L);
+  else
+    hipLaunchKernelGGL(hist_kernel<false>, dim3(w.nblk), dim3(256), lds_bytes, s, assign, n, k, w.ppb, w.offs, (int)lds,
+                       w.arrive, L);
   hipLaunchKernelGGL(scan_kernel, dim3((unsigned)cdiv(k, 32)), dim3(1024), 0, s, w.offs, w.nblk, k, w.chunk, w.cnt,
                      w.cstart, w.choff, w.arrive);
   hipLaunchKernelGGL(scatter_kernel, dim3(w.nblk), dim3(256), lds_bytes, s, assign, n, k, w.ppb, w.offs, w.cstart,
@@ -941,9 +977,11 @@ km_status launch_cluster_sort(const int32_t *assign, int64_t n, int k, void *ws,
 
 km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, int64_t *counts, int policy,
                         void *ws, hipStream_t s, const int *seg_lo, const int *seg_hi, double *objective,
-                        int64_t norms_of) {
+                        bool norms) {
   UpdWs w = carve(P, k, ws, nullptr);
-  km_status sst = launch_sort(assign, P.n, k, w, s);
+  LooseRows L{};
+  if (objective && P.fmt == KM_F32) L = LooseRows{static_cast<const float *>(P.data), P.ld, P.d, norms, w.loose};
+  km_status sst = launch_sort(assign, P.n, k, w, s, L);
   if (sst != KM_OK) return sst;
 
   const int d = P.d;
@@ -985,7 +1023,7 @@ km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, 
     if (objective && P.fmt == KM_F32) {
       hipLaunchKernelGGL(segsum_f32_kernel<true>, dim3(w.maxchunks, slices), dim3(256), 0, s, F, fld, df, w.perm,
                          w.cnt, w.cstart, w.choff, k, w.chunk, static_cast<float *>(w.partial), w.dp,
-                         norms_of ? nullptr : static_cast<const float *>(C), w.partialO);
+                         norms ? nullptr : static_cast<const float *>(C), w.partialO);
     } else if (df > 0) {
       hipLaunchKernelGGL(segsum_f32_kernel<false>, dim3(w.maxchunks, slices), dim3(256), 0, s, F, fld, df, w.perm,
                          w.cnt, w.cstart, w.choff, k, w.chunk, static_cast<float *>(w.partial), w.dp, nullptr, nullptr);
@@ -1002,8 +1040,7 @@ km_status launch_update(const Points &P, const int32_t *assign, int k, void *C, 
     hipLaunchKernelGGL(finalize_f32_kernel, dim3(k + fold, (unsigned)cdiv(w.dp, 256)), dim3(256), 0, s,
                        static_cast<const float *>(w.partial), w.dp, w.cnt, w.choff, static_cast<float *>(w.Z),
                        w.fresh, is_bits_fmt(P.fmt) ? w.partialA : nullptr, w.partialM,
-                       P.fmt == KM_LVQ4 ? w.partialB : nullptr, d_bits, cm, w.partialO, w.cstart, k, (int)slices,
-                       norms_of ? norms_of : P.n,
+                       P.fmt == KM_LVQ4 ? w.partialB : nullptr, d_bits, cm, w.partialO, w.loose, 4 * w.nblk, k, (int)slices,
                        objective);
   }
   KMQ_LAUNCH_CHECK("update: segmented sums");

@@ -145,6 +145,46 @@ def test_not_finite(km, torch, k, tiles):
     assert not (host(a) == k // 2).any()
 
 
+@pytest.mark.parametrize("how,want", [("no_centroid", np.inf), ("no_centroid_and_nan", np.nan), ("centroid", np.nan)])
+@few_and_many
+def test_objective_of_infinite_rows(km, torch, how, want, tiles):
+    """An infinite coordinate for which every score is +infinity makes every objective +infinity (of a call, of a fit's
+    updates and last pass, of FINE with and without an update), NaN beside it NaN; a score of -infinity NaN."""
+    n, d, k = 900 if tiles == "few" else 70000, 64, 90
+    X, C = points(n, d, k, 21)
+    X[:, 0], C[:, 0] = -np.abs(X[:, 0]), -np.abs(C[:, 0]) - 0.1
+    if how == "centroid":
+        X[n // 2, 0] = -np.inf
+    else:
+        X[n // 2, 0] = np.inf
+    if how == "no_centroid_and_nan":
+        X[n // 3, 5] = np.nan
+    P, Ct = km.points_f32(to_dev(X, torch)), to_dev(C, torch)
+    a, _, J = km.kmeans_assign(P, Ct, objective=True)
+    assert (host(a)[n // 2] < k) == (how == "centroid")
+    np.testing.assert_array_equal(host(J), [want])
+    if how != "centroid":  # (a centroid that takes an infinity is infinite after the update)
+        _, _, J = km.kmeans_fit(P, k, 2, C=Ct.clone())
+        np.testing.assert_array_equal(host(J), [want] * 3)
+        meso = to_dev(np.where(np.arange(n) == 3, -1, np.arange(n) % 3).astype(np.int32), torch)
+        for iters in (0, 1):
+            _, _, _, J = km.kmeans_fine(P, meso, 3, k, iters, C=Ct.clone(), policy=km.KM_EMPTY_KEEP, objective=True)
+            np.testing.assert_array_equal(host(J), [want])
+
+
+@few_and_many
+def test_objective_near_the_end_of_fp32(km, torch, tiles):
+    """Squared distances of 2^127.4 each, in a call and in a fit's update: their sums are past fp32's range."""
+    n, d, k = 900 if tiles == "few" else 70000, 64, 3
+    g = np.random.default_rng(2)
+    X, C = g.standard_normal((n, d)).astype(np.float32), g.standard_normal((k, d)).astype(np.float32)
+    X[:, 0], C[:, 0] = 1.5e19 * g.choice([-1, 1], n), 0
+    C[:, 1] = np.arange(k)
+    P = km.points_f32(to_dev(X, torch))
+    for J in (km.kmeans_assign(P, to_dev(C, torch), objective=True)[2], km.kmeans_fit(P, k, 1, C=to_dev(C, torch))[2]):
+        np.testing.assert_allclose(host(J)[0], n * float(X[0, 0]) ** 2, rtol=1e-6)
+
+
 def test_one_stage(km, torch):
     """Fewer dims than a stage of few tiles, odd and even numbers of stages, points with a stride."""
     for n, d, k in ((130, 32, 70), (65, 64, 64), (64, 68, 65), (200, 100, 1)):

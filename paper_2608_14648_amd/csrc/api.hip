@@ -65,11 +65,12 @@ class Scratch {
     if (p_) (void)hipFreeAsync(p_, s_);
   }
   km_status alloc(size_t bytes) {
-    // KMQ_FAIL_ALLOC=1 makes every scratch allocation fail before any HIP call:
-    // the failure path can be exercised on a machine without a GPU
+    // KMQ_FAIL_ALLOC=1 makes every scratch allocation fail before any HIP call (">N":
+    // those of more than N bytes): the failure paths can be exercised on a machine
+    // without a GPU
     const char *fail = getenv("KMQ_FAIL_ALLOC");
-    if (fail && fail[0] == '1') {
-      set_error("scratch allocation of %zu bytes failed: refused (KMQ_FAIL_ALLOC=1)", bytes);
+    if (fail && (fail[0] == '1' || (fail[0] == '>' && bytes > strtoull(fail + 1, nullptr, 10)))) {
+      set_error("scratch allocation of %zu bytes failed: refused (KMQ_FAIL_ALLOC=%s)", bytes, fail);
       return KM_ENOMEM;
     }
     km_status st = prepare_pool();
@@ -294,9 +295,14 @@ km_status pca_project(const float *X, int64_t n, int32_t d, const float *mean, c
   KMQ_CHECK(aligned16(X) && aligned16(mean), KM_EINVAL, "X and mean must be 16-byte aligned");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   Scratch ws(s);
-  km_status st = ws.alloc(pca_project_bytes(n, d, d_out));
+  bool split = project_split(d, d);
+  km_status st = ws.alloc(pca_project_bytes(n, d, d_out, split));
+  if (st == KM_ENOMEM && split) {  // the fp32 kernel needs less
+    split = false;
+    st = ws.alloc(pca_project_bytes(n, d, d_out, split));
+  }
   if (st != KM_OK) return st;
-  return launch_pca_project(X, n, d, (int64_t)d, mean, W, d_out, Y, ws.get(), s);
+  return launch_pca_project(X, n, d, (int64_t)d, mean, W, d_out, Y, ws.get(), split, s);
 }
 
 km_status rabitq_encode(const float *X, int64_t n, int32_t d, int64_t ldx, const float *P, float *m, uint32_t *bits,
@@ -312,9 +318,14 @@ km_status rabitq_encode(const float *X, int64_t n, int32_t d, int64_t ldx, const
   KMQ_CHECK((flags & ~KM_Q_FIT_PARAMS) == 0, KM_EINVAL, "unknown flags 0x%x", flags);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   Scratch ws(s);
-  km_status st = ws.alloc(rabitq_encode_bytes(n, d, Y != nullptr));
+  bool split = project_split(d, ldx);
+  km_status st = ws.alloc(rabitq_encode_bytes(n, d, Y != nullptr, split));
+  if (st == KM_ENOMEM && split) {  // the fp32 kernel needs less
+    split = false;
+    st = ws.alloc(rabitq_encode_bytes(n, d, Y != nullptr, split));
+  }
   if (st != KM_OK) return st;
-  return launch_rabitq_encode(X, n, d, ldx, P, m, bits, alpha, Y, flags, ws.get(), s);
+  return launch_rabitq_encode(X, n, d, ldx, P, m, bits, alpha, Y, flags, ws.get(), split, s);
 }
 
 }  // extern "C"

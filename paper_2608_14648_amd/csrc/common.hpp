@@ -251,11 +251,13 @@ km_status launch_quantize(const float *X, int64_t n, int d, int64_t ldx, int fmt
                           float *params, float *alpha, int d_front, float *front, int flags, void *ws,
                           hipStream_t s);
 
-size_t colmean_bytes(int64_t n, int d);
-size_t rabitq_encode_bytes(int64_t n, int d, bool y_given);
+// split: the rotation on the fp16 matrix cores (project_split allowing)
+size_t rabitq_encode_bytes(int64_t n, int d, bool y_given, bool split);
 km_status launch_rabitq_encode(const float *X, int64_t n, int d, int64_t ldx, const float *P, float *m,
-                               uint32_t *bits, float *alpha, float *Y, int flags, void *ws, hipStream_t s);
-// top (nullable): each column's largest |x - mean|
+                               uint32_t *bits, float *alpha, float *Y, int flags, void *ws, bool split,
+                               hipStream_t s);
+size_t colmean_bytes(int64_t n, int d, bool ranges = false);
+// top (nullable): each column's largest |x - mean| (workspace with ranges)
 km_status launch_colmean(const float *X, int64_t n, int d, int64_t ldx, float *m, void *ws, hipStream_t s,
                          float *top = nullptr);
 
@@ -263,9 +265,11 @@ km_status launch_colmean(const float *X, int64_t n, int d, int64_t ldx, float *m
 size_t pca_cov_bytes(int64_t n, int d);
 km_status launch_pca_cov(const float *X, int64_t n, int d, float *mean, float *cov, void *ws,
                          hipStream_t s);
+// whether the fp16 matrix cores can take a projection of these rows (split below)
+bool project_split(int d, int64_t ldx);
 km_status launch_pca_project(const float *X, int64_t n, int d, int64_t ldx, const float *mean, const float *W,
-                             int d_out, float *Y, void *ws, hipStream_t s);
-size_t pca_project_bytes(int64_t n, int d, int d_out);
+                             int d_out, float *Y, void *ws, bool split, hipStream_t s);
+size_t pca_project_bytes(int64_t n, int d, int d_out, bool split);
 
 // ---- device helpers ---------------------------------------------------------
 

@@ -584,17 +584,21 @@ int cu_count() {
   return cus;
 }
 
-size_t pca_cov_bytes(int64_t n, int d) {
+// workspace: the partial tiles, and before them the column sums and ranges in their place |
+// the columns' largest |x - mean|
+static size_t cov_partial_bytes(int64_t n, int d) {
   const CovPlan p = cov_plan(n, d);
-  return (size_t)p.nsplit * p.ntiles * kCT * kCT * sizeof(double) + colmean_bytes(n, d) + 4 * (size_t)d + 768;
+  return (std::max((size_t)p.nsplit * p.ntiles * kCT * kCT * sizeof(double), colmean_bytes(n, d, true)) + 255) &
+         ~(size_t)255;
 }
+
+size_t pca_cov_bytes(int64_t n, int d) { return cov_partial_bytes(n, d) + 4 * (size_t)d; }
 
 km_status launch_pca_cov(const float *X, int64_t n, int d, float *mean, float *cov, void *ws, hipStream_t s) {
   const CovPlan p = cov_plan(n, d);
   double *partial = static_cast<double *>(ws);
-  void *mws = static_cast<uint8_t *>(ws) + (((size_t)p.nsplit * p.ntiles * kCT * kCT * sizeof(double) + 255) & ~(size_t)255);
-  float *top = reinterpret_cast<float *>(static_cast<uint8_t *>(mws) + ((colmean_bytes(n, d) + 255) & ~(size_t)255));
-  km_status st = launch_colmean(X, n, d, d, mean, mws, s, top);
+  float *top = reinterpret_cast<float *>(static_cast<uint8_t *>(ws) + cov_partial_bytes(n, d));
+  km_status st = launch_colmean(X, n, d, d, mean, ws, s, top);
   if (st != KM_OK) return st;
   hipLaunchKernelGGL(cov_kernel, dim3((unsigned)(8 * cdiv(p.ntiles * p.nsplit, 8))), dim3(kCovThreads), 0, s, X, n, d,
                      mean, top, p.T, p.ntiles, p.nsplit, p.rows_per_split, partial);
@@ -606,16 +610,16 @@ km_status launch_pca_cov(const float *X, int64_t n, int d, float *mean, float *c
 
 // The fp16 matrix cores take the rows whose 256 span less than 2 GB (as the fp32
 // kernel's do), from two stages of 16 dims on.
-static bool project_split(int d, int64_t ldx) {
+bool project_split(int d, int64_t ldx) {
   return d >= 32 && d <= kSplitProjMaxD && ldx % 4 == 0 && (int64_t)kPT * ldx * 4 < ((int64_t)1 << 31);
 }
 
-size_t pca_project_bytes(int64_t n, int d, int d_out) {
-  return (((size_t)d * d_out * sizeof(float) + 255) & ~(size_t)255) + 256 + split_project_bytes(n, d, d_out);
+size_t pca_project_bytes(int64_t n, int d, int d_out, bool split) {
+  return (((size_t)d * d_out * sizeof(float) + 255) & ~(size_t)255) + 256 + (split ? split_project_bytes(n, d, d_out) : 0);
 }
 
 km_status launch_pca_project(const float *X, int64_t n, int d, int64_t ldx, const float *mean, const float *W,
-                             int d_out, float *Y, void *ws, hipStream_t s) {
+                             int d_out, float *Y, void *ws, bool split, hipStream_t s) {
   float *Wt = static_cast<float *>(ws);
   const int64_t e = (int64_t)d * d_out;
   hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)cdiv(e, 256)), dim3(256), 0, s, W, d, d_out, Wt);
@@ -623,7 +627,7 @@ km_status launch_pca_project(const float *X, int64_t n, int d, int64_t ldx, cons
     const int n_ptiles = (int)cdiv(n, kPT), n_otiles = (int)cdiv(d_out, kPT);
     const int64_t nblk = cdiv(n_ptiles, 8) * 8 * n_otiles;
     SplitPrep sp{};
-    if (project_split(d, ldx)) {
+    if (split) {
       uint8_t *w = static_cast<uint8_t *>(ws) + ((e * sizeof(float) + 255) & ~(size_t)255);
       const km_status st = launch_split_project(X, n, d, ldx, mean, W, d_out, Y, w, &sp, s);
       if (st != KM_OK) return st;

@@ -339,8 +339,9 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float *v, int n) {
 
 constexpr int kMaxSumBlocks = 1024;
 
-size_t colmean_bytes(int64_t n, int d) {  // with room for the column ranges
-  return (size_t)std::min<int64_t>(kMaxSumBlocks, cdiv(n, 64)) * d * (sizeof(double) + 2 * sizeof(float)) + 256;
+size_t colmean_bytes(int64_t n, int d, bool ranges) {
+  return (size_t)std::min<int64_t>(kMaxSumBlocks, cdiv(n, 64)) * d * (sizeof(double) + (ranges ? 2 * sizeof(float) : 0)) +
+         256;
 }
 
 km_status launch_colmean(const float *X, int64_t n, int d, int64_t ldx, float *m, void *ws, hipStream_t s, float *top) {
@@ -371,25 +372,26 @@ static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // workspace: column-mean partials | transposed P | zero centre (d) | rotated rows y
 // (n x d, only when the caller does not take them)
-size_t rabitq_encode_bytes(int64_t n, int d, bool y_given) {
-  return al256(colmean_bytes(n, d)) + al256(pca_project_bytes(n, d, d)) + al256((size_t)d * sizeof(float)) +
+size_t rabitq_encode_bytes(int64_t n, int d, bool y_given, bool split) {
+  return al256(colmean_bytes(n, d)) + al256(pca_project_bytes(n, d, d, split)) + al256((size_t)d * sizeof(float)) +
          (y_given ? 0 : al256((size_t)n * d * sizeof(float)));
 }
 
 // RabitQ codes (Sec. 3.1): centre (column mean when fitting), rotate with the
 // projection kernel, then sign bits and alpha of the rotated residual (centre 0).
 km_status launch_rabitq_encode(const float *X, int64_t n, int d, int64_t ldx, const float *P, float *m,
-                               uint32_t *bits, float *alpha, float *Y, int flags, void *ws, hipStream_t s) {
+                               uint32_t *bits, float *alpha, float *Y, int flags, void *ws, bool split,
+                               hipStream_t s) {
   uint8_t *w = static_cast<uint8_t *>(ws);
   void *wmean = w;
   void *wproj = w + al256(colmean_bytes(n, d));
-  float *zero = reinterpret_cast<float *>(w + al256(colmean_bytes(n, d)) + al256(pca_project_bytes(n, d, d)));
+  float *zero = reinterpret_cast<float *>(w + al256(colmean_bytes(n, d)) + al256(pca_project_bytes(n, d, d, split)));
   if (Y == nullptr) Y = zero + al256((size_t)d * sizeof(float)) / sizeof(float);
   if (flags & KM_Q_FIT_PARAMS) {
     km_status st = launch_colmean(X, n, d, ldx, m, wmean, s);
     if (st != KM_OK) return st;
   }
-  km_status st = launch_pca_project(X, n, d, ldx, m, P, d, Y, wproj, s);
+  km_status st = launch_pca_project(X, n, d, ldx, m, P, d, Y, wproj, split, s);
   if (st != KM_OK) return st;
   hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)cdiv(d, 256)), dim3(256), 0, s, zero, d);
   hipLaunchKernelGGL(sign1_encode_kernel, dim3((unsigned)cdiv(n, 4)), dim3(256), 0, s, Y, n, d, (int64_t)d, zero, 0,

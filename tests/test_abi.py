@@ -325,3 +325,31 @@ def test_allocation_failure_is_reported(kmq):
     # that way: it still validates its arguments on the host
     L = kmq.lib()
     assert L.kmeans_assign_noalloc(None, FAKE, 4, FAKE, None, None, None) == -1
+
+
+@pytest.mark.parametrize("call,limit", [
+    # scratch without the split image and a little more; with it, at least 256 KB more
+    ("L.pca_project(F, 5000, 256, F, F, 256, F, None)", 300_000),
+    ("L.rabitq_encode(F, 5000, 256, 256, F, F, F, F, F, 1, None)", 500_000),
+    ("L.kmeans_assign(ct.byref(P), F, 1000, F, None, None, None)", 200_000),
+    ("L.kmeans_assign_pruned(ct.byref(P), F, 1000, F, F, None, None, ct.byref(R), None, None)", 3_500_000),
+])
+def test_less_scratch_is_tried(kmq, call, limit):
+    """Where the scratch of the fp16 matrix cores is refused, the call asks for the fp32 kernel's, which is granted here:
+    the status is that of the missing GPU (or of a call that ran) and not KM_ENOMEM."""
+    code = (
+        "import ctypes as ct, sys\n"
+        f"sys.path.insert(0, {ROOT!r})\n"
+        "from paper_2608_14648_amd import _kmq as k\n"
+        "L = k.lib()\n"
+        "P = k.KmPoints(k.KM_F32, 256, 20000, ct.c_void_p(0x10000), 256, None, None, None, 0, 0, None, 0, None)\n"
+        "R = k.KmPrune(2.1, 0, 0)\n"
+        "F = ct.c_void_p(0x10000)\n"
+        f"print({call})\n"
+    )
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1")
+    for lim, want in ((limit, "-4"), (1000, "-3")):
+        r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120,
+                           env=dict(env, KMQ_FAIL_ALLOC=f">{lim}"))
+        assert r.returncode == 0, r.stderr
+        assert r.stdout.strip() == want, (lim, r.stdout)

@@ -468,3 +468,22 @@ def test_pruned(km, torch, n, d, df, k, how):
         assert cnt[0] == cnt[1] == 0
     else:
         assert a[n // 2] == prev[n // 2] and np.isnan(dist[n // 2])
+
+
+def test_less_scratch(km, torch, monkeypatch):
+    """Calls whose split image is refused: the fp32 kernel's results."""
+    n, d, k = 20000, 256, 1000
+    X, C = points(n, d, k, 9)
+    W = (np.random.default_rng(9).standard_normal((d, d)) / 16).astype(np.float32)
+    Xt, Ct, Wt, zero = to_dev(X, torch), to_dev(C, torch), to_dev(W, torch), torch.zeros(d, device="cuda")
+    monkeypatch.setenv("KMQ_FAIL_ALLOC", ">300000")  # past the fp32 kernels' 262400 and 176128 bytes, less than the split's
+    Y = host(km.pca_project(Xt, zero, Wt)).astype(np.float64)
+    a, sc, _ = km.kmeans_assign(km.points_f32(Xt), Ct)
+    monkeypatch.setenv("KMQ_FAIL_ALLOC", ">500000")
+    _, _, _, R = km.rabitq_encode(Xt[:5000].contiguous(), Wt, zero, want_rotated=True)
+    monkeypatch.delenv("KMQ_FAIL_ALLOC")
+    check(X, C, host(a), host(sc), np.arange(500))
+    want = X.astype(np.float64) @ W.astype(np.float64)
+    bound = (d * 2.0 ** -23) * (np.abs(X.astype(np.float64)) @ np.abs(W.astype(np.float64)))
+    assert (np.abs(Y - want) <= bound).all()
+    assert (np.abs(host(R) - want[:5000]) <= bound[:5000]).all()

@@ -67,11 +67,13 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Chunks halve from 512 members until there are 2048 workgroups (8 per CU): a workgroup
 // reads its members in rounds of 32 and waits for each.  20k x 128 fp32 rows, 64
 // clusters: 13.6 us with chunks of 512, 7.2 with 64; 1M SQ8 rows of 768, 1000 clusters:
-// 147 us with 512 (1953 workgroups and the clusters' remainders), 148 with 256.
-int chunk_members(const Points &P) {
+// 147 us with 512 (1953 workgroups and the clusters' remainders), 148 with 256.  No smaller
+// than that leaves 128 chunks per cluster, though: one thread adds up a column's (100k x 768
+// 1-bit codes, 2 clusters: 118 us a call with chunks of 64, 46 with 512).
+int chunk_members(const Points &P, int k) {
   const int64_t slices = cdiv(P.d, P.fmt == KM_F32 || P.fmt == KM_HYBRID ? 256 : P.fmt == KM_BF16 ? 512 : 1024);
   int c = kChunk;
-  while (c > kChunkMin && cdiv(P.n, c) * slices < 2048) c /= 2;
+  while (c > kChunkMin && cdiv(P.n, c) * slices < 2048 && cdiv(P.n, c / 2) <= 128 * (int64_t)k) c /= 2;
   return c;
 }
 
@@ -80,7 +82,7 @@ UpdWs carve(const Points &P, int k, void *base, size_t *bytes_out) {
   w.ppb = (int)std::max<int64_t>(256, cdiv(cdiv(P.n, kHistBlocks), 256) * 256);
   w.nblk = (int)cdiv(P.n, w.ppb);
   w.L = (int64_t)k * w.nblk;
-  w.chunk = chunk_members(P);
+  w.chunk = chunk_members(P, k);
   w.maxchunks = (int)(cdiv(P.n, w.chunk) + k);
   w.dp = P.d;
   uint8_t *b = static_cast<uint8_t *>(base);
@@ -764,6 +766,23 @@ struct Compose {
 // chunks of (partialM / (2^19 - 1)) W + partialB, over n.
 // One more workgroup, where objective is given, sums segsum_f32_kernel's partials
 // (`slices` per chunk) and hist_kernel's (nloose).
+// A cluster's chunks are read eight at a time and added one by one (the order, and the
+// result, are those of a plain loop): a chunk of fp32 sums costs 0.05 us instead of 0.23, the
+// kernel's time where a few clusters have all the chunks (100k x 64 fp32 rows, one cluster,
+// 1563 chunks: 358 us a call one by one, 85 so).
+template <class Load, class Add>
+__device__ __forceinline__ void chunks_in_order(int c0, int c1, Load load, Add add) {
+  int c = c0;
+  for (; c + 7 < c1; c += 8) {
+    decltype(load(0)) v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = load(c + i);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) add(v[i]);
+  }
+  for (; c < c1; ++c) add(load(c));
+}
+
 __global__ __launch_bounds__(256) void finalize_f32_kernel(const float *partial, int dp, const int *cnt,
                                                            const int *choff, float *Z, uint8_t *fresh,
                                                            const uint32_t *partialA, const float *partialM,
@@ -793,18 +812,34 @@ __global__ __launch_bounds__(256) void finalize_f32_kernel(const float *partial,
   if (partialA && col >= d_bits) {
     const uint32_t *pu = reinterpret_cast<const uint32_t *>(partial);
     double a = 0.0;
-    for (int c = choff[j]; c < choff[j + 1]; ++c) {
-      const double sc = (double)partialM[c] / kAlphaSteps;
-      s += sc * (double)pu[(int64_t)c * dp + col];
-      a += sc * (double)partialA[c];
-    }
+    struct Chunk {
+      float m;
+      uint32_t w, a;
+    };
+    chunks_in_order(
+        choff[j], choff[j + 1],
+        [&](int c) { return Chunk{partialM[c], pu[(int64_t)c * dp + col], partialA[c]}; },
+        [&](const Chunk &v) {
+          const double sc = (double)v.m / kAlphaSteps;
+          s += sc * (double)v.w;
+          a += sc * (double)v.a;
+        });
     s = 2.0 * s - a;
   } else if (partialB) {
     const uint32_t *pu = reinterpret_cast<const uint32_t *>(partial);
-    for (int c = choff[j]; c < choff[j + 1]; ++c)
-      s += (double)partialM[c] / kLvqSteps * (double)pu[(int64_t)c * dp + col] + partialB[c];
+    struct Chunk {
+      float m;
+      uint32_t w;
+      double b;
+    };
+    chunks_in_order(
+        choff[j], choff[j + 1],
+        [&](int c) { return Chunk{partialM[c], pu[(int64_t)c * dp + col], partialB[c]}; },
+        [&](const Chunk &v) { s += (double)v.m / kLvqSteps * (double)v.w + v.b; });
   } else {
-    for (int c = choff[j]; c < choff[j + 1]; ++c) s += (double)partial[(int64_t)c * dp + col];
+    chunks_in_order(
+        choff[j], choff[j + 1], [&](int c) { return partial[(int64_t)c * dp + col]; },
+        [&](float v) { s += (double)v; });
   }
   const float z = (float)(s / (double)nj);
   Z[(int64_t)j * dp + col] = z;
@@ -823,7 +858,8 @@ __global__ __launch_bounds__(256) void finalize_sq8_kernel(const int *partial, i
   }
   if (nj == 0 || col >= d) return;
   int64_t S = 0;
-  for (int c = choff[j]; c < choff[j + 1]; ++c) S += partial[(int64_t)c * d + col];
+  chunks_in_order(
+      choff[j], choff[j + 1], [&](int c) { return partial[(int64_t)c * d + col]; }, [&](int v) { S += v; });
   // mean of the codes rounded half up: floor((2S + n) / (2n))
   const uint8_t z = (uint8_t)((2 * S + nj) / (2 * (int64_t)nj));
   Z[(int64_t)j * d + col] = z;

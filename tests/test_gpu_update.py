@@ -64,3 +64,32 @@ def test_sq8_means_are_exact(km, torch, n, k):
     np.testing.assert_array_equal(host(cnt), N)
     has = N > 0
     np.testing.assert_array_equal(host(C)[has], ((2 * S + N[:, None]) // np.maximum(2 * N[:, None], 1))[has])
+
+
+@pytest.mark.parametrize("n,k", [(9000, 1), (9000, 2), (700, 1), (40000, 3)])
+@pytest.mark.parametrize("fmt", ["sign1", "lvq4"])
+def test_means_of_many_chunks(km, torch, fmt, n, k):
+    """Clusters of 11 to 105 chunks, which are added up eight at a time and the rest, against 64-bit means of the decoded
+    points.  A chunk's alphas are multiples of its largest over 2^23 - 1, LVQ4's scales of its largest over 2^19 - 1."""
+    g = np.random.default_rng(n + k)
+    d = 64
+    X = g.standard_normal((n, d)).astype(np.float32)
+    a = g.integers(0, k, n).astype(np.int32)
+    if fmt == "sign1":
+        bits, m, alpha, _ = km.quantize_sign1(to_dev(X, torch))
+        P = km.points_sign1(bits, alpha, m, d)
+        b = (host(bits).view(np.uint32)[:, :, None] >> np.arange(32, dtype=np.uint32)) & 1
+        al = host(alpha).astype(np.float64)
+        dec = host(m).astype(np.float64) + al[:, None] * (2.0 * b.reshape(n, d) - 1)
+        room = 2.0 ** -23 * al.max() + 2.0 ** -22 * np.abs(dec).max()
+    else:
+        codes, par = km.quantize_lvq4(to_dev(X, torch))
+        P = km.points_lvq4(codes, par, d)
+        c = host(codes)
+        c = np.stack([c & 15, c >> 4], 2).reshape(n, d).astype(np.float64)
+        s, lo = host(par)[:, :1].astype(np.float64), host(par)[:, 1:2].astype(np.float64)
+        dec = s * c + lo
+        room = 15 * 2.0 ** -19 * s.max() + 2.0 ** -22 * np.abs(dec).max()
+    C, _ = km.kmeans_update(P, to_dev(a, torch), torch.zeros((k, d), device="cuda"), policy=km.KM_EMPTY_KEEP)
+    want = np.stack([dec[a == j].mean(0) for j in range(k)])
+    assert (np.abs(host(C) - want) <= room).all(), np.abs(host(C) - want).max() / room

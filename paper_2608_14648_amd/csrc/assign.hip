@@ -2930,6 +2930,23 @@ static int tile_groups(int64_t npt, int nct, int64_t cus, int slack = 0) {
   return g;
 }
 
+// LVQ4.  Merging groups takes two more launches, 10 us of a short call: none where a
+// workgroup that sweeps all tiles (3 us each and 0.7 per 128 dims, measured at 100 points)
+// is done in 30 us, with 1.5 point tiles per CU at a time.  1000 x 416, k = 256: 39 us in two
+// groups, 29 in one; 1000 x 1024, k = 601: 42 in five, 50 in one.
+// Three workgroups share a CU: as many groups as there can be where all of them run at
+// once (5000 x 1024, k = 4096: 69 us in 6 groups, 58 in 8).  Past that uneven rounds cost
+// little and the keys (10 us at 250k points) count: within 5 % of the best.  250k x 416, k =
+// 601 takes 121 us per pass in 1, 3 or 5 groups; a call of 20k x 768, k = 4096 117 us in 5
+// groups, 89 in 8.
+static int lvq4_groups(int64_t n, int k, int d) {
+  const int64_t npt = cdiv(n, kLvT), nct = cdiv(k, kLvT), cus = cu_count();
+  if (nct * (30 + 7 * cdiv(d, 128)) * std::max<int64_t>(3 * cus, 2 * npt) <= 300 * 3 * cus) return 1;
+  const int64_t most = std::min<int64_t>(8, nct);
+  if (npt * most <= 3 * cus) return (int)most;
+  return tile_groups(npt, (int)nct, cus, 5);
+}
+
 // hybrid points whose tail words fit the direct-copy kernel's resident LDS array
 static bool hyb_direct(const Points &P) { return P.fmt == KM_HYBRID && P.d - P.d_front <= 32 * kHybMaxTW; }
 
@@ -2941,10 +2958,7 @@ int assign_groups(const Points &P, int k) {
   const int64_t npt = cdiv(P.n, kQT);
   const int nct = (int)cdiv(k, q8_tile_centroids(k));
   if (P.fmt == KM_F32 || hyb_direct(P)) return tile_groups(npt, nct, cu_count());
-  // LVQ4's workgroups share CUs, so uneven rounds cost little and the keys (10 us at
-  // 250k points) count: within 5 % of the best.  250k x 416, k = 601 takes 121 us per pass in
-  // 1, 3 or 5 groups; a call of 20k x 768, k = 4096 117 us in 5 groups, 89 in 8.
-  if (P.fmt == KM_LVQ4) return tile_groups(cdiv(P.n, kLvT), (int)cdiv(k, kLvT), cu_count(), 5);
+  if (P.fmt == KM_LVQ4) return lvq4_groups(P.n, k, P.d);
   if (P.fmt == KM_HYBRID) {
     constexpr int TC = Geo<Blocking<KM_F32>::CB, Blocking<KM_F32>::PB>::TC;
     return (int)std::min<int64_t>(8, cdiv(k, TC));

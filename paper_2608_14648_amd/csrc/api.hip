@@ -204,6 +204,16 @@ static km_status check_centroids(const Points &p, const void *C, int k) {
   return KM_OK;
 }
 
+// p for k centroids: the fp16 matrix cores only where they pay.
+static Points for_centroids(Points p, int k, bool fit) {
+  p.split = p.split && split_pays(p, k, fit);
+  return p;
+}
+
+// Whether the objective is summed from the distances (fp32 points of 32 dims and more, and what the
+// fp16 matrix cores take) or from the scores.
+static bool direct_objective(const Points &p) { return p.fmt == KM_F32 ? p.d >= 32 : p.split; }
+
 // The raw rows of p as fp32 points (the last update of a fit).
 static Points raw_points(const Points &p) {
   Points r{};
@@ -341,7 +351,7 @@ struct AssignScratch {
 static AssignScratch assign_scratch(const Points &p, int k, const float *score, const double *objective) {
   AssignScratch a;
   a.b_prep = al(prep_bytes(p, k));
-  if (p.split) {  // the objective needs neither scores nor point-only terms
+  if (direct_objective(p)) {  // needs neither scores nor point-only terms
     a.b_score = a.b_xc = 0;
     a.b_part = objective ? al(direct_objective_bytes()) : 0;
     return a;
@@ -358,6 +368,7 @@ static km_status check_assign_args(const km_points *P, const void *C, int32_t k,
   st = check_centroids(*p, C, k);
   if (st != KM_OK) return st;
   KMQ_CHECK(assign != nullptr, KM_EINVAL, "assign is NULL");
+  *p = for_centroids(*p, k, false);
   return KM_OK;
 }
 
@@ -374,7 +385,8 @@ static km_status assign_on(const Points &p, const void *C, int32_t k, int32_t *a
   if (st != KM_OK) return st;
   st = launch_assign(p, C, cp, k, assign, sc, s);
   if (st != KM_OK) return st;
-  if (objective && p.split) return launch_direct_objective(p, static_cast<const float *>(C), cp, k, assign, objective, part, s);
+  if (objective && direct_objective(p))
+    return launch_direct_objective(p, static_cast<const float *>(C), cp, k, assign, objective, part, s);
   if (objective) {
     st = launch_xconst(p, xc, s);
     if (st != KM_OK) return st;
@@ -529,7 +541,7 @@ static km_status fit_on(const Points &p, int k, int iters, const int64_t *init_i
   // direct: the objective of a pass over fp32 points is summed by the update that follows
   // it, from the rows that reads; by a pass of its own where none does or it reads the
   // raw rows, and for hybrid points
-  const bool direct = objective && p.split;
+  const bool direct = objective && direct_objective(p);
   const bool scores = objective && !direct;
   const size_t b_score = scores ? al(sizeof(float) * (size_t)p.n) : 0;
   const size_t b_xc = scores ? al(sizeof(float) * (size_t)p.n) : 0;
@@ -575,6 +587,7 @@ static km_status fit_on(const Points &p, int k, int iters, const int64_t *init_i
 
 static km_status fit_impl(Points p, int k, int iters, const int64_t *init_idx, void *C, int32_t *assign,
                           double *objective, int policy, StageClock &clk, hipStream_t s) {
+  p = for_centroids(p, k, true);
   km_status st = fit_on(p, k, iters, init_idx, C, assign, objective, policy, clk, s);
   if (st == KM_ENOMEM && p.split) {  // nothing was launched; the fp32 kernel needs less scratch
     p.split = false;
@@ -901,14 +914,14 @@ static km_status fit_pruned_on(const Points &p, int k, int iters, const int64_t 
                                double *objective, int policy, const km_prune *pr, int D0, km_fit_stats *stats,
                                uint64_t *counters, hipStream_t s) {
   km_status st;
-  const size_t b_prep = al(prep_bytes(p, k));
+  const Points p1 = for_centroids(p, k, true);  // the first pass, a full one
+  const size_t b_prep = al(prep_bytes(p1, k));
   const size_t b_upd = al(std::max(update_bytes(p, k), p.raw ? update_bytes(raw_points(p), k) : (size_t)0));
-  const bool scores = objective && !p.split;
+  const bool direct = objective && direct_objective(p1), scores = objective && !direct;
   const size_t b_score = scores ? al(sizeof(float) * (size_t)p.n) : 0;
   const size_t b_xc = scores ? al(sizeof(float) * (size_t)p.n) : 0;
-  const size_t b_part = !objective ? 0
-                        : scores ? al(sizeof(double) * (size_t)objective_blocks(p.n))
-                                 : al(direct_objective_bytes());
+  const size_t b_part = direct ? al(direct_objective_bytes())
+                               : scores ? al(sizeof(double) * (size_t)objective_blocks(p.n)) : 0;
   const size_t b_idx = init_idx ? al(sizeof(int64_t) * (size_t)k) : 0;
   const size_t b_pr = al(pruned_bytes(p, k));
   const size_t b_cnt = al(3 * sizeof(unsigned long long));
@@ -933,10 +946,10 @@ static km_status fit_pruned_on(const Points &p, int k, int iters, const int64_t 
     }
     // the first pass is a full assignment
     CentroidPrep cp;
-    KMQ_STAGE(clk, kStPrep, launch_prep(p, C, k, wprep, &cp, s));
-    KMQ_STAGE(clk, kStAssign, launch_assign(p, C, cp, k, assign, sc, s));
-    if (objective && p.split)
-      KMQ_STAGE(clk, kStOther, launch_direct_objective(p, static_cast<const float *>(C), cp, k, assign, objective, part, s));
+    KMQ_STAGE(clk, kStPrep, launch_prep(p1, C, k, wprep, &cp, s));
+    KMQ_STAGE(clk, kStAssign, launch_assign(p1, C, cp, k, assign, sc, s));
+    if (direct)
+      KMQ_STAGE(clk, kStOther, launch_direct_objective(p1, static_cast<const float *>(C), cp, k, assign, objective, part, s));
     if (scores) {
       KMQ_STAGE(clk, kStOther, launch_xconst(p, xc, s));
       KMQ_STAGE(clk, kStOther, launch_objective(p, xc, sc, p.n, objective, part, objective_blocks(p.n), s));

@@ -2816,18 +2816,20 @@ __global__ __launch_bounds__(256) void cost_kernel(const float *X, int64_t n, in
 // where its row holds NaN.  One with an infinite coordinate and a centroid had the score
 // -infinity and adds NaN.  HYB: the front dims like that, plus the tail's score
 // sigma^2 Q - alpha 2 sigma (2D - T) and its point-only term alpha^2 (d - d0).
-template <bool HYB>
+// G lanes share a point: 16 for at most 64 dims, 32 for at most 128, so that few idle
+// (100k points, front 32 + tail 128, k = 100: 74 us a call with 64, 48 so).
+template <bool HYB, int G>
 __global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, int64_t n, int d, int64_t ldx,
                                                                const float *C, int64_t ldc, int k,
                                                                const int32_t *assign, Points P, CentroidPrep cp,
                                                                double *partials) {
   __shared__ double sh[256];
   constexpr int NP = 4;  // points at a time: their loads are in flight together
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x % G;
   double s = 0.0;
-  const int64_t stride = (int64_t)gridDim.x * 4;
+  const int64_t stride = (int64_t)gridDim.x * (256 / G);
   const int dt = P.d - P.d_front;
-  for (int64_t p = (int64_t)blockIdx.x * 4 + wv; p < n; p += NP * stride) {
+  for (int64_t p = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G; p < n; p += NP * stride) {
     int64_t pt[NP];
     int a[NP];
     bool in[NP];
@@ -2843,7 +2845,7 @@ __global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, i
     }
     int D[NP] = {0, 0, 0, 0};
     if constexpr (HYB) {
-      for (int i = 16 * lane; i < dt; i += 1024) {
+      for (int i = 16 * lane; i < dt; i += 16 * G) {
         uint4 q[NP];
         uint32_t w[NP];
 #pragma unroll
@@ -2861,7 +2863,7 @@ __global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, i
       }
     }
     double t[NP] = {0.0, 0.0, 0.0, 0.0};
-    for (int i = 4 * lane; i < d; i += 256) {
+    for (int i = 4 * lane; i < d; i += 4 * G) {
       f32x4 xv[NP], cv[NP];
 #pragma unroll
       for (int e = 0; e < NP; ++e) {
@@ -2881,7 +2883,7 @@ __global__ __launch_bounds__(256) void direct_objective_kernel(const float *X, i
       if (p + e * stride >= n) continue;
       const double al = HYB ? (double)P.alpha[pt[e]] : 0.0;
       if (!in[e]) {
-        for (int i = lane; i < d; i += 64) s += (double)x[e][i] * (double)x[e][i];
+        for (int i = lane; i < d; i += G) s += (double)x[e][i] * (double)x[e][i];
         s += al * al * dt + INFINITY;
         continue;
       }
@@ -3191,6 +3193,23 @@ static size_t split_scratch(const Points &P, int k) {
   return split_bytes(P.n, k, hyb ? P.d_front : P.d, hyb);
 }
 
+// split_kernel takes two launches more than the fp32 kernels (the centroids' image, and the
+// fp32 kernel behind it), 7 us of a call whose kernels are shorter than their launches.  It pays
+// from four stages of 32 dims on 256 x 256 tiles in the longest chain of a CU (a tile of 128
+// centroids counts half).  fp32 kernel against split_kernel, us per call: two stages 38 / 46
+// (20k x 32, k = 1000) and 31 / 38 (100k x 64, k = 64), three 44 / 54 (10k x 96, k = 500), four 47 / 39
+// (100k x 64, k = 256), eight 79 / 48 (20k x 128, k = 1000); hybrid, front dims counted: 31 / 39 at one
+// stage, 42 / 42 at three, 0.82 of the time at four.  In a fit the kernels wait for each other and not
+// for the host, so three are enough (30k x 96, k = 200, 4 passes: 1.16 of the time with the fp32 kernel).
+bool split_pays(const Points &P, int k, bool fit) {
+  if (small_f32(P, k)) return true;
+  const bool half = q8_tile_centroids(k) == 128;
+  const int64_t npt = cdiv(P.n, kQT), nct = cdiv(k, half ? 128 : 256);
+  const int64_t g = tile_groups(npt, (int)nct, cu_count());
+  const int64_t stages = cdiv(P.fmt == KM_HYBRID ? P.d_front : P.d, 32);
+  return cdiv(npt * g, cu_count()) * cdiv(nct, g) * stages * (half ? 1 : 2) >= (fit ? 6 : 8);
+}
+
 size_t prep_bytes(const Points &P, int k) {
   size_t b = align256(16 * (size_t)k) + align256(prep_codes_bytes(P, k));
   if (assign_groups(P, k) > 1) b += align256(8 * (size_t)P.n);
@@ -3396,13 +3415,27 @@ size_t direct_objective_bytes() { return sizeof(double) * kDirectBlocks; }
 
 km_status launch_direct_objective(const Points &P, const float *C, const CentroidPrep &cp, int k,
                                   const int32_t *assign, double *out, double *partials, hipStream_t s) {
-  const int nb = (int)std::min<int64_t>(kDirectBlocks, cdiv(P.n, 4));
-  if (P.fmt == KM_HYBRID)
-    hipLaunchKernelGGL(direct_objective_kernel<true>, dim3(nb), dim3(256), 0, s, P.front, P.n, P.d_front,
-                       (int64_t)P.d_front, C, (int64_t)P.d, k, assign, P, cp, partials);
+  const bool hyb = P.fmt == KM_HYBRID;
+  const int d = hyb ? P.d_front : P.d;
+  const int g = d <= 64 ? 16 : d <= 128 ? 32 : 64;
+  const int nb = (int)std::min<int64_t>(kDirectBlocks, cdiv(P.n, 256 / g));
+  auto run = [&](auto hyb_, auto g_) {
+    hipLaunchKernelGGL((direct_objective_kernel<decltype(hyb_)::value, decltype(g_)::value>), dim3(nb), dim3(256), 0, s,
+                       hyb ? P.front : static_cast<const float *>(P.data), P.n, d, hyb ? (int64_t)d : P.ld, C,
+                       (int64_t)P.d, k, assign, P, cp, partials);
+  };
+  auto by_dims = [&](auto hyb_) {
+    if (g == 16)
+      run(hyb_, std::integral_constant<int, 16>{});
+    else if (g == 32)
+      run(hyb_, std::integral_constant<int, 32>{});
+    else
+      run(hyb_, std::integral_constant<int, 64>{});
+  };
+  if (hyb)
+    by_dims(std::true_type{});
   else
-    hipLaunchKernelGGL(direct_objective_kernel<false>, dim3(nb), dim3(256), 0, s, static_cast<const float *>(P.data),
-                       P.n, P.d, P.ld, C, (int64_t)P.d, k, assign, P, cp, partials);
+    by_dims(std::false_type{});
   hipLaunchKernelGGL(direct_objective_sum_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
   KMQ_LAUNCH_CHECK("direct objective");
   return KM_OK;

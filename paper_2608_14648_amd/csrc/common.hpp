@@ -99,6 +99,9 @@ int cu_count();
 km_status launch_prep(const Points &P, const void *C, int k, void *ws_prep, CentroidPrep *out,
                       hipStream_t s);
 size_t prep_bytes(const Points &P, int k);
+// whether the fp16 matrix cores are the faster ones for these points and k centroids (P.split says that
+// they can); fit: for a pass among others
+bool split_pays(const Points &P, int k, bool fit);
 // aoff is added to every stored centroid index (C and cp may be a slice of a larger set)
 // One launch for many (row range, centroid range) segments of fp32, SQ8 or bf16
 // points: segment i is rows [segs[i].x, + segs[i].y) against centroids

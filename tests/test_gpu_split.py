@@ -50,14 +50,25 @@ def check(X, C, a, sc, rows=None):
     return xn + s[i, got]
 
 
-def spread_rows(n, k, tiles):
-    """Row numbers of a call that repeats n rows: as they are, up to 4 tiles of 64 x 64 per CU, or past that."""
+def spread_rows(n, k, tiles, d=32):
+    """Row numbers of a call that repeats n rows: as they are, up to 4 tiles of 64 x 64 per CU; past that, where short
+    chains of tiles are left to the fp32 kernel; or to chains of four stages of 32 dims per CU and more, split_kernel's."""
     if tiles == "few":
         return np.arange(n)
-    return np.arange(n + 256 * -(-4 * 256 // (4 * -(-k // 64)))) % n
+    if tiles == "many":
+        return np.arange(n + 256 * -(-4 * 256 // (4 * -(-k // 64)))) % n
+    tc = 128 if k <= 128 else 256
+    nct = -(-k // tc)
+
+    def chain(npt):
+        return min(-(-npt * g // 256) * -(-nct // g) for g in range(1, min(8, nct) + 1)) * -(-d // 32) * tc / 256
+    npt = max(-(-n // 256), 4 * 256 // (4 * -(-k // 64)) + 1)
+    while chain(npt) < 4:
+        npt += 64
+    return np.arange(256 * npt - 3) % n
 
 
-few_and_many = pytest.mark.parametrize("tiles", ["few", "many"])
+few_and_many = pytest.mark.parametrize("tiles", ["few", "many", "split"])
 
 
 # k around the 64-, 128- and 256-centroid tiles and the centroid-tile groups, n around the 256-point tile, d from the
@@ -67,7 +78,7 @@ few_and_many = pytest.mark.parametrize("tiles", ["few", "many"])
 @few_and_many
 def test_edges(km, torch, n, d, k, tiles):
     X, C = points(n, d, k, n + d + k)
-    i = spread_rows(n, k, tiles)
+    i = spread_rows(n, k, tiles, d)
     a, sc, obj = km.kmeans_assign(km.points_f32(to_dev(X[i], torch)), to_dev(C, torch), objective=True)
     a, sc = host(a), host(sc)
     np.testing.assert_array_equal(a, a[i])
@@ -81,7 +92,7 @@ def test_edges(km, torch, n, d, k, tiles):
 @few_and_many
 def test_smallest_index_wins(km, torch, tiles):
     """Equal centroids in other blocks, lane halves, wave halves, tiles and groups of the sweep."""
-    n, d, k = 700 if tiles == "few" else 5000, 64, 1300
+    n, d, k = {"few": 700, "many": 5000, "split": 50000}[tiles], 64, 1300
     X, C = points(n, d, k, 3, spread=0.0)
     for src, copies in {5: (9, 37, 133, 300, 1299), 64: (68, 200, 700), 250: (251, 255, 513)}.items():
         C[list(copies)] = C[src]
@@ -113,7 +124,7 @@ def test_ranges(km, torch, how, k, tiles):
     else:                           # past fp16's range at the centroids' scale: their tile goes to the fp32 kernel
         X[300] *= np.float32(2.0 ** 14)
         X[301] *= np.float32(2.0 ** 7)
-    i = spread_rows(n, k, tiles)
+    i = spread_rows(n, k, tiles, d)
     a, sc, obj = km.kmeans_assign(km.points_f32(to_dev(X[i], torch)), to_dev(C, torch), objective=True)
     dist = check(X, C, host(a)[:n], host(sc)[:n])[i]
     X = X[i]
@@ -124,9 +135,9 @@ def test_ranges(km, torch, how, k, tiles):
 @few_and_many
 def test_not_finite(km, torch, k, tiles):
     """Rows with NaN or infinities: they answer as in the fp32 kernel and leave the others alone; the objective is NaN."""
-    n, d = 3000 if tiles == "few" else 70000, 64
+    n, d = {"few": 3000, "many": 70000, "split": 300000}[tiles], 64
     if k == 2600:
-        n = 1500 if tiles == "few" else 3000
+        n = {"few": 1500, "many": 3000, "split": 30000}[tiles]
     X, C = points(max(n, k), d, k, 5)
     X = X[:n].copy()
     X[260, 3], X[700, 63] = np.nan, np.inf
@@ -150,7 +161,7 @@ def test_not_finite(km, torch, k, tiles):
 def test_objective_of_infinite_rows(km, torch, how, want, tiles):
     """An infinite coordinate for which every score is +infinity makes every objective +infinity (of a call, of a fit's
     updates and last pass, of FINE with and without an update), NaN beside it NaN; a score of -infinity NaN."""
-    n, d, k = 900 if tiles == "few" else 70000, 64, 90
+    n, d, k = {"few": 900, "many": 70000, "split": 300000}[tiles], 64, 90
     X, C = points(n, d, k, 21)
     X[:, 0], C[:, 0] = -np.abs(X[:, 0]), -np.abs(C[:, 0]) - 0.1
     if how == "centroid":
@@ -175,7 +186,7 @@ def test_objective_of_infinite_rows(km, torch, how, want, tiles):
 @few_and_many
 def test_objective_near_the_end_of_fp32(km, torch, tiles):
     """Squared distances of 2^127.4 each, in a call and in a fit's update: their sums are past fp32's range."""
-    n, d, k = 900 if tiles == "few" else 70000, 64, 3
+    n, d, k = {"few": 900, "many": 70000, "split": 300000}[tiles], 64, 3
     g = np.random.default_rng(2)
     X, C = g.standard_normal((n, d)).astype(np.float32), g.standard_normal((k, d)).astype(np.float32)
     X[:, 0], C[:, 0] = 1.5e19 * g.choice([-1, 1], n), 0
@@ -290,6 +301,42 @@ def hybrid_scores(front, bits, alpha, C, m, d0):
     cn = (cf ** 2).sum(1)
     tail = sg.astype(np.float64) ** 2 * (q ** 2).sum(1) - 2 * alpha[:, None] * sg.astype(np.float64) * (b @ q.T)
     return cn - 2 * f @ cf.T + tail, tail, (f ** 2).sum(1), cn
+
+
+# as above, the rows repeated to chains that split_kernel takes
+@pytest.mark.parametrize("n,d,d0,k", [(257, 96, 32, 128), (300, 160, 64, 129), (513, 288, 96, 300), (700, 704, 64, 257),
+                                      (600, 1024, 384, 1100), (255, 672, 32, 60)])
+@pytest.mark.parametrize("how", ["plain", "tiny_centroid", "not_finite"])
+def test_hybrid_many(km, torch, n, d, d0, k, how):
+    import oracle as orc
+    X, C = points(n, d, k, n + d0)
+    if how == "tiny_centroid":
+        C[0, :d0] *= np.float32(2.0 ** -12)
+        X[::9, :d0] = C[0, :d0] * np.float32(1.25)
+    m = orc.col_mean(X)
+    bits, alpha = orc.sign1_encode(X, m, d0)
+    front = np.ascontiguousarray(X[:, :d0])
+    i = spread_rows(n, k, "split", d0)
+    fr, bad = front[i], []
+    if how == "not_finite":
+        bad = [len(i) - 5]
+        fr[bad, 1] = np.nan
+    P = km.points_hybrid(to_dev(fr, torch), to_dev(bits[i].view(np.int32), torch), to_dev(alpha[i], torch),
+                         to_dev(m, torch), d)
+    a, sc, obj = km.kmeans_assign(P, to_dev(C, torch), objective=True)
+    a, sc = host(a), host(sc)
+    assert (a[bad] == np.iinfo(np.int32).max).all() and (sc[bad] == np.inf).all()
+    ok = np.setdiff1d(np.arange(len(i)), bad)
+    s, tail, xn, cn = hybrid_scores(front, bits, alpha, C, m, d0)
+    got, r = a[ok], i[ok]
+    size = xn[r] + cn[got] + np.abs(tail).max(1)[r]
+    assert ((s[r, got] - s.min(1)[r]) / size).max() <= NEAR_TIE_REL
+    assert (np.abs(sc[ok] - s[r, got]) <= 2 * (6 * (d0 // 16) * 2.0 ** -23 + 3 * 2.0 ** -22) * size).all()
+    if bad:
+        assert np.isnan(host(obj)[0])
+    else:
+        want = (s[r, got] + xn[r] + alpha.astype(np.float64)[r] ** 2 * (d - d0)).sum()
+        assert abs(host(obj)[0] - want) <= 2.0 ** -21 * size.sum()
 
 
 # A tile of 3 stages, the fewest there are (front of 32 dims, tail of one stage), in workgroups that sweep 8 and 16

@@ -305,7 +305,7 @@ km_status pca_project(const float *X, int64_t n, int32_t d, const float *mean, c
   KMQ_CHECK(aligned16(X) && aligned16(mean), KM_EINVAL, "X and mean must be 16-byte aligned");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   Scratch ws(s);
-  bool split = project_split(d, d);
+  bool split = project_split(n, d, d_out, d);
   km_status st = ws.alloc(pca_project_bytes(n, d, d_out, split));
   if (st == KM_ENOMEM && split) {  // the fp32 kernel needs less
     split = false;
@@ -328,7 +328,7 @@ km_status rabitq_encode(const float *X, int64_t n, int32_t d, int64_t ldx, const
   KMQ_CHECK((flags & ~KM_Q_FIT_PARAMS) == 0, KM_EINVAL, "unknown flags 0x%x", flags);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   Scratch ws(s);
-  bool split = project_split(d, ldx);
+  bool split = project_split(n, d, d, ldx);
   km_status st = ws.alloc(rabitq_encode_bytes(n, d, Y != nullptr, split));
   if (st == KM_ENOMEM && split) {  // the fp32 kernel needs less
     split = false;

@@ -268,8 +268,8 @@ km_status launch_colmean(const float *X, int64_t n, int d, int64_t ldx, float *m
 size_t pca_cov_bytes(int64_t n, int d);
 km_status launch_pca_cov(const float *X, int64_t n, int d, float *mean, float *cov, void *ws,
                          hipStream_t s);
-// whether the fp16 matrix cores can take a projection of these rows (split below)
-bool project_split(int d, int64_t ldx);
+// whether the fp16 matrix cores take a projection of these rows (split below)
+bool project_split(int64_t n, int d, int d_out, int64_t ldx);
 km_status launch_pca_project(const float *X, int64_t n, int d, int64_t ldx, const float *mean, const float *W,
                              int d_out, float *Y, void *ws, bool split, hipStream_t s);
 size_t pca_project_bytes(int64_t n, int d, int d_out, bool split);

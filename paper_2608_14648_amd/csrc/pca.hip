@@ -608,10 +608,20 @@ km_status launch_pca_cov(const float *X, int64_t n, int d, float *mean, float *c
   return KM_OK;
 }
 
-// The fp16 matrix cores take the rows whose 256 span less than 2 GB (as the fp32
-// kernel's do), from two stages of 16 dims on.
-bool project_split(int d, int64_t ldx) {
-  return d >= 32 && d <= kSplitProjMaxD && ldx % 4 == 0 && (int64_t)kPT * ldx * 4 < ((int64_t)1 << 31);
+// The fp16 matrix cores can take the rows whose 256 span less than 2 GB (as the fp32
+// kernel's do), from two stages of 16 dims on.  They cost three launches more, 13 us of a
+// call shorter than that, so a CU's chain of 256 x 256 tiles and stages of 32 dims has to be long
+// enough, and where the outputs bound a pass (tiles of 256, 32 or 64 dims) they gain nothing.
+// us per call, fp32 kernel first: to 16 outputs 50k x 64 (two stages) 33 / 47, 100k x 64 (four) 51 / 47,
+// 1000 x 160 (five) 53 / 48, 1M x 64 (32) 345 / 198; to 256 outputs 100k x 64 (four) 59 / 71, 100k x 96 (six)
+// 76 / 78, 20k x 128 (four) 49 / 51, 1000 x 192 (six, one tile) 62 / 52, 100k x 128 (eight) 92 / 82, 1M x 64
+// 437 / 460, 1M x 48 452 / 427.
+bool project_split(int64_t n, int d, int d_out, int64_t ldx) {
+  if (d < 32 || d > kSplitProjMaxD || ldx % 4 != 0 || (int64_t)kPT * ldx * 4 >= ((int64_t)1 << 31)) return false;
+  const int64_t rounds = cdiv(cdiv(n, kPT) * cdiv(d_out, kPT), cu_count()), chain = rounds * cdiv(d, 32);
+  if (d_out <= 128) return chain >= 4 && (d > 32 || d_out <= 64);
+  const int64_t steps = cdiv(d, 16);
+  return chain >= (rounds == 1 ? 5 : 8) && steps != 2 && steps != 4;
 }
 
 size_t pca_project_bytes(int64_t n, int d, int d_out, bool split) {

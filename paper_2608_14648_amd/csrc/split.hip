@@ -100,27 +100,41 @@ __global__ __launch_bounds__(256) void split_prep_kernel(const float *C, int64_t
 
 // ---- projection: scales and the image of W ------------------------------------------
 // Every dim's largest |x - mean| over 1024 rows spread over X, as a bit pattern (NaN and
-// infinities are the largest): 16 dims per workgroup, 64 rows at a time.
+// infinities are the largest): 16 dims per workgroup, 4 per thread of 4 rows, all loads in
+// flight at once.
 __global__ __launch_bounds__(1024) void proj_sample_kernel(const float *X, int64_t n, int d, int64_t ldx,
                                                            const float *mean, uint32_t *top, SplitRoute *route) {
-  __shared__ uint32_t sh[1024];
+  __shared__ uint32_t sh[16][16];
   const int t = threadIdx.x;
-  const int c = blockIdx.x * 16 + (t & 15);
-  uint32_t m = 0;
+  const int c = blockIdx.x * 16 + 4 * (t & 3);
   const int rows = (int)min<int64_t>(n, 1024);
-  if (c < d) {
-    const float mc = mean[c];
-#pragma unroll 4
-    for (int i = t >> 4; i < rows; i += 64)
-      m = max(m, __float_as_uint(X[(int64_t)((double)i * (double)n / rows) * ldx + c] - mc) & 0x7fffffffu);
+  uint32_t m[4] = {0u, 0u, 0u, 0u};
+  if (c < d) {  // d % 4 == 0
+    const f32x4 mc = *reinterpret_cast<const f32x4 *>(mean + c);
+    f32x4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = min((t >> 2) + 256 * q, rows - 1);
+      v[q] = *reinterpret_cast<const f32x4 *>(X + (int64_t)((double)i * (double)n / rows) * ldx + c);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = max(m[e], __float_as_uint(v[q][e] - mc[e]) & 0x7fffffffu);
   }
-  sh[t] = m;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) m[e] = max(m[e], (uint32_t)__shfl_xor((int)m[e], o));
+    if ((t & 63) < 4) sh[t >> 6][4 * (t & 3) + e] = m[e];
+  }
   __syncthreads();
-  for (int st = 512; st >= 16; st >>= 1) {
-    if (t < st) sh[t] = max(sh[t], sh[t + st]);
-    __syncthreads();
+  if (t < 16 && (int)blockIdx.x * 16 + t < d) {
+    uint32_t a = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) a = max(a, sh[w][t]);
+    top[blockIdx.x * 16 + t] = a;
   }
-  if (t < 16 && c < d) top[c] = sh[t];
   if (t == 0 && blockIdx.x == 0) route->ok = 1;
 }
 

@@ -400,11 +400,18 @@ def test_project(km, torch, n, d, dout, how):
     assert (err <= bound[fin]).all(), (err / bound[fin]).max()
 
 
+# the same where split_kernel takes few dims: two rounds of 256-point tiles, dims a stage of 16 does not divide
+@pytest.mark.parametrize("n,d,dout", [(66000, 36, 8), (65600, 60, 100), (197000, 32, 36), (66000, 100, 132)])
+@pytest.mark.parametrize("how", ["plain", "rows", "not_finite", "columns"])
+def test_project_many(km, torch, n, d, dout, how):
+    test_project(km, torch, n, d, dout, how)
+
+
 @pytest.mark.parametrize("row", [0, 31, 69, 32, 255])
 def test_project_one_small_row(km, torch, row):
     """One row whose centred values are 2^-24 of the others', alone in its tile, in either block of a wave: the split
     would keep 2^-37 of the others, so the row goes to the fp32 kernel, also where its uncentred values are large."""
-    n, d, dout = 256, 64, 40
+    n, d, dout = 256, 128, 40
     g = np.random.default_rng(row)
     m = np.where(np.arange(d) < 16, 64, 0).astype(np.float32)
     X = (m + g.standard_normal((n, d)) * 2.0 ** 10).astype(np.float32)

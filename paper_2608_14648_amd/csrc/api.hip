@@ -887,12 +887,12 @@ km_status kmeans_assign_pruned(const km_points *P, const void *C, int32_t k, con
   st = check_prune(p, pr, &D0);
   if (st != KM_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  size_t b_pr = al(pruned_bytes(p, k));
+  size_t b_pr = al(pruned_bytes(p, k, D0));
   Scratch ws(s);
   st = ws.alloc(b_pr + al(3 * sizeof(unsigned long long)));
   if (st == KM_ENOMEM && p.split) {  // the fp32 kernel needs less
     p.split = false;
-    b_pr = al(pruned_bytes(p, k));
+    b_pr = al(pruned_bytes(p, k, D0));
     st = ws.alloc(b_pr + al(3 * sizeof(unsigned long long)));
   }
   if (st != KM_OK) return st;
@@ -923,7 +923,7 @@ static km_status fit_pruned_on(const Points &p, int k, int iters, const int64_t 
   const size_t b_part = direct ? al(direct_objective_bytes())
                                : scores ? al(sizeof(double) * (size_t)objective_blocks(p.n)) : 0;
   const size_t b_idx = init_idx ? al(sizeof(int64_t) * (size_t)k) : 0;
-  const size_t b_pr = al(pruned_bytes(p, k));
+  const size_t b_pr = al(pruned_bytes(p, k, D0));
   const size_t b_cnt = al(3 * sizeof(unsigned long long));
   Scratch ws(s);
   st = ws.alloc(b_prep + b_upd + b_score + b_xc + b_part + b_idx + b_pr + b_cnt);

@@ -242,7 +242,7 @@ km_status launch_scatter_assign(const int *perm, const int32_t *a_perm, int64_t 
 // skm.hip: dimension pruning inside STEP 2
 double prune_factor(int D, int d, double eps0);
 int prune_front_default(int d);
-size_t pruned_bytes(const Points &P, int k);  // any d'
+size_t pruned_bytes(const Points &P, int k, int D0);
 km_status launch_assign_pruned(const Points &P, const void *C, int k, const int32_t *prev, int32_t *assign,
                                double *dist, double *objective, double eps0, int D0,
                                unsigned long long *cnt, void *ws, hipStream_t s);

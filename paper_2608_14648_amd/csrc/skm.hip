@@ -512,12 +512,24 @@ double prune_factor(int D, int d, double eps0) {
 
 int prune_front_default(int d) { return std::min(d, 32 * ((d + 255) / 256)); }
 
-size_t pruned_bytes(const Points &P, int k) {
+// From two stages of 16 front dims on the front of fp32 points can run on the fp16 matrix cores,
+// and the fp32 kernel takes what they leave (split.hip): two launches more, so from chains of 16
+// stages of 128 centroids x 32 dims per CU on (12 where most CUs have a tile, 8 where they have
+// four).  us per call, fp32 kernel first: 20k x 128, k = 256, d' = 32 (2 stages) 48 / 54; 5k x 128,
+// k = 1000 (8) 48 / 54; 100k x 128, k = 256 (8) 73 / 67; 50k x 128, k = 1000 (16) 80 / 59; 1k x 768, k = 1000,
+// d' = 96 (24) 85 / 56
+static bool prune_split(const Points &P, int k, int D0) {
+  if (P.fmt != KM_F32 || !P.split || D0 <= 16) return false;
+  const int64_t tiles = cdiv(P.n, kFT), rounds = cdiv(tiles, cu_count()), chain = rounds * cdiv(k, kFT) * cdiv(D0, 32);
+  return chain >= (rounds >= 4 ? 8 : 2 * tiles >= cu_count() ? 12 : 16);
+}
+
+size_t pruned_bytes(const Points &P, int k, int D0) {
   const size_t n = (size_t)P.n;
   const size_t W4 = 4 * (size_t)cdiv(k, kFT);
   return al256(4 * n) + al256(4 * n) + al256(4 * (size_t)k) + al256(4 * W4 * n) + al256(8 * n) +
          al256(8 * kSumBlocks) + al256(16 * (size_t)front_blocks(P.n, k)) + al256(8 * 4 * (size_t)kRefineBlocks) +
-         (P.fmt == KM_F32 && P.split ? split_bytes(P.n, k, std::min(P.d, 64 * kMaxFront), false) : 0);
+         (prune_split(P, k, D0) ? split_bytes(P.n, k, D0, false) : 0);
 }
 
 km_status launch_assign_pruned(const Points &P, const void *C, int k, const int32_t *prev, int32_t *assign,
@@ -580,9 +592,7 @@ km_status launch_assign_pruned(const Points &P, const void *C, int k, const int3
   }
   const size_t cld = P.fmt == KM_F32 ? 4 * (size_t)d : (size_t)d;
   if (P.fmt == KM_F32) {
-    // from two stages of 16 front dims on, the front runs on the fp16 matrix cores and the
-    // fp32 kernel takes what they leave (split.hip)
-    const bool split = P.split && D0 > 16;
+    const bool split = prune_split(P, k, D0);
     CentroidPrep cp{};
     cp.cn = static_cast<const float *>(cn);
     if (split) cp.sp = split_layout(n, k, D0, false, w);

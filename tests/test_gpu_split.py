@@ -524,6 +524,13 @@ def test_pruned(km, torch, n, d, df, k, how):
         assert a[n // 2] == prev[n // 2] and np.isnan(dist[n // 2])
 
 
+# the same where split_kernel takes few front dims: many centroids, fronts a stage of 16 does not divide
+@pytest.mark.parametrize("n,d,df,k", [(100, 128, 40, 2100), (64, 96, 24, 2200), (150, 48, 48, 1100)])
+@pytest.mark.parametrize("how", ["plain", "far_points", "tiny_centroid", "not_finite"])
+def test_pruned_many(km, torch, n, d, df, k, how):
+    test_pruned(km, torch, n, d, df, k, how)
+
+
 def test_less_scratch(km, torch, monkeypatch):
     """Calls whose split image is refused: the fp32 kernel's results."""
     n, d, k = 20000, 256, 1000

@@ -735,9 +735,20 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
   if (seg_rows > 0) {
     for (int i = 0; i < k_meso; ++i)
       if (n_i[i] > 0) segs.push_back(make_int4((int)start[i], (int)n_i[i], (int)off[i], kf[i]));
+    int64_t ntiles[3] = {0, 0, 0};
+    auto cls_of = [&](const int4 &sg) {
+      const int c = segment_tile_centroids(p, sg.w);
+      return c == 64 ? 0 : c == 128 ? 1 : 2;
+    };
+    for (const int4 &sg : segs) ntiles[cls_of(sg)] += cdiv(sg.y, seg_rows);
+    // 64-centroid tiles save matrix work; where all tiles have a CU of their own, a launch more costs
+    // as much time as its tiles take (5k x 768 in 20 segments of 51 to 69 centroids: 185 us a pass in
+    // one launch, 248 in two)
+    const bool join = ntiles[0] > 0 && ntiles[1] > 0 && ntiles[0] + ntiles[1] <= cu_count();
     for (int cls = 0; cls < 3; ++cls) {
       for (int si = 0; si < (int)segs.size(); ++si) {
-        if (segment_tile_centroids(p, segs[si].w) != 64 << cls) continue;
+        const int c = cls_of(segs[si]);
+        if ((join && c == 0 ? 1 : c) != cls) continue;
         for (int64_t tt = 0; tt * seg_rows < segs[si].y; ++tt) tiles.push_back(make_int2(si, (int)tt));
       }
       cls_end[cls] = (int64_t)tiles.size();

@@ -421,3 +421,23 @@ def test_fine_f32_objective_of_repeated_values(km, torch, v):
     C, _, _, J1 = km.kmeans_fine(P, meso, km_, k, 1, policy=km.KM_EMPTY_KEEP, objective=True)
     _, _, _, J0 = km.kmeans_fine(P, meso, km_, k, 0, C=C, objective=True)
     assert abs(host(J1)[0] - host(J0)[0]) <= 2.0 ** -24 * n * d * v * v
+
+
+@pytest.mark.parametrize("n", [900, 90000])
+def test_fine_f32_tile_sizes_together(km, torch, n):
+    """Fine counts on both sides of the 64-centroid tile, in so few point tiles that they share one launch and in so
+    many that they do not: the result is that of the meso-clusters one at a time."""
+    rng = np.random.default_rng(n)
+    d, km_ = 36, 3
+    meso = rng.choice(km_, n, p=[.3, .33, .37]).astype(np.int32)
+    X = to_dev((rng.standard_normal((n, d)) + meso[:, None]).astype(np.float32), torch)
+    C, a, kf, _ = km.kmeans_fine(km.points_f32(X), to_dev(meso, torch), km_, 192, 1, policy=km.KM_EMPTY_KEEP)
+    assert kf.min() <= 64 < kf.max()
+    for i in range(km_):
+        rows = np.nonzero(meso == i)[0]
+        off = kf[:i].sum()
+        Ci, ai, ki, _ = km.kmeans_fine(km.points_f32(X[to_dev(rows, torch)].contiguous()),
+                                       torch.zeros(len(rows), dtype=torch.int32, device="cuda"), 1, int(kf[i]), 1,
+                                       policy=km.KM_EMPTY_KEEP)
+        np.testing.assert_array_equal(host(a)[rows], host(ai) + off)
+        np.testing.assert_allclose(host(C)[off:off + kf[i]], host(Ci), rtol=0, atol=1e-5)

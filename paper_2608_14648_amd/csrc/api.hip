@@ -206,7 +206,8 @@ static km_status check_centroids(const Points &p, const void *C, int k) {
 
 // p for k centroids: the fp16 matrix cores only where they pay.
 static Points for_centroids(Points p, int k, bool fit) {
-  p.split = p.split && split_pays(p, k, fit);
+  p.fit = fit;
+  p.split = p.split && split_pays(p, k);
   return p;
 }
 
@@ -655,6 +656,7 @@ static km_status fine_impl(const Points &p0, const int32_t *meso, int k_meso, in
                            hipStream_t s) {
   km_status st;
   Points p = p0;
+  p.fit = true;
   p.split = false;  // the segmented passes take the fp32 kernel
   // meso-cluster order of the points (stable) and the meso-cluster sizes
   Scratch wsort(s);

@@ -2661,7 +2661,7 @@ __global__ __launch_bounds__(256) void xconst_kernel(Points P, const int *prow, 
   const int lane = threadIdx.x & 63;
   const int64_t i0 = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i0 >= P.n) return;
-  const int64_t p = prow ? prow[i0] : i0;
+  const int64_t p = FMT == KM_F32 && prow ? prow[i0] : i0;
   double s = 0.0;
   if (FMT == KM_F32 || FMT == KM_HYBRID) {
     const float *x = FMT == KM_F32 ? static_cast<const float *>(P.data) + p * P.ld : P.front + p * P.d_front;
@@ -2934,16 +2934,18 @@ static int tile_groups(int64_t npt, int nct, int64_t cus, int slack = 0) {
 
 // LVQ4.  Merging groups takes two more launches, 10 us of a short call: none where a
 // workgroup that sweeps all tiles (3 us each and 0.7 per 128 dims, measured at 100 points)
-// is done in 30 us, with 1.5 point tiles per CU at a time.  1000 x 416, k = 256: 39 us in two
-// groups, 29 in one; 1000 x 1024, k = 601: 42 in five, 50 in one.
+// is done in 30 us, with 1.5 point tiles per CU at a time; in a fit, where they take their
+// kernels' 5 us, in 15.  1000 x 416, k = 256: 39 us in two groups, 29 in one; 1000 x 1024, k = 601: 42 in
+// five, 50 in one; fits of 4 iterations: 20k x 256, k = 256 239 in two, 207 in one, 20k x 64, k = 1000
+// 245 in eight, 298 in one.
 // Three workgroups share a CU: as many groups as there can be where all of them run at
 // once (5000 x 1024, k = 4096: 69 us in 6 groups, 58 in 8).  Past that uneven rounds cost
 // little and the keys (10 us at 250k points) count: within 5 % of the best.  250k x 416, k =
 // 601 takes 121 us per pass in 1, 3 or 5 groups; a call of 20k x 768, k = 4096 117 us in 5
 // groups, 89 in 8.
-static int lvq4_groups(int64_t n, int k, int d) {
+static int lvq4_groups(int64_t n, int k, int d, bool fit) {
   const int64_t npt = cdiv(n, kLvT), nct = cdiv(k, kLvT), cus = cu_count();
-  if (nct * (30 + 7 * cdiv(d, 128)) * std::max<int64_t>(3 * cus, 2 * npt) <= 300 * 3 * cus) return 1;
+  if (nct * (30 + 7 * cdiv(d, 128)) * std::max<int64_t>(3 * cus, 2 * npt) <= (fit ? 150 : 300) * 3 * cus) return 1;
   const int64_t most = std::min<int64_t>(8, nct);
   if (npt * most <= 3 * cus) return (int)most;
   return tile_groups(npt, (int)nct, cus, 5);
@@ -2960,7 +2962,7 @@ int assign_groups(const Points &P, int k) {
   const int64_t npt = cdiv(P.n, kQT);
   const int nct = (int)cdiv(k, q8_tile_centroids(k));
   if (P.fmt == KM_F32 || hyb_direct(P)) return tile_groups(npt, nct, cu_count());
-  if (P.fmt == KM_LVQ4) return lvq4_groups(P.n, k, P.d);
+  if (P.fmt == KM_LVQ4) return lvq4_groups(P.n, k, P.d, P.fit);
   if (P.fmt == KM_HYBRID) {
     constexpr int TC = Geo<Blocking<KM_F32>::CB, Blocking<KM_F32>::PB>::TC;
     return (int)std::min<int64_t>(8, cdiv(k, TC));
@@ -3201,13 +3203,13 @@ static size_t split_scratch(const Points &P, int k) {
 // (100k x 64, k = 256), eight 79 / 48 (20k x 128, k = 1000); hybrid, front dims counted: 31 / 39 at one
 // stage, 42 / 42 at three, 0.82 of the time at four.  In a fit the kernels wait for each other and not
 // for the host, so three are enough (30k x 96, k = 200, 4 passes: 1.16 of the time with the fp32 kernel).
-bool split_pays(const Points &P, int k, bool fit) {
+bool split_pays(const Points &P, int k) {
   if (small_f32(P, k)) return true;
   const bool half = q8_tile_centroids(k) == 128;
   const int64_t npt = cdiv(P.n, kQT), nct = cdiv(k, half ? 128 : 256);
   const int64_t g = tile_groups(npt, (int)nct, cu_count());
   const int64_t stages = cdiv(P.fmt == KM_HYBRID ? P.d_front : P.d, 32);
-  return cdiv(npt * g, cu_count()) * cdiv(nct, g) * stages * (half ? 1 : 2) >= (fit ? 6 : 8);
+  return cdiv(npt * g, cu_count()) * cdiv(nct, g) * stages * (half ? 1 : 2) >= (P.fit ? 6 : 8);
 }
 
 size_t prep_bytes(const Points &P, int k) {

@@ -31,6 +31,7 @@ struct Points {
   const float *raw;    // nullable: fp32 rows in the clustering space (last update of a fit)
   int64_t raw_ld;
   const float *vparams;  // LVQ4: per-vector (s, b, A, N)
+  bool fit;              // one pass among others: the kernels wait for each other and not for their launches
   bool split;            // F32, HYBRID: assignments take the fp16 matrix cores (split.hpp) where the data allow
 };
 
@@ -99,9 +100,8 @@ int cu_count();
 km_status launch_prep(const Points &P, const void *C, int k, void *ws_prep, CentroidPrep *out,
                       hipStream_t s);
 size_t prep_bytes(const Points &P, int k);
-// whether the fp16 matrix cores are the faster ones for these points and k centroids (P.split says that
-// they can); fit: for a pass among others
-bool split_pays(const Points &P, int k, bool fit);
+// whether the fp16 matrix cores are the faster ones for these points and k centroids (P.split says that they can)
+bool split_pays(const Points &P, int k);
 // aoff is added to every stored centroid index (C and cp may be a slice of a larger set)
 // One launch for many (row range, centroid range) segments of fp32, SQ8 or bf16
 // points: segment i is rows [segs[i].x, + segs[i].y) against centroids

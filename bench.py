@@ -750,8 +750,12 @@ def wl_hier(fmt):
             work_fine = 2.0 * spec.d * float((n_i * res["kf"]).sum())
             work = K * ((Tm + 1) * work_meso + (Tf + 1) * work_fine)
             ach = work / (s["assign_ms"] * 1e-3) / 1e12
-            peak = "fp32" if fmt == "f32" else "int8"
-            kern = "split_kernel (meso), assign_f32_kernel (fine)" if fmt == "f32" else "assign_q8_kernel<sq8>"
+            # fp32: the meso launches issue three fp16 products per fp32 one, the fine launches fp32 products;
+            # the peak of the mix is all work over the least time of both parts
+            kern, peak = "assign_q8_kernel<sq8>", PEAK["int8"]
+            if fmt == "f32":
+                kern = "split_kernel (meso), assign_f32_kernel (fine)"
+                peak = work / K / ((Tm + 1) * 3 * work_meso / PEAK["fp16"] + (Tf + 1) * work_fine / PEAK["fp32"])
             return line(K / elapsed, "fits/s", "f32" if fmt == "f32" else "u8",
                         {"workload": wname, "N": spec.n, "d": spec.d, "k": k, "k_meso": kmeso, "iters_meso": Tm,
                          "iters_fine": Tf, "iters_refine": 0, "format": fmt},
@@ -760,8 +764,8 @@ def wl_hier(fmt):
                         ms_per_fit=float(res["ph"].sum()),
                         phase_ms={"meso": res["ph"][0], "fine": res["ph"][1]},
                         roofline={"bound": "mfma", "kernel": f"{kern} (meso launches and segmented fine launches)",
-                                  "achieved": ach, "peak": PEAK[peak], "unit": PEAK_UNIT[peak],
-                                  "frac": ach / PEAK[peak], "traffic": None,
+                                  "achieved": ach, "peak": peak, "unit": PEAK_UNIT["fp32" if fmt == "f32" else "int8"],
+                                  "frac": ach / peak, "traffic": None,
                                   "algorithmic_work_per_fit": work / K},
                         stages={fmt: stage_summary(s)})
 

@@ -210,8 +210,8 @@ km_status kmeans_assign(const km_points *P, const void *C, int32_t k, int32_t *a
  * groups, objective partials) lives in a static device array of 64 MiB that the
  * library holds on every device it runs on until the process ends, so the call
  * makes no allocation of any kind.
- *   (fp32 points whose centroids, 4 k d bytes prepared for the matrix cores, do not fit
- *   take the fp32 kernel: the same results to rounding.)
+ *   (fp32 points and hybrid fronts whose centroids, 4 bytes per dim prepared for the
+ *   matrix cores, do not fit take the fp32 kernels: the same results to rounding.)
  *   KM_EINVAL when the call would need more than 64 MiB of scratch: about
  *   16 bytes per point with the objective, 8 without (fp32, bfloat16 and SQ8
  *   points in centroid-tile groups), plus the prepared centroids (k x d bytes for

@@ -25,11 +25,11 @@ constexpr int kSeedPad = 256;  // -inf seeds past the last centroid
 // would reduce them first costs more.
 //
 // The scale puts the largest |c| of all centroids at [2^7, 2^8): every coordinate is
-// held to 2^-33 of that maximum or 2^-23 of itself, and points up to 2^8 times larger
-// stay below fp16's 65504 (larger ones, infinities and NaN give NaN scores, which flag
-// their tile for the fp32 kernel).  The absolute part disappears behind the fp32
-// rounding of ||c||^2 (2^-25 of it) as long as no centroid is tiny beside that
-// maximum: ||c|| >= 2^-8 max|c| is asked of every centroid (or ||c|| = 0, whose products
+// held to 2^-32 of that maximum or 2^-23 of itself, and points up to 2^7 times larger
+// always stay below fp16's 65504, up to 2^8 times larger mostly (what does not, infinities
+// and NaN give NaN scores, which flag their tile for the fp32 kernel).  The absolute part
+// stays at the fp32 rounding of ||c||^2 (2^-24 of it) as long as no centroid is tiny beside
+// that maximum: ||c|| >= 2^-8 max|c| is asked of every centroid (or ||c|| = 0, whose products
 // are exact).  Centroids with NaN or infinities, or so large or small that the
 // scale's square leaves fp32's range, take the fp32 kernel as well.
 __global__ __launch_bounds__(256) void split_prep_kernel(const float *C, int64_t ldc, int k, int d,

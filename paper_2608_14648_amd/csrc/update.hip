@@ -822,8 +822,8 @@ __global__ __launch_bounds__(256) void finalize_f32_kernel(const float *partial,
         for (int e = 0; e < 8; ++e) s += v[e];
       }
     };
+    sum(loose, nloose);  // first: the number of chunks arrives meanwhile
     sum(partialO, np);
-    sum(loose, nloose);
     s = block_sum_f64(s, shd);
     if (threadIdx.x == 0) *objective = s;
     return;

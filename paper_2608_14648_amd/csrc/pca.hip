@@ -62,7 +62,7 @@ __device__ __forceinline__ void lds_copy16(const void *base, uint32_t off, uint3
 // memory every 4096 rows: the instruction's rounding, and the little it cuts, grow with
 // the number of additions (at 8192 rows the relative error of the covariance was that
 // of the fp32 kernel's, 2.1e-7).  2M x 1024:
-// 20.5 -> 8 ms against v_mfma_f32_32x32x2_f32 tiles centred as they were read; three
+// 20.5 -> 8.8 ms against v_mfma_f32_32x32x2_f32 tiles centred as they were read; three
 // matrix products of 2.6 TFLOP take 6.1 ms at the rate of a large library product.
 // Workgroups of one split are neighbours on one XCD, whose L2 then serves the rows
 // that its tiles share.

@@ -262,8 +262,8 @@ __global__ __launch_bounds__(256) void proj_prep_kernel(const float *W, int d, i
 // centroids exchanged in the MFMA so that a lane holds one output of many points and
 // the stores are coalesced; s (x - mean) is formed as the points are read, and the
 // values go out with their column's scale instead of into an argmax.
-// 2M x 1024 -> 256: 8.6 -> 4.1 ms against project_kernel (10.2 GB read and written:
-// 2.1 ms at the rate of a large copy); 500k x 1024 x 1024 (RabitQ's rotation): 8.5 -> 4.1.
+// 2M x 1024 -> 256: 8.6 -> 3.5 ms against project_kernel (10.2 GB read and written:
+// 2.1 ms at the rate of a large copy); 500k x 1024 x 1024 (RabitQ's rotation): 8.5 -> 3.4.
 //
 // PRUNE (the first test of a pruned pass, at d' dims): the threshold test of every pair,
 // acc - s^2 ||c'||^2 / 2 < (||x'||^2 - tau r(d')) s^2 / 2 drops it, and a point's survivors as
